@@ -331,7 +331,7 @@ def classify(hidden: torch.Tensor, w_pool, b_pool, w_cls, b_cls) -> torch.Tensor
     """samp_classify: float32 logits [B, classes] from the first token of each sequence."""
     B, S, H = hidden.shape
     Cn = w_cls.shape[0]
-    logits = torch.zeros((B, Cn), dtype=torch.float32, device=hidden.device)
+    logits = torch.empty((B, Cn), dtype=torch.float32, device=hidden.device)
     _check(lib().samp_classify(_dp(hidden), B, S, H, _dp(w_pool), _dp(b_pool), _dp(w_cls), _dp(b_cls), Cn, _dp(logits), _stream()))
     return logits
 

@@ -593,6 +593,13 @@ def test_classification_target_within_accumulation_tolerance(P, B, S, H, Cn):
     assert np.array_equal(got.argmax(axis=1), want.argmax(axis=1))
 
 
+@pytest.mark.parametrize("B,S,H,Cn", [(3, 2, 8, 1), (1, 3, 776, 9), (2, 1, 4096, 8)])
+def test_classification_target_at_ragged_widths(P, B, S, H, Cn):
+    """Widths that leave part of the last 256-channel section (or almost all of the first) empty, and class counts on
+    either side of the eight rows a wave takes at a time."""
+    test_classification_target_within_accumulation_tolerance(P, B, S, H, Cn)
+
+
 def test_entry_quantiser_bit_exact(P):
     """samp_quantize_f16_i8: the un-masked entry quantiser, incl. ties, values beyond the clamp and a ragged tail of
     the grid (element count not a multiple of the block size)."""
