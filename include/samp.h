@@ -73,9 +73,9 @@ enum {
 };
 
 /* Supported shapes: head size hidden/heads == 64; hidden % 128 == 0; ffn % 128 == 0;
- * hidden <= 2048; 1 <= max_seq <= SAMP_MAX_SEQ; 1 <= max_batch <= SAMP_MAX_BATCH.  Up to 512 tokens a sequence's
- * attention scores stay in registers; longer sequences take a three-sweep attention kernel that
- * recomputes them (same results, about half the rate per token pair).  Row counts are 32-bit:
+ * hidden <= 2048; 1 <= max_seq <= SAMP_MAX_SEQ; 1 <= max_batch <= SAMP_MAX_BATCH.  Up to 2048 tokens (1536 with
+ * SAMP_P_FP16) a sequence's attention scores stay in registers; longer sequences take a three-sweep
+ * attention kernel that recomputes them (same results, about half the rate per token pair).  Row counts are 32-bit:
  * max_batch * max_seq <= SAMP_MAX_TOKENS.                                                         */
 #define SAMP_MAX_SEQ 4096
 #define SAMP_MAX_TOKENS (1 << 24)

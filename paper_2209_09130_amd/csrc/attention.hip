@@ -4,15 +4,15 @@
 // calibration, so both batched products are int8 x int8 -> int32):
 //     score = float(q.k) * m_sc;  P = softmax(score);  Pq = rne(P / s_p);  ctx = rne(float(Pq.V) * m_ctx)
 // Because the step of P is static, P must be fully normalised before it is rounded: a block keeps
-// a whole strip of scores on chip (32 queries x all keys of the sequence, <= 512), so the scores
+// a whole strip of scores on chip (32 queries x all keys of the sequence, <= 2048), so the scores
 // never touch memory and no running rescale is needed.  Longer sequences take the three-sweep
 // kernels further down, which recompute the scores instead of keeping them.
 //
-// One block = (sequence, head, 32 queries), 4 waves; wave w owns key tiles w, w+4, ... (32 keys
-// each).  S^T = K.Q^T is computed so that in the 32x32 MFMA result a lane holds ONE query and 16
+// One block = (sequence, head, 32 queries), 4 waves (8 for INT8 beyond 512 keys); wave w owns key
+// tiles w, w+4, ... (32 keys each).  S^T = K.Q^T is computed so that in the 32x32 MFMA result a lane holds ONE query and 16
 // keys: after the softmax those 16 values are, as they stand, the lane's operand of the P.V MFMA.
 // Its other operand is V^T, staged per wave through LDS.  Row maxima, row sums and the partial
-// P.V products are combined across the 4 waves through LDS (integer partial sums: exact).
+// P.V products are combined across the waves through LDS (integer partial sums: exact).
 // Every floating-point value that decides an int8 code follows one fixed sequence of binary32
 // operations; exp and the row sum are evaluated in binary64 and rounded once.
 #include "samp_common.h"
@@ -25,7 +25,7 @@ namespace samp {
 namespace {
 
 constexpr int QB = 32;                 // queries per block
-constexpr int ONE_PASS_MAX_LEN = 512;  // longest sequence whose score strip stays in registers
+constexpr int ONE_PASS_MAX_LEN = 512;  // longest sequence that four waves take in the INT8 flavour
 constexpr int VT_STRIDE_I8 = 36;       // bytes per V^T row (32 keys + pad), int8
 constexpr int VT_STRIDE_F16 = 72;      // bytes per V^T row (32 keys + pad), fp16
 
@@ -73,6 +73,54 @@ __device__ __forceinline__ int opaque_zero()
     return z;
 }
 
+// Sum of the V codes a lane holds of one key tile (its channel, the keys of its half), added to `sum`.  The unsigned operand
+// forms are fed to the matrix core as code - 128; 128 times the sum over all keys is what they miss.
+__device__ __forceinline__ int add_codes(const v4i &vf, int sum)
+{
+#pragma unroll
+    for (int q = 0; q < 4; q++) sum = __builtin_amdgcn_sdot4(vf[q], 0x01010101, sum, false);
+    return sum;
+}
+
+// The V rows of key tile j0 as a lane transposes them: d[u][t] holds four channels (4 (lane & 15) ..) of key
+// j0 + 4 ((lane >> 4) + 4 u) + t; rows past the end repeat the last one.
+__device__ __forceinline__ void load_v_tile(const int8_t *vp, unsigned ld, int j0, int n, int lane, unsigned (&d)[2][4])
+{
+    const int cq = lane & 15;
+    if (j0 + 32 <= n) {                                  // wave-uniform; four consecutive key rows: one address, three strides
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const int8_t *p0 = vp + (unsigned)(j0 + 4 * ((lane >> 4) + 4 * u)) * ld + 4 * cq;
+#pragma unroll
+            for (int t = 0; t < 4; t++) d[u][t] = *reinterpret_cast<const unsigned *>(p0 + t * ld);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+                d[u][t] = *reinterpret_cast<const unsigned *>(vp + (unsigned)min(j0 + 4 * ((lane >> 4) + 4 * u) + t, n - 1) * ld + 4 * cq);
+    }
+}
+
+// V^T of that tile into LDS: 4 keys x 4 channels byte blocks transposed in registers (v_perm_b32) and stored as dwords of four
+// consecutive keys per channel
+__device__ __forceinline__ void store_vt_tile(const unsigned (&d)[2][4], int lane, int8_t *slab)
+{
+    const int cq = lane & 15;
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const int kq = (lane >> 4) + 4 * u;
+        const unsigned t01l = __builtin_amdgcn_perm(d[u][1], d[u][0], 0x05010400u), t23l = __builtin_amdgcn_perm(d[u][3], d[u][2], 0x05010400u);
+        const unsigned t01h = __builtin_amdgcn_perm(d[u][1], d[u][0], 0x07030602u), t23h = __builtin_amdgcn_perm(d[u][3], d[u][2], 0x07030602u);
+        unsigned *dst = reinterpret_cast<unsigned *>(&slab[(4 * cq) * VT_STRIDE_I8 + 4 * kq]);
+        dst[0 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23l, t01l, 0x05040100u);
+        dst[1 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23l, t01l, 0x07060302u);
+        dst[2 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23h, t01h, 0x05040100u);
+        dst[3 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23h, t01h, 0x07060302u);
+    }
+}
+
 struct SeqInfo { int t0, n; };
 __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 {
@@ -82,26 +130,30 @@ __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 
 // PU: the softmax codes are unsigned, rne(P / s_p) in [0, 255] (the variant that spends all 256 codes
 //     on [0, 1]).  The matrix core multiplies signed bytes, so it is fed code - 128 (a flip of the top
-//     bit) and the missing 128 * sum_k V[k] is added back from a second product of the same V tile with
-//     a row of ones; both are exact in int32.
+//     bit) and the missing 128 * sum_k V[k] of the same V tiles is added back; both are exact in int32.
 // HIST: also counts every softmax code of a valid (query, key) pair into p_hist[256] (a diagnostic:
 //     which of the 256 integers the softmax output uses, as Appendix B tabulates).
 // At least two waves per SIMD are asked for so that the register budget is one the matrix-core results fit
 // without the accumulation registers: the products then land where the vector ALU reads them.
-template <int NT, bool PU, bool HIST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_i8_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu,
+// NW: waves of the block.  Four up to 512 keys; eight up to 2048 (NT = 3 to 8 key tiles per wave), so that the strip of scores of a
+// long sequence stays in registers too.  A sequence of 1100 tokens then evaluates each exponential once and forms each
+// score once, where three sweeps over recomputed scores (the kernels further down) evaluate it twice and form it three
+// times: three sequences of 1100 tokens (twelve heads) 94 -> 52 us, two of 2048 190 -> 118 us.
+template <int NT, bool PU, bool HIST, int NW = 4>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5 ? 4 : 2))) void attention_i8_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu,
                                                            int max_len, int H, float m_sc, float inv_sp, float m_ctx,
                                                            int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist)
 {
     __shared__ unsigned hist[HIST ? 256 : 1];
     // One slab per wave: first its V^T tiles (written and read by that wave alone), then, once its last P.V
     // product has read them, its partial context for the other waves; sharing the bytes lets a third block fit a CU.
-    constexpr int VT_TILE = 64 * VT_STRIDE_I8, SO_BYTES = QB * 64 * 4;
-    constexpr int SLAB = NT * VT_TILE > SO_BYTES ? NT * VT_TILE : SO_BYTES;
-    __shared__ __attribute__((aligned(16))) int8_t slab[4][SLAB];
+    // It holds at most four tiles: a fifth one (and so on) takes a tile's place when that one has been multiplied.
+    constexpr int VT_TILE = 64 * VT_STRIDE_I8, SO_BYTES = QB * 64 * 4, VT_TILES = NT < 4 ? NT : 4;
+    constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
+    __shared__ __attribute__((aligned(16))) int8_t slab[NW][SLAB];
     auto so = [&](int wave) { return reinterpret_cast<int(*)[64]>(slab[wave]); };
-    __shared__ float smax[4][QB];
-    __shared__ double ssum[4][QB];
+    __shared__ float smax[NW][QB];
+    __shared__ double ssum[NW][QB];
 
     // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
     // sequences, whose tokens it also owns in the kernels before and after this one
@@ -114,8 +166,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;                          // row offsets inside a sequence fit 32 bits
-    const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64;
-    if (HIST) hist[tid] = 0;                                      // ordered before its use by the barriers below
+    const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64, *vp = base + 2 * H;
+    if (HIST && tid < 256) hist[tid] = 0;                                      // ordered before its use by the barriers below
 
     // Q strip: second MFMA operand, lane (query r, half g) holds 16 consecutive bytes of the head dim
     const int qrow = min(q0 + r, n - 1);
@@ -127,7 +179,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + 4 * i) * 32;
+        const int j0 = (w + NW * i) * 32;
         if (j0 < n) {                                           // wave-uniform
             // the K rows are requested first, then the V rows: the first product then waits for the K rows only
             const int krow = min(j0 + r, n - 1);
@@ -135,42 +187,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
             v4i kf[2];
 #pragma unroll
             for (int ks = 0; ks < 2; ks++) kf[ks] = *reinterpret_cast<const v4i *>(kp + ks * 32 + g * 16);
-            // stage V^T of this key tile: a lane transposes two 4 keys x 4 channels byte blocks in
-            // registers (v_perm_b32) and stores them as dwords of 4 consecutive keys per channel
-            const int8_t *vp = base + 2 * H;
             const bool full = j0 + 32 <= n;                      // wave-uniform
-            const int cq = lane & 15;
             unsigned d[2][4];                                    // all eight loads are issued before the first is used
-            if (full) {                                          // four consecutive key rows: one address, three strides
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    const int8_t *p0 = vp + (unsigned)(j0 + 4 * ((lane >> 4) + 4 * u)) * ld + 4 * cq;
-#pragma unroll
-                    for (int t = 0; t < 4; t++) d[u][t] = *reinterpret_cast<const unsigned *>(p0 + t * ld);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 2; u++)
-#pragma unroll
-                    for (int t = 0; t < 4; t++)
-                        d[u][t] = *reinterpret_cast<const unsigned *>(vp + (unsigned)min(j0 + 4 * ((lane >> 4) + 4 * u) + t, n - 1) * ld + 4 * cq);
-            }
+            if (i < VT_TILES) load_v_tile(vp, ld, j0, n, lane, d);
             v16i acc;
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[e] = 0;
 #pragma unroll
             for (int ks = 0; ks < 2; ks++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[ks], qf[ks], acc, 0, 0, 0);
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-                const int kq = (lane >> 4) + 4 * u;
-                const unsigned t01l = __builtin_amdgcn_perm(d[u][1], d[u][0], 0x05010400u), t23l = __builtin_amdgcn_perm(d[u][3], d[u][2], 0x05010400u);
-                const unsigned t01h = __builtin_amdgcn_perm(d[u][1], d[u][0], 0x07030602u), t23h = __builtin_amdgcn_perm(d[u][3], d[u][2], 0x07030602u);
-                unsigned *dst = reinterpret_cast<unsigned *>(&slab[w][i * VT_TILE + (4 * cq) * VT_STRIDE_I8 + 4 * kq]);
-                dst[0 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23l, t01l, 0x05040100u);
-                dst[1 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23l, t01l, 0x07060302u);
-                dst[2 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23h, t01h, 0x05040100u);
-                dst[3 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23h, t01h, 0x07060302u);
-            }
+            if (i < VT_TILES) store_vt_tile(d, lane, &slab[w][i * VT_TILE]);
             if (full) {                                          // a full tile needs no masking
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
@@ -190,15 +215,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
     __syncthreads();
-    mx = __builtin_fmaxf(__builtin_fmaxf(smax[0][r], smax[1][r]), __builtin_fmaxf(smax[2][r], smax[3][r]));
+#pragma unroll
+    for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
 
     // tiles past the end are skipped here and below; only a ragged tile holds masked keys (score -inf), whose
     // argument is clamped so that the exponential comes out as 0; in a full tile every argument is finite
     double part = 0.0;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + 4 * i) * 32;
-        if (j0 + 32 <= n) {
+        const int j0 = (w + NW * i) * 32;
+        if (NT <= 4 && j0 + 32 <= n) {                           // (one copy of the exponentials where there are many tiles: the code must fit the cache)
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const float ev = (float)exp_nonpos((double)(sc[i][e] - mx));
@@ -217,22 +243,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     part += __shfl_xor(part, 32, 64);
     if (g == 0) ssum[w][r] = part;
     __syncthreads();
-    const float S = (float)(((ssum[0][r] + ssum[1][r]) + ssum[2][r]) + ssum[3][r]);
+    double total = ssum[0][r];
+#pragma unroll
+    for (int u = 1; u < NW; u++) total += ssum[u][r];
+    const float S = (float)total;
     const float rS = __fdiv_rn(1.0f, S);
 
     // Every accumulator register starts from a zero of its own that the compiler cannot see through: with literal
     // zeros it gives the first product of each path registers of its own and copies all 32 accumulators where the
     // paths join.
-    v16i o[2], o1[PU ? 2 : 1];
+    v16i o[2];
+    int vsum[2] = {0, 0};
 #pragma unroll
     for (int cb = 0; cb < 2; cb++)
 #pragma unroll
-        for (int e = 0; e < 16; e++) { o[cb][e] = opaque_zero(); if (PU) o1[cb][e] = opaque_zero(); }
+        for (int e = 0; e < 16; e++) o[cb][e] = opaque_zero();
     const float lo = PU ? 0.0f : -127.0f, hi = PU ? 255.0f : 127.0f;
-    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + 4 * i) * 32;
+        const int j0 = (w + NW * i) * 32;
+        const int j3 = j0 + 3 * 32 * NW;                          // the tile that takes the place of the one before this
+        unsigned d[2][4];
+        if (i > 0 && i + 3 < NT && j3 < n) load_v_tile(vp, ld, j3, n, lane, d);
         if (j0 < n) {
             v4i pf;
 #pragma unroll
@@ -252,17 +284,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
                 v4i vf;
 #pragma unroll
                 for (int q = 0; q < 4; q++)
-                    vf[q] = *reinterpret_cast<const int *>(&slab[w][i * VT_TILE + (cb * 32 + r) * VT_STRIDE_I8 + 8 * q + 4 * g]);
+                    vf[q] = *reinterpret_cast<const int *>(&slab[w][(i & 3) * VT_TILE + (cb * 32 + r) * VT_STRIDE_I8 + 8 * q + 4 * g]);
                 o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf, vf, o[cb], 0, 0, 0);
-                if (PU) o1[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ones, vf, o1[cb], 0, 0, 0);
+                if (PU) vsum[cb] = add_codes(vf, vsum[cb]);
             }
         }
+        if (i > 0 && i + 3 < NT && j3 < n) store_vt_tile(d, lane, &slab[w][((i + 3) & 3) * VT_TILE]);
     }
     if (PU) {
 #pragma unroll
-        for (int cb = 0; cb < 2; cb++)
+        for (int cb = 0; cb < 2; cb++) {
+            vsum[cb] = 128 * (vsum[cb] + __shfl_xor(vsum[cb], 32, 64));          // the other half's keys
 #pragma unroll
-            for (int e = 0; e < 16; e++) o[cb][e] += o1[cb][e] * 128;
+            for (int e = 0; e < 16; e++) o[cb][e] += vsum[cb];
+        }
     }
     // partial context of this wave: lane holds channel cb*32 + r and queries 8q + 4g + t
 #pragma unroll
@@ -271,18 +306,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         for (int e = 0; e < 16; e++) so(w)[8 * (e >> 2) + 4 * g + (e & 3)][cb * 32 + r] = o[cb][e];
     __syncthreads();
 
-    const int query = tid >> 3, c0 = (tid & 7) * 8;
+    constexpr int CPT = 32 / NW;                                  // channels per thread: 8 or 4
+    const int query = tid / (64 / CPT), c0 = tid % (64 / CPT) * CPT;
     if (q0 + query < n) {
-        int codes[8];
+        int pk[CPT / 4];
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int O = ((so(0)[query][c0 + e] + so(1)[query][c0 + e]) + so(2)[query][c0 + e]) + so(3)[query][c0 + e];
-            codes[e] = qcode((float)O * m_ctx);
+        for (int d = 0; d < CPT / 4; d++) {
+            int codes[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                int O = 0;
+#pragma unroll
+                for (int u = 0; u < NW; u++) O += so(u)[query][c0 + 4 * d + e];
+                codes[e] = qcode((float)O * m_ctx);
+            }
+            pk[d] = pack4(codes[0], codes[1], codes[2], codes[3]);
         }
-        v2i pk = {pack4(codes[0], codes[1], codes[2], codes[3]), pack4(codes[4], codes[5], codes[6], codes[7])};
-        *reinterpret_cast<v2i *>(ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0) = pk;
+        int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0;
+        if constexpr (CPT == 8) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
+        else *reinterpret_cast<int *>(dst) = pk[0];
     }
-    if (HIST && hist[tid]) atomicAdd(&p_hist[tid], (unsigned long long)hist[tid]);   // after the barrier above
+    if (HIST && tid < 256 && hist[tid]) atomicAdd(&p_hist[tid], (unsigned long long)hist[tid]);   // after the barrier above
 }
 
 // ---- QKV GEMM and attention of one (sequence, head) in one kernel ------------------------------------------
@@ -808,16 +852,45 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     }
 }
 
+// The V rows of key tile j0 as a lane transposes them: d[u][t] holds eight channels (8 (lane & 7) ..) of key
+// j0 + 2 ((lane >> 3) + 8 u) + t; and V^T of that tile into LDS, as dwords of two consecutive keys per channel.
+__device__ __forceinline__ void load_v_tile_f16(const __half *vp, unsigned ld, int j0, int n, int lane, v8h (&d)[2][2])
+{
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int t = 0; t < 2; t++)
+            d[u][t] = *reinterpret_cast<const v8h *>(vp + (unsigned)min(j0 + 2 * ((lane >> 3) + 8 * u) + t, n - 1) * ld + 8 * (lane & 7));
+}
+__device__ __forceinline__ void store_vt_tile_f16(const v8h (&d)[2][2], int lane, char *slab)
+{
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const v4i a = __builtin_bit_cast(v4i, d[u][0]), b = __builtin_bit_cast(v4i, d[u][1]);
+        char *dst = slab + 8 * (lane & 7) * VT_STRIDE_F16 + 4 * ((lane >> 3) + 8 * u);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            *reinterpret_cast<unsigned *>(dst + (2 * e) * VT_STRIDE_F16) = __builtin_amdgcn_perm((unsigned)b[e], (unsigned)a[e], 0x05040100u);
+            *reinterpret_cast<unsigned *>(dst + (2 * e + 1) * VT_STRIDE_F16) = __builtin_amdgcn_perm((unsigned)b[e], (unsigned)a[e], 0x07060302u);
+        }
+    }
+}
+
 // FP16 flavour: fp16 q, k, v; binary32 scores, fast exp; P rounded to fp16 before P.V; binary32
 // accumulation of P.V.  Optionally records the largest softmax output (calibration of the P step).
+// Up to 2048 keys (NT = 16 key tiles per wave) the strip of scores stays in registers; the order of all sums is that of the
+// three-sweep kernel, tile by tile, so both give the same bytes.  V rows
+// are transposed in registers two keys at a time (dword stores).  Twelve heads, three sequences of 1100 tokens: 76 -> 51 us, 17 of
+// 301 36.5 -> 30 us.
 template <int NT>
-__global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
                                                             int max_len, int H, float scale, __half *__restrict__ ctx,
                                                             float *__restrict__ p_absmax)
 {
-    // one slab per wave, as in the INT8 kernel: first its V^T tiles, then its partial context for the other waves
-    constexpr int VT_TILE = 64 * VT_STRIDE_F16, SO_BYTES = QB * 64 * 4;
-    constexpr int SLAB = NT * VT_TILE > SO_BYTES ? NT * VT_TILE : SO_BYTES;
+    // one slab per wave, as in the INT8 kernel: first its V^T tiles (two; a further one takes a tile's place when that one has
+    // been multiplied), then its partial context for the other waves
+    constexpr int VT_TILE = 64 * VT_STRIDE_F16, SO_BYTES = QB * 64 * 4, VT_TILES = NT < 2 ? NT : 2;
+    constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
     __shared__ __attribute__((aligned(16))) char slab[4][SLAB];
     auto so = [&](int wave) { return reinterpret_cast<float(*)[64]>(slab[wave]); };
     __shared__ float smax[4][QB];
@@ -834,7 +907,7 @@ __global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__rest
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;
-    const __half *base = qkv + (size_t)sq.t0 * ld + head * 64;
+    const __half *base = qkv + (size_t)sq.t0 * ld + head * 64, *vp = base + 2 * H;
 
     const int qrow = min(q0 + r, n - 1);
     v8h qf[4];
@@ -847,24 +920,17 @@ __global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__rest
     for (int i = 0; i < NT; i++) {
         const int j0 = (w + 4 * i) * 32;
         if (j0 < n) {
-            const int krow = min(j0 + r, n - 1);
-            const __half *kp = base + (unsigned)krow * ld + H;
+            const __half *kp = base + (unsigned)min(j0 + r, n - 1) * ld + H;
+            v8h kf[4], d[2][2];                                  // all loads are issued before the first is used
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++) kf[ks] = *reinterpret_cast<const v8h *>(kp + ks * 16 + g * 8);
+            if (i < VT_TILES) load_v_tile_f16(vp, ld, j0, n, lane, d);
             v16f acc;
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[e] = 0.0f;
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const v8h *>(kp + ks * 16 + g * 8), qf[ks], acc, 0, 0, 0);
-            // stage V^T: lane copies 4 x 8 channels of one key
-            const __half *vp = base + 2 * H;
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int idx = lane + 64 * u, key = idx >> 3, c0 = (idx & 7) * 8;
-                const v8h v = *reinterpret_cast<const v8h *>(vp + (unsigned)min(j0 + key, n - 1) * ld + c0);
-#pragma unroll
-                for (int e = 0; e < 8; e++)
-                    *reinterpret_cast<_Float16 *>(&slab[w][i * VT_TILE + (c0 + e) * VT_STRIDE_F16 + key * 2]) = v[e];
-            }
+            for (int ks = 0; ks < 4; ks++) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[ks], qf[ks], acc, 0, 0, 0);
+            if (i < VT_TILES) store_vt_tile_f16(d, lane, &slab[w][i * VT_TILE]);
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
@@ -905,6 +971,10 @@ __global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__rest
         for (int e = 0; e < 16; e++) o[cb][e] = 0.0f;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
+        const int j1 = (w + 4 * (i + 1)) * 32;                     // the tile that takes the place of the one before this
+        const bool more = i > 0 && i + 1 < NT && j1 < n;
+        v8h d[2][2];
+        if (more) load_v_tile_f16(vp, ld, j1, n, lane, d);
         if ((w + 4 * i) * 32 < n) {
 #pragma unroll
             for (int hf = 0; hf < 2; hf++) {                    // keys 8q+4g+t for q in {2hf, 2hf+1}
@@ -913,7 +983,7 @@ __global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__rest
                 for (int e = 0; e < 8; e++) pf[e] = to_half(sc[i][8 * hf + e] * rS);
 #pragma unroll
                 for (int cb = 0; cb < 2; cb++) {
-                    const char *rowp = &slab[w][i * VT_TILE + (cb * 32 + r) * VT_STRIDE_F16];
+                    const char *rowp = &slab[w][(i & 1) * VT_TILE + (cb * 32 + r) * VT_STRIDE_F16];
                     const v4h lo = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 4 * g) * 2);
                     const v4h hi = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 8 + 4 * g) * 2);
                     const v8h vf = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -921,6 +991,7 @@ __global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__rest
                 }
             }
         }
+        if (more) store_vt_tile_f16(d, lane, &slab[w][((i + 1) & 1) * VT_TILE]);
     }
 #pragma unroll
     for (int cb = 0; cb < 2; cb++)
@@ -939,8 +1010,8 @@ __global__ __launch_bounds__(256) void attention_f16_kernel(const __half *__rest
 }
 
 
-// ---- sequences longer than 512 keys: the same arithmetic as above, tile by tile ---------------------
-// A strip of 32 x n scores no longer fits the registers, so the kernels below sweep the key tiles three
+// ---- sequences whose scores do not fit the registers: the same arithmetic as above, tile by tile ---------------------
+// Beyond 2048 keys (1536 with the binary16 softmax output) the kernels below sweep the key tiles three
 // times: row maxima, row sums, then codes and P.V.  The integer products q.k are recomputed in each
 // sweep (two MFMAs per 32 x 32 tile; exact, so all sweeps see the same scores), the exponentials in the
 // last two.  A wave still owns key tiles w, w+4, ... and visits them in ascending order, so every
@@ -1097,32 +1168,20 @@ __global__ __launch_bounds__(256) void attention_i8_long_kernel(const int8_t *__
 // ---- INT8 attention block whose softmax output stays binary16 (not on the 8-bit grid) ---------------
 // P16 = fl16(e * rS), ctx = rne(fl32(sum_k P16[k] V[k]) * m) with m = s_v / s_ctx.  The sum is evaluated
 // exactly: a binary16 value in [0, 1] is an integer multiple of 2^-24, so P16 * 2^24 is an integer below
-// 2^28 that splits into four 7-bit digits; each digit plane is one more int8 operand for the matrix core
-// (non-negative, so no sign trick), the four int32 products recombine in 64-bit integers, and one
-// conversion rounds the true sum to binary32.
+// 2^25 that splits into four bytes; each byte plane is one more int8 operand for the matrix core (the lower
+// three as byte - 128, with 128 times the sum of V added back; the top byte is 0 or 1), the int32
+// products recombine in 64-bit integers, and one conversion rounds the true sum to binary32.
 
-// V^T of key tile j0 into a wave's own LDS slab: 4 keys x 4 channels byte blocks transposed in registers
+// V^T of key tile j0 into a wave's own LDS slab
 __device__ __forceinline__ void stage_vt_i8(const int8_t *vp, unsigned ld, int j0, int n, int lane, int8_t *slab)
 {
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const int cq = lane & 15, kq = (lane >> 4) + 4 * u;
-        unsigned d[4];
-#pragma unroll
-        for (int t = 0; t < 4; t++)
-            d[t] = *reinterpret_cast<const unsigned *>(vp + (unsigned)min(j0 + 4 * kq + t, n - 1) * ld + 4 * cq);
-        const unsigned t01l = __builtin_amdgcn_perm(d[1], d[0], 0x05010400u), t23l = __builtin_amdgcn_perm(d[3], d[2], 0x05010400u);
-        const unsigned t01h = __builtin_amdgcn_perm(d[1], d[0], 0x07030602u), t23h = __builtin_amdgcn_perm(d[3], d[2], 0x07030602u);
-        unsigned *dst = reinterpret_cast<unsigned *>(&slab[(4 * cq) * VT_STRIDE_I8 + 4 * kq]);
-        dst[0 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23l, t01l, 0x05040100u);
-        dst[1 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23l, t01l, 0x07060302u);
-        dst[2 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23h, t01h, 0x05040100u);
-        dst[3 * (VT_STRIDE_I8 / 4)] = __builtin_amdgcn_perm(t23h, t01h, 0x07060302u);
-    }
+    unsigned d[2][4];
+    load_v_tile(vp, ld, j0, n, lane, d);
+    store_vt_tile(d, lane, slab);
 }
 
 // digit planes of one key tile: ev[e] = fl32(exp(score - max)) of the lane's 16 keys; pf[k] is the int8 operand
-// holding digit k (7 bits) of P16 * 2^24 for those keys
+// holding byte k of P16 * 2^24 for those keys, bytes 0..2 with the top bit flipped (byte - 128 as a signed byte)
 __device__ __forceinline__ void p16_digits(const float (&ev)[16], float rS, v4i (&pf)[4])
 {
 #pragma unroll
@@ -1131,60 +1190,75 @@ __device__ __forceinline__ void p16_digits(const float (&ev)[16], float rS, v4i 
 #pragma unroll
         for (int t = 0; t < 4; t++) fixed[t] = (unsigned)((float)to_half(ev[4 * q + t] * rS) * 16777216.0f);
 #pragma unroll
-        for (int k = 0; k < 4; k++)
-            pf[k][q] = (int)(((fixed[0] >> (7 * k)) & 127u) | (((fixed[1] >> (7 * k)) & 127u) << 8) |
-                             (((fixed[2] >> (7 * k)) & 127u) << 16) | (((fixed[3] >> (7 * k)) & 127u) << 24));
+        for (int k = 0; k < 4; k++) {
+            const unsigned sel = 0x0c0c0000u | (unsigned)((4 + k) << 8) | (unsigned)k;
+            const unsigned lo = __builtin_amdgcn_perm(fixed[1], fixed[0], sel), hi = __builtin_amdgcn_perm(fixed[3], fixed[2], sel);
+            pf[k][q] = (int)(__builtin_amdgcn_perm(hi, lo, 0x05040100u) ^ (k < 3 ? 0x80808080u : 0u));
+        }
     }
 }
 
-// digit planes times the V^T tile in the slab, channel block cb: o[k] += pf[k] . V
-__device__ __forceinline__ void p16_mfma(const v4i (&pf)[4], const int8_t *slab, int cb, int r, int g, v16i (&o)[4])
+// digit planes times the V^T tile in the slab, channel block cb: o[k] += pf[k] . V; vsum: the sum of the lane's V codes
+__device__ __forceinline__ void p16_mfma(const v4i (&pf)[4], const int8_t *slab, int cb, int r, int g, v16i (&o)[4], int &vsum)
 {
     v4i vf;
 #pragma unroll
     for (int q = 0; q < 4; q++) vf[q] = *reinterpret_cast<const int *>(&slab[(cb * 32 + r) * VT_STRIDE_I8 + 8 * q + 4 * g]);
 #pragma unroll
     for (int k = 0; k < 4; k++) o[k] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf[k], vf, o[k], 0, 0, 0);
+    vsum = add_codes(vf, vsum);
 }
 
-// channel block cb: 2^24 times a wave's partial context in 64-bit integers, the four waves added, scaled back
-// (exact) and rounded once to binary32.  Contains block-wide barriers.
-__device__ __forceinline__ void p16_finish(const v16i (&o)[4], int cb, long long (&so)[4][QB][32], float m_ctx,
-                                           int8_t *ctx_rows, int H, int rows_left, int tid)
+// adds 2^24 times a wave's partial context of one channel block to the block's 64-bit sums (exact in any order)
+__device__ __forceinline__ void p16_add(const v16i (&o)[4], int vsum, long long (&so)[QB][32], int r, int g)
 {
-    const int lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
-    const int query = tid >> 3, c0 = (tid & 7) * 4;
-    if (cb) __syncthreads();                                      // the previous block's partials have been read
+    const long long ones = (long long)(vsum + __shfl_xor(vsum, 32, 64)) * (128 * (1 + 256 + 65536));     // the 128s taken off three digits
 #pragma unroll
     for (int e = 0; e < 16; e++) {
-        const long long v = ((((long long)o[3][e] * 128 + o[2][e]) * 128 + o[1][e]) * 128) + o[0][e];
-        so[w][8 * (e >> 2) + 4 * g + (e & 3)][r] = v;
+        const long long v = ((((long long)o[3][e] * 256 + o[2][e]) * 256 + o[1][e]) * 256) + o[0][e] + ones;
+        atomicAdd(reinterpret_cast<unsigned long long *>(&so[8 * (e >> 2) + 4 * g + (e & 3)][r]), (unsigned long long)v);
     }
-    __syncthreads();
-    if (query < rows_left) {
+}
+
+// The block's sums, complete after a barrier: scaled back (exact) and rounded once to binary32.
+template <int NW>
+__device__ __forceinline__ void p16_store(const long long (&so)[2][QB][32], float m_ctx, int8_t *ctx_rows, int H, int rows_left, int tid)
+{
+    constexpr int CPT = 32 / NW;
+    const int query = tid / (64 / CPT), c0 = tid % (64 / CPT) * CPT;
+    if (query >= rows_left) return;
+    int pk[CPT / 4];
+#pragma unroll
+    for (int d = 0; d < CPT / 4; d++) {
         int codes[4];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const long long O = ((so[0][query][c0 + e] + so[1][query][c0 + e]) + so[2][query][c0 + e]) + so[3][query][c0 + e];
-            const float Of = (float)((double)O * 5.9604644775390625e-08);              // * 2^-24
-            codes[e] = qcode(Of * m_ctx);
+            const int c = c0 + 4 * d + e;
+            codes[e] = qcode((float)((double)so[c >> 5][query][c & 31] * 5.9604644775390625e-08) * m_ctx);      // * 2^-24
         }
-        *reinterpret_cast<int *>(ctx_rows + (size_t)query * H + cb * 32 + c0) = pack4(codes[0], codes[1], codes[2], codes[3]);
+        pk[d] = pack4(codes[0], codes[1], codes[2], codes[3]);
     }
+    int8_t *dst = ctx_rows + (size_t)query * H + c0;
+    if constexpr (CPT == 8) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
+    else *reinterpret_cast<int *>(dst) = pk[0];
 }
 
-// NT > 0: up to 128 NT keys, the strip of scores stays in registers (one pass, as attention_i8_kernel);
+// NT > 0: up to 32 NT NW keys, the strip of scores stays in registers (one pass, as attention_i8_kernel);
 // NT == 0: any length, three sweeps (as attention_i8_long_kernel).
-template <int NT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void
+// What bounds it is vector arithmetic, 28 operations of the softmax and 12 of the digits per score, and how many blocks a
+// CU holds: key tiles past a sequence's end cost nothing, the waves' partial contexts meet in one 16 KB array of 64-bit
+// sums instead of an array per wave, and digits are whole bytes (three byte permutes for four keys and a plane).  17
+// sequences of 301 tokens (twelve heads) 51 -> 40 us, three of 1100 110 -> 75 us.
+template <int NT, int NW = 4>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void
 attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, float m_sc, float m_ctx,
                         int8_t *__restrict__ ctx)
 {
     constexpr int NSLAB = NT > 0 ? NT : 1;
-    __shared__ __attribute__((aligned(16))) int8_t vt[4][NSLAB][64 * VT_STRIDE_I8];
-    __shared__ long long so[4][QB][32];
-    __shared__ float smax[4][QB];
-    __shared__ double ssum[4][QB];
+    __shared__ __attribute__((aligned(16))) int8_t vt[NW][NSLAB][64 * VT_STRIDE_I8];
+    __shared__ long long so[2][QB][32];
+    __shared__ float smax[NW][QB];
+    __shared__ double ssum[NW][QB];
 
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -1202,6 +1276,8 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     v4i qf[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ks++) qf[ks] = *reinterpret_cast<const v4i *>(base + (unsigned)qrow * ld + ks * 32 + g * 16);
+#pragma unroll
+    for (int i = 0; i < 2 * QB * 32 / (64 * NW); i++) (&so[0][0][0])[i * 64 * NW + tid] = 0;      // used after two barriers
 
     float scr[NSLAB][16];
     float sc[16];
@@ -1209,19 +1285,18 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     if constexpr (NT > 0) {
 #pragma unroll
         for (int i = 0; i < NT; i++) {
-            const int j0 = (w + 4 * i) * 32;
+            const int j0 = (w + NW * i) * 32;
             if (j0 < n) {
+                unsigned d[2][4];
+                load_v_tile(vp, ld, j0, n, lane, d);             // requested with the keys, not after them
                 score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, scr[i]);
-                stage_vt_i8(vp, ld, j0, n, lane, vt[w][i]);
-            } else {
+                store_vt_tile(d, lane, vt[w][i]);
 #pragma unroll
-                for (int e = 0; e < 16; e++) scr[i][e] = -INFINITY;
+                for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, scr[i][e]);
             }
-#pragma unroll
-            for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, scr[i][e]);
         }
     } else {
-        for (int j0 = w * 32; j0 < n; j0 += 128) {
+        for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
             score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
 #pragma unroll
             for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, sc[e]);
@@ -1230,19 +1305,22 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
     __syncthreads();
-    mx = __builtin_fmaxf(__builtin_fmaxf(smax[0][r], smax[1][r]), __builtin_fmaxf(smax[2][r], smax[3][r]));
+#pragma unroll
+    for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
 
     double part = 0.0;
     if constexpr (NT > 0) {
 #pragma unroll
         for (int i = 0; i < NT; i++)
+            if ((w + NW * i) * 32 < n) {
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                scr[i][e] = (float)exp_nonpos((double)__builtin_fmaxf(scr[i][e] - mx, -746.0f));
-                part += (double)scr[i][e];
+                for (int e = 0; e < 16; e++) {
+                    scr[i][e] = (float)exp_nonpos((double)__builtin_fmaxf(scr[i][e] - mx, -746.0f));
+                    part += (double)scr[i][e];
+                }
             }
     } else {
-        for (int j0 = w * 32; j0 < n; j0 += 128) {
+        for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
             score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
 #pragma unroll
             for (int e = 0; e < 16; e++) part += (double)(float)exp_nonpos((double)__builtin_fmaxf(sc[e] - mx, -746.0f));
@@ -1251,36 +1329,41 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     part += __shfl_xor(part, 32, 64);
     if (g == 0) ssum[w][r] = part;
     __syncthreads();
-    const float S = (float)(((ssum[0][r] + ssum[1][r]) + ssum[2][r]) + ssum[3][r]);
+    double total = ssum[0][r];
+#pragma unroll
+    for (int u = 1; u < NW; u++) total += ssum[u][r];
+    const float S = (float)total;
     const float rS = __fdiv_rn(1.0f, S);
 
-    int8_t *ctx_rows = ctx + (size_t)(sq.t0 + q0) * H + head * 64;
     if constexpr (NT > 0) {
         // the digit planes of all tiles stay in registers; one channel block at a time halves the accumulators
         v4i pf[NT][4];
 #pragma unroll
-        for (int i = 0; i < NT; i++) p16_digits(scr[i], rS, pf[i]);
+        for (int i = 0; i < NT; i++)
+            if ((w + NW * i) * 32 < n) p16_digits(scr[i], rS, pf[i]);
 #pragma unroll
         for (int cb = 0; cb < 2; cb++) {
             v16i o[4];
+            int vsum = 0;
 #pragma unroll
             for (int k = 0; k < 4; k++)
 #pragma unroll
-                for (int e = 0; e < 16; e++) o[k][e] = 0;
+                for (int e = 0; e < 16; e++) o[k][e] = opaque_zero();
 #pragma unroll
             for (int i = 0; i < NT; i++)
-                if ((w + 4 * i) * 32 < n) p16_mfma(pf[i], vt[w][i], cb, r, g, o);
-            p16_finish(o, cb, so, m_ctx, ctx_rows, H, n - q0, tid);
+                if ((w + NW * i) * 32 < n) p16_mfma(pf[i], vt[w][i], cb, r, g, o, vsum);
+            if (w * 32 < n) p16_add(o, vsum, so[cb], r, g);
         }
     } else {
         v16i o[2][4];                                         // [channel block][digit plane]
+        int vsum[2] = {0, 0};
 #pragma unroll
         for (int cb = 0; cb < 2; cb++)
 #pragma unroll
             for (int k = 0; k < 4; k++)
 #pragma unroll
                 for (int e = 0; e < 16; e++) o[cb][k][e] = 0;
-        for (int j0 = w * 32; j0 < n; j0 += 128) {
+        for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
             score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
             // the slab is written and read by this wave only, in program order
             __builtin_amdgcn_wave_barrier();
@@ -1290,12 +1373,14 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
             for (int e = 0; e < 16; e++) sc[e] = (float)exp_nonpos((double)__builtin_fmaxf(sc[e] - mx, -746.0f));
             v4i pf[4];
             p16_digits(sc, rS, pf);
-            p16_mfma(pf, vt[w][0], 0, r, g, o[0]);
-            p16_mfma(pf, vt[w][0], 1, r, g, o[1]);
+            p16_mfma(pf, vt[w][0], 0, r, g, o[0], vsum[0]);
+            p16_mfma(pf, vt[w][0], 1, r, g, o[1], vsum[1]);
         }
-        p16_finish(o[0], 0, so, m_ctx, ctx_rows, H, n - q0, tid);
-        p16_finish(o[1], 1, so, m_ctx, ctx_rows, H, n - q0, tid);
+        p16_add(o[0], vsum[0], so[0], r, g);
+        p16_add(o[1], vsum[1], so[1], r, g);
     }
+    __syncthreads();
+    p16_store<NW>(so, m_ctx, ctx + (size_t)(sq.t0 + q0) * H + head * 64, H, n - q0, tid);
 }
 
 __device__ __forceinline__ void score_tile_f16(const __half *base, unsigned ld, int H, int j0, int n, int r, int g,
@@ -1375,14 +1460,9 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
     for (int j0 = w * 32; j0 < n; j0 += 128) {
         score_tile_f16(base, ld, H, j0, n, r, g, qf, scale, sc);
         __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int idx = lane + 64 * u, key = idx >> 3, c0 = (idx & 7) * 8;
-            const v8h v = *reinterpret_cast<const v8h *>(vp + (unsigned)min(j0 + key, n - 1) * ld + c0);
-#pragma unroll
-            for (int e = 0; e < 8; e++)
-                *reinterpret_cast<_Float16 *>(&vt[w][(c0 + e) * VT_STRIDE_F16 + key * 2]) = v[e];
-        }
+        v8h d[2][2];
+        load_v_tile_f16(vp, ld, j0, n, lane, d);
+        store_vt_tile_f16(d, lane, vt[w]);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int hf = 0; hf < 2; hf++) {
@@ -1418,6 +1498,22 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
 
 }  // namespace
 
+// 513 to 2048 tokens: eight waves, a wave's NT key tiles as few as the longest sequence allows (registers and LDS, and with
+// them the blocks per CU, follow NT)
+template <bool PU>
+static void launch_attention_i8_8waves(const int8_t *qkv, const int *cu, int max_len, int H, float m_sc, float inv_sp, float m_ctx,
+                                       int8_t *ctx, dim3 grid, hipStream_t st, const Timing *tm)
+{
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, (unsigned long long *)nullptr); };
+    switch ((max_len + 255) / 256) {
+    case 3: return go(attention_i8_kernel<3, PU, false, 8>);
+    case 4: return go(attention_i8_kernel<4, PU, false, 8>);
+    case 5: return go(attention_i8_kernel<5, PU, false, 8>);
+    case 6: return go(attention_i8_kernel<6, PU, false, 8>);
+    default: return go(attention_i8_kernel<8, PU, false, 8>);
+    }
+}
+
 template <bool PU, bool HIST>
 static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
                                         float inv_sp, float m_ctx, int8_t *ctx, unsigned long long *p_hist, hipStream_t st,
@@ -1432,6 +1528,8 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
         launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
     else if (max_len <= ONE_PASS_MAX_LEN)
         launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
+    else if (!HIST && max_len <= 8 * 256)
+        launch_attention_i8_8waves<PU>(qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, grid, st, tm);
     else
         launch_kernel(attention_i8_long_kernel<PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
 }
@@ -1510,26 +1608,35 @@ hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const 
 hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
                                    float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm)
 {
-    dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B), block(256);
-    if (max_len <= 128) launch_kernel(attention_i8_p16_kernel<1>, grid, block, 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx);
-    else if (max_len <= 256) launch_kernel(attention_i8_p16_kernel<2>, grid, block, 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx);
-    else if (max_len <= ONE_PASS_MAX_LEN) launch_kernel(attention_i8_p16_kernel<4>, grid, block, 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx);
-    else launch_kernel(attention_i8_p16_kernel<0>, grid, block, 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx);
+    dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
+    auto go = [&](auto kern, int waves) { launch_kernel(kern, grid, dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx); };
+    if (max_len <= 128) go(attention_i8_p16_kernel<1>, 4);
+    else if (max_len <= 256) go(attention_i8_p16_kernel<2>, 4);
+    else if (max_len <= 384) go(attention_i8_p16_kernel<3>, 4);
+    else if (max_len <= ONE_PASS_MAX_LEN) go(attention_i8_p16_kernel<4>, 4);
+    else if (max_len <= 1024) go(attention_i8_p16_kernel<4, 8>, 8);
+    else if (max_len <= 1536) go(attention_i8_p16_kernel<6, 8>, 8);      // (beyond, V^T and the sums do not fit LDS together)
+    else go(attention_i8_p16_kernel<0>, 4);
     return hipGetLastError();
 }
 
 hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max_len, int H, int heads, float scale,
                                 __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm)
 {
-    dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B), block(256);
-    if (max_len <= 128)
-        launch_kernel(attention_f16_kernel<1>, grid, block, 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax);
-    else if (max_len <= 256)
-        launch_kernel(attention_f16_kernel<2>, grid, block, 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax);
-    else if (max_len <= ONE_PASS_MAX_LEN)
-        launch_kernel(attention_f16_kernel<4>, grid, block, 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax);
-    else
-        launch_kernel(attention_f16_long_kernel, grid, block, 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax);
+    dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax); };
+    switch ((max_len + 127) / 128) {                              // key tiles per wave
+    case 1: go(attention_f16_kernel<1>); break;
+    case 2: go(attention_f16_kernel<2>); break;
+    case 3: go(attention_f16_kernel<3>); break;
+    case 4: go(attention_f16_kernel<4>); break;
+    case 5: case 6: go(attention_f16_kernel<6>); break;
+    case 7: case 8: go(attention_f16_kernel<8>); break;
+    case 9: case 10: go(attention_f16_kernel<10>); break;
+    case 11: case 12: go(attention_f16_kernel<12>); break;
+    case 13: case 14: case 15: case 16: go(attention_f16_kernel<16>); break;
+    default: go(attention_f16_long_kernel);
+    }
     return hipGetLastError();
 }
 

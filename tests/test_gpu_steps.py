@@ -509,6 +509,39 @@ def test_long_kernel_equals_one_pass_kernel_on_short_sequences(P):
     assert np.array_equal(mixed[cu[1]:], short)
 
 
+@pytest.mark.parametrize("longest", [640, 641, 769, 1025, 1281, 1537, 1793, 2048])
+def test_every_number_of_key_tiles_per_wave(P, longest):
+    """Lengths on either side of each step of the dispatch (tiles held per wave, the V^T tiles that take turns in LDS), with
+    short sequences whose later tiles do not exist: INT8 in its three softmax forms bit-exact, FP16 within tolerance."""
+    rng = np.random.default_rng(longest)
+    heads, lens = 1, [longest, 33, longest - 1, 1, 257]
+    cu = _cu(lens)
+    qkv = np.clip(np.rint(rng.standard_normal((int(cu[-1]), 3 * 64)) * 26), -127, 127).astype(np.int8)
+    sc = (0.0209, 0.0249, 0.021, 0.0003, 0.0021)
+    for kw in ({}, {"p_unsigned": True}):
+        want = oracle.attention_i8(qkv, cu, heads, *sc, **kw)
+        assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), longest, heads, *sc, **kw)), want)
+        assert np.abs(want).max() > 10
+    want = oracle.attention_i8_p16(qkv, cu, heads, sc[0], sc[1], sc[2], sc[4])
+    assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), longest, heads, *sc, p_fp16=True)), want)
+    f = (rng.standard_normal((int(cu[-1]), 3 * 64)) * 0.6).astype(np.float16)
+    want = oracle.attention_f16(f, cu, heads).astype(np.float64)
+    assert np.abs(host(P.attention_f16(dev(f), dev(cu), longest, heads)).astype(np.float64) - want).max() <= 2e-3
+
+
+def test_fp16_attention_is_the_same_bytes_in_one_pass_and_in_three_sweeps(P):
+    """A batch whose longest sequence exceeds 2048 tokens takes the three-sweep kernel; its other sequences must come out as
+    they do alone, where the scores of every length stay in registers."""
+    rng = np.random.default_rng(5)
+    heads, lens = 2, [2049, 130, 700, 390, 1500]
+    cu = _cu(lens)
+    f = (rng.standard_normal((int(cu[-1]), 3 * 64 * heads)) * 0.6).astype(np.float16)
+    mixed = host(P.attention_f16(dev(f), dev(cu), max(lens), heads))
+    for b in range(1, len(lens)):
+        alone = host(P.attention_f16(dev(f[cu[b]:cu[b + 1]]), dev(_cu(lens[b:b + 1])), lens[b], heads))
+        assert np.array_equal(mixed[cu[b]:cu[b + 1]].view(np.uint16), alone.view(np.uint16))
+
+
 # ------------------------------------------------------------------ fused bias + residual + LayerNorm (+ quant)
 @pytest.mark.parametrize("H", [128, 768, 1024])
 @pytest.mark.parametrize("in8,res8,out8", [(1, 1, 1), (1, 1, 0), (0, 0, 1), (0, 0, 0), (1, 0, 1), (0, 1, 0)])
