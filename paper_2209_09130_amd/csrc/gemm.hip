@@ -89,6 +89,13 @@ struct EpiRequant {                               // code = rne(fmaf(acc, m[n], 
     typedef int pack_t;
     __device__ __forceinline__ void load_tables(float *tab, int n0, int bn, int tid, int nthreads) const
     { copy_table(tab, m, n0, bn, tid, nthreads); copy_table(tab + bn, b, n0, bn, tid, nthreads); }
+    // four consecutive channels of one token
+    __device__ __forceinline__ int four(const v4i &acc, const float *tab, int bn, int n) const
+    {
+        const v4f mm = *reinterpret_cast<const v4f *>(tab + n), bb = *reinterpret_cast<const v4f *>(tab + bn + n);
+        return pack_codes(code_bits(__builtin_fmaf((float)acc.x, mm.x, bb.x)), code_bits(__builtin_fmaf((float)acc.y, mm.y, bb.y)),
+                          code_bits(__builtin_fmaf((float)acc.z, mm.z, bb.z)), code_bits(__builtin_fmaf((float)acc.w, mm.w, bb.w)));
+    }
     struct Tab { v4f m[4], b[4]; };
     __device__ __forceinline__ Tab load_tab(const float *tab, int bn, int n_loc, int g) const { return load_tab_mb<Tab>(tab, bn, n_loc, g); }
     __device__ __forceinline__ void tile(const v16i &acc, const Tab &t, const float *tab, int bn, int n_loc, int g, int (&pk)[4]) const
@@ -178,6 +185,19 @@ struct EpiGeluTable {
         copy_table(tab + bn, bias, n0, bn, tid, nthreads);
         v2i *lut = reinterpret_cast<v2i *>(tab + 2 * bn);
         for (int i = tid; i < bins; i += nthreads) lut[i] = reinterpret_cast<const v2i *>(entries)[i];
+    }
+    __device__ __forceinline__ int four(const v4i &acc, const float *tab, int bn, int n) const
+    {
+        const v2i *lut = reinterpret_cast<const v2i *>(tab + 2 * bn);
+        const v4f mm = *reinterpret_cast<const v4f *>(tab + n), bb = *reinterpret_cast<const v4f *>(tab + bn + n);
+        unsigned c[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const float y = __builtin_fmaf((float)acc[k], mm[k], bb[k]);
+            const v2i e = lut[__float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(y, rate, offset), 8388608.0f, t_max)) - 0x4B000000u];
+            c[k] = (y >= __int_as_float(e.x) ? (unsigned)e.y >> 8 : (unsigned)e.y) & 0xffu;
+        }
+        return (int)(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24);
     }
     struct Tab { v4f m[4], b[4]; };
     __device__ __forceinline__ Tab load_tab(const float *tab, int bn, int n_loc, int g) const { return load_tab_mb<Tab>(tab, bn, n_loc, g); }
@@ -764,6 +784,282 @@ hipError_t launch_longk(const void *A, const void *W, void *out, const Epi &epi,
     return hipGetLastError();
 }
 
+// ---- few token rows ----------------------------------------------------------------------------------
+// Up to a few hundred token rows a GEMM of the path is a chain of latencies, not of work: the matrix instructions of a tile
+// take tens of nanoseconds, the loop over K stages above pays one memory latency per ring refill.  Here a block computes a small
+// tile (16 MT tokens x 16 NT channels) with its NWAVES waves splitting K: every wave streams its own share of the 128-byte
+// slabs of both operands through LDS of its own (direct loads, up to R slabs requested before the first is used, no barrier
+// in the loop) and forms the whole tile for that share; the int32 partial tiles meet in LDS behind the block's only
+// barrier.  Integer sums do not depend on the order, so the result is the same bytes as from every other configuration.
+// Blocks are numbered channels outermost, so that an XCD reads an eighth of the weights and all of the few token rows.
+template <class Epi, int MT, int NT, int NWAVES, int R>
+struct SmallGemm {
+    static constexpr int BM = 16 * MT, BN = 16 * NT, SLAB = (BM + BN) * 128, PIECES = SLAB / 1024;
+    static constexpr int RING_BYTES = NWAVES * R * SLAB, PART_BYTES = NWAVES * MT * NT * 1024;
+    static constexpr int TAB_OFF = RING_BYTES > PART_BYTES ? RING_BYTES : PART_BYTES;
+};
+
+template <class Epi, int MT, int NT, int NWAVES, int R>
+__global__ __launch_bounds__(64 * NWAVES)
+void gemm_nt_small_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, Epi epi, int host_rows,
+                          const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+{
+    typedef SmallGemm<Epi, MT, NT, NWAVES, R> G;
+    constexpr int BM = G::BM, BN = G::BN;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    float *tab = reinterpret_cast<float *>(lds + G::TAB_OFF);
+    const int M = dev_rows ? *dev_rows : host_rows;
+    const int tiles_m = (M + BM - 1) / BM, tiles = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= tiles) return;
+    const int tile = xcd_contiguous(blockIdx.x, tiles);
+    const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // pieces of 8 rows x 128 bytes, the token rows first; the wave takes slabs wave, wave + NWAVES, ...
+    const char *src[G::PIECES];
+#pragma unroll
+    for (int j = 0; j < G::PIECES; j++) {
+        const int row = 8 * j + (lane >> 3), chunk = ((lane & 7) ^ swz<128>(row)) << 4;
+        src[j] = (j < BM / 8 ? A + (size_t)min(m0 + row, M - 1) * Kbytes : W + (size_t)(n0 + row - BM) * Kbytes) + chunk + wave * 128;
+    }
+    char *ring = lds + wave * (R * G::SLAB);
+    auto issue = [&](int s, int slot) {
+#pragma unroll
+        for (int j = 0; j < G::PIECES; j++)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + (size_t)s * (NWAVES * 128)),
+                                             (__attribute__((address_space(3))) void *)(ring + slot * G::SLAB + j * 1024), 16, 0, 0);
+    };
+    const int slabs = Kbytes / (128 * NWAVES);                                   // of this wave (the launcher checks that they are whole)
+#pragma unroll
+    for (int s = 0; s < R; s++)
+        if (s < slabs) issue(s, s);
+    epi.load_tables(tab, n0, BN, tid, 64 * NWAVES);
+
+    v4i acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; i++)
+#pragma unroll
+        for (int j = 0; j < NT; j++) acc[i][j] = v4i{0, 0, 0, 0};
+    const int r = lane & 15, q = lane >> 4;
+    auto consume = [&](int slot) {
+        const char *a = ring + slot * G::SLAB;
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            v4i fa[MT], fw[NT];
+#pragma unroll
+            for (int i = 0; i < MT; i++) fa[i] = *reinterpret_cast<const v4i *>(a + (16 * i + r) * 128 + (((4 * k + q) ^ swz<128>(16 * i + r)) << 4));
+#pragma unroll
+            for (int j = 0; j < NT; j++)
+                fw[j] = *reinterpret_cast<const v4i *>(a + (BM + 16 * j + r) * 128 + (((4 * k + q) ^ swz<128>(BM + 16 * j + r)) << 4));
+#pragma unroll
+            for (int i = 0; i < MT; i++)
+#pragma unroll
+                for (int j = 0; j < NT; j++) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fw[j], fa[i], acc[i][j], 0, 0, 0);
+        }
+    };
+    // a wave waits for its own loads only; every wait below lets the slabs behind the one needed stay in flight
+    int s = 0;
+    for (; s + R < slabs; s += R)
+#pragma unroll
+        for (int u = 0; u < R; u++) {
+            if (s + u + R - 1 < slabs) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 1) * G::PIECES) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            consume(u);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                  // the slot has been read
+            if (s + u + R < slabs) issue(s + u + R, u);
+        }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < R; u++)
+        if (s + u < slabs) consume(u);
+
+    // partial tiles take the ring's place: [wave][tile][lane]
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MT; i++)
+#pragma unroll
+        for (int j = 0; j < NT; j++) *reinterpret_cast<v4i *>(lds + ((wave * MT + i) * NT + j) * 1024 + lane * 16) = acc[i][j];
+    __syncthreads();
+    // lane: token 16 i + (lane & 15), channels 16 j + 4 (lane >> 4) .. + 3
+    for (int t = wave; t < MT * NT; t += NWAVES) {
+        v4i sum = {0, 0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < NWAVES; w++) sum += *reinterpret_cast<const v4i *>(lds + (w * MT * NT + t) * 1024 + lane * 16);
+        const int i = t / NT, j = t % NT, row = m0 + 16 * i + r, nl = 16 * j + 4 * q;
+        const int pk = epi.four(sum, tab, BN, nl);
+        if (row < M) *reinterpret_cast<int *>(out + (size_t)row * N + n0 + nl) = pk;
+    }
+}
+
+template <class Epi, int MT, int NT, int NWAVES, int R>
+hipError_t launch_small(const void *A, const void *W, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
+{
+    typedef SmallGemm<Epi, MT, NT, NWAVES, R> G;
+    const size_t LDS = G::TAB_OFF + (size_t)Epi::NTAB * G::BN * sizeof(float) + extra_lds_of(epi, 0);
+    if (N % G::BN || K % (128 * NWAVES) || LDS > 160 * 1024) return hipErrorInvalidValue;
+    auto kern = gemm_nt_small_kernel<Epi, MT, NT, NWAVES, R>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set.store(true, std::memory_order_release);
+    }
+    const int tiles_n = N / G::BN, tiles_m = (rows.host_rows + G::BM - 1) / G::BM;
+    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(64 * NWAVES), LDS, st, tm, (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows,
+                  rows.dev_rows, N, K, tiles_n);
+    return hipGetLastError();
+}
+
+// The smallest of four tiles that the chip holds all at once (blocks per CU by LDS): a second round of blocks costs more than a
+// larger tile.  hipErrorNotSupported: none, the problem has enough rows for the kernels above (or a K they split differently).
+// Measured, us per launch in a chain (before: the 64 x 96 and 64 x 128 tiles of configuration 2): N x K = 768 x 3072, 19 rows
+// 9.9 -> 3.7, 256 rows 10.7 -> 4.7, 1024 rows 10.7 -> 7.7; 768 x 768, 19 rows 4.3 -> 2.5, 1024 rows 5.3 -> 4.1; 2304 x 768,
+// 128 rows 5.2 -> 3.4.
+template <class Epi, int MT, int NT, int NWAVES, int R>
+bool small_fits(const Epi &epi, Rows rows, int N)
+{
+    typedef SmallGemm<Epi, MT, NT, NWAVES, R> G;
+    if (N % G::BN) return false;
+    const size_t lds = G::TAB_OFF + (size_t)Epi::NTAB * G::BN * sizeof(float) + extra_lds_of(epi, 0);
+    const long per_cu = std::min<long>((long)(160 * 1024 / lds), 2048 / (64 * NWAVES));
+    return (long)(N / G::BN) * ((rows.host_rows + G::BM - 1) / G::BM) <= 256 * per_cu;
+}
+template <class Epi, int NWAVES, int R1, int R2>
+hipError_t launch_small_waves(const void *A, const void *W, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
+{
+    if (small_fits<Epi, 2, 1, NWAVES, R1>(epi, rows, N)) return launch_small<Epi, 2, 1, NWAVES, R1>(A, W, out, epi, rows, N, K, st, tm);
+    if (small_fits<Epi, 2, 2, NWAVES, R2>(epi, rows, N)) return launch_small<Epi, 2, 2, NWAVES, R2>(A, W, out, epi, rows, N, K, st, tm);
+    if (small_fits<Epi, 4, 2, NWAVES, 1>(epi, rows, N)) return launch_small<Epi, 4, 2, NWAVES, 1>(A, W, out, epi, rows, N, K, st, tm);
+    if (small_fits<Epi, 4, 4, NWAVES, 1>(epi, rows, N)) return launch_small<Epi, 4, 4, NWAVES, 1>(A, W, out, epi, rows, N, K, st, tm);
+    return hipErrorNotSupported;
+}
+template <class Epi>
+hipError_t launch_small_any(const void *A, const void *W, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
+{
+    if (K % 1024 == 0) {                                          // eight waves; rings as deep as LDS allows where a wave has more than one slab
+        if (K > 1024) return launch_small_waves<Epi, 8, 3, 2>(A, W, out, epi, rows, N, K, st, tm);
+        return launch_small_waves<Epi, 8, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
+    }
+    if (K % 768 == 0) return launch_small_waves<Epi, 6, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
+    return hipErrorNotSupported;
+}
+
+// The FP16 counterpart.  Binary32 sums are formed in K order whatever the tile, so K is not split; what four waves share is the
+// issue of the loads (one wave that loads and multiplies spends most of its time issuing loads: 768 x 3072, 19 rows, 13 us).
+// A block of four waves computes 32 tokens x 32 CW channels: all waves stream the operands through an R-deep ring of stages of
+// four 128-byte slabs, wave w loading slab w, and the first CW waves each multiply one 32 x 32 tile.
+template <int CW, int R>
+__global__ __launch_bounds__(256)
+void gemm_nt_small_f16_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, EpiF16 epi, int host_rows,
+                              const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+{
+    constexpr int BM = 32, BN = 32 * CW, SLAB = (BM + BN) * 128, PIECES = SLAB / 1024, STAGE = 4 * SLAB;
+    static_assert(R >= 2 && (R - 1) * PIECES < 64, "wait count range");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int M = dev_rows ? *dev_rows : host_rows;
+    const int tiles_m = (M + BM - 1) / BM, tiles = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= tiles) return;
+    const int tile = xcd_contiguous(blockIdx.x, tiles);
+    const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 31, g = lane >> 5;
+    const char *src[PIECES];
+#pragma unroll
+    for (int j = 0; j < PIECES; j++) {
+        const int row = 8 * j + (lane >> 3), chunk = ((lane & 7) ^ swz<128>(row)) << 4;
+        src[j] = (j < BM / 8 ? A + (size_t)min(m0 + row, M - 1) * Kbytes : W + (size_t)(n0 + row - BM) * Kbytes) + chunk + wave * 128;
+    }
+    auto issue = [&](int st, int slot) {
+#pragma unroll
+        for (int j = 0; j < PIECES; j++)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + (size_t)st * 512),
+                                             (__attribute__((address_space(3))) void *)(lds + slot * STAGE + wave * SLAB + j * 1024), 16, 0, 0);
+    };
+    const int stages = Kbytes / 512;
+#pragma unroll
+    for (int s = 0; s < R - 1; s++)
+        if (s < stages) issue(s, s);
+    v16f acc;
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.0f;
+    const unsigned lbase = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    unsigned off[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) off[k] = lbase + r * 128 + (((2 * k + g) ^ swz<128>(r)) << 4);
+    const int w_off = (BM + 32 * wave) * 128;
+    int slot = 0, fill = R - 1;
+    for (int st = 0; st < stages; st++) {
+        if (st + R - 2 < stages) wait_vm_and_barrier<(R - 2) * PIECES>(); else wait_vm_and_barrier<0>();
+        if (st + R - 1 < stages) issue(st + R - 1, fill);          // takes the place of the stage read before the barrier
+        if (wave < CW) {
+            // fragments of slab u + 1 are on their way from LDS while slab u is multiplied
+            v4i fa[2][4], fw[2][4];
+            auto fetch = [&](int u) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    fa[u & 1][k] = lds_read128<0>(off[k] + slot * STAGE + u * SLAB);
+                    fw[u & 1][k] = lds_read128<0>(off[k] + slot * STAGE + u * SLAB + w_off);
+                }
+            };
+            fetch(0);
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (u < 3) { fetch(u + 1); wait_lds_reads<8>(); } else wait_lds_reads<0>();
+                tie(fa[u & 1], std::make_integer_sequence<int, 4>());
+                tie(fw[u & 1], std::make_integer_sequence<int, 4>());
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 4; k++) acc = F16::mma(fw[u & 1][k], fa[u & 1][k], acc);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        slot = slot + 1 == R ? 0 : slot + 1;
+        fill = fill + 1 == R ? 0 : fill + 1;
+    }
+    if (wave >= CW) return;
+    const int row = m0 + r, n = n0 + 32 * wave + 4 * g;
+    EpiF16::Tab t;
+#pragma unroll
+    for (int q = 0; q < 4; q++) t.b[q] = epi.bias ? *reinterpret_cast<const v4f *>(epi.bias + n + 8 * q) : v4f{0.f, 0.f, 0.f, 0.f};
+    v2i pk[4];
+    epi.tile(acc, t, nullptr, BN, 0, g, pk);
+    if (row < M) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) *reinterpret_cast<v2i *>(out + ((size_t)row * N + n + 8 * q) * 2) = pk[q];
+    }
+}
+
+template <int CW, int R>
+hipError_t launch_small_f16(const void *A, const void *W, void *out, const EpiF16 &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
+{
+    const size_t LDS = (size_t)R * (32 + 32 * CW) * 512;
+    if (N % (32 * CW) || K % 256) return hipErrorInvalidValue;
+    auto kern = gemm_nt_small_f16_kernel<CW, R>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set.store(true, std::memory_order_release);
+    }
+    const int tiles_n = N / (32 * CW), tiles_m = (rows.host_rows + 31) / 32;
+    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows,
+                  rows.dev_rows, N, K * 2, tiles_n);
+    return hipGetLastError();
+}
+
+// As for INT8: the smallest tile that the chip holds all at once.  Us per launch in a chain (before: 64 x 96 tiles): 768 x 3072,
+// 19 rows 17.4 -> 10.8, 427 rows 17.8 -> 11.8; 768 x 768, 19 rows 6.0 -> 4.2; 2304 x 768, 128 rows 7.6 -> 5.6.  The widest tile
+// reads its operands too slowly for long rows (768 x 3072, 1024 rows: 19.5 against 17.9 us).
+hipError_t launch_small_f16_any(const void *A, const void *W, void *out, const EpiF16 &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
+{
+    if (K % 256) return hipErrorNotSupported;
+    const long tiles_m = (rows.host_rows + 31) / 32;
+    if (N % 32 == 0 && tiles_m * (N / 32) <= 512) return launch_small_f16<1, 2>(A, W, out, epi, rows, N, K, st, tm);      // two blocks per CU
+    if (N % 64 == 0 && tiles_m * (N / 64) <= 256) return launch_small_f16<2, 2>(A, W, out, epi, rows, N, K, st, tm);
+    if (N % 128 == 0 && K <= 1024 && tiles_m * (N / 128) <= 256) return launch_small_f16<4, 2>(A, W, out, epi, rows, N, K, st, tm);
+    return hipErrorNotSupported;
+}
+
 // Tile configuration per problem shape.  What bounds the main loop on this chip is the rate at which
 // a CU pulls operand stages out of L2 (20 to 40 bytes per clock per CU, whichever way they are loaded),
 // so small problems want many small tiles (more CUs pulling), large ones the larger tile (less traffic):
@@ -773,6 +1069,10 @@ hipError_t launch_longk(const void *A, const void *W, void *out, const Epi &epi,
 //      3072 bytes or more (FFN2) get a 3-deep ring (72 KB, still two blocks per CU) when there is at most one
 //      block per CU: -4 % on the BERT-base forward (with more blocks than CUs it measured slower); a 4-deep ring is faster for the kernel alone but crowds out the other group's kernels
 constexpr int LONG_K_BYTES = 3072;
+// From 2048 rows the wide GEMMs fill the chip with 128 x 192 tiles; below they leave most CUs idle (us per launch in a chain, 128 x
+// 192 against 64 x 128 tiles at 1024 rows: 2304 x 768 9.8 / 7.4, FFN1 3072 x 768 12.1 / 9.1, FFN1 4096 x 1024 17.3 / 11.8, FP16 2304 x
+// 768 17.9 / 12.1; at 1536 rows 9.9 / 7.8, 12.3 / 11.7, 17.5 / 15.2, 18.2 / 13.0)
+constexpr int WIDE_TILE_MIN_ROWS = 2048;
 constexpr int BIG_TILE_MIN_ROWS = 16384;                         // from here on the 256 x 256 tiles fill the chip several times over
 
 constexpr int big_tile_width(int cfg) { return cfg == 6 ? 192 : 256; }
@@ -784,7 +1084,7 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
     int cfg = gemm_config_override.load(std::memory_order_relaxed);
     const bool forced = cfg >= 0;
     const int kbytes = K * T::ELEM;
-    if (cfg >= 3 && (N % big_tile_width(cfg) || kbytes % 128)) cfg = -1;   // whole columns of tiles, whole 128-byte stages
+    if (cfg >= 3 && cfg < 8 && (N % big_tile_width(cfg) || kbytes % 128)) cfg = -1;   // whole columns of tiles, whole 128-byte stages
     if (cfg >= 0 && cfg < 3 && kbytes % 128) cfg = 0;
     if (cfg < 0) {
         if (kbytes % 128) cfg = 0;
@@ -793,19 +1093,31 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
             // fewer 128 x 128 tiles than CUs: the smaller tiles of configuration 2 (BERT-large's 1024-wide GEMMs at
             // 4096 tokens, 256 tiles, measured -4.4 % on that forward with 128 x 128 against 64 x 128)
             cfg = tiles < 256 ? 2 : 1;
-            // wide GEMMs (QKV, FFN1) from about a thousand tokens: 128 x 192 tiles, 64 x 96 per wave, two blocks
+            // wide GEMMs (QKV, FFN1): 128 x 192 tiles, 64 x 96 per wave, two blocks
             // per CU.  Measured in the BERT-base forward at 2 x 2048 tokens: -5 % with FFN1 (whose table-lookup epilogue
             // in the 64 x 128 configuration costs more than it saves: its table in LDS takes the third resident block
             // away), another -1.4 % with QKV; the FP16 forward gains 2 %
-            if (N % 192 == 0 && N >= 2304 && rows.host_rows >= 1024) cfg = 6;
+            if (N % 192 == 0 && N >= 2304 && rows.host_rows >= WIDE_TILE_MIN_ROWS) cfg = 6;
             // widths that 192 does not divide (FFN1 of BERT-large, 4096): 128 x 256 tiles (-3.5 % on that forward
             // at 2 x 4096 tokens against 128 x 128; 256 x 128 -0.5 %, 64 x 128 +5.5 %)
-            else if (N % 256 == 0 && N >= 2304 && rows.host_rows >= 1024) cfg = 4;
+            else if (N % 256 == 0 && N >= 2304 && rows.host_rows >= WIDE_TILE_MIN_ROWS) cfg = 4;
             // many tokens (INT8): wave tiles of 64 x 128 halve the LDS operand traffic per MFMA, two such blocks
             // per CU overlap one's epilogue with the other's main loop; long operand rows amortise the epilogue of a
             // 256 x 256 tile by themselves
             if (std::is_same<T, I8>::value && N % 256 == 0 && rows.host_rows >= BIG_TILE_MIN_ROWS)
                 cfg = kbytes >= LONG_K_BYTES ? 7 : 4;
+        }
+    }
+    if constexpr (std::is_same<T, I8>::value && (std::is_same<Epi, EpiRequant>::value || std::is_same<Epi, EpiGeluTable>::value)) {
+        if (!forced) {
+            const hipError_t e = launch_small_any<Epi>(A, W, out, epi, rows, N, K, st, tm);
+            if (e != hipErrorNotSupported) return e;
+        }
+    }
+    if constexpr (std::is_same<T, F16>::value) {
+        if (!forced) {
+            const hipError_t e = launch_small_f16_any(A, W, out, epi, rows, N, K, st, tm);
+            if (e != hipErrorNotSupported) return e;
         }
     }
     switch (cfg) {

@@ -259,6 +259,46 @@ def test_fp16_gemm_within_accumulation_tolerance(P, M, N, K, bias, gelu):
     assert (got != want).mean() < 5e-3
 
 
+# ------------------------------------------------------------------ few token rows
+@pytest.mark.parametrize("K,N", [(768, 768), (1024, 2304), (1536, 256), (3072, 768), (4096, 1024)])
+def test_int8_gemm_of_few_rows_bit_exact(P, K, N):
+    """Row counts on either side of the edges of the small tiles (and of the steps from one tile to the next), with K split
+    over six or eight waves that hold one or several slabs each; both epilogues."""
+    rng = np.random.default_rng(K + N)
+    W = rng.integers(-127, 128, (N, K), dtype=np.int8)
+    s_w, bias = _tables(rng, N)
+    m, b = oracle.fold_requant(0.037, s_w, bias, 0.021 * np.sqrt(K / 768))
+    mg, s_out = oracle.fold_dequant(0.05 * np.sqrt(768 / K), s_w), 0.0147
+    spec, entries = P.gelu_table_build(s_out)
+    table = (spec, dev(entries.view(np.int32)))
+    for M in (1, 16, 17, 31, 33, 65, 129, 257, 513):
+        A = rng.integers(-127, 128, (M, K), dtype=np.int8)
+        acc = oracle.gemm_i8_i32(A, W)
+        assert np.array_equal(host(P.gemm_i8_requant(dev(A), dev(W), dev(m), dev(b))), oracle.epilogue_requant(acc, m, b)), M
+        assert np.array_equal(host(P.gemm_i8_gelu_quant(dev(A), dev(W), dev(mg), dev(bias), s_out, table)),
+                              oracle.epilogue_gelu_quant(acc, mg, bias, s_out)), M
+
+
+@pytest.mark.parametrize("K,N", [(256, 128), (768, 768), (768, 2304), (3072, 768)])
+def test_fp16_gemm_of_few_rows_is_the_same_bytes_as_the_large_tiles(P, K, N):
+    """Sums are formed in the same order in every tile configuration, so the small tiles must give the bytes of a forced
+    large one; rows past the last token are neither read nor written."""
+    import torch
+    rng = np.random.default_rng(K + N + 1)
+    W = dev((rng.standard_normal((N, K)) * 0.05).astype(np.float16))
+    bias = dev((rng.standard_normal(N) * 0.1).astype(np.float32))
+    for M in (1, 31, 32, 33, 97, 256, 500):
+        A = dev(rng.standard_normal((M, K)).astype(np.float16))
+        for gelu in (False, True):
+            got = P.gemm_f16(A, W, bias, gelu)
+            P.set_gemm_config(1)
+            try:
+                want = P.gemm_f16(A, W, bias, gelu)
+            finally:
+                P.set_gemm_config(-1)
+            assert torch.equal(got.view(torch.int16), want.view(torch.int16)), (M, gelu)
+
+
 # ------------------------------------------------------------------ attention
 def _cu(lens):
     return np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
