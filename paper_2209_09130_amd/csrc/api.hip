@@ -170,10 +170,10 @@ const Timing *timing(samp_encoder *e, int which)
 int choose_groups(const samp_encoder *e, int B, int S)
 {
     int g = e->groups_wanted;
-    // measured (BERT-base, 128 tokens): below about 2560 token rows one chain is faster (batch 16: 0.68 against 0.74 ms),
-    // from there on two are, at every size (batch 32: 0.83 against 0.97 ms, 128 x 512: -1.4 to -5 %, batch 256: -10 %);
-    // three or four never beat two
-    if (g <= 0) g = ((long)B * S >= 2560) ? 2 : 1;
+    // Measured: below about two million values (token rows x hidden) one chain is faster (us, one / two groups: BERT-base 16 x 128
+    // 629 / 713, 20 x 128 713 / 783), from there on two are, at every size (24 x 128 843 / 739, BERT-large 8 x 256 1991 / 1871,
+    // BERT-base 128 x 512 -4 %); three or four never beat two
+    if (g <= 0) g = ((long)B * S * e->cfg.hidden >= 2000000) ? 2 : 1;
     if (g > MAX_GROUPS) g = MAX_GROUPS;
     if (g > B) g = B;
     return g;

@@ -17,6 +17,7 @@ namespace {
 //   mean / variance in binary64 (two passes over registers), rounded once to binary32
 //   y = fmaf((z - mu) * rstd, gamma, beta);  out = rne(y / s_out) or fp16(y)
 // ---------------------------------------------------------------------------------------------
+constexpr int LN_WAVE_MAX_ROWS = 2048;   // below: one wave per row
 constexpr int LN_ROWS = 8;               // token rows per block of the LayerNorm step (16 lanes each): small blocks slot in beside the other group's kernels
 
 template <int CTRL> __device__ __forceinline__ int dpp_mov(int v)
@@ -165,16 +166,111 @@ __global__ __launch_bounds__(16 * LN_ROWS) void add_ln_kernel(AddLnArgs a)
                                  (size_t)out_row * H, a.absmax_out);
 }
 
+// The same step with one wave per row, for the widths that 64 lanes divide into whole dwords of channels (H = 64 CPL).  A
+// launch of a few thousand rows lasts as long as one row's chain of vector arithmetic: 800 instructions of a wave that holds four
+// rows, 300 of one that holds one.  Us per launch in a chain, int8 in and out, H = 768: 19 rows 3.6 -> 2.3, 2048 rows 3.9 -> 3.1; H = 1024: 4.7 -> 2.4, 5.1 -> 3.4.
+template <bool I8, int CPL> __device__ __forceinline__ void load_lane(const void *p, size_t elem, float (&v)[CPL])
+{
+    static_assert(CPL % 4 == 0, "whole dwords of int8 channels per lane");
+#pragma unroll
+    for (int d = 0; d < CPL / 4; d++) {
+        if (I8) {
+            const int q = *reinterpret_cast<const int *>((const int8_t *)p + elem + 4 * d);
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[4 * d + e] = (float)(int8_t)(q >> (8 * e));
+        } else {
+            const v4h h = *reinterpret_cast<const v4h *>((const __half *)p + elem + 4 * d);
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[4 * d + e] = (float)h[e];
+        }
+    }
+}
+template <int CPL> __device__ __forceinline__ void load_lane_f32(const float *p, float (&v)[CPL])
+{
+#pragma unroll
+    for (int q = 0; q < CPL / 4; q++) *reinterpret_cast<v4f *>(v + 4 * q) = *reinterpret_cast<const v4f *>(p + 4 * q);
+}
+
+__device__ __forceinline__ double lane_double(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double row64_sum(double v)
+{
+    v = row16_sum(v);
+    return (lane_double(v, 0) + lane_double(v, 16)) + (lane_double(v, 32) + lane_double(v, 48));
+}
+
+// second half of a row held by a wave, as ln_finish()
+template <int CPL, bool OUT_I8>
+__device__ __forceinline__ void ln_finish_wave(const float (&z)[CPL], double sum, const float (&gamma)[CPL], const float (&beta)[CPL], float eps,
+                                               float s_out, void *out, size_t obase)
+{
+    constexpr int H = 64 * CPL;
+    const double mu = row64_sum(sum) / (double)H;
+    double sq = 0.0;
+#pragma unroll
+    for (int e = 0; e < CPL; e++) { const double d = (double)z[e] - mu; sq = __builtin_fma(d, d, sq); }
+    const double var = row64_sum(sq) / (double)H;
+    const float mu32 = (float)mu, rstd32 = (float)(1.0 / sqrt(var + (double)eps)), inv_s = OUT_I8 ? 1.0f / s_out : 0.0f;
+#pragma unroll
+    for (int q = 0; q < CPL / 4; q++) {
+        float y[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) y[t] = __builtin_fmaf((z[4 * q + t] - mu32) * rstd32, gamma[4 * q + t], beta[4 * q + t]);
+        if (OUT_I8)
+            *reinterpret_cast<int *>((int8_t *)out + obase + 4 * q) =
+                pack_codes(code_bits(y[0] * inv_s), code_bits(y[1] * inv_s), code_bits(y[2] * inv_s), code_bits(y[3] * inv_s));
+        else
+            *reinterpret_cast<v4h *>((__half *)out + obase + 4 * q) = v4h{to_half(y[0]), to_half(y[1]), to_half(y[2]), to_half(y[3])};
+    }
+}
+
+template <int CPL, bool IN_I8, bool RES_I8, bool OUT_I8>
+__global__ __launch_bounds__(256) void add_ln_wave_kernel(AddLnArgs a)
+{
+    constexpr int H = 64 * CPL;
+    const int M = a.rows.dev_rows ? *a.rows.dev_rows : a.rows.host_rows;
+    const int nblk = (M + 3) / 4;
+    if ((int)blockIdx.x >= nblk) return;
+    const int row = xcd_contiguous(blockIdx.x, nblk) * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (row >= M) return;
+    const int c = (threadIdx.x & 63) * CPL;
+    const int out_row = a.row_map ? a.row_map[row] : row;
+    float x[CPL], r[CPL], z[CPL], gamma[CPL], beta[CPL];
+    load_lane<IN_I8>(a.in, (size_t)row * H + c, x);
+    load_lane<RES_I8>(a.res, (size_t)row * H + c, r);
+    load_lane_f32(a.bias + c, z);
+    load_lane_f32(a.gamma + c, gamma);
+    load_lane_f32(a.beta + c, beta);
+    double sum = 0.0;
+#pragma unroll
+    for (int e = 0; e < CPL; e++) {
+        const float u = IN_I8 ? __builtin_fmaf(x[e], a.s_in, z[e]) : x[e] + z[e];
+        z[e] = RES_I8 ? __builtin_fmaf(r[e], a.s_res, u) : u + r[e];
+        sum += (double)z[e];
+    }
+    ln_finish_wave<CPL, OUT_I8>(z, sum, gamma, beta, a.eps, a.s_out, a.out, (size_t)out_row * H + c);
+}
+
 template <int NJ>
 hipError_t launch_add_ln_nj(const AddLnArgs &a, hipStream_t st, const Timing *tm)
 {
-    dim3 grid((a.rows.host_rows + LN_ROWS - 1) / LN_ROWS), block(16 * LN_ROWS);
-    // width 768 has an instance without tests against H (at 1024 the requests of a whole row in flight take so many
+    // one wave per row at widths of 256, 512, 768 and 1024 (calibration, which also wants the absmax of the output, keeps the other
+    // form) for launches of less than 2048 rows: beyond, two batch groups share the chip and a launch takes vector time away from
+    // the other group's GEMMs, of which four rows per wave need a third less (BERT-large 32 x 256: 4484 against 4809 us)
+    // width 768 has an instance of that form without tests against H (at 1024 the requests of a whole row in flight take so many
     // registers that the forward gets slower)
-    constexpr bool WHOLE_WIDTHS = NJ == 3;
+    constexpr bool WHOLE_WIDTHS = NJ == 3, WAVE = NJ <= 4;
+    const bool wave = WAVE && a.H == 256 * NJ && a.rows.host_rows < LN_WAVE_MAX_ROWS && !a.absmax_out;
+    const int per_block = wave ? 4 : LN_ROWS;
+    dim3 grid((a.rows.host_rows + per_block - 1) / per_block), block(wave ? 256 : 16 * LN_ROWS);
 #define SAMP_LN_CASE(I, R, O)                                                                              \
     if (a.in_i8 == I && a.res_i8 == R && a.out_i8 == O) {                                                  \
-        if (WHOLE_WIDTHS && a.H == 256 * NJ) launch_kernel(add_ln_kernel<NJ, I, R, O, WHOLE_WIDTHS>, grid, block, 0, st, tm, a); \
+        if (wave) launch_kernel(add_ln_wave_kernel<WAVE ? 4 * NJ : 4, I, R, O>, grid, block, 0, st, tm, a); \
+        else if (WHOLE_WIDTHS && a.H == 256 * NJ) launch_kernel(add_ln_kernel<NJ, I, R, O, WHOLE_WIDTHS>, grid, block, 0, st, tm, a); \
         else launch_kernel(add_ln_kernel<NJ, I, R, O, false>, grid, block, 0, st, tm, a);                  \
         return hipGetLastError();                                                                          \
     }
@@ -238,10 +334,57 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(EmbedArgs a)
     ln_finish<NJ, OUT_I8>(z, sum, H, sub, a.gamma, a.beta, a.eps, a.s_out, a.out, (size_t)t * H, nullptr);
 }
 
+// one wave per position, as add_ln_wave_kernel: its ids, its place and whether it exists are the same for all lanes
+template <int CPL, bool OUT_I8>
+__global__ __launch_bounds__(256) void embed_ln_wave_kernel(EmbedArgs a)
+{
+    constexpr int H = 64 * CPL;
+    const int rowid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (rowid >= a.B * a.S) return;
+    const int lane = threadIdx.x & 63, c = lane * CPL;
+    const int b = rowid / a.S, s = rowid - b * a.S;
+    int t = rowid;
+    if (a.cu) {
+        const int t0 = a.cu[b], n = a.cu[b + 1] - t0;
+        if (s >= n) {
+            if (a.out_zero_pad)
+                for (int k = lane * 8; k < H; k += 512) *reinterpret_cast<v4i *>(a.out_zero_pad + (size_t)rowid * H + k) = v4i{0, 0, 0, 0};
+            return;
+        }
+        t = t0 + s;
+        if (lane == 0 && a.row_map) a.row_map[t] = rowid;
+    }
+    const int id = min(max(a.token_ids[rowid], 0), a.vocab - 1);
+    const int sid = a.segment_ids ? min(max(a.segment_ids[rowid], 0), a.segments - 1) : 0;
+    const int pid = min(s, a.positions - 1);
+    float x[CPL], g[CPL], z[CPL], gamma[CPL], beta[CPL];
+    load_lane<false>(a.tok, (size_t)id * H + c, x);
+    load_lane<false>(a.seg, (size_t)sid * H + c, g);
+    load_lane<false>(a.pos, (size_t)pid * H + c, z);
+    load_lane_f32(a.gamma + c, gamma);
+    load_lane_f32(a.beta + c, beta);
+    double sum = 0.0;
+#pragma unroll
+    for (int e = 0; e < CPL; e++) {
+        z[e] = (x[e] + g[e]) + z[e];
+        sum += (double)z[e];
+    }
+    ln_finish_wave<CPL, OUT_I8>(z, sum, gamma, beta, a.eps, a.s_out, a.out, (size_t)t * H + c);
+}
+
 template <int NJ>
 hipError_t launch_embed_ln_nj(const EmbedArgs &a, hipStream_t st, const Timing *tm)
 {
-    dim3 grid((a.B * a.S + 15) / 16), block(256);
+    const dim3 block(256);
+    if constexpr (NJ <= 4) {
+        if (a.H == 256 * NJ) {
+            const dim3 grid((a.B * a.S + 3) / 4);
+            if (a.out_i8) launch_kernel(embed_ln_wave_kernel<4 * NJ, true>, grid, block, 0, st, tm, a);
+            else launch_kernel(embed_ln_wave_kernel<4 * NJ, false>, grid, block, 0, st, tm, a);
+            return hipGetLastError();
+        }
+    }
+    const dim3 grid((a.B * a.S + 15) / 16);
     if (a.out_i8) launch_kernel(embed_ln_kernel<NJ, true>, grid, block, 0, st, tm, a);
     else launch_kernel(embed_ln_kernel<NJ, false>, grid, block, 0, st, tm, a);
     return hipGetLastError();
