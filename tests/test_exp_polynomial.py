@@ -63,3 +63,49 @@ def test_exponential_polynomial_is_accurate_far_beyond_a_binary32_ulp():
     assert exp_nonpos(0.0, log2e, shift, ln2_hi, ln2_lo, poly)[0] == 1.0
     # far below the range of binary32 the scaling flushes to zero, as the exponential does
     assert exp_nonpos(-1.0e9, log2e, shift, ln2_hi, ln2_lo, poly)[0] == 0.0
+
+
+def test_table_exponential_is_as_accurate():
+    """exp_nonpos(float, table): 256 powers of two (csrc/exp2_table.h) and a polynomial of degree 3 in the rest."""
+    getcontext().prec = 60
+    text = open(os.path.join(os.path.dirname(SRC), "exp2_table.h")).read()
+    entries = [int(t, 16) for t in re.findall(r"0x([0-9a-f]{16})", text)]
+    assert len(entries) == 256
+    ln2 = Decimal(2).ln()
+    power = lambda k: struct.unpack("<d", struct.pack("<Q", entries[k & 255] + ((k << 12) << 32) & (2 ** 64 - 1)))[0]
+    for j in range(256):
+        assert power(j) == float((ln2 * j / 256).exp())
+    assert power(-256 * 150) == 2.0 ** -150 and power(-256 * 149 + 255) == math.ldexp(power(255), -149)
+    body = open(SRC).read()
+    body = body[body.index("float exp_nonpos(float x, const ExpTable &table)"):]
+    body = body[:body.index("const double scale")]
+    num = r"-?(?:0x[0-9a-fA-F.]+p[-+]?\d+|\d+\.\d+(?:e[-+]?\d+)?)"
+    lits = [float.fromhex(t) if "0x" in t else float(t) for t in re.findall(num, body)]
+    floor, rate, shift, rate_again, shift_again = lits[:5]
+    poly = lits[5:]
+    assert floor == -104.0 and rate == rate_again == float(256 / ln2) and shift == shift_again == 1.5 * 2.0 ** 52 and len(poly) == 4
+
+    def table_exp(x):
+        x = max(x, floor)
+        shifted = fma(x, rate, shift)
+        k = int(shifted - shift)
+        f = fma(x, rate, -(shifted - shift))
+        q = poly[0]
+        for c in poly[1:]:
+            q = fma(q, f, c)
+        scale = power(k)
+        return fma(scale, f * q, scale), f
+
+    f32 = lambda v: struct.unpack("f", struct.pack("f", v))[0]
+    rnd = random.Random(12)
+    xs = [f32(-rnd.random() * 103.9) for _ in range(4000)] + [f32(-rnd.random() * 0.7) for _ in range(1500)] + [0.0, -104.0]
+    xs += [f32(-(k + 0.5) * math.log(2) / 256) for k in range(0, 38000, 301)]        # the ends of the reduced range
+    worst = 0.0
+    for x in xs:
+        y, f = table_exp(x)
+        assert abs(f) <= 0.5001
+        exact = Fraction(str(Decimal(x).exp()))
+        worst = max(worst, float(abs(Fraction(y) - exact) / exact))
+    assert worst < 2.0 ** -48, math.log2(worst)                               # the bound of the polynomial above
+    assert table_exp(0.0)[0] == 1.0
+    assert f32(table_exp(-1.0e9)[0]) == 0.0                                   # below half of the smallest binary32 number
