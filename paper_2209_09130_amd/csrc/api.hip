@@ -301,7 +301,10 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             // (calibration taps q, k, v and the softmax output, so it keeps the two kernels; with binary32 exponentials
             //  the 256-token flavour pays as well: BERT-large 32 x 256 with FP16 attention blocks -12.7 %)
             if (!am && S <= 256 && (enc->fusion_wanted == 2 || (enc->fusion_wanted == 0 && B * heads >= 128))) {
-                HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, cu, B, S, H, 0.125f,
+                // up to about one block per CU the INT8 feed-forward kernels of the other batch group need the LDS more than
+                // this kernel needs 128-byte stages (BERT-base 32 x 128 Quant-FFN-Only 0.946 / 0.964 ms; 256 x 128 5.18 / 5.15)
+                const bool small_ring = ffn8 && B * heads < 256;
+                HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, cu, B, S, H, 0.125f, small_ring,
                                                  (__half *)w.ctx, st, timing(enc, SAMP_PROF_QKV_ATTN)));
             } else {
                 HIP_TRY(launch_gemm_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, false, (__half *)w.qkv, rows,
@@ -869,7 +872,7 @@ int samp_qkv_attention_f16(const uint16_t *x, const uint16_t *w_qkv, const float
     if (B < 1 || max_len < 1 || max_len > 256) return fail(SAMP_ERR_SHAPE, "B >= 1 and 1 <= max_len <= 256 required");
     if (heads < 1 || hidden != heads * 64) return fail(SAMP_ERR_SHAPE, "head size must be 64");
     if (!aligned(x, 16) || !aligned(w_qkv, 16) || !aligned(ctx, 16)) return fail(SAMP_ERR_ARG, "tensors must be 16-byte aligned");
-    HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)w_qkv, bias, cu, B, max_len, hidden, 0.125f, (__half *)ctx,
+    HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)w_qkv, bias, cu, B, max_len, hidden, 0.125f, false, (__half *)ctx,
                                      (hipStream_t)stream, nullptr));
     return SAMP_OK;
 }

@@ -19,6 +19,7 @@
 #include "mfma_tile.h"
 #include "exp2_table.h"
 
+#include <algorithm>
 #include <atomic>
 #include <hip/hip_ext.h>
 
@@ -358,9 +359,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
 // and, for FP16, partial contexts are accumulated per key tile modulo 4 in ascending order, which is how the four
 // waves of those kernels form them), so the context is the same bytes.  QT = 2 is the same for up to 256 tokens: a
 // 256 x 192 block tile, wave tiles of 128 x 96, a wave's 64 queries 32 at a time.
-template <int QT>                                          // QT 32-query tiles per wave: sequences of at most 128 QT tokens
+//
+// The ring holds two 128-byte stages: whole cache lines per operand row (a line that is asked for in two halves, some stages
+// apart, is fetched twice).  For QT = 1 two blocks' rings fill a CU's 160 KB of LDS exactly, so the tables of the epilogue
+// come last, into the stage that the last one but one leaves free (LATE).  A stand-in that only loads the stages pulls 35 to 41
+// bytes per clock and CU like this, 24 with 64-byte stages; forward, three 64-byte stages against two of 128: BERT-base 256 x 128
+// Fully-Quant 4.43 / 4.21 ms, 32 x 128 FP16 1.380 / 1.324, BERT-large 64 x 128 Fully-Quant 3.94 / 3.78, Quant-FFN-Only 4.73 / 4.48.  Three 64-byte stages are kept for rows that are no
+// multiple of 128 bytes (an odd number of heads in INT8) and for QT = 2, whose registers do not hold 128-byte stages' offsets,
+// and where the caller asks for the smaller ring (62 KB).
+template <int QT, int STAGE>                               // QT 32-query tiles per wave: sequences of at most 128 QT tokens
 struct QkvTile {                                           // the block tile both flavours of the kernel share
-    static constexpr int TM = 2 * QT, TN = 3, BKB = 64, NSTAGE = 3, NWAVES = 4, CH = 4, RPI = 16, KS = 2;
+    static constexpr int TM = 2 * QT, TN = 3, BKB = STAGE, NSTAGE = STAGE == 128 ? 2 : 3, NWAVES = 4, CH = BKB / 16, RPI = 64 / CH, KS = BKB / 32;
+    static constexpr bool LATE = QT == 1 && STAGE == 128;
     static constexpr int BM = 128 * QT, BN = 192;
     static constexpr int A_BYTES = BM * BKB, STAGE_BYTES = (BM + BN) * BKB, RING_BYTES = NSTAGE * STAGE_BYTES;
     static constexpr int NLD = (BM + BN) / RPI / NWAVES;          // 1 KiB pieces per wave and stage
@@ -374,11 +384,11 @@ struct QkvTile {                                           // the block tile bot
 // register group: exactly a dword (fp16: 8 bytes) of V^T, which the P.V product wants key-contiguous.  The sums are
 // the same (the same products over the same k).  ALL_LIVE: every 32-token tile of the block holds tokens (no tests in
 // the loop).
-template <int QT, bool HALF, bool VWAVE, bool ALL_LIVE, class Acc, class LoadTables>
+template <int QT, int STAGE, bool HALF, bool VWAVE, bool ALL_LIVE, class Acc, class LoadTables>
 __device__ __forceinline__ void qkv_tile_gemm(const char *__restrict__ X, const char *__restrict__ W, int t0, int n, int head, int H,
                                               int Kbytes, char *lds, int wave, int lane, Acc (&acc)[3][2 * QT], LoadTables load_tables)
 {
-    typedef QkvTile<QT> Tile;
+    typedef QkvTile<QT, STAGE> Tile;
     constexpr int TM = Tile::TM, TN = Tile::TN, BKB = Tile::BKB, NSTAGE = Tile::NSTAGE, NWAVES = Tile::NWAVES;
     constexpr int CH = Tile::CH, RPI = Tile::RPI, KS = Tile::KS, BM = Tile::BM;
     constexpr int A_BYTES = Tile::A_BYTES, STAGE_BYTES = Tile::STAGE_BYTES, RING_BYTES = Tile::RING_BYTES, NLD = Tile::NLD;
@@ -387,26 +397,26 @@ __device__ __forceinline__ void qkv_tile_gemm(const char *__restrict__ X, const 
     const int r = lane & 31, g = lane >> 5;
     // operand rows: the sequence's tokens (rows past its end repeat the last one), and the head's 64 rows of each of
     // the query, key and value thirds of the weight matrix
-    const char *src[NLD];
+    // (32-bit offsets from a base that is the same for the whole wave: half the registers of a pointer per load)
+    constexpr int NLDA = BM / RPI / NWAVES;                       // the first NLDA pieces hold token rows
+    const char *bases[2] = {X + (size_t)t0 * Kbytes, W + (size_t)head * 64 * Kbytes};
+    unsigned off[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; j++) {
-        const int srow = RPI * (wave + NWAVES * j) + lane / CH;
-        if (srow < BM) {
-            const int am = min(srow, n - 1);
-            src[j] = X + (size_t)(t0 + am) * Kbytes + (((lane % CH) ^ swz<BKB>(srow)) << 4);
-        } else {
-            const int row = srow - BM;
-            src[j] = W + (size_t)((row >> 6) * H + head * 64 + (row & 63)) * Kbytes + (((lane % CH) ^ swz<BKB>(row)) << 4);
-        }
+        const int srow = RPI * (wave + NWAVES * j) + lane / CH, row = j < NLDA ? min(srow, n - 1) : srow - BM;
+        off[j] = (unsigned)(j < NLDA ? row : (row >> 6) * H + (row & 63)) * (unsigned)Kbytes + (((lane % CH) ^ swz<BKB>(j < NLDA ? srow : row)) << 4);
     }
     const int KT = Kbytes / BKB;
     int fill_slot = 0, fill_kt = 0;
     auto issue = [&]() {
         char *st = lds + fill_slot * STAGE_BYTES;
 #pragma unroll
-        for (int j = 0; j < NLD; j++)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + (size_t)fill_kt * BKB),
+        for (int j = 0; j < NLD; j++) {
+            unsigned o = off[j];
+            asm volatile("" : "+v"(o));                            // keeps the offset a 32-bit one: scalar base + vector offset
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(bases[j >= NLDA] + (size_t)fill_kt * BKB + o),
                                              (__attribute__((address_space(3))) void *)(st + (wave + NWAVES * j) * 1024), 16, 0, 0);
+        }
         fill_kt++;
         fill_slot = fill_slot + 1 == NSTAGE ? 0 : fill_slot + 1;
     };
@@ -429,7 +439,7 @@ __device__ __forceinline__ void qkv_tile_gemm(const char *__restrict__ X, const 
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; s++)
         if (s < KT) issue();
-    load_tables();
+    if (!Tile::LATE) load_tables();
 
 #pragma unroll
     for (int i = 0; i < TN; i++)
@@ -476,6 +486,7 @@ __device__ __forceinline__ void qkv_tile_gemm(const char *__restrict__ X, const 
         ready(fa[ks & 1], fw[ks & 1]);
         __builtin_amdgcn_sched_barrier(0);
         if (refill && ks == 0) issue();
+        if (Tile::LATE && !more && ks == 0) load_tables();         // direct loads: the last wait below covers them
         multiply(fa[ks & 1], fw[ks & 1]);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -483,42 +494,54 @@ __device__ __forceinline__ void qkv_tile_gemm(const char *__restrict__ X, const 
     for (; kt + NSTAGE - 1 < KT; kt++)
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) step(ks, true, true, std::integral_constant<int, (NSTAGE - 2) * NLD>());
-    for (; kt + 1 < KT; kt++)
+    if constexpr (NSTAGE > 2)
+        for (; kt + 1 < KT; kt++)
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) step(ks, false, true, std::integral_constant<int, 0>());
+            for (int ks = 0; ks < KS; ks++) step(ks, false, true, std::integral_constant<int, 0>());
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) step(ks, false, false, std::integral_constant<int, 0>());
     wait_vm_and_barrier<0>();                                     // the ring is idle from here on
 }
 
 // one of four copies of the loop: by wave column (value channels or not) and by whether all token tiles are live
-template <int QT, bool HALF, class Acc, class LoadTables>
+template <int QT, int STAGE, bool HALF, class Acc, class LoadTables>
 __device__ __forceinline__ void qkv_tile_gemm_any(const char *__restrict__ X, const char *__restrict__ W, int t0, int n, int head, int H,
                                                   int Kbytes, char *lds, int wave, int lane, Acc (&acc)[3][2 * QT], LoadTables load_tables)
 {
-    const bool all_live = n > QkvTile<QT>::BM - 32;               // block-uniform; wave & 1 is wave-uniform
+    const bool all_live = n > QkvTile<QT, STAGE>::BM - 32;               // block-uniform; wave & 1 is wave-uniform
     if (wave & 1) {
-        if (all_live) qkv_tile_gemm<QT, HALF, true, true>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
-        else qkv_tile_gemm<QT, HALF, true, false>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
+        if (all_live) qkv_tile_gemm<QT, STAGE, HALF, true, true>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
+        else qkv_tile_gemm<QT, STAGE, HALF, true, false>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
     } else {
-        if (all_live) qkv_tile_gemm<QT, HALF, false, true>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
-        else qkv_tile_gemm<QT, HALF, false, false>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
+        if (all_live) qkv_tile_gemm<QT, STAGE, HALF, false, true>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
+        else qkv_tile_gemm<QT, STAGE, HALF, false, false>(X, W, t0, n, head, H, Kbytes, lds, wave, lane, acc, load_tables);
     }
 }
 
-template <int QT, bool PU>                                 // PU: unsigned softmax codes, as in attention_i8_kernel
+// `words` dwords into LDS by one wave, 64 per direct load; the caller waits for them (vmcnt) before its next barrier
+__device__ __forceinline__ void load_direct(float *dst, const void *src, int words, int lane)
+{
+    for (int i = 0; i < words; i += 64)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((const int *)src + i + lane),
+                                         (__attribute__((address_space(3))) void *)(dst + i), 4, 0, 0);
+}
+
+template <int QT, bool PU, int STAGE>                      // PU: unsigned softmax codes, as in attention_i8_kernel
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ m_tab,
                              const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, float m_sc,
                              float inv_sp, float m_ctx, int8_t *__restrict__ ctx)
 {
-    typedef QkvTile<QT> Tile;
+    typedef QkvTile<QT, STAGE> Tile;
     constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, RING_BYTES = Tile::RING_BYTES, NKT = 4 * QT;
     constexpr int QK_STRIDE = 80, VT_STRIDE = BM + 4;             // bytes per token row of q / k, per channel row of V^T
-    constexpr int Q_OFF = 0, K_OFF = BM * QK_STRIDE, VT_OFF = 2 * BM * QK_STRIDE;
-    static_assert(VT_OFF + 64 * VT_STRIDE <= RING_BYTES, "q, k and V^T take the place of the ring");
+    constexpr int TAB_BYTES = 4096;                               // multipliers and offsets of the 192 columns, table of the exponential
+    constexpr int Q_OFF = Tile::LATE ? TAB_BYTES : 0, K_OFF = Q_OFF + BM * QK_STRIDE, VT_OFF = K_OFF + BM * QK_STRIDE;
+    static_assert(VT_OFF + 64 * VT_STRIDE + Q_OFF <= RING_BYTES, "q, k and V^T take the place of the ring, clear of a table at either end");
+    static_assert(2 * BN * 4 + sizeof(ExpTable) <= TAB_BYTES, "");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    float *tab = reinterpret_cast<float *>(lds + RING_BYTES);     // multipliers, then offsets, of the 192 columns
+    // LATE: at the end of the ring that the second last of the H / STAGE stages lies in
+    float *tab = reinterpret_cast<float *>(lds + (!Tile::LATE ? RING_BYTES : (H / STAGE) & 1 ? RING_BYTES - TAB_BYTES : 0));
     ExpTable &exp_table = *reinterpret_cast<ExpTable *>(tab + 2 * BN);
 
     const int heads = H >> 6;
@@ -532,7 +555,17 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
     const int r = lane & 31, g = lane >> 5;
 
     v16i acc[TN][TM];
-    qkv_tile_gemm_any<QT, false>(X, W, sq.t0, n, head, H, H, lds, wave, lane, acc, [&]() {
+    qkv_tile_gemm_any<QT, STAGE, false>(X, W, sq.t0, n, head, H, H, lds, wave, lane, acc, [&]() {
+        if constexpr (Tile::LATE) {
+            load_direct(tab + 2 * BN + wave * 128, (const int *)EXP2_TABLE + wave * 128, 128, lane);
+            if (wave < 3) {
+                const int col = wave * H + head * 64;
+                load_direct(tab + wave * 64, m_tab + col, 64, lane);
+                if (b_tab) load_direct(tab + BN + wave * 64, b_tab + col, 64, lane);
+                else tab[BN + wave * 64 + lane] = 0.0f;
+            }
+            return;
+        }
         exp_table[tid] = EXP2_TABLE[tid];
         for (int c = tid; c < BN; c += 256) {
             const int col = (c >> 6) * H + head * 64 + (c & 63);
@@ -705,19 +738,21 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
 // arithmetic of attention_f16_kernel.  The products P.V of the four key tiles are formed from zero one by one and
 // added in the order in which that kernel adds its four waves' partial contexts (tiles past the end add +0), and the
 // row sums likewise, so the context is the same bytes as from the two kernels.
-template <int QT>
+template <int QT, int STAGE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ bias,
                               const int *__restrict__ cu, int max_len, int H, float scale, __half *__restrict__ ctx)
 {
-    typedef QkvTile<QT> Tile;
+    typedef QkvTile<QT, STAGE> Tile;
     constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, RING_BYTES = Tile::RING_BYTES, NKT = 4 * QT;
     constexpr int QK_STRIDE = 144, VT_STRIDE = 2 * BM + 8;        // bytes per token row of q / k (64 fp16 + pad), per channel row of V^T (all keys + pad)
-    constexpr int Q_OFF = 0, K_OFF = BM * QK_STRIDE, VT_OFF = 2 * BM * QK_STRIDE;
+    constexpr int TAB_BYTES = 1024;                               // bias of the 192 columns
+    constexpr int Q_OFF = Tile::LATE ? TAB_BYTES : 0, K_OFF = Q_OFF + BM * QK_STRIDE, VT_OFF = K_OFF + BM * QK_STRIDE;
     constexpr int QKV_BYTES = VT_OFF + 64 * VT_STRIDE;            // q, k and V^T take the place of the ring (and more, for 256 tokens)
     constexpr int TAB_OFF = QKV_BYTES > RING_BYTES ? QKV_BYTES : RING_BYTES;
+    static_assert(!Tile::LATE || QKV_BYTES + TAB_BYTES <= RING_BYTES, "clear of a table at either end of the ring");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    float *tab = reinterpret_cast<float *>(lds + TAB_OFF);        // bias of the 192 columns
+    float *tab = reinterpret_cast<float *>(lds + (!Tile::LATE ? TAB_OFF : (H / 64) & 1 ? RING_BYTES - TAB_BYTES : 0));
 
     const int heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -730,7 +765,14 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     const int r = lane & 31, g = lane >> 5;
 
     v16f acc[TN][TM];
-    qkv_tile_gemm_any<QT, true>(X, W, sq.t0, n, head, H, 2 * H, lds, wave, lane, acc, [&]() {
+    qkv_tile_gemm_any<QT, STAGE, true>(X, W, sq.t0, n, head, H, 2 * H, lds, wave, lane, acc, [&]() {
+        if constexpr (Tile::LATE) {
+            if (wave < 3) {
+                if (bias) load_direct(tab + wave * 64, bias + wave * H + head * 64, 64, lane);
+                else tab[wave * 64 + lane] = 0.0f;
+            }
+            return;
+        }
         for (int c = tid; c < BN; c += 256) tab[c] = bias ? bias[(c >> 6) * H + head * 64 + (c & 63)] : 0.0f;
     });
 
@@ -1570,24 +1612,35 @@ hipError_t launch_attention_i8(const int8_t *qkv, const int *cu, int B, int max_
     return hipGetLastError();
 }
 
-template <int QT, bool PU>
-static hipError_t launch_qkv_attention_i8_variant(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int *cu,
+template <int QT, bool PU, int STAGE>
+static hipError_t launch_qkv_attention_i8_stages(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int *cu,
                                                   int B, int max_len, int H, float m_sc, float inv_sp, float m_ctx, int8_t *ctx,
                                                   hipStream_t st, const Timing *tm)
 {
-    const size_t lds = QkvTile<QT>::RING_BYTES + 2 * 192 * sizeof(float) + sizeof(ExpTable);
+    typedef QkvTile<QT, STAGE> Tile;
+    const size_t lds = Tile::RING_BYTES + (Tile::LATE ? 0 : 2 * 192 * sizeof(float) + sizeof(ExpTable));
     if (lds > 64 * 1024) {
         static std::atomic<bool> attr_set{false};
         if (!attr_set.load(std::memory_order_acquire)) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(qkv_attention_i8_kernel<QT, PU>),
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(qkv_attention_i8_kernel<QT, PU, STAGE>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             attr_set.store(true, std::memory_order_release);
         }
     }
-    launch_kernel(qkv_attention_i8_kernel<QT, PU>, dim3((unsigned)(B * (H / 64))), dim3(256), lds, st, tm, (const char *)x,
+    launch_kernel(qkv_attention_i8_kernel<QT, PU, STAGE>, dim3((unsigned)(B * (H / 64))), dim3(256), lds, st, tm, (const char *)x,
                   (const char *)w_qkv, m, b, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx);
     return hipGetLastError();
+}
+
+template <int QT, bool PU>
+static hipError_t launch_qkv_attention_i8_variant(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int *cu,
+                                                  int B, int max_len, int H, float m_sc, float inv_sp, float m_ctx, int8_t *ctx,
+                                                  hipStream_t st, const Timing *tm)
+{
+    if constexpr (QT == 1)
+        if (H % 128 == 0) return launch_qkv_attention_i8_stages<QT, PU, 128>(x, w_qkv, m, b, cu, B, max_len, H, m_sc, inv_sp, m_ctx, ctx, st, tm);
+    return launch_qkv_attention_i8_stages<QT, PU, 64>(x, w_qkv, m, b, cu, B, max_len, H, m_sc, inv_sp, m_ctx, ctx, st, tm);
 }
 
 hipError_t launch_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int *cu, int B,
@@ -1603,28 +1656,24 @@ hipError_t launch_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const f
 }
 
 hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const float *bias, const int *cu, int B, int max_len,
-                                    int H, float scale, __half *ctx, hipStream_t st, const Timing *tm)
+                                    int H, float scale, bool small_ring, __half *ctx, hipStream_t st, const Timing *tm)
 {
     if (max_len > 256 || H % 64 || B <= 0) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(B * (H / 64)));
-    if (max_len <= 128) {
-        const size_t lds = QkvTile<1>::RING_BYTES + 192 * sizeof(float);
-        launch_kernel(qkv_attention_f16_kernel<1>, grid, dim3(256), lds, st, tm, (const char *)x, (const char *)w_qkv, bias, cu,
-                      max_len, H, scale, ctx);
-    } else {
-        constexpr size_t qkv_bytes = 2 * 256 * 144 + 64 * (2 * 256 + 8);
-        const size_t lds = (qkv_bytes > (size_t)QkvTile<2>::RING_BYTES ? qkv_bytes : (size_t)QkvTile<2>::RING_BYTES) + 192 * sizeof(float);
-        static std::atomic<bool> attr_set{false};
+    auto go = [&](auto kern, size_t lds, std::atomic<bool> &attr_set) {
         if (!attr_set.load(std::memory_order_acquire)) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(qkv_attention_f16_kernel<2>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             attr_set.store(true, std::memory_order_release);
         }
-        launch_kernel(qkv_attention_f16_kernel<2>, grid, dim3(256), lds, st, tm, (const char *)x, (const char *)w_qkv, bias, cu,
-                      max_len, H, scale, ctx);
-    }
-    return hipGetLastError();
+        launch_kernel(kern, grid, dim3(256), lds, st, tm, (const char *)x, (const char *)w_qkv, bias, cu, max_len, H, scale, ctx);
+        return hipGetLastError();
+    };
+    static std::atomic<bool> attr_set[3];
+    constexpr size_t tab = 192 * sizeof(float), qkv_bytes = 2 * 256 * 144 + 64 * (2 * 256 + 8);
+    if (max_len > 128) return go(qkv_attention_f16_kernel<2, 64>, std::max<size_t>(qkv_bytes, QkvTile<2, 64>::RING_BYTES) + tab, attr_set[2]);
+    if (small_ring) return go(qkv_attention_f16_kernel<1, 64>, QkvTile<1, 64>::RING_BYTES + tab, attr_set[1]);
+    return go(qkv_attention_f16_kernel<1, 128>, QkvTile<1, 128>::RING_BYTES, attr_set[0]);
 }
 
 hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,

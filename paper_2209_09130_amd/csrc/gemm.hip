@@ -57,6 +57,7 @@ struct EpiRawI32 {                                // test hook: the exact int32 
     static constexpr int NTAB = 0;
     struct Tab {};
     __device__ __forceinline__ void load_tables(float *, int, int, int, int) const {}
+    __device__ __forceinline__ void load_tables_direct(float *, int, int, int, int, int) const {}
     __device__ __forceinline__ Tab load_tab(const float *, int, int, int) const { return {}; }
     __device__ __forceinline__ void direct(int row, int n, int a0, int a1, int a2, int a3) const
     { *reinterpret_cast<v4i *>(out + (size_t)row * N + n) = v4i{a0, a1, a2, a3}; }
@@ -66,6 +67,22 @@ __device__ __forceinline__ void copy_table(float *dst, const float *src, int n0,
 {
     for (int c = tid * 4; c < bn; c += nthreads * 4)
         *reinterpret_cast<v4f *>(dst + c) = src ? *reinterpret_cast<const v4f *>(src + n0 + c) : v4f{0.f, 0.f, 0.f, 0.f};
+}
+
+// The same copies as direct loads, which the caller waits for (vmcnt) before its next barrier: `words` dwords, 64 per
+// instruction, the instructions dealt out over the waves.
+__device__ __forceinline__ void copy_direct(void *dst, const void *src, int words, int wave, int nwaves, int lane)
+{
+    for (int i = wave * 64; i < words; i += nwaves * 64)             // wave-uniform
+        if (i + lane < words)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((const int *)src + i + lane),
+                                             (__attribute__((address_space(3))) void *)((int *)dst + i), 4, 0, 0);
+}
+__device__ __forceinline__ void copy_table_direct(float *dst, const float *src, int n0, int bn, int wave, int nwaves, int lane)
+{
+    if (src) copy_direct(dst, src + n0, bn, wave, nwaves, lane);
+    else
+        for (int c = wave * 64 + lane; c < bn; c += nwaves * 64) dst[c] = 0.0f;
 }
 
 // the multiplier and offset vectors of one 32-channel tile: group q holds channels n_loc + 8q + 4g .. + 3
@@ -89,6 +106,8 @@ struct EpiRequant {                               // code = rne(fmaf(acc, m[n], 
     typedef int pack_t;
     __device__ __forceinline__ void load_tables(float *tab, int n0, int bn, int tid, int nthreads) const
     { copy_table(tab, m, n0, bn, tid, nthreads); copy_table(tab + bn, b, n0, bn, tid, nthreads); }
+    __device__ __forceinline__ void load_tables_direct(float *tab, int n0, int bn, int wave, int nwaves, int lane) const
+    { copy_table_direct(tab, m, n0, bn, wave, nwaves, lane); copy_table_direct(tab + bn, b, n0, bn, wave, nwaves, lane); }
     // four consecutive channels of one token
     __device__ __forceinline__ int four(const v4i &acc, const float *tab, int bn, int n) const
     {
@@ -124,6 +143,8 @@ struct EpiGeluQuant {
     typedef int pack_t;
     __device__ __forceinline__ void load_tables(float *tab, int n0, int bn, int tid, int nthreads) const
     { copy_table(tab, m, n0, bn, tid, nthreads); copy_table(tab + bn, bias, n0, bn, tid, nthreads); }
+    __device__ __forceinline__ void load_tables_direct(float *tab, int n0, int bn, int wave, int nwaves, int lane) const
+    { copy_table_direct(tab, m, n0, bn, wave, nwaves, lane); copy_table_direct(tab + bn, bias, n0, bn, wave, nwaves, lane); }
     struct Tab { v4f m[4], b[4]; };
     __device__ __forceinline__ Tab load_tab(const float *tab, int bn, int n_loc, int g) const { return load_tab_mb<Tab>(tab, bn, n_loc, g); }
     __device__ __forceinline__ void tile(const v16i &acc, const Tab &tb, const float *tab, int bn, int n_loc, int g, int (&pk)[4]) const
@@ -186,6 +207,12 @@ struct EpiGeluTable {
         v2i *lut = reinterpret_cast<v2i *>(tab + 2 * bn);
         for (int i = tid; i < bins; i += nthreads) lut[i] = reinterpret_cast<const v2i *>(entries)[i];
     }
+    __device__ __forceinline__ void load_tables_direct(float *tab, int n0, int bn, int wave, int nwaves, int lane) const
+    {
+        copy_table_direct(tab, m, n0, bn, wave, nwaves, lane);
+        copy_table_direct(tab + bn, bias, n0, bn, wave, nwaves, lane);
+        copy_direct(tab + 2 * bn, entries, 2 * bins, wave, nwaves, lane);
+    }
     __device__ __forceinline__ int four(const v4i &acc, const float *tab, int bn, int n) const
     {
         const v2i *lut = reinterpret_cast<const v2i *>(tab + 2 * bn);
@@ -237,6 +264,8 @@ struct EpiF16 {                                   // fp16(act(acc + bias[n]))
     typedef v2i pack_t;
     __device__ __forceinline__ void load_tables(float *tab, int n0, int bn, int tid, int nthreads) const
     { copy_table(tab, bias, n0, bn, tid, nthreads); }
+    __device__ __forceinline__ void load_tables_direct(float *tab, int n0, int bn, int wave, int nwaves, int lane) const
+    { copy_table_direct(tab, bias, n0, bn, wave, nwaves, lane); }
     struct Tab { v4f b[4]; };
     __device__ __forceinline__ Tab load_tab(const float *tab, int bn, int n_loc, int g) const
     {
@@ -445,9 +474,25 @@ hipError_t launch_cfg(const void *A, const void *W, void *out, const Epi &epi, R
 // so a wave tile of TM x TN such products needs (TM + TN) / (TM TN) KiB per 32 clocks -- with 2 x 2 the
 // four SIMDs of a CU ask for the whole LDS bandwidth, with 4 x 4 for half of it -- and a block tile of
 // BM x BN pulls (BM + BN) bytes per BM BN multiply-adds out of L2.  One wave per SIMD, so the latencies
-// are hidden by software pipelining instead of by other waves: the K stages (64 bytes) travel through
+// are hidden by software pipelining instead of by other waves: the K stages (64 or 128 bytes) travel through
 // an NSTAGE-deep ring of direct global->LDS loads, and the operand fragments of the next 32-byte step
 // are fetched from LDS into a second register set while the MFMAs of the current one run.
+//
+// 128-byte stages read whole cache lines: a stand-in that only loads the stages of 128 x 256 tiles (32768 x 3072 x 768) pulls 35 to
+// 41 bytes per clock and CU with them and 24 with 64-byte stages, whose lines are fetched twice.  They cost a deeper ring or a
+// resident block: 128 x 192 tiles are the largest of which two blocks keep two such stages each (2 x 80 KB, all of a CU's
+// LDS), so their epilogue tables have to wait for a free stage (LATE).  Forward, three 64-byte stages against two of 128 bytes:
+// BERT-base 32 x 128 -1.1 %, 64 ragged -2.7 %, BERT-large 32 x 256 Fully-Quant (QKV alone) -2.1 %; as 192 x 128 tiles for FFN1 of
+// BERT-large (128 x 256 and 64-byte stages now) +0.7 %.
+template <class Epi> constexpr int late_table_bytes(int bn)
+{
+    return (Epi::NTAB * bn * (int)sizeof(float) + (std::is_same<Epi, EpiGeluTable>::value ? GELU_TABLE_MAX_BINS * 8 : 0) + 1023) / 1024 * 1024;
+}
+template <class Epi> constexpr bool big_tables_late(int bm, int bn, int bkb, int nstage)
+{
+    return Epi::STAGED && nstage == 2 && (bm + bn) * bkb * nstage == 80 * 1024;
+}
+
 template <class T, class Epi, int TM, int TN, int BKB, int NSTAGE, int WPE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, Epi epi, int host_rows,
@@ -463,6 +508,10 @@ void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, 
     static_assert((BM + BN) % (RPI * NWAVES) == 0, "a stage must split into whole pieces per wave");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     float *tab = reinterpret_cast<float *>(lds + RING_BYTES);
+    // Two 128-byte stages of which two blocks exactly fill a CU's LDS: the epilogue's tables go into the stage that the last
+    // one but one leaves free, at the end of the ring that lies in it; the output slabs keep clear of both ends.
+    constexpr bool LATE = big_tables_late<Epi>(BM, BN, BKB, NSTAGE);
+    constexpr int LATE_BYTES = LATE ? late_table_bytes<Epi>(BN) : 0;
 
     const int M = dev_rows ? *dev_rows : host_rows;
     const int tiles = ((M + BM - 1) / BM) * tiles_n;
@@ -474,26 +523,28 @@ void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, 
     const int wm = (wave >> 1) * 32 * TM, wn = (wave & 1) * 32 * TN;
     const int r = lane & 31, g = lane >> 5;
 
-    const char *src[NLD];
+    // 32-bit offsets from a base that is the same for the whole wave: half the registers of a pointer per load, and the step to
+    // the next stage is scalar
+    constexpr int NLDA = BM / RPI / NWAVES;                       // the first NLDA pieces hold token rows
+    static_assert(BM % (RPI * NWAVES) == 0, "a piece of every wave holds rows of one operand");
+    const char *bases[2] = {A + (size_t)m0 * Kbytes, W + (size_t)n0 * Kbytes};
+    unsigned off[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; j++) {
-        const int srow = RPI * (wave + NWAVES * j) + lane / CH;
-        if (srow < BM) {
-            int am = m0 + srow; if (am > M - 1) am = M - 1;
-            src[j] = A + (size_t)am * Kbytes + (((lane % CH) ^ swz<BKB>(srow)) << 4);
-        } else {
-            const int row = srow - BM;
-            src[j] = W + (size_t)(n0 + row) * Kbytes + (((lane % CH) ^ swz<BKB>(row)) << 4);
-        }
+        const int srow = RPI * (wave + NWAVES * j) + lane / CH, row = j < NLDA ? min(srow, M - 1 - m0) : srow - BM;
+        off[j] = (unsigned)row * (unsigned)Kbytes + (((lane % CH) ^ swz<BKB>(j < NLDA ? srow : row)) << 4);
     }
     const int KT = Kbytes / BKB;
     int fill_slot = 0, fill_kt = 0;                               // next stage to request and the ring slot it goes to
     auto issue = [&]() {
         char *st = lds + fill_slot * STAGE_BYTES;
 #pragma unroll
-        for (int j = 0; j < NLD; j++)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + (size_t)fill_kt * BKB),
+        for (int j = 0; j < NLD; j++) {
+            unsigned o = off[j];
+            asm volatile("" : "+v"(o));                            // keeps the offset a 32-bit one: scalar base + vector offset
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(bases[j >= NLDA] + (size_t)fill_kt * BKB + o),
                                              (__attribute__((address_space(3))) void *)(st + (wave + NWAVES * j) * 1024), 16, 0, 0);
+        }
         fill_kt++;
         fill_slot = fill_slot + 1 == NSTAGE ? 0 : fill_slot + 1;
     };
@@ -519,7 +570,8 @@ void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, 
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; s++)
         if (s < KT) issue();
-    epi.load_tables(tab, n0, BN, tid, NT);
+    if constexpr (LATE) tab = reinterpret_cast<float *>(lds + ((KT & 1) ? RING_BYTES - LATE_BYTES : 0));
+    else epi.load_tables(tab, n0, BN, tid, NT);
 
     typename T::acc_t acc[TN][TM];
 #pragma unroll
@@ -562,6 +614,7 @@ void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, 
         ready(fa[ks & 1], fw[ks & 1]);
         __builtin_amdgcn_sched_barrier(0);
         if (refill && ks == 0) issue();
+        if (LATE && !more && ks == 0) epi.load_tables_direct(tab, n0, BN, wave, NWAVES, lane);
         multiply(fa[ks & 1], fw[ks & 1]);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -574,8 +627,10 @@ void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, 
         for (int ks = 0; ks < KS; ks++) step(ks, false, true, std::integral_constant<int, 0>());
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) step(ks, false, false, std::integral_constant<int, 0>());
-    typename Epi::Tab first_tab = epi.load_tab(tab, BN, wn, g);    // arrives while the waves gather
+    typename Epi::Tab first_tab;
+    if (!LATE) first_tab = epi.load_tab(tab, BN, wn, g);          // arrives while the waves gather
     wait_vm_and_barrier<0>();                                     // the ring is idle from here on
+    if (LATE) first_tab = epi.load_tab(tab, BN, wn, g);
 
     if constexpr (!Epi::STAGED) {
 #pragma unroll
@@ -596,11 +651,11 @@ void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, 
         constexpr int OB = Epi::OUT_BYTES;
         constexpr int STRIDE = BN * OB + 16;
         constexpr int CHUNKS = BN * OB / 16;
-        static_assert(2 * 64 * STRIDE <= RING_BYTES, "two staging slabs must fit in the ring");
+        static_assert(2 * 64 * STRIDE + 2 * LATE_BYTES <= RING_BYTES, "two staging slabs must fit in the ring");
         static_assert((64 * CHUNKS) % NT == 0, "output chunks must split evenly over the threads");
 #pragma unroll
         for (int j = 0; j < TM; j++) {
-            char *slab = lds + (j & 1) * 64 * STRIDE;             // alternate slabs: one barrier per pass
+            char *slab = lds + LATE_BYTES + (j & 1) * 64 * STRIDE;             // alternate slabs: one barrier per pass
             const int lrow = (wave >> 1) * 32 + r;
             typename Epi::Tab cur = j == 0 ? first_tab : epi.load_tab(tab, BN, wn, g);
 #pragma unroll
@@ -640,8 +695,9 @@ hipError_t launch_big(const void *A, const void *W, void *out, const Epi &epi, R
                       const Timing *tm)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
-    constexpr size_t LDS_FIXED = (size_t)NSTAGE * (BM + BN) * BKB + (size_t)Epi::NTAB * BN * sizeof(float);
-    const size_t LDS = LDS_FIXED + extra_lds_of(epi, 0);
+    constexpr bool LATE = big_tables_late<Epi>(BM, BN, BKB, NSTAGE);
+    constexpr size_t LDS_FIXED = (size_t)NSTAGE * (BM + BN) * BKB + (LATE ? 0 : (size_t)Epi::NTAB * BN * sizeof(float));
+    const size_t LDS = LDS_FIXED + (LATE ? 0 : extra_lds_of(epi, 0));
     if (N % BN || (K * T::ELEM) % BKB || LDS > 160 * 1024) return hipErrorInvalidValue;
     auto kern = gemm_nt_big_kernel<T, Epi, TM, TN, BKB, NSTAGE, WPE>;
     static std::atomic<bool> attr_set{false};
@@ -1105,7 +1161,7 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
             // per CU overlap one's epilogue with the other's main loop; long operand rows amortise the epilogue of a
             // 256 x 256 tile by themselves
             if (std::is_same<T, I8>::value && N % 256 == 0 && rows.host_rows >= BIG_TILE_MIN_ROWS)
-                cfg = kbytes >= LONG_K_BYTES ? 7 : 4;
+                cfg = kbytes >= LONG_K_BYTES ? 7 : N % 192 == 0 ? 6 : 4;
         }
     }
     if constexpr (std::is_same<T, I8>::value && (std::is_same<Epi, EpiRequant>::value || std::is_same<Epi, EpiGeluTable>::value)) {
@@ -1124,7 +1180,7 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
     case 3: return launch_big<T, Epi, 4, 4, 128, 2>(A, W, out, epi, rows, N, K, st, tm);      // 256 x 256, two 128-byte stages
     case 4: return launch_big<T, Epi, 2, 4, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 128 tokens x 256 channels, two blocks per CU
     case 5: return launch_big<T, Epi, 4, 2, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 256 tokens x 128 channels, two blocks per CU
-    case 6: return launch_big<T, Epi, 2, 3, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 128 x 192, two blocks per CU
+    case 6: return launch_big<T, Epi, 2, 3, 128, 2, 2>(A, W, out, epi, rows, N, K, st, tm);   // 128 x 192, two 128-byte stages, two blocks per CU
     case 7: return launch_big<T, Epi, 4, 4, 64, 4>(A, W, out, epi, rows, N, K, st, tm);       // 256 x 256, four 64-byte stages
     case 1:
         // the GELU epilogue is as much vector work as the main loop is matrix work: 64-byte stages leave room

@@ -352,6 +352,52 @@ def test_qkv_gemm_and_attention_in_one_kernel_bit_exact(P, lens, heads, offsets)
     assert np.array_equal(no_bias, oracle.attention_i8(oracle.epilogue_requant(oracle.gemm_i8_i32(x, w), m, np.zeros(3 * H, np.float32)), cu, heads, *sc))
 
 
+@pytest.mark.parametrize("M,N,K", [(130, 384, 384), (65, 192 * 2, 640)])
+def test_tables_that_arrive_with_the_last_stage_of_an_odd_number(P, M, N, K):
+    """128 x 192 tiles (configuration 6): the epilogue's tables take the ring stage that the last one but one leaves free,
+    the upper one when the number of 128-byte stages is odd.  Without an offset vector they are filled with zeros."""
+    rng = np.random.default_rng(M + N + K)
+    A = rng.integers(-127, 128, (M, K), dtype=np.int8)
+    W = rng.integers(-127, 128, (N, K), dtype=np.int8)
+    s_w, bias = _tables(rng, N)
+    m, b = oracle.fold_requant(0.037, s_w, bias, 0.021 * np.sqrt(K / 768))
+    md = oracle.fold_dequant(0.05 * np.sqrt(768 / K), s_w)
+    spec, entries = P.gelu_table_build(0.0147)
+    acc = oracle.gemm_i8_i32(A, W)
+    P.set_gemm_config(6)
+    try:
+        req = host(P.gemm_i8_requant(dev(A), dev(W), dev(m), dev(b)))
+        none = host(P.gemm_i8_requant(dev(A), dev(W), dev(m), None))
+        gel = host(P.gemm_i8_gelu_quant(dev(A), dev(W), dev(md), dev(bias), 0.0147, (spec, dev(entries))))
+    finally:
+        P.set_gemm_config(-1)
+    assert np.array_equal(req, oracle.epilogue_requant(acc, m, b))
+    assert np.array_equal(none, oracle.epilogue_requant(acc, m, np.zeros(N, np.float32)))
+    assert np.array_equal(gel, oracle.epilogue_gelu_quant(acc, md, bias, 0.0147))
+
+
+def test_qkv_attention_with_an_odd_number_of_stages(P):
+    """The same in the QKV + attention kernels (INT8: three 128-byte stages for six heads, FP16: five for five heads)."""
+    rng = np.random.default_rng(61)
+    lens = [128, 3, 77]
+    cu = _cu(lens)
+    H, T = 384, int(cu[-1])
+    x, w = rng.integers(-127, 128, (T, H), dtype=np.int8), rng.integers(-127, 128, (3 * H, H), dtype=np.int8)
+    m = (26.0 / (73.3 * 73.3 * np.sqrt(H)) * (0.8 + 0.4 * rng.random(3 * H))).astype(np.float32)
+    b = (rng.standard_normal(3 * H) * 3).astype(np.float32)
+    sc = (0.0209, 0.0249, 0.021, 0.0003, 0.0021)
+    got = host(P.qkv_attention_i8(dev(x), dev(w), dev(m), dev(b), dev(cu), max(lens), 6, *sc))
+    assert np.array_equal(got, oracle.attention_i8(oracle.epilogue_requant(oracle.gemm_i8_i32(x, w), m, b), cu, 6, *sc))
+    H = 320
+    x = rng.standard_normal((T, H)).astype(np.float16)
+    w = (rng.standard_normal((3 * H, H)) * 0.6 / np.sqrt(H)).astype(np.float16)
+    for bias in ((rng.standard_normal(3 * H) * 0.1).astype(np.float32), None):
+        got = host(P.qkv_attention_f16(dev(x), dev(w), None if bias is None else dev(bias), dev(cu), max(lens), 5)).astype(np.float64)
+        zeros = np.zeros(3 * H, np.float32)
+        d = np.abs(got - oracle.attention_f16(oracle.gemm_f16(x, w, zeros if bias is None else bias, False), cu, 5).astype(np.float64))
+        assert d.max() <= 4e-3 and d.mean() <= 2e-4                # the bound of the test of this kernel below
+
+
 @pytest.mark.parametrize("S,B,heads,unsigned", [(128, 3, 2, False), (256, 2, 1, False), (384, 2, 1, False),
                                                 (512, 2, 1, False), (512, 1, 2, True), (96, 3, 1, False), (320, 2, 1, False)])
 def test_int8_attention_without_sequence_offsets_bit_exact(P, S, B, heads, unsigned):
