@@ -1157,9 +1157,9 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
             // widths that 192 does not divide (FFN1 of BERT-large, 4096): 128 x 256 tiles (-3.5 % on that forward
             // at 2 x 4096 tokens against 128 x 128; 256 x 128 -0.5 %, 64 x 128 +5.5 %)
             else if (N % 256 == 0 && N >= 2304 && rows.host_rows >= WIDE_TILE_MIN_ROWS) cfg = 4;
-            // many tokens (INT8): wave tiles of 64 x 128 halve the LDS operand traffic per MFMA, two such blocks
-            // per CU overlap one's epilogue with the other's main loop; long operand rows amortise the epilogue of a
-            // 256 x 256 tile by themselves
+            // many tokens (INT8): the 128 x 192 tiles also where few rows of tiles would do with larger ones (BERT-base 128 x 512,
+            // 128 x 256 tiles of 64-byte stages: +0.5 %); long operand rows amortise the epilogue of a 256 x 256 tile by
+            // themselves (FFN2 there on 128 x 192: +1.4 %); 128 x 256 where 192 does not divide the width
             if (std::is_same<T, I8>::value && N % 256 == 0 && rows.host_rows >= BIG_TILE_MIN_ROWS)
                 cfg = kbytes >= LONG_K_BYTES ? 7 : N % 192 == 0 ? 6 : 4;
         }
