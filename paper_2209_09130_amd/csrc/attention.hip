@@ -67,10 +67,13 @@ __device__ __forceinline__ double exp_nonpos(double x)
 // The same function, for the kernels that hold EXP2_TABLE in LDS: x = (k + f) ln2 / 256 with |f| <= 1/2,
 //     exp(x) = 2^(k/256) + 2^(k/256) f q(f),
 // q a polynomial of degree 3 that interpolates (2^(f/256) - 1) / f at the four Chebyshev nodes of [-0.5001, 0.5001]
-// (solved and rounded as above).  Same accuracy (2^-50 for x > -50, 2^-49 at -104), checked the same way.  The vector arithmetic
-// is what bounds the softmax: this takes 12 operations (a clamp among them) for the polynomial's 16, and its table read runs
-// beside them (2.4 clocks of LDS time per wave and read where many entries are equal; those are broadcast).  Forward, before and
-// after: BERT-base 128 x 512 Fully-Quant 3.7 % shorter, 6 x 500..1100 3.9 %, 33 x 40..301 binary16 softmax 2.6 %.
+// (solved and rounded as above).  f is formed with 256 / ln2 in two parts: the rounding of a single constant is multiplied by x and
+// alone costs 2^-49.1 at -104.  Relative error below 2^-51.9 over the whole range (the roundings of the table entry and of the last
+// operation), checked the same way; the polynomial above reaches 2^-49.6.  The vector arithmetic
+// is what bounds the softmax: this takes 13 operations (a clamp among them) for the polynomial's 16, and its table read runs
+// beside them (2.4 clocks of LDS time per wave and read where many entries are equal; those are broadcast).  Forward with the
+// polynomial and with this: BERT-base 128 x 512 Fully-Quant 12104 / 11603 us, 6 x 500..1100 1933 / 1860, 33 x 40..301 binary16
+// softmax 1709 / 1685 (the second part of the constant is 1.1, 1.5 and 0.7 % of that).
 // The result underflows to a binary32 zero below -103.98, so the argument is clamped at -104, also that of a masked key.
 typedef uint64_t ExpTable[256];
 __device__ __forceinline__ float exp_nonpos(float x, const ExpTable &table)
@@ -79,7 +82,8 @@ __device__ __forceinline__ float exp_nonpos(float x, const ExpTable &table)
     const double shifted = __builtin_fma(xd, 0x1.71547652b82fep+8, 6755399441055744.0);
     const unsigned k = (unsigned)__double_as_longlong(shifted);
     const uint64_t entry = table[k & 255];
-    const double f = __builtin_fma(xd, 0x1.71547652b82fep+8, -(shifted - 6755399441055744.0));
+    double f = __builtin_fma(xd, 0x1.71547652b82fep+8, -(shifted - 6755399441055744.0));
+    f = __builtin_fma(xd, 0x1.777d0ffda0d24p-48, f);
     double q = 0x1.3b2ab83ecf101p-39;
     q = __builtin_fma(q, f, 0x1.c6b0902ba1a20p-29);
     q = __builtin_fma(q, f, 0x1.ebfbdff82c585p-19);

@@ -1,5 +1,7 @@
 // 2^(j/256), j = 0..255, as the bits of a binary64 number from which j * 2^12 is taken off the high dword: adding k << 12 to
 // that dword, with k = 256 n + j, then gives 2^(k/256).  Each value is 2^(j/256) from 60 digits, rounded to nearest.
+// A table of 2^(j/N) with a short polynomial for the rest is P. T. P. Tang's method (Table-driven implementation of the
+// exponential function in IEEE floating-point arithmetic, ACM TOMS 15(2), 1989).
 #pragma once
 #include <cstdint>
 
