@@ -5,7 +5,10 @@
 // the 50 bytes per clock a CU pulls out of L2.  So everything serves keeping that stream going: 16 waves, a row is read by
 // 32 lanes (768 and 1024 are whole multiples of their 256 channels), and a wave has its eight rows' loads of a channel
 // section outstanding at once.  With four waves that finished one row before they asked for the next, the kernel waited
-// out 192 memory latencies in a row: a request of one short sequence took 695 us, 190 of them here; now 505.
+// out 192 memory latencies in a row: one sequence, us per launch, 128 -> 17.2 at 768 and 193 -> 25.7 at 1024.
+// A lane keeps one sum for the even and one for the odd 256-channel sections, so that sums are formed in the order of 64 lanes
+// that read 512 channels at a time; a single sum per lane is twice as long a chain and its error 14 % larger at 768, 21 % at
+// 1024 (it is as fast at 768 and takes 24.4 us at 1024).
 #include "samp_common.h"
 
 namespace samp {
@@ -27,26 +30,37 @@ __device__ __forceinline__ void matrix_times_vector(const __half *__restrict__ W
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & 31, upper = lane >> 5;
     constexpr int ROWS = 2 * CLASSIFY_PAIRS;
     for (int n0 = wave * ROWS; n0 < N; n0 += CLASSIFY_WAVES * ROWS) {
-        float acc[CLASSIFY_PAIRS];
+        float acc[CLASSIFY_PAIRS], odd[CLASSIFY_PAIRS];
         const __half *row[CLASSIFY_PAIRS];
 #pragma unroll
         for (int p = 0; p < CLASSIFY_PAIRS; p++) {
-            acc[p] = 0.0f;
+            acc[p] = odd[p] = 0.0f;
             row[p] = W + (size_t)min(n0 + 2 * p + upper, N - 1) * H;            // rows past the end repeat the last one
         }
-#pragma unroll 4
-        for (int k = sub * 8; k < H; k += 256) {
-            v8h w[CLASSIFY_PAIRS];
+#pragma unroll 2
+        for (int k0 = sub * 8; k0 < H; k0 += 512) {
 #pragma unroll
-            for (int p = 0; p < CLASSIFY_PAIRS; p++) w[p] = *reinterpret_cast<const v8h *>(row[p] + k);
-            float xv[8];
+            for (int u = 0; u < 2; u++) {
+                const int k = k0 + 256 * u;
+                if (k < H) {
+                    v8h w[CLASSIFY_PAIRS];
 #pragma unroll
-            for (int e = 0; e < 8; e++) xv[e] = (float)x[k + e];
+                    for (int p = 0; p < CLASSIFY_PAIRS; p++) w[p] = *reinterpret_cast<const v8h *>(row[p] + k);
+                    float xv[8];
 #pragma unroll
-            for (int p = 0; p < CLASSIFY_PAIRS; p++)
+                    for (int e = 0; e < 8; e++) xv[e] = (float)x[k + e];
 #pragma unroll
-                for (int e = 0; e < 8; e++) acc[p] = __builtin_fmaf((float)w[p][e], xv[e], acc[p]);
+                    for (int p = 0; p < CLASSIFY_PAIRS; p++)
+#pragma unroll
+                        for (int e = 0; e < 8; e++) {
+                            float &a = u ? odd[p] : acc[p];
+                            a = __builtin_fmaf((float)w[p][e], xv[e], a);
+                        }
+                }
+            }
         }
+#pragma unroll
+        for (int p = 0; p < CLASSIFY_PAIRS; p++) acc[p] += odd[p];
 #pragma unroll
         for (int p = 0; p < CLASSIFY_PAIRS; p++) acc[p] = half_wave_sum(acc[p]);
 #pragma unroll

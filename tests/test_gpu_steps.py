@@ -719,6 +719,33 @@ def test_classification_target_at_ragged_widths(P, B, S, H, Cn):
     test_classification_target_within_accumulation_tolerance(P, B, S, H, Cn)
 
 
+@pytest.mark.parametrize("H", [8, 256, 264, 768, 1024, 1288, 4096])
+def test_classification_target_adds_up_in_the_order_of_64_lanes(P, H):
+    """The error of a binary32 sum follows its order: chains of one fused multiply-add per channel, one chain per eight
+    channels of a 512-channel section (H / 64 products long), met in a tree of 64.  The second product is replayed in
+    that order, each multiply-add in extended precision and rounded once; its input, the pooled vector, is read
+    through a unit matrix first (a sum of one product and zeros is exact)."""
+    rng = np.random.default_rng(H)
+    Cn = 203
+    hid = rng.standard_normal((1, 1, H)).astype(np.float16)
+    wp = (rng.standard_normal((H, H)) * H ** -0.5).astype(np.float16)
+    bp = (rng.standard_normal(H) * 0.1).astype(np.float32)
+    wc = (rng.standard_normal((Cn, H)) * 0.05).astype(np.float16)
+    pool = lambda w: host(P.classify(dev(hid), dev(wp), dev(bp), dev(w), dev(np.zeros(len(w), np.float32))))[0]
+    pooled = pool(np.eye(H, dtype=np.float16))
+    got = pool(wc)
+    chains = np.zeros((Cn, 64), np.float32)
+    for k in range(0, H, 8):
+        lane = k // 8 % 64
+        for e in range(k, k + 8):
+            chains[:, lane] = (wc[:, e].astype(np.longdouble) * np.longdouble(pooled[e]) + chains[:, lane]).astype(np.float32)
+    step = 32
+    while step:
+        chains = chains + chains[:, np.arange(64) ^ step]
+        step //= 2
+    assert np.array_equal(got, chains[:, 0])
+
+
 def test_entry_quantiser_bit_exact(P):
     """samp_quantize_f16_i8: the un-masked entry quantiser, incl. ties, values beyond the clamp and a ragged tail of
     the grid (element count not a multiple of the block size)."""
