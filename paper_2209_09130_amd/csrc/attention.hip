@@ -96,6 +96,10 @@ __device__ __forceinline__ float exp_nonpos(float x, const ExpTable &table)
 // scalar branch instead of a lane mask with copies of the live registers where the paths join.
 __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
 
+// The lane's number, counted anew where it is needed late: what is derived from it then need not stay in registers from the
+// kernel's first lines on.
+__device__ __forceinline__ int lane_again() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
 __device__ __forceinline__ int opaque_zero()
 {
     int z;
@@ -177,7 +181,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     __shared__ unsigned hist[HIST ? 256 : 1];
     // One slab per wave: first its V^T tiles (written and read by that wave alone), then, once its last P.V
     // product has read them, its partial context for the other waves; sharing the bytes lets a third block fit a CU.
-    // It holds at most four tiles: a fifth one (and so on) takes a tile's place when that one has been multiplied.
+    // It holds at most four tiles: a fifth one (and so on) takes the place of a tile that has been multiplied, two steps before it
+    // is used itself (three steps before, one more tile of scores is alive: five tiles of unsigned codes then took scratch).
     constexpr int VT_TILE = 64 * VT_STRIDE_I8, SO_BYTES = QB * 64 * 4, VT_TILES = NT < 4 ? NT : 4;
     constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
     __shared__ __attribute__((aligned(16))) int8_t slab[NW][SLAB];
@@ -285,9 +290,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
 #pragma unroll
     for (int i = 0; i < NT; i++) {
         const int j0 = (w + NW * i) * 32;
-        const int j3 = j0 + 3 * 32 * NW;                          // the tile that takes the place of the one before this
+        const int j2 = j0 + 2 * 32 * NW;                          // the tile that takes the place of the one before the last
         unsigned d[2][4];
-        if (i > 0 && i + 3 < NT && j3 < n) load_v_tile(vp, ld, j3, n, lane, d);
+        if (i > 1 && i + 2 < NT && j2 < n) load_v_tile(vp, ld, j2, n, lane_again(), d);
         if (j0 < n) {
             v4i pf;
 #pragma unroll
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
                 if (PU) vsum[cb] = add_codes(vf, vsum[cb]);
             }
         }
-        if (i > 0 && i + 3 < NT && j3 < n) store_vt_tile(d, lane, &slab[w][((i + 3) & 3) * VT_TILE]);
+        if (i > 1 && i + 2 < NT && j2 < n) store_vt_tile(d, lane_again(), &slab[w][((i + 2) & 3) * VT_TILE]);
     }
     if (PU) {
 #pragma unroll
