@@ -958,8 +958,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
                                                             float *__restrict__ p_absmax)
 {
     // one slab per wave, as in the INT8 kernel: first its V^T tiles (two; a further one takes a tile's place when that one has
-    // been multiplied), then its partial context for the other waves
-    constexpr int VT_TILE = 64 * VT_STRIDE_F16, SO_BYTES = QB * 64 * 4, VT_TILES = NT < 2 ? NT : 2;
+    // been multiplied), then its partial context for the other waves.  TIGHT: ten tiles of scores leave two waves per SIMD just
+    // enough registers if V rows are requested one tile later (four tiles in the slab) and tiles past the end are skipped in
+    // the sums of exponentials; without either it took 48 bytes of scratch (12 heads, 12 sequences of 1250 tokens: 213 -> 194 us).
+    // Fewer or more tiles do not need it, and 12 sequences of 1500 would lose 3 %.
+    constexpr bool TIGHT = NT == 10;
+    constexpr int VT_TILE = 64 * VT_STRIDE_F16, SO_BYTES = QB * 64 * 4, VT_TILES = TIGHT ? 4 : NT < 2 ? NT : 2, AHEAD = TIGHT ? 2 : 1;
     constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
     __shared__ __attribute__((aligned(16))) char slab[4][SLAB];
     auto so = [&](int wave) { return reinterpret_cast<float(*)[64]>(slab[wave]); };
@@ -1020,11 +1024,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     float part = 0.0f;
 #pragma unroll
     for (int i = 0; i < NT; i++)
+        if (!TIGHT || (w + 4 * i) * 32 < n) {                     // tiles past the end add zeros
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-            const float ev = __builtin_amdgcn_exp2f((sc[i][e] - mx) * 1.44269504088896341f);
-            sc[i][e] = ev;
-            part += ev;
+            for (int e = 0; e < 16; e++) {
+                const float ev = __builtin_amdgcn_exp2f((sc[i][e] - mx) * 1.44269504088896341f);
+                sc[i][e] = ev;
+                part += ev;
+            }
         }
     part += __shfl_xor(part, 32, 64);
     if (g == 0) ssum[w][r] = part;
@@ -1041,8 +1047,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
         for (int e = 0; e < 16; e++) o[cb][e] = 0.0f;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j1 = (w + 4 * (i + 1)) * 32;                     // the tile that takes the place of the one before this
-        const bool more = i > 0 && i + 1 < NT && j1 < n;
+        const int j1 = (w + 4 * (i + AHEAD)) * 32;                 // the tile that takes the place of tile i - AHEAD
+        const bool more = i >= AHEAD && i + AHEAD < NT && j1 < n;
         v8h d[2][2];
         if (more) load_v_tile_f16(vp, ld, j1, n, lane, d);
         if ((w + 4 * i) * 32 < n) {
@@ -1053,7 +1059,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
                 for (int e = 0; e < 8; e++) pf[e] = to_half(sc[i][8 * hf + e] * rS);
 #pragma unroll
                 for (int cb = 0; cb < 2; cb++) {
-                    const char *rowp = &slab[w][(i & 1) * VT_TILE + (cb * 32 + r) * VT_STRIDE_F16];
+                    const char *rowp = &slab[w][i % VT_TILES * VT_TILE + (cb * 32 + r) * VT_STRIDE_F16];
                     const v4h lo = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 4 * g) * 2);
                     const v4h hi = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 8 + 4 * g) * 2);
                     const v8h vf = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -1061,7 +1067,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
                 }
             }
         }
-        if (more) store_vt_tile_f16(d, lane, &slab[w][((i + 1) & 1) * VT_TILE]);
+        if (more) store_vt_tile_f16(d, lane, &slab[w][(i + AHEAD) % VT_TILES * VT_TILE]);
     }
 #pragma unroll
     for (int cb = 0; cb < 2; cb++)

@@ -40,7 +40,7 @@ def kernels(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf is not installed")
-@pytest.mark.parametrize("kernel", ["attention_i8_kernel"])
+@pytest.mark.parametrize("kernel", ["attention_i8_kernel", "attention_i8_p16_kernel", "attention_f16_kernel"])
 def test_attention_kernels_use_no_scratch_memory(kernel, tmp_path):
     found = [(name, scratch) for name, scratch in kernels(tmp_path) if kernel in name]
     assert len(found) >= 4, found
