@@ -223,7 +223,7 @@ int check_forward_args(const samp_encoder_t *enc, const void *hidden, int B, int
 
 // The kernel sequence.  calib: FP16-only run that also records each tensor's absmax.
 int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int B, int S, void *out, void *workspace,
-        hipStream_t st, bool calib)
+        hipStream_t st, bool calib, bool beside)
 {
     const samp_config_t &c = enc->cfg;
     const int H = c.hidden, F = c.ffn, heads = c.heads, Lc = c.layers;
@@ -231,7 +231,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     const int Tmax = B * S;
     const bool packed = mask != nullptr;
     const int *cu = nullptr, *row_map = nullptr;
-    Rows rows{Tmax, nullptr};
+    Rows rows{Tmax, nullptr, beside};
     const void *x = nullptr;
     const bool first8 = (enc->L[0].mode & 1) != 0;
 
@@ -518,7 +518,7 @@ static int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids
                          void *out, void *workspace, hipStream_t st)
 {
     const int G = choose_groups(enc, B, S);
-    if (G == 1) return run(enc, hidden, ids, mask, B, S, out, workspace, st, false);
+    if (G == 1) return run(enc, hidden, ids, mask, B, S, out, workspace, st, false, false);
     if (!enc->streams_ready) {
         for (int i = 0; i < MAX_GROUPS - 1; i++) {
             HIP_TRY(hipStreamCreateWithFlags(&enc->side[i], hipStreamNonBlocking));
@@ -544,7 +544,7 @@ static int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids
         if (ids) part = Ids{ids->emb, ids->token_ids + (size_t)b0 * S, ids->segment_ids ? ids->segment_ids + (size_t)b0 * S : nullptr};
         const int rc = run(enc, ids ? nullptr : (const __half *)hidden + b0 * seq_elems, ids ? &part : nullptr,
                            mask ? mask + (size_t)b0 * S : nullptr, nb, S,
-                           (__half *)out + b0 * seq_elems, (char *)workspace + g * piece, gs, false);
+                           (__half *)out + b0 * seq_elems, (char *)workspace + g * piece, gs, false, true);
         if (rc != SAMP_OK) return rc;
         if (g > 0 && !serial) {
             HIP_TRY(hipEventRecord(enc->join[g - 1], gs));
@@ -586,7 +586,7 @@ int samp_encoder_forward_noalloc(samp_encoder_t *enc, const void *hidden, const 
     void *ws = nullptr;
     if (int rc = noalloc_scratch(&ws)) return rc;
     // one group, plain launches on the caller's stream: no side streams, events or graphs are created on this path
-    return run(enc, hidden, nullptr, mask, B, S, out, ws, static_cast<hipStream_t>(stream), false);
+    return run(enc, hidden, nullptr, mask, B, S, out, ws, static_cast<hipStream_t>(stream), false, false);
 }
 
 static int check_embedding(const samp_embedding_t *e, int H, int S)
@@ -694,7 +694,7 @@ int samp_encoder_calibrate(samp_encoder_t *enc, const void *hidden, const int32_
     if (!aligned(hidden, 16)) return fail(SAMP_ERR_ARG, "hidden must be 16-byte aligned");
     if (!enc->all_fp16) return fail(SAMP_ERR_ARG, "calibration needs an encoder whose layers are all SAMP_FP16");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (int rc = run(enc, hidden, nullptr, mask, B, S, nullptr, workspace, st, true)) return rc;
+    if (int rc = run(enc, hidden, nullptr, mask, B, S, nullptr, workspace, st, true, false)) return rc;
     const int n = enc->cfg.layers * 10;
     std::vector<float> am(n);
     Workspace w = carve(enc->cfg, B, S, workspace);

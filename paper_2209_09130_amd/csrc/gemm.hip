@@ -1127,8 +1127,13 @@ hipError_t launch_small_f16_any(const void *A, const void *W, void *out, const E
 constexpr int LONG_K_BYTES = 3072;
 // From 2048 rows the wide GEMMs fill the chip with 128 x 192 tiles; below they leave most CUs idle (us per launch in a chain, 128 x
 // 192 against 64 x 128 tiles at 1024 rows: 2304 x 768 9.8 / 7.4, FFN1 3072 x 768 12.1 / 9.1, FFN1 4096 x 1024 17.3 / 11.8, FP16 2304 x
-// 768 17.9 / 12.1; at 1536 rows 9.9 / 7.8, 12.3 / 11.7, 17.5 / 15.2, 18.2 / 13.0)
-constexpr int WIDE_TILE_MIN_ROWS = 2048;
+// 768 17.9 / 12.1; at 1536 rows 9.9 / 7.8, 12.3 / 11.7, 17.5 / 15.2, 18.2 / 13.0).  With another batch group on the chip the idle CUs
+// are that group's, and the forward crosses earlier (us, 6 layers of width 768, Fully-Quant / MHA-only / Quant-FFN-Only / FP16, 128 x 192
+// against 64 x 128 tiles: two groups of 1280 and 1408 rows 424 / 582 / 533 / 653 against 412 / 581 / 499 / 635, of 1408 rows
+// 401 / 555 / 443 / 594 against 405 / 575 / 447 / 609, of 1792 rows 412 / 598 / 476 / 668 against 447 / 659 / 503 / 690), where the rows
+// are all there: ragged batches, whose padded rows are counted here, stay at 2048 (two groups of 1536 with 984 tokens each:
+// Fully-Quant 390 against 384, FP16 570 against 551).
+constexpr int WIDE_TILE_MIN_ROWS = 2048, WIDE_TILE_MIN_ROWS_BESIDE = 1408;
 constexpr int BIG_TILE_MIN_ROWS = 16384;                         // from here on the 256 x 256 tiles fill the chip several times over
 
 constexpr int big_tile_width(int cfg) { return cfg == 6 ? 192 : 256; }
@@ -1145,6 +1150,7 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
     if (cfg < 0) {
         if (kbytes % 128) cfg = 0;
         else {
+            const int wide_min_rows = rows.beside && !rows.dev_rows ? WIDE_TILE_MIN_ROWS_BESIDE : WIDE_TILE_MIN_ROWS;
             const long tiles = (long)(N / 128) * ((rows.host_rows + 127) / 128);
             // fewer 128 x 128 tiles than CUs: the smaller tiles of configuration 2 (BERT-large's 1024-wide GEMMs at
             // 4096 tokens, 256 tiles, measured -4.4 % on that forward with 128 x 128 against 64 x 128)
@@ -1153,10 +1159,10 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
             // per CU.  Measured in the BERT-base forward at 2 x 2048 tokens: -5 % with FFN1 (whose table-lookup epilogue
             // in the 64 x 128 configuration costs more than it saves: its table in LDS takes the third resident block
             // away), another -1.4 % with QKV; the FP16 forward gains 2 %
-            if (N % 192 == 0 && N >= 2304 && rows.host_rows >= WIDE_TILE_MIN_ROWS) cfg = 6;
+            if (N % 192 == 0 && N >= 2304 && rows.host_rows >= wide_min_rows) cfg = 6;
             // widths that 192 does not divide (FFN1 of BERT-large, 4096): 128 x 256 tiles (-3.5 % on that forward
             // at 2 x 4096 tokens against 128 x 128; 256 x 128 -0.5 %, 64 x 128 +5.5 %)
-            else if (N % 256 == 0 && N >= 2304 && rows.host_rows >= WIDE_TILE_MIN_ROWS) cfg = 4;
+            else if (N % 256 == 0 && N >= 2304 && rows.host_rows >= wide_min_rows) cfg = 4;
             // many tokens (INT8): the 128 x 192 tiles also where few rows of tiles would do with larger ones (BERT-base 128 x 512,
             // 128 x 256 tiles of 64-byte stages: +0.5 %); long operand rows amortise the epilogue of a 256 x 256 tile by
             // themselves (FFN2 there on 128 x 192: +1.4 %); 128 x 256 where 192 does not divide the width

@@ -159,7 +159,9 @@ inline void launch_kernel(K kern, dim3 grid, dim3 block, size_t lds, hipStream_t
 }
 
 // Row limit of a launch: rows = *dev_rows if dev_rows != nullptr, else host_rows.
-struct Rows { int host_rows; const int *dev_rows; };
+// beside: the kernels of another batch group run on the chip at the same time (only the choice between kernels of equal results
+// looks at it).
+struct Rows { int host_rows; const int *dev_rows; bool beside = false; };
 
 // Threshold table of the FFN1 epilogue (gelu_table.hip): bin(y) = low mantissa bits of
 // med3(fmaf(y, rate, offset), 2^23, t_max); entry i = { binary32 Y_i, lo | hi << 8 }, code = y >= Y_i ? hi : lo.

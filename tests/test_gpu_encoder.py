@@ -627,6 +627,31 @@ def test_batch_groups_and_graph_replay_do_not_change_results(P, varlen):
     compare(base.cpu().numpy(), want, lens, False, f"groups/graph varlen={varlen}", loose_bound(w.modes, sc))
 
 
+@pytest.mark.parametrize("modes", [(FULL_INT8, FP16), (FFN_INT8, MHA_INT8)])
+@pytest.mark.parametrize("hidden,batch,varlen", [(768, 21, False), (768, 22, False), (768, 22, True), (768, 31, False), (768, 32, False),
+                                                 (1024, 24, False), (512, 31, False), (512, 33, True)])
+def test_a_batch_in_two_groups_is_the_same_bytes_at_the_bounds_of_the_kernel_choice(P, modes, hidden, batch, varlen):
+    """Tile sizes and the LayerNorm's form are chosen by a launch's rows and by whether another batch group runs beside it: two
+    groups of 1280 to 2176 rows (either side of the bounds of the wide tiles, the small tiles and the LayerNorm) against one
+    group of all rows, whose kernels are others."""
+    import torch
+    w = W.Workload("two groups", 2, hidden, hidden // 64, 4 * hidden, batch, 128, modes, varlen=varlen, plain_params=False,
+                   calib_batch=1, calib_seq=32)
+    wts = W.make_weights(w)
+    hid, _, mask = W.make_hidden(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    h, m = torch.from_numpy(hid).cuda(), torch.from_numpy(mask).cuda() if varlen else None
+    enc = P.Encoder(*args(w), w.modes, wts, sc, max_batch=w.batch, max_seq=w.seq)
+    enc.set_graph(False)
+    outs = []
+    for groups in (1, 2):
+        enc.set_groups(groups)
+        outs.append(enc.forward(h, m).clone())
+        torch.cuda.synchronize()
+    enc.close()
+    assert torch.equal(*outs)
+
+
 @pytest.mark.parametrize("varlen", [False, True])
 def test_forward_captured_into_a_graph_of_the_caller(P, varlen):
     """A caller that records the forward into a HIP graph of its own switches the library's graph cache off; the plain
