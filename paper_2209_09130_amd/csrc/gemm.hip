@@ -971,6 +971,10 @@ hipError_t launch_small(const void *A, const void *W, void *out, const Epi &epi,
 // Measured, us per launch in a chain (before: the 64 x 96 and 64 x 128 tiles of configuration 2): N x K = 768 x 3072, 19 rows
 // 9.9 -> 3.7, 256 rows 10.7 -> 4.7, 1024 rows 10.7 -> 7.7; 768 x 768, 19 rows 4.3 -> 2.5, 1024 rows 5.3 -> 4.1; 2304 x 768,
 // 128 rows 5.2 -> 3.4.
+// Beside another batch group half of the chip is there for it (us, forward of 6 layers of width 512, counting on the whole chip / on
+// half of it: FP16 at 2048 and 1920 rows 540 / 486, Fully-Quant at 2 x 2048 rows 386 / 372).
+constexpr int CUS = 256;
+long cus_for(Rows rows) { return rows.beside ? CUS / 2 : CUS; }
 template <class Epi, int MT, int NT, int NWAVES, int R>
 bool small_fits(const Epi &epi, Rows rows, int N)
 {
@@ -978,7 +982,7 @@ bool small_fits(const Epi &epi, Rows rows, int N)
     if (N % G::BN) return false;
     const size_t lds = G::TAB_OFF + (size_t)Epi::NTAB * G::BN * sizeof(float) + extra_lds_of(epi, 0);
     const long per_cu = std::min<long>((long)(160 * 1024 / lds), 2048 / (64 * NWAVES));
-    return (long)(N / G::BN) * ((rows.host_rows + G::BM - 1) / G::BM) <= 256 * per_cu;
+    return (long)(N / G::BN) * ((rows.host_rows + G::BM - 1) / G::BM) <= cus_for(rows) * per_cu;
 }
 template <class Epi, int NWAVES, int R1, int R2>
 hipError_t launch_small_waves(const void *A, const void *W, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
@@ -1110,9 +1114,9 @@ hipError_t launch_small_f16_any(const void *A, const void *W, void *out, const E
 {
     if (K % 256) return hipErrorNotSupported;
     const long tiles_m = (rows.host_rows + 31) / 32;
-    if (N % 32 == 0 && tiles_m * (N / 32) <= 512) return launch_small_f16<1, 2>(A, W, out, epi, rows, N, K, st, tm);      // two blocks per CU
-    if (N % 64 == 0 && tiles_m * (N / 64) <= 256) return launch_small_f16<2, 2>(A, W, out, epi, rows, N, K, st, tm);
-    if (N % 128 == 0 && K <= 1024 && tiles_m * (N / 128) <= 256) return launch_small_f16<4, 2>(A, W, out, epi, rows, N, K, st, tm);
+    if (N % 32 == 0 && tiles_m * (N / 32) <= 2 * cus_for(rows)) return launch_small_f16<1, 2>(A, W, out, epi, rows, N, K, st, tm);      // two blocks per CU
+    if (N % 64 == 0 && tiles_m * (N / 64) <= cus_for(rows)) return launch_small_f16<2, 2>(A, W, out, epi, rows, N, K, st, tm);
+    if (N % 128 == 0 && K <= 1024 && tiles_m * (N / 128) <= cus_for(rows)) return launch_small_f16<4, 2>(A, W, out, epi, rows, N, K, st, tm);
     return hipErrorNotSupported;
 }
 
