@@ -17,7 +17,8 @@ namespace {
 //   mean / variance in binary64 (two passes over registers), rounded once to binary32
 //   y = fmaf((z - mu) * rstd, gamma, beta);  out = rne(y / s_out) or fp16(y)
 // ---------------------------------------------------------------------------------------------
-constexpr int LN_WAVE_MAX_ROWS = 2048;   // below: one wave per row
+constexpr int LN_WAVE_MAX_ROWS = 4096;             // below: one wave per row, if no other batch group runs at the same time,
+constexpr long LN_WAVE_MAX_VALUES_BESIDE = 1450000;       // or rows x width are below this
 constexpr int LN_ROWS = 8;               // token rows per block of the LayerNorm step (16 lanes each): small blocks slot in beside the other group's kernels
 
 template <int CTRL> __device__ __forceinline__ int dpp_mov(int v)
@@ -259,12 +260,19 @@ template <int NJ>
 hipError_t launch_add_ln_nj(const AddLnArgs &a, hipStream_t st, const Timing *tm)
 {
     // one wave per row at widths of 256, 512, 768 and 1024 (calibration, which also wants the absmax of the output, keeps the other
-    // form) for launches of less than 2048 rows: beyond, two batch groups share the chip and a launch takes vector time away from
-    // the other group's GEMMs, of which four rows per wave need a third less (BERT-large 32 x 256: 4484 against 4809 us)
+    // form), as long as a launch lasts no longer than a row's chain: forward of 6 layers, one batch group, us, four rows / one row per
+    // wave, width 768 at 2048 rows Fully-Quant 331 / 314 and FP16 509 / 491, at 2560 rows 378 / 354 and 578 / 555, width 512 at 3840
+    // rows 322 / 313 and 406 / 384; width 256 at 4096 rows 247 / 245 and 267 / 263, at 7680 rows 255 / 262 and 302 / 302.  Beside
+    // another batch group a launch takes vector time away from that group's GEMMs, of which four rows per wave need a third less
+    // (BERT-large 32 x 256: 4484 against 4809 us), and the forward crosses at about one and a half million values (same units,
+    // Fully-Quant / MHA-only / Quant-FFN-Only / FP16): width 768, 1664 and 1536 rows 420 / 573 / 465 / 609 against 407 / 567 / 458 / 609, 2048 and 1920 rows
+    // 438 / 635 / 491 / 667 against 442 / 623 / 508 / 671; width 1024, 2 x 1152 rows 531 / 721 / 594 / 773 against 507 / 694 / 591 / 751,
+    // 2 x 1792 rows 587 / 869 / 666 / 948 against 616 / 852 / 705 / 930.
     // width 768 has an instance of that form without tests against H (at 1024 the requests of a whole row in flight take so many
     // registers that the forward gets slower)
     constexpr bool WHOLE_WIDTHS = NJ == 3, WAVE = NJ <= 4;
-    const bool wave = WAVE && a.H == 256 * NJ && a.rows.host_rows < LN_WAVE_MAX_ROWS && !a.absmax_out;
+    const bool wave = WAVE && a.H == 256 * NJ && !a.absmax_out &&
+                      (a.rows.beside ? (long)a.rows.host_rows * a.H < LN_WAVE_MAX_VALUES_BESIDE : a.rows.host_rows < LN_WAVE_MAX_ROWS);
     const int per_block = wave ? 4 : LN_ROWS;
     dim3 grid((a.rows.host_rows + per_block - 1) / per_block), block(wave ? 256 : 16 * LN_ROWS);
 #define SAMP_LN_CASE(I, R, O)                                                                              \
