@@ -83,7 +83,8 @@ def test_int8_gemm_requant_epilogue_bit_exact(P, M, N, K, with_bias):
 def test_every_gemm_tile_configuration_gives_the_same_results(P, config):
     """The library picks a tile configuration by problem size; force each one in turn on a problem that
     spans several tiles and a ragged last row tile, for all three INT8 epilogues and the FP16 GEMM.
-    Left to itself (-1) it takes 64 x 96 tiles of six waves here (384 channels, few tiles)."""
+    Left to itself (-1) it takes the tiles for few rows here, and 64 x 96 tiles of six waves for the raw sums and for GELU
+    without a table (384 channels, few tiles)."""
     rng = np.random.default_rng(77)
     M, N, K = 333, 384, 768
     A = rng.integers(-127, 128, (M, K), dtype=np.int8)
@@ -168,9 +169,9 @@ def test_table_lookup_gelu_epilogue_in_the_small_tile_configurations(P, config):
 
 @pytest.mark.parametrize("N", [256, 384])
 def test_long_rows_with_few_tiles_take_the_deeper_ring(P, N):
-    """Operand rows of 3072 bytes with at most one block per CU run through a 3-deep stage ring (FFN2 at small
-    batch), in 64 x 128 tiles or, where the channel count allows it, 64 x 96 tiles whose six waves do not split the
-    stage loads evenly: INT8 requantising GEMM bit-exact, FP16 GEMM within one ulp, ragged last row tile."""
+    """Operand rows of 3072 bytes with at most one block per CU, ragged last row tile: raw INT8 sums run through a 3-deep stage
+    ring, in 64 x 128 tiles or, where the channel count allows it, 64 x 96 tiles whose six waves do not split the stage
+    loads evenly; the requantising GEMM (bit-exact) and the FP16 GEMM (within one ulp) take the tiles for few rows."""
     rng = np.random.default_rng(91 + N)
     M, K = 300, 3072
     A = rng.integers(-127, 128, (M, K), dtype=np.int8)
@@ -299,6 +300,35 @@ def test_fp16_gemm_of_few_rows_is_the_same_bytes_as_the_large_tiles(P, K, N):
             assert torch.equal(got.view(torch.int16), want.view(torch.int16)), (M, gelu)
 
 
+# ------------------------------------------------------------------ one to two thousand token rows
+@pytest.mark.parametrize("M,N,K", [(1400, 768, 768), (1400, 768, 3072), (1100, 1024, 4096), (2050, 768, 768), (2050, 768, 3072),
+                                   (2050, 1024, 4096)])
+def test_gemms_of_one_to_two_thousand_rows(P, M, N, K):
+    """Too many rows for the small tiles, too few for the wide ones: 64 x 96 (N = 768) and 64 x 128 tiles, up to one block per CU
+    with the stages in flight held in registers, ragged last row tile.  Every byte is that of a forced 128 x 128 tile; INT8 rows
+    around the tiles' edges against the oracle."""
+    import torch
+    rng = np.random.default_rng(M + N + K)
+    A = rng.integers(-127, 128, (M, K), dtype=np.int8)
+    W = rng.integers(-127, 128, (N, K), dtype=np.int8)
+    s_w, bias = _tables(rng, N)
+    m, b = oracle.fold_requant(0.037, s_w, bias, 0.021 * np.sqrt(K / 768))
+    Ah, Wh = dev((rng.standard_normal((M, K)) * 0.5).astype(np.float16)), dev((rng.standard_normal((N, K)) * 0.05).astype(np.float16))
+    runs = [lambda: P.gemm_i8_requant(dev(A), dev(W), dev(m), dev(b)), lambda: P.gemm_f16(Ah, Wh, dev(bias), False),
+            lambda: P.gemm_f16(Ah, Wh, None, True)]
+    got = [run() for run in runs]
+    P.set_gemm_config(1)
+    try:
+        want = [run() for run in runs]
+    finally:
+        P.set_gemm_config(-1)
+    for g, w in zip(got, want):
+        assert torch.equal(g.view(torch.int8), w.view(torch.int8))
+    rows = np.unique(np.concatenate([np.arange(8), 64 + np.arange(-4, 4), 128 + np.arange(-4, 4), M // 64 * 64 + np.arange(-4, 4), [M - 1]]))
+    rows = rows[rows < M]
+    assert np.array_equal(host(got[0])[rows], oracle.epilogue_requant(oracle.gemm_i8_i32(A[rows], W), m, b))
+
+
 # ------------------------------------------------------------------ attention
 def _cu(lens):
     return np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -374,6 +404,23 @@ def test_tables_that_arrive_with_the_last_stage_of_an_odd_number(P, M, N, K):
     assert np.array_equal(req, oracle.epilogue_requant(acc, m, b))
     assert np.array_equal(none, oracle.epilogue_requant(acc, m, np.zeros(N, np.float32)))
     assert np.array_equal(gel, oracle.epilogue_gelu_quant(acc, md, bias, 0.0147))
+
+
+@pytest.mark.parametrize("M,N,K", [(130, 384, 192), (65, 384, 320), (130, 384, 128), (64, 768, 64)])
+def test_fp16_tables_that_arrive_with_the_last_stage(P, M, N, K):
+    """The same for FP16, whose stages hold 64 elements (three, five, two and one), with and without an offset vector."""
+    rng = np.random.default_rng(M + N + K)
+    A = (rng.standard_normal((M, K)) * 0.5).astype(np.float16)
+    W = (rng.standard_normal((N, K)) * 0.05).astype(np.float16)
+    for bias in ((rng.standard_normal(N) * 0.1).astype(np.float32), None):
+        for gelu in (False, True):
+            P.set_gemm_config(6)
+            try:
+                got = host(P.gemm_f16(dev(A), dev(W), None if bias is None else dev(bias), gelu)).astype(np.float64)
+            finally:
+                P.set_gemm_config(-1)
+            want = oracle.gemm_f16(A, W, bias, gelu).astype(np.float64)
+            assert (np.abs(got - want) <= np.maximum(np.abs(want), 2.0 ** -14) * 2.0 ** -10 + 1e-6).all()     # one ulp, as above
 
 
 def test_qkv_attention_with_an_odd_number_of_stages(P):
@@ -534,9 +581,10 @@ def test_fp16_qkv_gemm_and_attention_in_one_kernel(P, lens, heads, offsets):
 
 @pytest.mark.parametrize("lens,heads", [([513], 1), ([700, 31, 1024], 2), ([2048, 515], 1)])
 def test_long_sequence_attention_matches_the_oracle(P, lens, heads):
-    """More than 512 keys: the three-sweep kernels (row maxima, row sums, codes and P.V, recomputing the integer
-    scores each time) must give what the oracle's plain definition gives: int8 contexts bit-exact for signed and
-    unsigned softmax codes, the code histogram exact, the fp16 flavour within its tolerance."""
+    """More than 512 keys: the calls that count codes take the three-sweep kernels (row maxima, row sums, codes and P.V,
+    recomputing the integer scores each time), the plain ones eight waves that keep the scores; both must give what the
+    oracle's plain definition gives: int8 contexts bit-exact for signed and unsigned softmax codes, the code histogram
+    exact, the fp16 flavour within its tolerance."""
     rng = np.random.default_rng(sum(lens) + 9)
     H = heads * 64
     cu = _cu(lens)
@@ -582,10 +630,16 @@ def test_attention_at_the_longest_supported_sequence(P):
 
 
 def test_long_kernel_equals_one_pass_kernel_on_short_sequences(P):
-    """A batch whose longest row exceeds 512 tokens runs every sequence, also the short ones, through the three-sweep
-    kernel: their contexts must be the bytes the one-pass kernel writes when the same short sequences come alone."""
+    """A batch whose longest row exceeds 512 tokens runs every sequence, also the short ones, through the eight-wave kernel,
+    beyond 2048 through the three-sweep kernel: their contexts must be the bytes the four-wave kernel writes when the same
+    short sequences come alone."""
+    for longest in (600, 2100):
+        long_against_short(P, longest)
+
+
+def long_against_short(P, longest):
     rng = np.random.default_rng(77)
-    heads, lens = 2, [600, 128, 37, 512]
+    heads, lens = 2, [longest, 128, 37, 512]
     H = heads * 64
     cu = _cu(lens)
     qkv = np.clip(np.rint(rng.standard_normal((int(cu[-1]), 3 * H)) * 26), -127, 127).astype(np.int8)
@@ -615,6 +669,22 @@ def test_every_number_of_key_tiles_per_wave(P, longest):
     assert np.abs(host(P.attention_f16(dev(f), dev(cu), longest, heads)).astype(np.float64) - want).max() <= 2e-3
 
 
+def test_three_sweep_attention_of_ragged_sequences(P):
+    """Beyond 2048 tokens (1536 with the binary16 softmax output) without a histogram: sequences of every number of key tiles per
+    wave, down to one key, behind one that is too long for the registers; all three INT8 forms bit-exact."""
+    rng = np.random.default_rng(2100)
+    heads, lens = 1, [2100, 33, 1, 700, 1281, 128]
+    cu = _cu(lens)
+    qkv = np.clip(np.rint(rng.standard_normal((int(cu[-1]), 3 * 64)) * 26), -127, 127).astype(np.int8)
+    sc = (0.0209, 0.0249, 0.021, 0.0002, 0.0015)
+    for kw in ({}, {"p_unsigned": True}):
+        want = oracle.attention_i8(qkv, cu, heads, *sc, **kw)
+        assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), max(lens), heads, *sc, **kw)), want)
+        assert np.abs(want).max() > 10
+    want = oracle.attention_i8_p16(qkv, cu, heads, sc[0], sc[1], sc[2], sc[4])
+    assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), max(lens), heads, *sc, p_fp16=True)), want)
+
+
 def test_fp16_attention_is_the_same_bytes_in_one_pass_and_in_three_sweeps(P):
     """A batch whose longest sequence exceeds 2048 tokens takes the three-sweep kernel; its other sequences must come out as
     they do alone, where the scores of every length stay in registers."""
@@ -632,8 +702,19 @@ def test_fp16_attention_is_the_same_bytes_in_one_pass_and_in_three_sweeps(P):
 @pytest.mark.parametrize("H", [128, 768, 1024])
 @pytest.mark.parametrize("in8,res8,out8", [(1, 1, 1), (1, 1, 0), (0, 0, 1), (0, 0, 0), (1, 0, 1), (0, 1, 0)])
 def test_add_ln_bit_exact(P, H, in8, res8, out8):
+    check_add_ln(P, 37, H, in8, res8, out8)
+
+
+@pytest.mark.parametrize("M,H", [(4099, 768), (4099, 1024), (37, 512), (5, 256)])
+@pytest.mark.parametrize("in8,res8,out8", [(1, 1, 1), (1, 1, 0), (0, 0, 1), (0, 0, 0), (1, 0, 1), (0, 1, 0)])
+def test_add_ln_in_the_forms_that_37_rows_do_not_take(P, M, H, in8, res8, out8):
+    """From 4096 rows 16 lanes share a row at every width (with a ragged last block here); widths of 256 and 512 with one wave
+    per row."""
+    check_add_ln(P, M, H, in8, res8, out8)
+
+
+def check_add_ln(P, M, H, in8, res8, out8):
     rng = np.random.default_rng(H + in8 * 4 + res8 * 2 + out8)
-    M = 37
     a = rng.integers(-127, 128, (M, H), dtype=np.int8) if in8 else (rng.standard_normal((M, H)) * 0.5).astype(np.float16)
     r = rng.integers(-127, 128, (M, H), dtype=np.int8) if res8 else rng.standard_normal((M, H)).astype(np.float16)
     bias = (rng.standard_normal(H) * 0.1).astype(np.float32)
