@@ -385,7 +385,12 @@ hipError_t launch_embed_ln_nj(const EmbedArgs &a, hipStream_t st, const Timing *
 {
     const dim3 block(256);
     if constexpr (NJ <= 4) {
-        if (a.H == 256 * NJ) {
+        // up to some thousand positions a launch lasts as long as a row's chain; beyond, what counts is memory, and one wave per row
+        // with less than 16 bytes of output per lane is the slower way to write it (us, 65536 positions, 16 lanes / one wave per row:
+        // width 256 INT8 20.1 / 29.6, FP16 24.5 / 30.1, 512 33.2 / 37.3, 41.0 / 39.1, 768 45.4 / 47.5, 56.7 / 53.0, 1024 59.1 / 57.7,
+        // 73.5 / 74.5; 8192 positions 1024 FP16 16.6 / 15.2)
+        const bool wave = (long)a.B * a.S < 16384 || 4 * NJ * (a.out_i8 ? 1 : 2) >= 16;
+        if (a.H == 256 * NJ && wave) {
             const dim3 grid((a.B * a.S + 3) / 4);
             if (a.out_i8) launch_kernel(embed_ln_wave_kernel<4 * NJ, true>, grid, block, 0, st, tm, a);
             else launch_kernel(embed_ln_wave_kernel<4 * NJ, false>, grid, block, 0, st, tm, a);

@@ -777,6 +777,22 @@ def test_embedding_kernel_bit_exact(P, H):
         P.embed_ln(short, dev(ids), None, False)                    # position table shorter than the sequences
 
 
+@pytest.mark.parametrize("H", [256, 768])
+def test_embedding_kernel_of_many_positions(P, H):
+    """From 16384 positions the lanes of a row are chosen by the bytes each writes (16 lanes at 256 and for INT8 at 768, a wave
+    for FP16 at 768); the last block is a ragged one."""
+    rng = np.random.default_rng(H)
+    V, B, S = 97, 127, 131
+    emb = {"tok": (rng.standard_normal((V, H)) * 0.5).astype(np.float16), "seg": (rng.standard_normal((2, H)) * 0.5).astype(np.float16),
+           "pos": (rng.standard_normal((S, H)) * 0.5).astype(np.float16), "gamma": (1 + 0.2 * rng.standard_normal(H)).astype(np.float32),
+           "beta": (0.3 * rng.standard_normal(H)).astype(np.float32), "eps": 1e-12}
+    ids, seg = rng.integers(0, V, (B, S)).astype(np.int32), rng.integers(0, 2, (B, S)).astype(np.int32)
+    E = P.Embedding(emb["tok"], emb["seg"], emb["pos"], emb["gamma"], emb["beta"], emb["eps"])
+    for out_i8, s_out in ((False, 1.0), (True, 0.031)):
+        want = np.concatenate([oracle.embed_ln(emb, ids[b], seg[b], out_i8, s_out) for b in range(B)])
+        assert np.array_equal(host(P.embed_ln(E, dev(ids), dev(seg), out_i8, s_out)), want)
+
+
 # ------------------------------------------------------------------ classification target
 @pytest.mark.parametrize("B,S,H,Cn", [(5, 7, 128, 3), (32, 128, 768, 15), (2, 1, 1024, 119)])
 def test_classification_target_within_accumulation_tolerance(P, B, S, H, Cn):
