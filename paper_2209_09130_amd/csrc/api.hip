@@ -170,9 +170,12 @@ const Timing *timing(samp_encoder *e, int which)
 int choose_groups(const samp_encoder *e, int B, int S)
 {
     int g = e->groups_wanted;
-    // Measured: below about two million values (token rows x hidden) one chain is faster (us, one / two groups: BERT-base 16 x 128
-    // 629 / 713, 20 x 128 713 / 783), from there on two are, at every size (24 x 128 843 / 739, BERT-large 8 x 256 1991 / 1871,
-    // BERT-base 128 x 512 -4 %); three or four never beat two
+    // Measured: below about two million values (token rows x hidden) one chain is faster, from there on two are.  Forwards of 6 layers
+    // on sequences of 128 tokens, Fully-Quant / FP16, us, one group / two groups, width 768: 20 sequences 355 / 378 and 503 / 594, 22
+    // 402 / 375 and 570 / 560, 26 430 / 388 and 617 / 589; width 1024: 15 405 / 442 and 597 / 700, 17 499 / 450 and 759 / 678; width 512: 28
+    // 313 / 346 and 380 / 470, 32 336 / 329 and 413 / 413; narrow widths, whose chains are launches and little else, a little later,
+    // width 256: 52 253 / 346 and 299 / 351, 64 257 / 297 and 318 / 327, 96 337 / 309 and 405 / 389; width 128: 128 245 / 262 and 263 / 292,
+    // 192 338 / 294 and 336 / 321.  BERT-base 128 x 512 -4 %; three or four groups never beat two
     if (g <= 0) g = ((long)B * S * e->cfg.hidden >= 2000000) ? 2 : 1;
     if (g > MAX_GROUPS) g = MAX_GROUPS;
     if (g > B) g = B;
@@ -302,7 +305,10 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             //  the 256-token flavour pays as well: BERT-large 32 x 256 with FP16 attention blocks -12.7 %)
             if (!am && S <= 256 && (enc->fusion_wanted == 2 || (enc->fusion_wanted == 0 && B * heads >= 128))) {
                 // up to about one block per CU the INT8 feed-forward kernels of the other batch group need the LDS more than
-                // this kernel needs 128-byte stages (BERT-base 32 x 128 Quant-FFN-Only 0.946 / 0.964 ms; 256 x 128 5.18 / 5.15)
+                // this kernel needs 128-byte stages (Quant-FFN-Only, 6 layers, us, smaller / larger ring by blocks per launch: width
+                // 768 in two groups 192: 492 / 501, 240: 580 / 582, 252: 597 / 594, 264: 683 / 686, 312: 750 / 741, 384: 862 / 845,
+                // 576: 1149 / 1100; in one group 192: 355 / 359, 240: 407 / 413; width 1024 in two groups 192: 632 / 636, 240: 686 / 681,
+                // 256: 715 / 708, in one 192: 489 / 499)
                 const bool small_ring = ffn8 && B * heads < 256;
                 HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, cu, B, S, H, 0.125f, small_ring,
                                                  (__half *)w.ctx, st, timing(enc, SAMP_PROF_QKV_ATTN)));

@@ -1000,6 +1000,7 @@ hipError_t launch_small_any(const void *A, const void *W, void *out, const Epi &
         if (K > 1024) return launch_small_waves<Epi, 8, 3, 2>(A, W, out, epi, rows, N, K, st, tm);
         return launch_small_waves<Epi, 8, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
     }
+    // (whole slabs for other numbers of waves are not instantiated: K of 256, 384, 512, 640 and 1280 take the kernels above)
     if (K % 768 == 0) return launch_small_waves<Epi, 6, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
     return hipErrorNotSupported;
 }
