@@ -18,7 +18,8 @@ namespace {
 //   y = fmaf((z - mu) * rstd, gamma, beta);  out = rne(y / s_out) or fp16(y)
 // ---------------------------------------------------------------------------------------------
 constexpr int LN_WAVE_MAX_ROWS = 4096;             // below: one wave per row, if no other batch group runs at the same time,
-constexpr long LN_WAVE_MAX_VALUES_BESIDE = 1450000;       // or rows x width are below this
+                                                   // or rows x width are below this (padded rows of a ragged batch count half)
+constexpr long ln_wave_max_values_beside(int width) { return width == 1024 ? 1650000 : 1450000; }
 constexpr int LN_ROWS = 8;               // token rows per block of the LayerNorm step (16 lanes each): small blocks slot in beside the other group's kernels
 
 template <int CTRL> __device__ __forceinline__ int dpp_mov(int v)
@@ -267,12 +268,17 @@ hipError_t launch_add_ln_nj(const AddLnArgs &a, hipStream_t st, const Timing *tm
     // (BERT-large 32 x 256: 4484 against 4809 us), and the forward crosses at about one and a half million values (same units,
     // Fully-Quant / MHA-only / Quant-FFN-Only / FP16): width 768, 1664 and 1536 rows 420 / 573 / 465 / 609 against 407 / 567 / 458 / 609, 2048 and 1920 rows
     // 438 / 635 / 491 / 667 against 442 / 623 / 508 / 671; width 1024, 2 x 1152 rows 531 / 721 / 594 / 773 against 507 / 694 / 591 / 751,
-    // 2 x 1792 rows 587 / 869 / 666 / 948 against 616 / 852 / 705 / 930.
+    // 2 x 1792 rows 587 / 869 / 666 / 948 against 616 / 852 / 705 / 930; at 2 x 1536 rows it is one wave per row for sequences of 256 and 512
+    // tokens (Fully-Quant / Quant-FFN-Only / FP16 620 / 742 / 977 against 597 / 724 / 951 and 663 / 804 / 1035 against 641 / 796 / 1032) and 16
+    // lanes for 128 (559 / 631 / 892 against 550 / 646 / 889).  Ragged batches have fewer rows than are counted here (two groups of 1920
+    // padded rows, 1080 tokens each, Fully-Quant / FP16 404 / 572 against 393 / 559, 2560: 432 / 637 against 418 / 627, 3328: 504 / 757 against
+    // 505 / 751; width 1024, 1536 padded rows, Fully-Quant / Quant-FFN-Only 509 / 576 against 473 / 553, 2048: 550 / 626 against 539 / 609).
     // width 768 has an instance of that form without tests against H (at 1024 the requests of a whole row in flight take so many
     // registers that the forward gets slower)
     constexpr bool WHOLE_WIDTHS = NJ == 3, WAVE = NJ <= 4;
     const bool wave = WAVE && a.H == 256 * NJ && !a.absmax_out &&
-                      (a.rows.beside ? (long)a.rows.host_rows * a.H < LN_WAVE_MAX_VALUES_BESIDE : a.rows.host_rows < LN_WAVE_MAX_ROWS);
+                      (a.rows.beside ? (long)a.rows.host_rows * a.H / (a.rows.dev_rows ? 2 : 1) < ln_wave_max_values_beside(256 * NJ)
+                                     : a.rows.host_rows < LN_WAVE_MAX_ROWS);
     const int per_block = wave ? 4 : LN_ROWS;
     dim3 grid((a.rows.host_rows + per_block - 1) / per_block), block(wave ? 256 : 16 * LN_ROWS);
 #define SAMP_LN_CASE(I, R, O)                                                                              \

@@ -629,10 +629,10 @@ def test_batch_groups_and_graph_replay_do_not_change_results(P, varlen):
 
 @pytest.mark.parametrize("modes", [(FULL_INT8, FP16), (FFN_INT8, MHA_INT8)])
 @pytest.mark.parametrize("hidden,batch,varlen", [(768, 21, False), (768, 22, False), (768, 22, True), (768, 31, False), (768, 32, False),
-                                                 (1024, 24, False), (512, 31, False), (512, 33, True)])
+                                                 (768, 48, False), (768, 52, True), (1024, 24, False), (512, 31, False), (512, 33, True)])
 def test_a_batch_in_two_groups_is_the_same_bytes_at_the_bounds_of_the_kernel_choice(P, modes, hidden, batch, varlen):
     """Tile sizes and the LayerNorm's form are chosen by a launch's rows and by whether another batch group runs beside it: two
-    groups of 1280 to 2176 rows (either side of the bounds of the wide tiles, the small tiles and the LayerNorm) against one
+    groups of 1280 to 3328 rows (either side of the bounds of the wide tiles, their stages, the small tiles and the LayerNorm) against one
     group of all rows, whose kernels are others."""
     import torch
     w = W.Workload("two groups", 2, hidden, hidden // 64, 4 * hidden, batch, 128, modes, varlen=varlen, plain_params=False,
