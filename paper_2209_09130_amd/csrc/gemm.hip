@@ -1191,7 +1191,17 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
     case 3: return launch_big<T, Epi, 4, 4, 128, 2>(A, W, out, epi, rows, N, K, st, tm);      // 256 x 256, two 128-byte stages
     case 4: return launch_big<T, Epi, 2, 4, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 128 tokens x 256 channels, two blocks per CU
     case 5: return launch_big<T, Epi, 4, 2, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 256 tokens x 128 channels, two blocks per CU
-    case 6: return launch_big<T, Epi, 2, 3, 128, 2, 2>(A, W, out, epi, rows, N, K, st, tm);   // 128 x 192, two 128-byte stages, two blocks per CU
+    case 6:                                                                                    // 128 x 192, two 128-byte stages, two blocks per CU
+        // FP16 beside another batch group, with more than one block for most CUs and not two for all: three 64-byte stages, which leave
+        // that group a quarter of the LDS (us, 6 layers of width 768, 128-byte / 64-byte stages by rows per group: FP16, sequences of 128
+        // tokens 3072 970 / 926, 3328 1033 / 1013, 3584 1084 / 1049, 4096 1134 / 1143, 5120 1363 / 1415, of 512 tokens 3072 1259 / 1185, 3584
+        // 1354 / 1332, of 350 tokens 3500 1259 / 1211, of 256 tokens 3072 1062 / 1079, 3584 1187 / 1179; MHA-only at 3584 rows 1003 / 980 (128
+        // tokens), 1113 / 1036 (256), 1204 / 1147 (512).  Below it is one or the other: 2816 rows of 128 tokens FP16 945 / 902, MHA-only
+        // 825 / 864; 2560 rows of 256 tokens FP16 889 / 920.  A ragged batch of 3328 padded rows per group: 757 / 768)
+        if constexpr (std::is_same<T, F16>::value)
+            if (!forced && rows.beside && !rows.dev_rows && rows.host_rows >= 3072 && rows.host_rows < 4096)
+                return launch_big<T, Epi, 2, 3, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);
+        return launch_big<T, Epi, 2, 3, 128, 2, 2>(A, W, out, epi, rows, N, K, st, tm);
     case 7: return launch_big<T, Epi, 4, 4, 64, 4>(A, W, out, epi, rows, N, K, st, tm);       // 256 x 256, four 64-byte stages
     case 1:
         // the GELU epilogue is as much vector work as the main loop is matrix work: 64-byte stages leave room
