@@ -310,6 +310,19 @@ SAMP_API int samp_gemm_i8_gelu_quant(const int8_t *A, const int8_t *W, const flo
                                      const samp_gelu_table_t *table, const void *table_entries, int8_t *out, int32_t M,
                                      int32_t N, int32_t K, void *stream);
 
+/* INT8 weights in the order in which the encoder's INT8 GEMMs read them, and those GEMMs on their own: 1 KB blocks of
+ * 16 rows x 64 bytes, row blocks outermost; inside a block the four 16-byte columns one after the other, 16 rows each.
+ * Wp: dev int8, N * K bytes, 16-byte aligned, not W itself; N % 16 == 0, K % 64 == 0.                */
+SAMP_API int samp_pack_weight_i8(const int8_t *W, int32_t N, int32_t K, int8_t *Wp, void *stream);
+/* As samp_gemm_i8_requant and (with a table) samp_gemm_i8_gelu_quant, on packed weights; K % 256 == 0.  tile: -1 by size,
+ * or 0..6 for tiles of 32 x 64, 64 x 64, 64 x 128, 64 x 192, 64 x 256, 128 x 128, 128 x 192 rows x channels (SAMP_ERR_SHAPE
+ * if its width does not divide N); the results do not depend on it.                                */
+SAMP_API int samp_gemm_i8_requant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *b, int8_t *out,
+                                         int32_t M, int32_t N, int32_t K, int32_t tile, void *stream);
+SAMP_API int samp_gemm_i8_gelu_quant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *bias,
+                                            const samp_gelu_table_t *table, const void *table_entries, int8_t *out,
+                                            int32_t M, int32_t N, int32_t K, int32_t tile, void *stream);
+
 /* FP16 GEMM, binary32 accumulation: out = fp16(act(A . W^T + bias)); bias dev float [N] or NULL;
  * gelu != 0 applies GELU.  N % 128 == 0, K % 32 == 0.                                             */
 SAMP_API int samp_gemm_f16(const uint16_t *A, const uint16_t *W, const float *bias, int32_t gelu, uint16_t *out,

@@ -277,6 +277,34 @@ def gemm_i8_gelu_quant(A, W, m, bias, s_out: float, table=None) -> torch.Tensor:
     return out
 
 
+def pack_weight_i8(W) -> torch.Tensor:
+    """The int8 matrix [N, K] in the order in which the encoder's INT8 GEMMs read it (samp_pack_weight_i8)."""
+    N, K = W.shape
+    out = torch.empty(N * K, dtype=torch.int8, device=W.device)
+    _check(lib().samp_pack_weight_i8(_dp(W), N, K, _dp(out), _stream()))
+    return out
+
+
+def gemm_i8_requant_packed(A, Wp, m, b, tile: int = -1) -> torch.Tensor:
+    """gemm_i8_requant on packed weights; tile: -1 by size, or one of the tiles that samp.h lists."""
+    M, K = A.shape
+    N = m.numel()
+    out = torch.empty((M, N), dtype=torch.int8, device=A.device)
+    _check(lib().samp_gemm_i8_requant_packed(_dp(A), _dp(Wp), _dp(m), _dp(b), _dp(out), M, N, K, tile, _stream()))
+    return out
+
+
+def gemm_i8_gelu_quant_packed(A, Wp, m, bias, table, tile: int = -1) -> torch.Tensor:
+    """gemm_i8_gelu_quant on packed weights; table: (description, device entries) from gelu_table_build(s_out)."""
+    M, K = A.shape
+    N = m.numel()
+    out = torch.empty((M, N), dtype=torch.int8, device=A.device)
+    spec, entries = table
+    _check(lib().samp_gemm_i8_gelu_quant_packed(_dp(A), _dp(Wp), _dp(m), _dp(bias), C.byref(spec), _dp(entries), _dp(out), M, N, K,
+                                                tile, _stream()))
+    return out
+
+
 def gemm_f16(A, W, bias, gelu: bool) -> torch.Tensor:
     M, K = A.shape
     N = W.shape[0]

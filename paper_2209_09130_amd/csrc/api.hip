@@ -45,6 +45,7 @@ struct Layer {
     samp_layer_scales_t s;
     // INT8 blocks: int8 weights and folded epilogue tables; FP16 blocks: fp16 weights
     void *w_qkv, *w_o, *w_f1, *w_f2;
+    int8_t *p_qkv, *p_o, *p_f1, *p_f2;              // the int8 weights once more, packed (nullptr where no kernel reads them so)
     float *m_qkv, *bq_qkv, *m_o, *m_f1, *m_f2;
     float *b_qkv, *b_o, *b_f1, *b_f2, *g1, *be1, *g2, *be2;
     float m_sc, inv_sp, m_ctx;                      // attention multipliers of an INT8 MHA block
@@ -85,6 +86,9 @@ int check_config(const samp_config_t *c)
     return SAMP_OK;
 }
 
+// INT8 matrices of rows that are whole pairs of 128-byte stages are kept packed too
+bool packs(size_t K) { return K % 256 == 0; }
+
 size_t layer_arena_bytes(const samp_config_t &c, int mode)
 {
     const size_t H = c.hidden, F = c.ffn;
@@ -94,6 +98,17 @@ size_t layer_arena_bytes(const samp_config_t &c, int mode)
     n += 2 * up(3 * H * 4) + up(H * 4) + up(F * 4) + up(H * 4);             // m_qkv, bq_qkv, m_o, m_f1, m_f2
     n += up(3 * H * 4) + up(F * 4) + 6 * up(H * 4);                         // biases and LayerNorm vectors
     if (mode & 2) n += up((size_t)GELU_TABLE_MAX_BINS * 8);                 // FFN1 epilogue's threshold table
+    return n;
+}
+
+// the packed copies of a layer; they lie behind the layers, whose weights stay together
+size_t layer_packed_bytes(const samp_config_t &c, int mode)
+{
+    const size_t H = c.hidden, F = c.ffn;
+    size_t n = 0;
+    if ((mode & 1) && packs(H)) n += up(3 * H * H) + up(H * H);
+    if ((mode & 2) && packs(H)) n += up(F * H);
+    if ((mode & 2) && packs(F)) n += up(H * F);
     return n;
 }
 
@@ -287,7 +302,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                                 Y.inv_sp, Y.m_ctx, (Y.mode & SAMP_P_UNSIGNED) != 0, (int8_t *)w.ctx, st,
                                                 timing(enc, SAMP_PROF_QKV_ATTN)));
             else {
-                HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, w.qkv, Y.m_qkv, Y.bq_qkv, 0.f,
+                HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, Y.p_qkv, w.qkv, Y.m_qkv, Y.bq_qkv, 0.f,
                                        nullptr, rows, 3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
                 if (Y.mode & SAMP_P_FP16)
                     HIP_TRY(launch_attention_i8_p16((const int8_t *)w.qkv, cu, B, S, H, heads, Y.m_sc, Y.m_ctx, (int8_t *)w.ctx,
@@ -297,7 +312,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                                 (Y.mode & SAMP_P_UNSIGNED) != 0, (int8_t *)w.ctx, nullptr, st,
                                                 timing(enc, SAMP_PROF_ATTN)));
             }
-            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.ctx, (const int8_t *)Y.w_o, w.ao, Y.m_o, nullptr, 0.f,
+            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.ctx, (const int8_t *)Y.w_o, Y.p_o, w.ao, Y.m_o, nullptr, 0.f,
                                    nullptr, rows, H, H, st, timing(enc, SAMP_PROF_ATTN_OUT)));
         } else {
             if (am) HIP_TRY(launch_absmax_f16((const __half *)x, rows, H, H, am + 0, st));
@@ -332,9 +347,9 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             HIP_TRY(launch_add_ln(a, st, timing(enc, SAMP_PROF_LN1)));
         }
         if (ffn8) {
-            HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, w.f1, Y.m_f1, Y.b_f1,
+            HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, Y.p_f1, w.f1, Y.m_f1, Y.b_f1,
                                    1.0f / Y.s.ffn_mid, &Y.gelu, rows, F, H, st, timing(enc, SAMP_PROF_FFN1)));
-            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.f1, (const int8_t *)Y.w_f2, w.f2, Y.m_f2, nullptr, 0.f,
+            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.f1, (const int8_t *)Y.w_f2, Y.p_f2, w.f2, Y.m_f2, nullptr, 0.f,
                                    nullptr, rows, H, F, st, timing(enc, SAMP_PROF_FFN2)));
         } else {
             HIP_TRY(launch_gemm_f16((const __half *)w.h1, (const __half *)Y.w_f1, Y.b_f1, true, (__half *)w.f1, rows, F, H,
@@ -369,7 +384,7 @@ size_t samp_encoder_arena_bytes(const samp_config_t *cfg, const uint8_t *modes)
     size_t n = 0;
     for (int l = 0; l < cfg->layers; l++) {
         if (!valid_mode(modes[l])) { fail(SAMP_ERR_ARG, "unknown mode %d for layer %d", modes[l], l); return 0; }
-        n += layer_arena_bytes(*cfg, modes[l]);
+        n += layer_arena_bytes(*cfg, modes[l]) + layer_packed_bytes(*cfg, modes[l]);
     }
     return n + staging_bytes(*cfg);
 }
@@ -415,6 +430,9 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
     const size_t big = std::max(3 * H, F);
     __half *stage = cv.take<__half>(big * H);
     float *s_w = cv.take<float>(big);
+    size_t behind = cv.off;
+    for (int l = 0; l < cfg->layers; l++) behind += layer_arena_bytes(*cfg, modes[l]);
+    Carver cvp{static_cast<char *>(dev_arena), behind};
 
     std::vector<std::vector<uint32_t>> gelu_host;                // staging of the tables until the stream has copied them
     auto body = [&]() -> int {
@@ -441,7 +459,8 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
             Y.m_o = cv.take<float>(H); Y.m_f1 = cv.take<float>(F); Y.m_f2 = cv.take<float>(H);
 
             // fp16 matrix -> either kept as fp16 or quantised per output channel into int8
-            auto matrix = [&](const uint16_t *src, size_t N, size_t K, bool q8, void **dst) -> int {
+            auto matrix = [&](const uint16_t *src, size_t N, size_t K, bool q8, void **dst, int8_t **packed) -> int {
+                *packed = nullptr;
                 if (!q8) {
                     *dst = cv.take<__half>(N * K);
                     HIP_TRY(hipMemcpyAsync(*dst, src, N * K * 2, hipMemcpyHostToDevice, st));
@@ -449,10 +468,14 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
                     *dst = cv.take<int8_t>(N * K);
                     HIP_TRY(hipMemcpyAsync(stage, src, N * K * 2, hipMemcpyHostToDevice, st));
                     HIP_TRY(launch_quantize_weight(stage, (int)N, (int)K, (int8_t *)*dst, s_w, st));
+                    if (packs(K)) {
+                        *packed = cvp.take<int8_t>(N * K);
+                        HIP_TRY(launch_pack_weight((const int8_t *)*dst, (int)N, (int)K, *packed, st));
+                    }
                 }
                 return SAMP_OK;
             };
-            if (int rc = matrix(w.w_qkv, 3 * H, H, mha8, &Y.w_qkv)) return rc;
+            if (int rc = matrix(w.w_qkv, 3 * H, H, mha8, &Y.w_qkv, &Y.p_qkv)) return rc;
             if (mha8) {
                 const float so[3] = {Y.s.q, Y.s.k, Y.s.v};
                 for (int part = 0; part < 3; part++)
@@ -465,9 +488,9 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
                 Y.m_ctx = (Y.mode & SAMP_P_FP16) ? (float)((double)Y.s.v / (double)Y.s.ctx)
                                                  : (float)((double)Y.s.p * (double)Y.s.v / (double)Y.s.ctx);
             }
-            if (int rc = matrix(w.w_o, H, H, mha8, &Y.w_o)) return rc;
+            if (int rc = matrix(w.w_o, H, H, mha8, &Y.w_o, &Y.p_o)) return rc;
             if (mha8) HIP_TRY(launch_fold(nullptr, Y.s.ctx, s_w, nullptr, Y.s.attn_out, (int)H, Y.m_o, nullptr, st));
-            if (int rc = matrix(w.w_ffn1, F, H, ffn8, &Y.w_f1)) return rc;
+            if (int rc = matrix(w.w_ffn1, F, H, ffn8, &Y.w_f1, &Y.p_f1)) return rc;
             if (ffn8) HIP_TRY(launch_fold(nullptr, Y.s.ffn_in, s_w, nullptr, 1.0f, (int)F, Y.m_f1, nullptr, st));
             Y.gelu = GeluTable{{0.f, 0.f, 0.f, 0}, nullptr};
             if (ffn8) {
@@ -480,7 +503,7 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
                     Y.gelu.entries = dev_entries;
                 }
             }
-            if (int rc = matrix(w.w_ffn2, H, F, ffn8, &Y.w_f2)) return rc;
+            if (int rc = matrix(w.w_ffn2, H, F, ffn8, &Y.w_f2, &Y.p_f2)) return rc;
             if (ffn8) HIP_TRY(launch_fold(nullptr, Y.s.ffn_mid, s_w, nullptr, Y.s.ffn_out, (int)H, Y.m_f2, nullptr, st));
         }
         HIP_TRY(hipStreamSynchronize(st));
@@ -763,7 +786,7 @@ static int check_gemm(const void *A, const void *W, const void *out, int M, int 
 int samp_gemm_i8_i32(const int8_t *A, const int8_t *W, int32_t *C, int32_t M, int32_t N, int32_t K, void *stream)
 {
     if (int rc = check_gemm(A, W, C, M, N, K, 64)) return rc;
-    HIP_TRY(launch_gemm_i8(EPI_RAW_I32, A, W, C, nullptr, nullptr, 0.f, nullptr, Rows{M, nullptr}, N, K, (hipStream_t)stream, nullptr));
+    HIP_TRY(launch_gemm_i8(EPI_RAW_I32, A, W, nullptr, C, nullptr, nullptr, 0.f, nullptr, Rows{M, nullptr}, N, K, (hipStream_t)stream, nullptr));
     return SAMP_OK;
 }
 
@@ -772,7 +795,18 @@ int samp_gemm_i8_requant(const int8_t *A, const int8_t *W, const float *m, const
 {
     if (int rc = check_gemm(A, W, out, M, N, K, 64)) return rc;
     if (!m) return fail(SAMP_ERR_ARG, "multiplier table is NULL");
-    HIP_TRY(launch_gemm_i8(EPI_REQUANT, A, W, out, m, b, 0.f, nullptr, Rows{M, nullptr}, N, K, (hipStream_t)stream, nullptr));
+    HIP_TRY(launch_gemm_i8(EPI_REQUANT, A, W, nullptr, out, m, b, 0.f, nullptr, Rows{M, nullptr}, N, K, (hipStream_t)stream, nullptr));
+    return SAMP_OK;
+}
+
+static int check_gelu_table(const samp_gelu_table_t *table, const void *table_entries, GeluTable *gt)
+{
+    if (!table || !table_entries) return fail(SAMP_ERR_ARG, "a threshold table needs both its description and its entries");
+    if (!aligned(table_entries, 8)) return fail(SAMP_ERR_ARG, "table_entries must be 8-byte aligned");
+    if (table->bins < 2 || table->bins > GELU_TABLE_MAX_BINS || table->t_max != 8388608.0f + (float)(table->bins - 1) ||
+        !(table->rate > 0.0f) || !std::isfinite(table->rate) || !std::isfinite(table->offset))
+        return fail(SAMP_ERR_ARG, "the threshold table's description is not one samp_gelu_table_build wrote");
+    *gt = GeluTable{{table->rate, table->offset, table->t_max, table->bins}, static_cast<const uint32_t *>(table_entries)};
     return SAMP_OK;
 }
 
@@ -784,16 +818,51 @@ int samp_gemm_i8_gelu_quant(const int8_t *A, const int8_t *W, const float *m, co
     if (!m || !bias) return fail(SAMP_ERR_ARG, "multiplier or bias table is NULL");
     if (!good_scale(s_out)) return fail(SAMP_ERR_SCALE, "s_out must be finite and positive");
     GeluTable gt{{0.f, 0.f, 0.f, 0}, nullptr};
-    if (table || table_entries) {
-        if (!table || !table_entries) return fail(SAMP_ERR_ARG, "a threshold table needs both its description and its entries");
-        if (!aligned(table_entries, 8)) return fail(SAMP_ERR_ARG, "table_entries must be 8-byte aligned");
-        if (table->bins < 2 || table->bins > GELU_TABLE_MAX_BINS || table->t_max != 8388608.0f + (float)(table->bins - 1) ||
-            !(table->rate > 0.0f) || !std::isfinite(table->rate) || !std::isfinite(table->offset))
-            return fail(SAMP_ERR_ARG, "the threshold table's description is not one samp_gelu_table_build wrote");
-        gt = GeluTable{{table->rate, table->offset, table->t_max, table->bins}, static_cast<const uint32_t *>(table_entries)};
-    }
-    HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, A, W, out, m, bias, 1.0f / s_out, gt.entries ? &gt : nullptr, Rows{M, nullptr}, N, K,
+    if (table || table_entries)
+        if (int rc = check_gelu_table(table, table_entries, &gt)) return rc;
+    HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, A, W, nullptr, out, m, bias, 1.0f / s_out, gt.entries ? &gt : nullptr, Rows{M, nullptr}, N, K,
                            (hipStream_t)stream, nullptr));
+    return SAMP_OK;
+}
+
+int samp_pack_weight_i8(const int8_t *W, int32_t N, int32_t K, int8_t *Wp, void *stream)
+{
+    if (!W || !Wp) return fail(SAMP_ERR_ARG, "NULL matrix pointer");
+    if (N < 16 || N % 16 || K < 64 || K % 64 || (long long)N * K > INT32_MAX)
+        return fail(SAMP_ERR_SHAPE, "packing needs N %% 16 == 0, K %% 64 == 0, N * K < 2^31 (N=%d K=%d)", N, K);
+    if (!aligned(W, 16) || !aligned(Wp, 16)) return fail(SAMP_ERR_ARG, "matrices must be 16-byte aligned");
+    if (W == Wp) return fail(SAMP_ERR_ARG, "a matrix cannot be packed in place");
+    HIP_TRY(launch_pack_weight(W, N, K, Wp, (hipStream_t)stream));
+    return SAMP_OK;
+}
+
+static int check_packed(const void *A, const void *Wp, const void *out, int M, int N, int K, int tile)
+{
+    static const int width[] = {64, 64, 128, 192, 256, 128, 192};
+    if (int rc = check_gemm(A, Wp, out, M, N, K, 256)) return rc;
+    if (tile < -1 || tile > 6) return fail(SAMP_ERR_ARG, "tile must be in [-1, 6]");
+    if (tile >= 0 && N % width[tile]) return fail(SAMP_ERR_SHAPE, "tile %d needs N %% %d == 0 (N=%d)", tile, width[tile], N);
+    return SAMP_OK;
+}
+
+int samp_gemm_i8_requant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *b, int8_t *out, int32_t M,
+                                int32_t N, int32_t K, int32_t tile, void *stream)
+{
+    if (int rc = check_packed(A, Wp, out, M, N, K, tile)) return rc;
+    if (!m) return fail(SAMP_ERR_ARG, "multiplier table is NULL");
+    HIP_TRY(launch_gemm_i8_packed(EPI_REQUANT, A, Wp, out, m, b, nullptr, Rows{M, nullptr}, N, K, tile, (hipStream_t)stream, nullptr));
+    return SAMP_OK;
+}
+
+int samp_gemm_i8_gelu_quant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *bias,
+                                   const samp_gelu_table_t *table, const void *table_entries, int8_t *out, int32_t M, int32_t N,
+                                   int32_t K, int32_t tile, void *stream)
+{
+    if (int rc = check_packed(A, Wp, out, M, N, K, tile)) return rc;
+    if (!m || !bias) return fail(SAMP_ERR_ARG, "multiplier or bias table is NULL");
+    GeluTable gt;
+    if (int rc = check_gelu_table(table, table_entries, &gt)) return rc;
+    HIP_TRY(launch_gemm_i8_packed(EPI_GELU_QUANT, A, Wp, out, m, bias, &gt, Rows{M, nullptr}, N, K, tile, (hipStream_t)stream, nullptr));
     return SAMP_OK;
 }
 

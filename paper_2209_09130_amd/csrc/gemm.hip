@@ -100,6 +100,8 @@ template <class Tab> __device__ __forceinline__ Tab load_tab_mb(const float *tab
 
 struct EpiRequant {                               // code = rne(fmaf(acc, m[n], b[n]))
     const float *m, *b;
+    __device__ __forceinline__ const float *offsets() const { return b; }
+    __device__ __forceinline__ void load_lut_direct(v2i *, int, int, int) const {}
     static constexpr int OUT_BYTES = 1;
     static constexpr bool STAGED = true;
     static constexpr int NTAB = 2;
@@ -127,6 +129,15 @@ struct EpiRequant {                               // code = rne(fmaf(acc, m[n], 
                                code_bits(__builtin_fmaf((float)acc[4 * q + 2], mm.z, bb.z)),
                                code_bits(__builtin_fmaf((float)acc[4 * q + 3], mm.w, bb.w)));
         }
+    }
+    // the same four channels of N tokens
+    template <int N>
+    __device__ __forceinline__ void quads(const v4i (&acc)[N], const v4f &mm, const v4f &bb, const v2i *, int (&pk)[N]) const
+    {
+#pragma unroll
+        for (int i = 0; i < N; i++)
+            pk[i] = pack_codes(code_bits(__builtin_fmaf((float)acc[i].x, mm.x, bb.x)), code_bits(__builtin_fmaf((float)acc[i].y, mm.y, bb.y)),
+                               code_bits(__builtin_fmaf((float)acc[i].z, mm.z, bb.z)), code_bits(__builtin_fmaf((float)acc[i].w, mm.w, bb.w)));
     }
 };
 
@@ -200,6 +211,9 @@ struct EpiGeluTable {
     static constexpr int NTAB = 2;
     typedef int pack_t;
     __host__ __device__ int extra_lds_bytes() const { return bins * 8; }
+    __device__ __forceinline__ const float *offsets() const { return bias; }
+    __device__ __forceinline__ void load_lut_direct(v2i *lut, int wave, int nwaves, int lane) const
+    { copy_direct(lut, entries, 2 * bins, wave, nwaves, lane); }
     __device__ __forceinline__ void load_tables(float *tab, int n0, int bn, int tid, int nthreads) const
     {
         copy_table(tab, m, n0, bn, tid, nthreads);
@@ -246,6 +260,31 @@ struct EpiGeluTable {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < 4; q++) {
+            unsigned c[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                c[k] = y[4 * q + k] >= __int_as_float(e[4 * q + k].x) ? (unsigned)e[4 * q + k].y >> 8 : (unsigned)e[4 * q + k].y;
+            const unsigned lo = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0400u), hi = __builtin_amdgcn_perm(c[3], c[2], 0x0c0c0400u);
+            pk[q] = (int)__builtin_amdgcn_perm(hi, lo, 0x05040100u);
+        }
+    }
+    template <int N>
+    __device__ __forceinline__ void quads(const v4i (&acc)[N], const v4f &mm, const v4f &bb, const v2i *lut, int (&pk)[N]) const
+    {
+        float y[4 * N];
+        unsigned bin[4 * N];
+        v2i e[4 * N];
+#pragma unroll
+        for (int k = 0; k < 4 * N; k++) {
+            y[k] = __builtin_fmaf((float)acc[k >> 2][k & 3], mm[k & 3], bb[k & 3]);
+            bin[k] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(y[k], rate, offset), 8388608.0f, t_max)) - 0x4B000000u;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 4 * N; k++) e[k] = lut[bin[k]];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < N; q++) {
             unsigned c[4];
 #pragma unroll
             for (int k = 0; k < 4; k++)
@@ -713,6 +752,269 @@ hipError_t launch_big(const void *A, const void *W, void *out, const Epi &epi, R
     return hipGetLastError();
 }
 
+
+// ---- packed weights, straight into registers (INT8) --------------------------------------------------
+// The tile loops above move both operands through LDS, and LDS is what the large ones run out of: a 128 x 192 tile of four 64 x 96
+// wave tiles reads 20 KB of fragments and writes 10 KB for every 192 clocks of matrix work, and its ring holds one stage in flight
+// (40 KB per block).  Here the block's four waves stand side by side, each with all 16 MT tokens and 16 NTW channels of its own: no
+// other wave wants a wave's weight rows, so they go from L2 into registers, D stages ahead, and only the token rows are staged in
+// LDS (a ring of D + 1 stages of 128 bytes a row).
+// What makes that pay is the order of the weights in memory (pack_weight_kernel): 16 rows x 64 bytes, what one 16 x 16 x 64 product
+// takes, are 1 KB in the order of the lanes.  A probe that reads a 3 MB matrix from L2 into registers gets 130 bytes per ns and CU
+// in that order and 38 from 16 rows of 64 bytes where they lie in the matrix (each lane of a quad in a line of its own); rows
+// of 128 bytes into LDS get 125.
+// A lane's results are four channels of one token per 16 x 16 tile, the same four for all its tokens: its entries of the epilogue's
+// vectors are loaded once, into registers, and a wave's table lookups are the only LDS reads of the epilogue beside the output tile's.
+template <class F, int... I> __device__ __forceinline__ void each_index(F f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int MT, int NTW, int D> struct StreamTile {
+    static constexpr int BM = 16 * MT, BN = 64 * NTW, SLOT = BM * 128, RING = (D + 1) * SLOT, STRIDE = BN + 16;
+    static constexpr int OUT = BM * STRIDE, LUT_OFF = RING > OUT ? RING : OUT;       // the output tile takes the ring's place
+};
+
+template <class Epi, int MT, int NTW, int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ Wp, char *__restrict__ out, Epi epi, int host_rows,
+                           const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n, bool channels_first)
+{
+    typedef StreamTile<MT, NTW, D> Tile;
+    constexpr int BM = Tile::BM, BN = Tile::BN, SLOT = Tile::SLOT, RING = Tile::RING;
+    constexpr int G = MT < 4 ? MT : 4, H = MT / G, STEPS = 2 * H;          // token tiles per step; steps per 64 bytes of K
+    constexpr int NLDA = BM / 32, PER = NLDA + 2 * NTW;                    // loads of a wave and stage: token rows; all
+    static_assert(MT % G == 0 && BM % 32 == 0 && D >= 2, "whole steps, whole pieces of 8 rows per wave");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    v2i *lut = reinterpret_cast<v2i *>(lds + Tile::LUT_OFF);
+
+    const int M = dev_rows ? *dev_rows : host_rows;
+    const int tiles_m = (M + BM - 1) / BM, tiles = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= tiles) return;
+    const int tile = xcd_contiguous(blockIdx.x, tiles);
+    const int m0 = (channels_first ? tile % tiles_m : tile / tiles_n) * BM, n0 = (channels_first ? tile / tiles_m : tile % tiles_n) * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, q = lane >> 4;
+
+    const char *abase = A + (size_t)m0 * Kbytes, *wbase = Wp + (size_t)(n0 + 16 * NTW * wave) * Kbytes;
+    unsigned offa[NLDA];
+#pragma unroll
+    for (int j = 0; j < NLDA; j++) {
+        const int srow = 8 * (wave + 4 * j) + (lane >> 3);
+        offa[j] = (unsigned)min(srow, M - 1 - m0) * (unsigned)Kbytes + (((lane & 7) ^ swz<128>(srow)) << 4);
+    }
+    const unsigned offw = 16 * lane;
+    int fill = 0;                                                 // ring position of the next stage to request
+    auto issue_a = [&](int kt, int first, int last) {
+        const char *from = abase + (size_t)kt * 128;
+        asm volatile("" : "+s"(from));
+#pragma unroll
+        for (int j = first; j < last; j++) {
+            unsigned o = offa[j];
+            asm volatile("" : "+v"(o));                            // keeps the offset a 32-bit one: scalar base + vector offset
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + o),
+                                             (__attribute__((address_space(3))) void *)(lds + fill + (wave + 4 * j) * 1024), 16, 0, 0);
+        }
+        if (last == NLDA) fill = fill + SLOT == RING ? 0 : fill + SLOT;
+    };
+    // (written out so that the compiler does not wait for them: step() does, and ties the registers to its wait)
+    v4i w[D][2][NTW];
+    auto load_w = [&](int kt, int ks, v4i (&d)[NTW]) {
+#pragma unroll
+        for (int t = 0; t < NTW; t++)
+            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(d[t]) : "v"(offw), "s"(wbase + (size_t)(16 * t) * Kbytes + (size_t)(2 * kt + ks) * 1024));
+    };
+    const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    unsigned addr[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) addr[ks] = lds_base + r * 128 + (((4 * ks + q) ^ swz<128>(r)) << 4);
+
+    const int KT = Kbytes / 128;                                  // a multiple of D (the launcher checks)
+    v4f mm[NTW], bb[NTW];
+#pragma unroll
+    for (int s = 0; s < D; s++) {
+        issue_a(s, 0, NLDA);
+        load_w(s, 0, w[s][0]);
+        load_w(s, 1, w[s][1]);
+        if (s == 0) {
+            epi.load_lut_direct(lut, wave, 4, lane);
+#pragma unroll
+            for (int t = 0; t < NTW; t++) {
+                const int n = n0 + 16 * (NTW * wave + t) + 4 * q;
+                mm[t] = *reinterpret_cast<const v4f *>(epi.m + n);
+                bb[t] = epi.offsets() ? *reinterpret_cast<const v4f *>(epi.offsets() + n) : v4f{0.f, 0.f, 0.f, 0.f};
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    v4i acc[NTW][MT];
+#pragma unroll
+    for (int t = 0; t < NTW; t++)
+#pragma unroll
+        for (int i = 0; i < MT; i++) acc[t][i] = v4i{0, 0, 0, 0};
+    v4i fa[2][G];
+    int slot = 0;
+    auto fetch = [&](auto idx_tag, v4i (&f)[G]) {
+        constexpr int OFF = (decltype(idx_tag)::value % H) * G * 2048;
+        lds_read_frags<2048>(addr[decltype(idx_tag)::value / H] + slot + OFF, f, std::make_integer_sequence<int, G>());
+    };
+    constexpr std::integral_constant<int, 0> c0;
+    constexpr std::integral_constant<int, 1> c1;
+    constexpr std::integral_constant<int, 2> c2;
+    constexpr std::integral_constant<int, 3> c3;
+    // One step multiplies G token tiles by the wave's channels over 64 bytes of K, with the token fragments of the step after it on
+    // their way from LDS.  The loads of the stage D further on are dealt out over the steps (a burst of them would hold the wave up
+    // at its issue, with the matrix cores idle): token rows in each, weights into the registers that the step before has read last.
+    // LEFT: stages after this one, D where there are that many or more (copies of the code instead of tests: the waits are constants).
+    auto step = [&](auto left_tag, auto b_tag, auto idx_tag, int kt) {
+        constexpr int LEFT = decltype(left_tag)::value, B = decltype(b_tag)::value, IDX = decltype(idx_tag)::value, ks = IDX / H, h = IDX % H;
+        constexpr bool MORE = LEFT == D;
+        if constexpr (IDX == H) {                                 // the second half of this stage's weights has landed
+            wait_vm<MORE ? (D - 1) * PER + NLDA * H / STEPS : LEFT * PER>();
+            tie(w[B][1], std::make_integer_sequence<int, NTW>());
+        }
+        if constexpr (MORE) {
+            issue_a(kt + D, NLDA * IDX / STEPS, NLDA * (IDX + 1) / STEPS);
+            if constexpr (IDX == H) load_w(kt + D, 0, w[B][0]);
+        }
+        if constexpr (IDX + 1 < STEPS) {
+            fetch(std::integral_constant<int, IDX + 1>(), fa[(IDX + 1) & 1]);
+            wait_lds_reads<G>();
+        } else if constexpr (LEFT > 0) {                          // so have the next stage's token rows and the first half of its weights
+            wait_vm_and_barrier<MORE ? (D - 1) * PER : NTW + (LEFT - 1) * PER>();
+            slot = slot + SLOT == RING ? 0 : slot + SLOT;
+            fetch(c0, fa[0]);
+        } else {
+            wait_lds_reads<0>();
+        }
+        tie(fa[IDX & 1], std::make_integer_sequence<int, G>());
+        if constexpr (IDX == 0) tie(w[B][0], std::make_integer_sequence<int, NTW>());
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < NTW; t++)
+#pragma unroll
+            for (int i = 0; i < G; i++)
+                acc[t][G * h + i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[B][ks][t], fa[IDX & 1][i], acc[t][G * h + i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MORE && IDX + 1 == STEPS) load_w(kt + D, 1, w[B][1]);
+    };
+    auto stage = [&](auto left_tag, auto b_tag, int kt) {
+        step(left_tag, b_tag, c0, kt);
+        step(left_tag, b_tag, c1, kt);
+        if constexpr (H == 2) { step(left_tag, b_tag, c2, kt); step(left_tag, b_tag, c3, kt); }
+    };
+    wait_vm_and_barrier<NTW + (D - 1) * PER>();
+    fetch(c0, fa[0]);
+    const auto all = std::make_integer_sequence<int, D>();
+    for (int kt = 0; kt + D < KT; kt += D) each_index([&](auto b) { stage(std::integral_constant<int, D>(), b, kt + b); }, all);
+    each_index([&](auto b) { stage(std::integral_constant<int, D - 1 - decltype(b)::value>(), b, 0); }, all);
+    __syncthreads();                                              // the ring is idle from here on
+
+    constexpr int STRIDE = Tile::STRIDE, CHUNKS = BN / 16, PASSES = (BM * CHUNKS + 255) / 256;
+    constexpr bool EVEN = BM * CHUNKS % 256 == 0;
+#pragma unroll
+    for (int t = 0; t < NTW; t++)
+#pragma unroll
+        for (int h = 0; h < H; h++) {
+            v4i group[G];
+            int pk[G];
+#pragma unroll
+            for (int i = 0; i < G; i++) group[i] = acc[t][G * h + i];
+            epi.quads(group, mm[t], bb[t], lut, pk);
+#pragma unroll
+            for (int i = 0; i < G; i++)
+                *reinterpret_cast<int *>(lds + (16 * (G * h + i) + r) * STRIDE + 16 * (NTW * wave + t) + 4 * q) = pk[i];
+        }
+    __syncthreads();
+    v4i v[PASSES];
+#pragma unroll
+    for (int p = 0; p < PASSES; p++) {
+        const int idx = EVEN ? p * 256 + tid : min(p * 256 + tid, BM * CHUNKS - 1);
+        v[p] = *reinterpret_cast<const v4i *>(lds + (idx / CHUNKS) * STRIDE + (idx % CHUNKS) * 16);
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; p++) {
+        const int idx = p * 256 + tid, row = m0 + idx / CHUNKS;
+        if (row < M && (EVEN || idx < BM * CHUNKS)) *reinterpret_cast<v4i *>(out + (size_t)row * N + n0 + (idx % CHUNKS) * 16) = v[p];
+    }
+}
+
+template <class Epi, int MT, int NTW, int D>
+hipError_t launch_stream(const void *A, const void *Wp, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
+{
+    typedef StreamTile<MT, NTW, D> Tile;
+    const size_t LDS = Tile::LUT_OFF + extra_lds_of(epi, 0);
+    if (N % Tile::BN || K % (128 * D)) return hipErrorInvalidValue;
+    auto kern = gemm_nt_stream_kernel<Epi, MT, NTW, D>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           Tile::LUT_OFF + GELU_TABLE_MAX_BINS * 8);
+        if (e != hipSuccess) return e;
+        attr_set.store(true, std::memory_order_release);
+    }
+    // An XCD takes the tiles of an eighth of the token rows, as in every other kernel of the path, unless the weights
+    // are more than its L2 holds beside them and the rows are few: then it takes an eighth of the channels and all of the rows (us, token
+    // rows first / channels first: 1024 x 4096, 256 rows 7.8 / 6.4, 512 rows 10.6 / 7.1, 1024 rows 11.3 / 11.6, 2048 rows 13.9 / 14.5;
+    // 4096 x 1024, 512 rows 6.9 / 6.1, 1024 rows 10.6 / 8.6; 768 x 3072 and 3072 x 768 +-2 % up to 1024 rows)
+    const bool channels_first = (long)N * K >= 3 << 20 && rows.host_rows <= 1024;
+    const int tiles_n = N / Tile::BN, tiles_m = (rows.host_rows + Tile::BM - 1) / Tile::BM;
+    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)Wp, (char *)out, epi,
+                  rows.host_rows, rows.dev_rows, N, K, tiles_n, channels_first);
+    return hipGetLastError();
+}
+
+// The tile is the one whose estimated time is least.  The estimate, in us, is a fit to the times of these tiles at 16 to 16384 rows of eight
+// N x K from 768 x 768 to 4096 x 1024 (each alone on the chip, in chains over other weights at every launch, as in a forward; the choice
+// costs 1 % on average over the best of all tiles and depths): per 128-byte stage of K the products and the operand bytes of the blocks
+// that the busiest CU gets, and their epilogues.  Smallest first.
+struct StreamShape { int mt, ntw; };
+constexpr StreamShape STREAM_TILES[] = {{2, 1}, {4, 1}, {4, 2}, {4, 3}, {4, 4}, {8, 2}, {8, 3}};
+constexpr int STREAM_TILE_COUNT = sizeof(STREAM_TILES) / sizeof(STREAM_TILES[0]);
+int stream_tile(Rows rows, int N, int K)
+{
+    int best = -1;
+    double best_cost = 0.0;
+    for (int i = 0; i < STREAM_TILE_COUNT; i++) {
+        const int bm = 16 * STREAM_TILES[i].mt, bn = 64 * STREAM_TILES[i].ntw;
+        if (N % bn) continue;
+        const long tiles = (long)(N / bn) * ((rows.host_rows + bm - 1) / bm);
+        const double blocks = (double)((tiles + 255) / 256), area = bm * bn / 8192.0, sides = (bm + bn) / 256.0;
+        const double cost = blocks * (K / 128 * (0.016 * area + 0.30 * sides) + 0.81 * area);
+        if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+    }
+    return best;
+}
+// Stages in flight: a small tile's stage is short next to the latency of its loads (the weights of a layer come from beyond L2), so it asks
+// for more of them (us, 2 stages / as chosen here: 32 x 64 tiles, 768 x 768 at 427 rows 4.1 / 3.5, 1024 x 4096 at 427 rows 9.1 / 6.4; 64 x 64,
+// 768 x 3072 at 1024 rows 8.5 / 7.2; 64 x 128, 768 x 3072 at 2048 rows 10.2 / 9.0; 64 x 192, 768 x 3072 at 4096 rows 12.2 / 11.7; the
+// larger tiles are +-3 %).  KT, the number of stages, has to be a multiple.
+template <class Epi>
+hipError_t launch_packed(const void *A, const void *Wp, void *out, const Epi &epi, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm)
+{
+    if (K % 256 || N % 64) return hipErrorNotSupported;
+    switch (tile < 0 ? stream_tile(rows, N, K) : tile) {
+    case 0:
+        if (K % 512 == 0) return launch_stream<Epi, 2, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 768 == 0) return launch_stream<Epi, 2, 1, 6>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<Epi, 2, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 1:
+        if (K % 512 == 0) return launch_stream<Epi, 4, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 384 == 0) return launch_stream<Epi, 4, 1, 3>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<Epi, 4, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 2:
+        if (K % 512 == 0) return launch_stream<Epi, 4, 2, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 384 == 0) return launch_stream<Epi, 4, 2, 3>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<Epi, 4, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 3:
+        if (K % 384 == 0) return launch_stream<Epi, 4, 3, 3>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<Epi, 4, 3, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 4: return launch_stream<Epi, 4, 4, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 5: return launch_stream<Epi, 8, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 6: return launch_stream<Epi, 8, 3, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    }
+    return hipErrorInvalidValue;
+}
 
 // ---- long operand rows on few tiles ------------------------------------------------------------------
 // FFN2 at small batch: 24 (FP16: 48) stages of 128 bytes, 64 x 96 tiles that no more than fill the chip once.  Such
@@ -1239,9 +1541,19 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
 
 std::atomic<int> gemm_config_override{-1};                    // tuning aid: force one tile configuration (see launch())
 
-hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, void *out, const float *m, const float *b,
+// Few rows: the kernel that splits K over a block's waves asks for the whole of K at once and has smaller tiles for narrow matrices (us, K
+// split / packed weights: 768 x 768 at 128 rows 2.95 / 3.4, at 256 3.4 / 3.6, at 427 3.8 / 3.5; 768 x 3072 at 256 rows 5.1 / 6.3, at 512 6.25 / 6.25;
+// 1024 x 4096 at 256 rows 5.9 / 6.3, at 427 7.25 / 6.4; 1024 x 1024 at 256 rows 3.9 / 4.3, at 768 5.5 / 5.2; 2304 x 768 at 32 rows 3.25 / 3.4, at 64
+// 3.7 / 3.5; 3072 x 768 at 32 rows 3.7 / 3.8, at 64 4.05 / 3.8; 4096 x 1024 at 32 rows 4.0 / 4.1, at 64 4.6 / 4.15)
+static bool k_split_is_faster(Rows rows, int N) { return (long)rows.host_rows * N <= (N <= 1024 ? 300000 : 128000); }
+
+hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, const int8_t *Wp, void *out, const float *m, const float *b,
                           float inv_s_out, const GeluTable *gt, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
 {
+    if (Wp && gemm_config_override.load(std::memory_order_relaxed) < 0 && !k_split_is_faster(rows, N)) {
+        const hipError_t e = launch_gemm_i8_packed(epi, A, Wp, out, m, b, gt, rows, N, K, -1, st, tm);
+        if (e != hipErrorNotSupported) return e;
+    }
     switch (epi) {
     case EPI_RAW_I32: return launch<I8>(A, W, out, EpiRawI32{(int32_t *)out, N}, rows, N, K, st, tm);
     case EPI_REQUANT: return launch<I8>(A, W, out, EpiRequant{m, b}, rows, N, K, st, tm);
@@ -1252,6 +1564,16 @@ hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, vo
         return launch<I8>(A, W, out, EpiGeluQuant{m, b, inv_s_out}, rows, N, K, st, tm);
     }
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t *Wp, void *out, const float *m, const float *b,
+                                 const GeluTable *gt, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm)
+{
+    if (epi == EPI_REQUANT) return launch_packed(A, Wp, out, EpiRequant{m, b}, rows, N, K, tile, st, tm);
+    if (epi == EPI_GELU_QUANT && gt && gt->entries)
+        return launch_packed(A, Wp, out, EpiGeluTable{m, b, gt->entries, gt->spec.rate, gt->spec.offset, gt->spec.t_max, gt->spec.bins},
+                             rows, N, K, tile, st, tm);
+    return hipErrorNotSupported;
 }
 
 hipError_t launch_gemm_f16(const __half *A, const __half *W, const float *bias, bool gelu, __half *out, Rows rows,

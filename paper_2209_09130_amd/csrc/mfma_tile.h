@@ -27,6 +27,12 @@ __device__ __forceinline__ void wait_vm_and_barrier()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+template <int N> __device__ __forceinline__ void wait_vm()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Fragment fetches of the large-tile kernel are written as ds_read_b128 instructions of its own, with
 // explicit waits: left to the compiler, every group of MFMAs is preceded by a wait for ALL outstanding
 // LDS reads, including the ones just issued for the step after it, which puts the LDS latency in front

@@ -503,6 +503,16 @@ __global__ __launch_bounds__(256) void quantize_weight_kernel(const __half *__re
     for (int k = threadIdx.x; k < K; k += 256) Wq[(size_t)n * K + k] = (int8_t)qcode(__fdiv_rn((float)row[k], s));
 }
 
+// Weights in the order in which a wave takes them as the operand of a 16 x 16 x 64 product (create time): one thread per 16 bytes.
+__global__ __launch_bounds__(256) void pack_weight_kernel(const int8_t *__restrict__ W, int K, int chunks, int8_t *__restrict__ Wp)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;                  // chunk of the result: [row block][64-byte group][column][row]
+    if (i >= chunks) return;
+    const int r = i & 15, q = (i >> 4) & 3, block = i >> 6, groups = K >> 6;
+    const size_t row = (size_t)(block / groups) * 16 + r, col = (size_t)(block % groups) * 64 + 16 * q;
+    reinterpret_cast<v4i *>(Wp)[i] = *reinterpret_cast<const v4i *>(W + row * K + col);
+}
+
 // Epilogue tables: m[n] = s_in * s_w[n] / s_out, b[n] = bias[n] / s_out, formed in binary64 and
 // rounded once (s_out = 1 and bias = nullptr give the plain dequantising multiplier).
 __global__ void fold_kernel(float s_in, const float *__restrict__ s_w, const float *__restrict__ bias, float s_out, int N,
@@ -592,6 +602,13 @@ hipError_t launch_add_ln(const AddLnArgs &a, hipStream_t st, const Timing *tm)
 hipError_t launch_quantize_weight(const __half *W, int N, int K, int8_t *Wq, float *s_w, hipStream_t st)
 {
     hipLaunchKernelGGL(quantize_weight_kernel, dim3(N), dim3(256), 0, st, W, K, Wq, s_w);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_weight(const int8_t *W, int N, int K, int8_t *Wp, hipStream_t st)
+{
+    const int chunks = (int)((size_t)N * K / 16);
+    hipLaunchKernelGGL(pack_weight_kernel, dim3((chunks + 255) / 256), dim3(256), 0, st, W, K, chunks, Wp);
     return hipGetLastError();
 }
 

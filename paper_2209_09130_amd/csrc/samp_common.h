@@ -175,9 +175,14 @@ extern std::atomic<int> gemm_config_override;                           // < 0: 
 
 // gelu_table (EPI_GELU_QUANT only, may be null): the threshold table of this inv_s_out; without it the epilogue
 // evaluates GELU per element (certified binary32 fast path, binary64 where a rounding tie is near)
-hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, void *out, const float *m, const float *b,
+// Wp (may be null): the same weights in the order of launch_pack_weight
+hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, const int8_t *Wp, void *out, const float *m, const float *b,
                           float inv_s_out, const GeluTable *gelu_table, Rows rows, int N, int K, hipStream_t st,
                           const Timing *tm);
+// on packed weights alone; tile: -1 by size, or a number of stream_tile's list (hipErrorInvalidValue where it does not divide N).
+// hipErrorNotSupported: K is no multiple of 256, N none of 64, or the epilogue is another
+hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t *Wp, void *out, const float *m, const float *b,
+                                 const GeluTable *gelu_table, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm);
 hipError_t launch_gemm_f16(const __half *A, const __half *W, const float *bias, bool gelu, __half *out, Rows rows,
                            int N, int K, hipStream_t st, const Timing *tm);
 
@@ -221,6 +226,9 @@ struct EmbedArgs {
 hipError_t launch_embed_ln(const EmbedArgs &a, hipStream_t st, const Timing *tm);
 
 hipError_t launch_quantize_weight(const __half *W, int N, int K, int8_t *Wq, float *s_w, hipStream_t st);
+// W [N,K] in the order of the 16 x 16 x 64 matrix product: 1 KB blocks of 16 rows x 64 bytes, row blocks outermost, inside a block the
+// four 16-byte columns one after the other, 16 rows each.  N % 16 == 0, K % 64 == 0
+hipError_t launch_pack_weight(const int8_t *W, int N, int K, int8_t *Wp, hipStream_t st);
 hipError_t launch_fold(const float *s_in_dev_or_null, float s_in, const float *s_w, const float *bias, float s_out, int N,
                        float *m, float *b, hipStream_t st);
 hipError_t launch_seq_offsets(const int *mask, int B, int S, int *cu, hipStream_t st);

@@ -149,6 +149,34 @@ def test_large_tile_configurations_give_the_same_results(P, config, M, N, K):
     assert (np.abs(f16 - wantf) <= np.maximum(np.abs(wantf), 2.0 ** -14) * 2.0 ** -10 + 1e-6).all()
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("M,N,K", [(1, 768, 256), (130, 768, 768), (257, 768, 1024), (33, 768, 3072), (1100, 512, 512), (70, 128, 1280)])
+def test_gemms_on_packed_weights_give_the_same_codes(P, tile, M, N, K):
+    """Weights packed in the order of the matrix product and loaded straight into registers: every tile with one row, a last row tile
+    that is not full, two to twenty-four stages of K, both epilogues bit-exact.  The packed bytes against the definition."""
+    width = {0: 64, 1: 64, 2: 128, 3: 192, 4: 256, 5: 128, 6: 192}
+    rng = np.random.default_rng(M + N + K)
+    A = rng.integers(-127, 128, (M, K), dtype=np.int8)
+    W = rng.integers(-127, 128, (N, K), dtype=np.int8)
+    s_w, bias = _tables(rng, N)
+    m, b = oracle.fold_requant(0.037, s_w, bias, 0.021 * np.sqrt(K / 768))
+    md = oracle.fold_dequant(0.05 * np.sqrt(768 / K), s_w)
+    s_out = 0.0147
+    spec, entries = P.gelu_table_build(s_out)
+    packed = P.pack_weight_i8(dev(W))
+    assert np.array_equal(host(packed), W.reshape(N // 16, 16, K // 64, 4, 16).transpose(0, 2, 3, 1, 4).ravel())
+    if tile >= 0 and N % width[tile]:
+        with pytest.raises(P.SampError):
+            P.gemm_i8_requant_packed(dev(A), packed, dev(m), dev(b), tile)
+        return
+    acc = oracle.gemm_i8_i32(A, W)
+    assert np.array_equal(host(P.gemm_i8_requant_packed(dev(A), packed, dev(m), dev(b), tile)), oracle.epilogue_requant(acc, m, b))
+    assert np.array_equal(host(P.gemm_i8_requant_packed(dev(A), packed, dev(m), None, tile)),
+                          oracle.epilogue_requant(acc, m, np.zeros_like(b)))
+    assert np.array_equal(host(P.gemm_i8_gelu_quant_packed(dev(A), packed, dev(md), dev(bias), (spec, dev(entries)), tile)),
+                          oracle.epilogue_gelu_quant(acc, md, bias, s_out))
+
+
 @pytest.mark.parametrize("config", [-1, 0, 1, 2])
 def test_table_lookup_gelu_epilogue_in_the_small_tile_configurations(P, config):
     rng = np.random.default_rng(5 + config)

@@ -1,4 +1,4 @@
-"""What the compiler made of the kernels, read from the metadata of the built library (llvm-readelf prints it): an attention
+"""What the compiler made of the kernels, read from the metadata of the built library (llvm-readelf prints it): a
 kernel that does not fit its registers spills to scratch memory, which nothing else would report."""
 import os
 import re
@@ -40,8 +40,8 @@ def kernels(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf is not installed")
-@pytest.mark.parametrize("kernel", ["attention_i8_kernel", "attention_i8_p16_kernel", "attention_f16_kernel"])
-def test_attention_kernels_use_no_scratch_memory(kernel, tmp_path):
+@pytest.mark.parametrize("kernel", ["attention_i8_kernel", "attention_i8_p16_kernel", "attention_f16_kernel", "gemm_nt_stream_kernel"])
+def test_kernels_use_no_scratch_memory(kernel, tmp_path):
     found = [(name, scratch) for name, scratch in kernels(tmp_path) if kernel in name]
     assert len(found) >= 4, found
     assert not [k for k in found if k[1]]
