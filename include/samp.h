@@ -353,6 +353,11 @@ SAMP_API int samp_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const f
                                    const int32_t *cu_seqlens, int32_t B, int32_t max_len, int32_t hidden, int32_t heads,
                                    float s_q, float s_k, float s_v, float s_p, float s_ctx, int32_t p_kind, int8_t *ctx,
                                    void *stream);
+/* The same on w_qkv packed by samp_pack_weight_i8, for sequences of at most 128 tokens; hidden % 256 == 0. */
+SAMP_API int samp_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const float *m, const float *b,
+                                   const int32_t *cu_seqlens, int32_t B, int32_t max_len, int32_t hidden, int32_t heads,
+                                   float s_q, float s_k, float s_v, float s_p, float s_ctx, int32_t p_kind, int8_t *ctx,
+                                   void *stream);
 /* The FP16 counterpart: out = samp_gemm_f16(x, w_qkv, bias, no GELU) followed by samp_attention_f16, in one kernel,
  * byte for byte.  x dev fp16 [T,hidden], w_qkv dev fp16 [3 hidden, hidden], bias dev float [3 hidden] or NULL.  */
 SAMP_API int samp_qkv_attention_f16(const uint16_t *x, const uint16_t *w_qkv, const float *bias, const int32_t *cu_seqlens,

@@ -346,6 +346,16 @@ def qkv_attention_i8(x, w_qkv, m, b, cu, max_len: int, heads: int, s_q, s_k, s_v
     return ctx
 
 
+def qkv_attention_i8_packed(x, w_packed, m, b, cu, max_len: int, heads: int, s_q, s_k, s_v, s_p, s_ctx, p_unsigned: bool = False):
+    """qkv_attention_i8 on weights that pack_weight_i8 packed, for sequences of at most 128 tokens."""
+    T, H = x.shape
+    B = _batch_of(cu, T, max_len)
+    ctx = torch.zeros((T, H), dtype=torch.int8, device=x.device)
+    _check(lib().samp_qkv_attention_i8_packed(_dp(x), _dp(w_packed), _dp(m), _dp(b), _dp(cu), B, max_len, H, heads, _f(s_q), _f(s_k),
+                                       _f(s_v), _f(s_p), _f(s_ctx), int(bool(p_unsigned)), _dp(ctx), _stream()))
+    return ctx
+
+
 def qkv_attention_f16(x, w_qkv, bias, cu, max_len: int, heads: int):
     """samp_qkv_attention_f16: ctx [T, H] fp16 from packed fp16 rows x [T, H] and the fp16 QKV weights [3H, H]."""
     T, H = x.shape

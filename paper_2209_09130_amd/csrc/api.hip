@@ -297,11 +297,17 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             // (one block per CU, a wave's 64 queries one after the other) loses against the two kernels, whose exact
             // exponentials run four blocks to a CU (BERT-large 32 x 256: +6 %); it runs only when forced.
             const bool can_fuse = S <= (enc->fusion_wanted == 2 ? 256 : 128) && !(Y.mode & SAMP_P_FP16);
-            if (can_fuse && (enc->fusion_wanted == 2 || (enc->fusion_wanted == 0 && B * heads >= 128)))
-                HIP_TRY(launch_qkv_attention_i8((const int8_t *)x, (const int8_t *)Y.w_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc,
-                                                Y.inv_sp, Y.m_ctx, (Y.mode & SAMP_P_UNSIGNED) != 0, (int8_t *)w.ctx, st,
-                                                timing(enc, SAMP_PROF_QKV_ATTN)));
-            else {
+            if (can_fuse && (enc->fusion_wanted == 2 || (enc->fusion_wanted == 0 && B * heads >= 128))) {
+                const bool p_unsigned = (Y.mode & SAMP_P_UNSIGNED) != 0;
+                const Timing *tm = timing(enc, SAMP_PROF_QKV_ATTN);
+                hipError_t e = !Y.p_qkv ? hipErrorNotSupported
+                                        : launch_qkv_attention_i8_packed((const int8_t *)x, Y.p_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
+                                                                         Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
+                if (e == hipErrorNotSupported)
+                    e = launch_qkv_attention_i8((const int8_t *)x, (const int8_t *)Y.w_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
+                                                Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
+                HIP_TRY(e);
+            } else {
                 HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, Y.p_qkv, w.qkv, Y.m_qkv, Y.bq_qkv, 0.f,
                                        nullptr, rows, 3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
                 if (Y.mode & SAMP_P_FP16)
@@ -920,14 +926,16 @@ int samp_attention_i8(const int8_t *qkv, const int32_t *cu, int32_t B, int32_t m
     return SAMP_OK;
 }
 
-int samp_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int32_t *cu, int32_t B,
-                          int32_t max_len, int32_t hidden, int32_t heads, float s_q, float s_k, float s_v, float s_p,
-                          float s_ctx, int32_t p_kind, int8_t *ctx, void *stream)
+static int qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int32_t *cu, int32_t B,
+                            int32_t max_len, int32_t hidden, int32_t heads, float s_q, float s_k, float s_v, float s_p,
+                            float s_ctx, int32_t p_kind, int8_t *ctx, void *stream, bool packed)
 {
+    const int longest = packed ? 128 : 256;
     if (p_kind < 0 || p_kind > 1) return fail(SAMP_ERR_ARG, "p_kind must be 0 or 1");
     if (!x || !w_qkv || !m || !ctx) return fail(SAMP_ERR_ARG, "NULL pointer");
-    if (B < 1 || max_len < 1 || max_len > 256) return fail(SAMP_ERR_SHAPE, "B >= 1 and 1 <= max_len <= 256 required");
+    if (B < 1 || max_len < 1 || max_len > longest) return fail(SAMP_ERR_SHAPE, "B >= 1 and 1 <= max_len <= %d required", longest);
     if (heads < 1 || hidden != heads * 64) return fail(SAMP_ERR_SHAPE, "head size must be 64");
+    if (packed && hidden % 256) return fail(SAMP_ERR_SHAPE, "packed weights need hidden %% 256 == 0");
     if (!aligned(x, 16) || !aligned(w_qkv, 16) || !aligned(ctx, 16) || !aligned(m, 16) || (b && !aligned(b, 16)))
         return fail(SAMP_ERR_ARG, "tensors must be 16-byte aligned");
     if (!(good_scale(s_q) && good_scale(s_k) && good_scale(s_v) && good_scale(s_p) && good_scale(s_ctx)))
@@ -935,9 +943,23 @@ int samp_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, 
     const float m_sc = (float)((double)s_q * (double)s_k / std::sqrt(64.0));
     if (!good_score_multiplier(m_sc)) return fail(SAMP_ERR_SCALE, "s_q * s_k / 8 must not exceed %g", (double)MAX_SCORE_MULTIPLIER);
     const float m_ctx = (float)((double)s_p * (double)s_v / (double)s_ctx);
-    HIP_TRY(launch_qkv_attention_i8(x, w_qkv, m, b, cu, B, max_len, hidden, m_sc, 1.0f / s_p, m_ctx, p_kind == 1, ctx,
-                                    (hipStream_t)stream, nullptr));
+    HIP_TRY((packed ? launch_qkv_attention_i8_packed : launch_qkv_attention_i8)(x, w_qkv, m, b, cu, B, max_len, hidden, m_sc, 1.0f / s_p, m_ctx,
+                                                                                p_kind == 1, ctx, (hipStream_t)stream, nullptr));
     return SAMP_OK;
+}
+
+int samp_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int32_t *cu, int32_t B,
+                          int32_t max_len, int32_t hidden, int32_t heads, float s_q, float s_k, float s_v, float s_p,
+                          float s_ctx, int32_t p_kind, int8_t *ctx, void *stream)
+{
+    return qkv_attention_i8(x, w_qkv, m, b, cu, B, max_len, hidden, heads, s_q, s_k, s_v, s_p, s_ctx, p_kind, ctx, stream, false);
+}
+
+int samp_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const float *m, const float *b, const int32_t *cu, int32_t B,
+                                 int32_t max_len, int32_t hidden, int32_t heads, float s_q, float s_k, float s_v, float s_p,
+                                 float s_ctx, int32_t p_kind, int8_t *ctx, void *stream)
+{
+    return qkv_attention_i8(x, w_packed, m, b, cu, B, max_len, hidden, heads, s_q, s_k, s_v, s_p, s_ctx, p_kind, ctx, stream, true);
 }
 
 int samp_qkv_attention_f16(const uint16_t *x, const uint16_t *w_qkv, const float *bias, const int32_t *cu, int32_t B,

@@ -535,6 +535,135 @@ __device__ __forceinline__ void load_direct(float *dst, const void *src, int wor
                                          (__attribute__((address_space(3))) void *)(dst + i), 4, 0, 0);
 }
 
+// q and k as token rows of 64 codes, v transposed (a channel's codes of all keys in a row): strides of the LDS copies
+constexpr int QK_STRIDE_I8 = 80;
+template <int QT> constexpr int VT_ROW_I8 = 128 * QT + 4;
+
+// The attention of the QKV + attention kernels, from q, k and V^T in LDS: this wave's 32 QT queries against all keys.
+template <int QT, bool PU>
+__device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *lvt, const ExpTable &exp_table, int n, int t0, int head, int H,
+                                          float m_sc, float inv_sp, float m_ctx, int8_t *__restrict__ ctx, int wave, int lane)
+{
+    constexpr int QK_STRIDE = QK_STRIDE_I8, VT_STRIDE = VT_ROW_I8<QT>, NKT = 4 * QT;
+    const int r = lane & 31, g = lane >> 5;
+    // attention: this wave's 32 QT queries against all keys, 32 queries at a time
+#pragma unroll 1
+    for (int qt = 0; qt < QT; qt++) {
+        const int q0 = (wave * QT + qt) * QB;
+        if (q0 >= n) break;                                       // no barrier below
+        v4i qf[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) qf[ks] = *reinterpret_cast<const v4i *>(lq + (q0 + r) * QK_STRIDE + ks * 32 + g * 16);
+        float sc[NKT][16];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NKT; i++) {
+            const int j0 = 32 * i;
+            if (j0 < n) {                                        // wave-uniform
+                v4i kf[2];
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++) kf[ks] = *reinterpret_cast<const v4i *>(lk + (j0 + r) * QK_STRIDE + ks * 32 + g * 16);
+                v16i s;
+#pragma unroll
+                for (int e = 0; e < 16; e++) s[e] = 0;
+#pragma unroll
+                for (int ks = 0; ks < 2; ks++) s = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[ks], qf[ks], s, 0, 0, 0);
+                if (j0 + 32 <= n) {
+#pragma unroll
+                    for (int e = 0; e < 16; e++) {
+                        sc[i][e] = (float)s[e] * m_sc;
+                        mx = __builtin_fmaxf(mx, sc[i][e]);
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16; e++) {
+                        const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
+                        sc[i][e] = key < n ? (float)s[e] * m_sc : -INFINITY;
+                        mx = __builtin_fmaxf(mx, sc[i][e]);
+                    }
+                }
+            }
+        }
+        mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
+
+        // row sums: key tile i adds to partial sum i mod 4, in ascending order, as wave i mod 4 of the attention kernel does
+        double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < NKT; i++) {
+            if (32 * i < n) {
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    sc[i][e] = exp_nonpos(sc[i][e] - mx, exp_table);
+                    part[i & 3] += (double)sc[i][e];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) part[u] += __shfl_xor(part[u], 32, 64);
+        const float S = (float)(((part[0] + part[1]) + part[2]) + part[3]);
+        const float rS = __fdiv_rn(1.0f, S);
+
+        v16i o[2], o1[PU ? 2 : 1];
+#pragma unroll
+        for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) { o[cb][e] = opaque_zero(); if (PU) o1[cb][e] = opaque_zero(); }
+        const float lo = PU ? 0.0f : -127.0f, hi = PU ? 255.0f : 127.0f;
+        const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+#pragma unroll
+        for (int i = 0; i < NKT; i++) {
+            const int j0 = 32 * i;
+            if (j0 < n) {
+                v4i pf;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    float f[4];
+#pragma unroll
+                    for (int t = 0; t < 4; t++) f[t] = __builtin_amdgcn_fmed3f((sc[i][4 * q + t] * rS) * inv_sp, lo, hi) + SAMP_RNE_MAGIC;
+                    pf[q] = pack_codes(f[0], f[1], f[2], f[3]);
+                    if (PU) pf[q] ^= (int)0x80808080u;             // code - 128 as a signed byte
+                }
+#pragma unroll
+                for (int cb = 0; cb < 2; cb++) {
+                    v4i vf;
+#pragma unroll
+                    for (int q = 0; q < 4; q++)
+                        vf[q] = *reinterpret_cast<const int *>(lvt + (cb * 32 + r) * VT_STRIDE + j0 + 8 * q + 4 * g);
+                    o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf, o[cb], 0, 0, 0);   // channels x queries: a lane holds ONE query
+                    if (PU) o1[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, ones, o1[cb], 0, 0, 0);   // 128 times this is added back below
+                }
+            }
+        }
+
+        if (PU) {
+#pragma unroll
+            for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) o[cb][e] += o1[cb][e] * 128;
+        }
+        // context codes: the lane's query, channels cb*32 + 8q + 4g + t: four codes per dword into the wave's own query rows
+        // in LDS (read into qf above, read by no other wave), from where they leave as 32 bytes per lane
+        char *slab = lq + q0 * QK_STRIDE;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int cb = 0; cb < 2; cb++)
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                *reinterpret_cast<int *>(slab + r * QK_STRIDE + cb * 32 + 8 * q + 4 * g) =
+                    pack4(qcode((float)o[cb][4 * q] * m_ctx), qcode((float)o[cb][4 * q + 1] * m_ctx), qcode((float)o[cb][4 * q + 2] * m_ctx),
+                          qcode((float)o[cb][4 * q + 3] * m_ctx));
+        __builtin_amdgcn_wave_barrier();
+        const int query = lane >> 1, half = lane & 1;
+        if (q0 + query < n) {
+            const v4i lo = *reinterpret_cast<const v4i *>(slab + query * QK_STRIDE + half * 32);
+            const v4i hi = *reinterpret_cast<const v4i *>(slab + query * QK_STRIDE + half * 32 + 16);
+            int8_t *dst = ctx + (size_t)(t0 + q0 + query) * H + head * 64 + half * 32;
+            *reinterpret_cast<v4i *>(dst) = lo;
+            *reinterpret_cast<v4i *>(dst + 16) = hi;
+        }
+    }
+}
+
 template <int QT, bool PU, int STAGE>                      // PU: unsigned softmax codes, as in attention_i8_kernel
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ m_tab,
@@ -542,8 +671,8 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
                              float inv_sp, float m_ctx, int8_t *__restrict__ ctx)
 {
     typedef QkvTile<QT, STAGE> Tile;
-    constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, RING_BYTES = Tile::RING_BYTES, NKT = 4 * QT;
-    constexpr int QK_STRIDE = 80, VT_STRIDE = BM + 4;             // bytes per token row of q / k, per channel row of V^T
+    constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, RING_BYTES = Tile::RING_BYTES;
+    constexpr int QK_STRIDE = QK_STRIDE_I8, VT_STRIDE = VT_ROW_I8<QT>;
     constexpr int TAB_BYTES = 4096;                               // multipliers and offsets of the 192 columns, table of the exponential
     constexpr int Q_OFF = Tile::LATE ? TAB_BYTES : 0, K_OFF = Q_OFF + BM * QK_STRIDE, VT_OFF = K_OFF + BM * QK_STRIDE;
     static_assert(VT_OFF + 64 * VT_STRIDE + Q_OFF <= RING_BYTES, "q, k and V^T take the place of the ring, clear of a table at either end");
@@ -625,122 +754,87 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
     }
     __syncthreads();
 
-    // attention: this wave's 32 QT queries against all keys, 32 queries at a time
-#pragma unroll 1
-    for (int qt = 0; qt < QT; qt++) {
-        const int q0 = (wave * QT + qt) * QB;
-        if (q0 >= n) break;                                       // no barrier below
-        v4i qf[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ks++) qf[ks] = *reinterpret_cast<const v4i *>(lds + Q_OFF + (q0 + r) * QK_STRIDE + ks * 32 + g * 16);
-        float sc[NKT][16];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < NKT; i++) {
-            const int j0 = 32 * i;
-            if (j0 < n) {                                        // wave-uniform
-                v4i kf[2];
-#pragma unroll
-                for (int ks = 0; ks < 2; ks++) kf[ks] = *reinterpret_cast<const v4i *>(lds + K_OFF + (j0 + r) * QK_STRIDE + ks * 32 + g * 16);
-                v16i s;
-#pragma unroll
-                for (int e = 0; e < 16; e++) s[e] = 0;
-#pragma unroll
-                for (int ks = 0; ks < 2; ks++) s = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[ks], qf[ks], s, 0, 0, 0);
-                if (j0 + 32 <= n) {
-#pragma unroll
-                    for (int e = 0; e < 16; e++) {
-                        sc[i][e] = (float)s[e] * m_sc;
-                        mx = __builtin_fmaxf(mx, sc[i][e]);
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 16; e++) {
-                        const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
-                        sc[i][e] = key < n ? (float)s[e] * m_sc : -INFINITY;
-                        mx = __builtin_fmaxf(mx, sc[i][e]);
-                    }
-                }
-            }
-        }
-        mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
+    attend_i8<QT, PU>(lds + Q_OFF, lds + K_OFF, lds + VT_OFF, exp_table, n, sq.t0, head, H, m_sc, inv_sp, m_ctx, ctx, wave, lane);
+}
 
-        // row sums: key tile i adds to partial sum i mod 4, in ascending order, as wave i mod 4 of the attention kernel does
-        double part[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int i = 0; i < NKT; i++) {
-            if (32 * i < n) {
-#pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    sc[i][e] = exp_nonpos(sc[i][e] - mx, exp_table);
-                    part[i & 3] += (double)sc[i][e];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; u++) part[u] += __shfl_xor(part[u], 32, 64);
-        const float S = (float)(((part[0] + part[1]) + part[2]) + part[3]);
-        const float rS = __fdiv_rn(1.0f, S);
+// The same for at most 128 tokens on packed weights (the tile loop that keeps weights out of LDS): wave w owns 16 of the head's 64 channels in
+// each of the three parts, so a lane's query and key results are four channels of one token per 16 x 16 tile and its value results, formed
+// with the operands the other way round, four tokens of one channel.  Its multipliers and offsets fit 18 registers.  50 KB of LDS for two stages
+// of token rows (the row-major kernel: 80 KB).  Every value is formed by the same operations as there.
+template <bool PU, int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__restrict__ Wp, const float *__restrict__ m_tab,
+                                    const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, float m_sc,
+                                    float inv_sp, float m_ctx, int8_t *__restrict__ ctx)
+{
+    constexpr int MT = 8, BM = 16 * MT, RING = stream_ring_bytes<MT, D>();
+    constexpr int K_OFF = BM * QK_STRIDE_I8, VT_OFF = 2 * K_OFF;
+    static_assert(VT_OFF + 64 * VT_ROW_I8<1> <= RING, "q, k and V^T take the place of the ring");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    ExpTable &exp_table = *reinterpret_cast<ExpTable *>(lds + RING);
 
-        v16i o[2], o1[PU ? 2 : 1];
-#pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) { o[cb][e] = opaque_zero(); if (PU) o1[cb][e] = opaque_zero(); }
-        const float lo = PU ? 0.0f : -127.0f, hi = PU ? 255.0f : 127.0f;
-        const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-#pragma unroll
-        for (int i = 0; i < NKT; i++) {
-            const int j0 = 32 * i;
-            if (j0 < n) {
-                v4i pf;
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    float f[4];
-#pragma unroll
-                    for (int t = 0; t < 4; t++) f[t] = __builtin_amdgcn_fmed3f((sc[i][4 * q + t] * rS) * inv_sp, lo, hi) + SAMP_RNE_MAGIC;
-                    pf[q] = pack_codes(f[0], f[1], f[2], f[3]);
-                    if (PU) pf[q] ^= (int)0x80808080u;             // code - 128 as a signed byte
-                }
-#pragma unroll
-                for (int cb = 0; cb < 2; cb++) {
-                    v4i vf;
-#pragma unroll
-                    for (int q = 0; q < 4; q++)
-                        vf[q] = *reinterpret_cast<const int *>(lds + VT_OFF + (cb * 32 + r) * VT_STRIDE + j0 + 8 * q + 4 * g);
-                    o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf, o[cb], 0, 0, 0);   // channels x queries: a lane holds ONE query
-                    if (PU) o1[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, ones, o1[cb], 0, 0, 0);   // 128 times this is added back below
-                }
-            }
-        }
+    const int heads = H >> 6;
+    const int item = xcd_contiguous(blockIdx.x, gridDim.x);       // sequences outermost, as in the attention kernel
+    const int seq = item / heads, head = item % heads;
+    const SeqInfo sq = seq_info(cu, seq, max_len);
+    const int n = sq.n;
+    if (n <= 0) return;
+    const int lane = threadIdx.x & 63, wave = wave_index(), r = lane & 15, q = lane >> 4;
 
-        if (PU) {
+    unsigned offa[MT / 2];
 #pragma unroll
-            for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-                for (int e = 0; e < 16; e++) o[cb][e] += o1[cb][e] * 128;
-        }
-        // context codes: the lane's query, channels cb*32 + 8q + 4g + t: four codes per dword into the wave's own query rows
-        // in LDS (read into qf above, read by no other wave), from where they leave as 32 bytes per lane
-        char *slab = lds + Q_OFF + q0 * QK_STRIDE;
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                *reinterpret_cast<int *>(slab + r * QK_STRIDE + cb * 32 + 8 * q + 4 * g) =
-                    pack4(qcode((float)o[cb][4 * q] * m_ctx), qcode((float)o[cb][4 * q + 1] * m_ctx), qcode((float)o[cb][4 * q + 2] * m_ctx),
-                          qcode((float)o[cb][4 * q + 3] * m_ctx));
-        __builtin_amdgcn_wave_barrier();
-        const int query = lane >> 1, half = lane & 1;
-        if (q0 + query < n) {
-            const v4i lo = *reinterpret_cast<const v4i *>(slab + query * QK_STRIDE + half * 32);
-            const v4i hi = *reinterpret_cast<const v4i *>(slab + query * QK_STRIDE + half * 32 + 16);
-            int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + half * 32;
-            *reinterpret_cast<v4i *>(dst) = lo;
-            *reinterpret_cast<v4i *>(dst + 16) = hi;
-        }
+    for (int j = 0; j < MT / 2; j++) {
+        const int srow = 8 * (wave + 4 * j) + (lane >> 3);
+        offa[j] = (unsigned)min(srow, n - 1) * (unsigned)H + (((lane & 7) ^ swz<128>(srow)) << 4);
     }
+    const char *wbase[3];
+    const int c0 = head * 64 + 16 * wave;                         // the wave's channels in each part
+#pragma unroll
+    for (int t = 0; t < 3; t++) wbase[t] = Wp + (size_t)(t * H + c0) * H;
+    v4i acc[3][MT];
+#pragma unroll
+    for (int t = 0; t < 3; t++)
+#pragma unroll
+        for (int i = 0; i < MT; i++) acc[t][i] = v4i{0, 0, 0, 0};
+    v4f mm[2], bb[2];
+    float mv = 0.0f, bv = 0.0f;
+    auto started = [&]() {
+        load_direct(reinterpret_cast<float *>(lds + RING) + wave * 128, reinterpret_cast<const int *>(EXP2_TABLE) + wave * 128, 128, lane);
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            mm[t] = *reinterpret_cast<const v4f *>(m_tab + t * H + c0 + 4 * q);
+            bb[t] = b_tab ? *reinterpret_cast<const v4f *>(b_tab + t * H + c0 + 4 * q) : v4f{0.f, 0.f, 0.f, 0.f};
+        }
+        mv = m_tab[2 * H + c0 + r];
+        bv = b_tab ? b_tab[2 * H + c0 + r] : 0.0f;
+    };
+    auto loop = [&](auto live) {                                  // live(i): token tile i holds tokens
+        stream_tile_loop<MT, 3, D>(X + (size_t)sq.t0 * H, offa, wbase, H / 128, lds, wave, lane, started,
+            [&](int t, int i, const v4i &w, const v4i &f) {
+                if (live(i)) acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(t < 2 ? w : f, t < 2 ? f : w, acc[t][i], 0, 0, 0);
+            });
+    };
+    if (n > BM - 16) loop([](int) { return true; });
+    else loop([&](int i) { return 16 * i < n; });
+
+#pragma unroll
+    for (int t = 0; t < 2; t++)
+#pragma unroll
+        for (int i = 0; i < MT; i++) {
+            const v4i a = acc[t][i];
+            *reinterpret_cast<int *>(lds + t * K_OFF + (16 * i + r) * QK_STRIDE_I8 + 16 * wave + 4 * q) =
+                pack_codes(code_bits(__builtin_fmaf((float)a.x, mm[t].x, bb[t].x)), code_bits(__builtin_fmaf((float)a.y, mm[t].y, bb[t].y)),
+                           code_bits(__builtin_fmaf((float)a.z, mm[t].z, bb[t].z)), code_bits(__builtin_fmaf((float)a.w, mm[t].w, bb[t].w)));
+        }
+#pragma unroll
+    for (int i = 0; i < MT; i++) {
+        const v4i a = acc[2][i];
+        *reinterpret_cast<int *>(lds + VT_OFF + (16 * wave + r) * VT_ROW_I8<1> + 16 * i + 4 * q) =
+            pack_codes(code_bits(__builtin_fmaf((float)a.x, mv, bv)), code_bits(__builtin_fmaf((float)a.y, mv, bv)),
+                       code_bits(__builtin_fmaf((float)a.z, mv, bv)), code_bits(__builtin_fmaf((float)a.w, mv, bv)));
+    }
+    __syncthreads();
+    attend_i8<1, PU>(lds, lds + K_OFF, lds + VT_OFF, exp_table, n, sq.t0, head, H, m_sc, inv_sp, m_ctx, ctx, wave, lane);
 }
 
 // The FP16 flavour of the kernel above: fp16 QKV GEMM with its bias, q, k, v rounded to fp16 into LDS, then the
@@ -1668,6 +1762,19 @@ hipError_t launch_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const f
                           : launch_qkv_attention_i8_variant<1, false>(x, w_qkv, m, b, cu, B, max_len, H, m_sc, inv_sp, m_ctx, ctx, st, tm);
     return p_unsigned ? launch_qkv_attention_i8_variant<2, true>(x, w_qkv, m, b, cu, B, max_len, H, m_sc, inv_sp, m_ctx, ctx, st, tm)
                       : launch_qkv_attention_i8_variant<2, false>(x, w_qkv, m, b, cu, B, max_len, H, m_sc, inv_sp, m_ctx, ctx, st, tm);
+}
+
+hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const float *m, const float *b, const int *cu, int B,
+                                          int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
+                                          hipStream_t st, const Timing *tm)
+{
+    if (max_len > 128 || H % 256 || B <= 0) return hipErrorNotSupported;
+    auto go = [&](auto kern) {
+        launch_kernel(kern, dim3((unsigned)(B * (H / 64))), dim3(256), stream_ring_bytes<8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
+                      (const char *)w_packed, m, b, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx);
+        return hipGetLastError();
+    };
+    return p_unsigned ? go(qkv_attention_i8_packed_kernel<true, 2>) : go(qkv_attention_i8_packed_kernel<false, 2>);
 }
 
 hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const float *bias, const int *cu, int B, int max_len,

@@ -765,12 +765,8 @@ hipError_t launch_big(const void *A, const void *W, void *out, const Epi &epi, R
 // of 128 bytes into LDS get 125.
 // A lane's results are four channels of one token per 16 x 16 tile, the same four for all its tokens: its entries of the epilogue's
 // vectors are loaded once, into registers, and a wave's table lookups are the only LDS reads of the epilogue beside the output tile's.
-template <class F, int... I> __device__ __forceinline__ void each_index(F f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>()), ...);
-}
 template <int MT, int NTW, int D> struct StreamTile {
-    static constexpr int BM = 16 * MT, BN = 64 * NTW, SLOT = BM * 128, RING = (D + 1) * SLOT, STRIDE = BN + 16;
+    static constexpr int BM = 16 * MT, BN = 64 * NTW, RING = stream_ring_bytes<MT, D>(), STRIDE = BN + 16;
     static constexpr int OUT = BM * STRIDE, LUT_OFF = RING > OUT ? RING : OUT;       // the output tile takes the ring's place
 };
 
@@ -780,10 +776,7 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
                            const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n, bool channels_first)
 {
     typedef StreamTile<MT, NTW, D> Tile;
-    constexpr int BM = Tile::BM, BN = Tile::BN, SLOT = Tile::SLOT, RING = Tile::RING;
-    constexpr int G = MT < 4 ? MT : 4, H = MT / G, STEPS = 2 * H;          // token tiles per step; steps per 64 bytes of K
-    constexpr int NLDA = BM / 32, PER = NLDA + 2 * NTW;                    // loads of a wave and stage: token rows; all
-    static_assert(MT % G == 0 && BM % 32 == 0 && D >= 2, "whole steps, whole pieces of 8 rows per wave");
+    constexpr int BM = Tile::BM, BN = Tile::BN, G = MT < 4 ? MT : 4, H = MT / G;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     v2i *lut = reinterpret_cast<v2i *>(lds + Tile::LUT_OFF);
 
@@ -795,47 +788,23 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
 
-    const char *abase = A + (size_t)m0 * Kbytes, *wbase = Wp + (size_t)(n0 + 16 * NTW * wave) * Kbytes;
-    unsigned offa[NLDA];
+    unsigned offa[MT / 2];
 #pragma unroll
-    for (int j = 0; j < NLDA; j++) {
+    for (int j = 0; j < MT / 2; j++) {
         const int srow = 8 * (wave + 4 * j) + (lane >> 3);
         offa[j] = (unsigned)min(srow, M - 1 - m0) * (unsigned)Kbytes + (((lane & 7) ^ swz<128>(srow)) << 4);
     }
-    const unsigned offw = 16 * lane;
-    int fill = 0;                                                 // ring position of the next stage to request
-    auto issue_a = [&](int kt, int first, int last) {
-        const char *from = abase + (size_t)kt * 128;
-        asm volatile("" : "+s"(from));
+    const char *wbase[NTW];
 #pragma unroll
-        for (int j = first; j < last; j++) {
-            unsigned o = offa[j];
-            asm volatile("" : "+v"(o));                            // keeps the offset a 32-bit one: scalar base + vector offset
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + o),
-                                             (__attribute__((address_space(3))) void *)(lds + fill + (wave + 4 * j) * 1024), 16, 0, 0);
-        }
-        if (last == NLDA) fill = fill + SLOT == RING ? 0 : fill + SLOT;
-    };
-    // (written out so that the compiler does not wait for them: step() does, and ties the registers to its wait)
-    v4i w[D][2][NTW];
-    auto load_w = [&](int kt, int ks, v4i (&d)[NTW]) {
+    for (int t = 0; t < NTW; t++) wbase[t] = Wp + (size_t)(n0 + 16 * (NTW * wave + t)) * Kbytes;
+    v4i acc[NTW][MT];
 #pragma unroll
-        for (int t = 0; t < NTW; t++)
-            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(d[t]) : "v"(offw), "s"(wbase + (size_t)(16 * t) * Kbytes + (size_t)(2 * kt + ks) * 1024));
-    };
-    const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
-    unsigned addr[2];
+    for (int t = 0; t < NTW; t++)
 #pragma unroll
-    for (int ks = 0; ks < 2; ks++) addr[ks] = lds_base + r * 128 + (((4 * ks + q) ^ swz<128>(r)) << 4);
-
-    const int KT = Kbytes / 128;                                  // a multiple of D (the launcher checks)
+        for (int i = 0; i < MT; i++) acc[t][i] = v4i{0, 0, 0, 0};
     v4f mm[NTW], bb[NTW];
-#pragma unroll
-    for (int s = 0; s < D; s++) {
-        issue_a(s, 0, NLDA);
-        load_w(s, 0, w[s][0]);
-        load_w(s, 1, w[s][1]);
-        if (s == 0) {
+    stream_tile_loop<MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, Kbytes / 128, lds, wave, lane,
+        [&]() {
             epi.load_lut_direct(lut, wave, 4, lane);
 #pragma unroll
             for (int t = 0; t < NTW; t++) {
@@ -843,72 +812,8 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
                 mm[t] = *reinterpret_cast<const v4f *>(epi.m + n);
                 bb[t] = epi.offsets() ? *reinterpret_cast<const v4f *>(epi.offsets() + n) : v4f{0.f, 0.f, 0.f, 0.f};
             }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-
-    v4i acc[NTW][MT];
-#pragma unroll
-    for (int t = 0; t < NTW; t++)
-#pragma unroll
-        for (int i = 0; i < MT; i++) acc[t][i] = v4i{0, 0, 0, 0};
-    v4i fa[2][G];
-    int slot = 0;
-    auto fetch = [&](auto idx_tag, v4i (&f)[G]) {
-        constexpr int OFF = (decltype(idx_tag)::value % H) * G * 2048;
-        lds_read_frags<2048>(addr[decltype(idx_tag)::value / H] + slot + OFF, f, std::make_integer_sequence<int, G>());
-    };
-    constexpr std::integral_constant<int, 0> c0;
-    constexpr std::integral_constant<int, 1> c1;
-    constexpr std::integral_constant<int, 2> c2;
-    constexpr std::integral_constant<int, 3> c3;
-    // One step multiplies G token tiles by the wave's channels over 64 bytes of K, with the token fragments of the step after it on
-    // their way from LDS.  The loads of the stage D further on are dealt out over the steps (a burst of them would hold the wave up
-    // at its issue, with the matrix cores idle): token rows in each, weights into the registers that the step before has read last.
-    // LEFT: stages after this one, D where there are that many or more (copies of the code instead of tests: the waits are constants).
-    auto step = [&](auto left_tag, auto b_tag, auto idx_tag, int kt) {
-        constexpr int LEFT = decltype(left_tag)::value, B = decltype(b_tag)::value, IDX = decltype(idx_tag)::value, ks = IDX / H, h = IDX % H;
-        constexpr bool MORE = LEFT == D;
-        if constexpr (IDX == H) {                                 // the second half of this stage's weights has landed
-            wait_vm<MORE ? (D - 1) * PER + NLDA * H / STEPS : LEFT * PER>();
-            tie(w[B][1], std::make_integer_sequence<int, NTW>());
-        }
-        if constexpr (MORE) {
-            issue_a(kt + D, NLDA * IDX / STEPS, NLDA * (IDX + 1) / STEPS);
-            if constexpr (IDX == H) load_w(kt + D, 0, w[B][0]);
-        }
-        if constexpr (IDX + 1 < STEPS) {
-            fetch(std::integral_constant<int, IDX + 1>(), fa[(IDX + 1) & 1]);
-            wait_lds_reads<G>();
-        } else if constexpr (LEFT > 0) {                          // so have the next stage's token rows and the first half of its weights
-            wait_vm_and_barrier<MORE ? (D - 1) * PER : NTW + (LEFT - 1) * PER>();
-            slot = slot + SLOT == RING ? 0 : slot + SLOT;
-            fetch(c0, fa[0]);
-        } else {
-            wait_lds_reads<0>();
-        }
-        tie(fa[IDX & 1], std::make_integer_sequence<int, G>());
-        if constexpr (IDX == 0) tie(w[B][0], std::make_integer_sequence<int, NTW>());
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < NTW; t++)
-#pragma unroll
-            for (int i = 0; i < G; i++)
-                acc[t][G * h + i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[B][ks][t], fa[IDX & 1][i], acc[t][G * h + i], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (MORE && IDX + 1 == STEPS) load_w(kt + D, 1, w[B][1]);
-    };
-    auto stage = [&](auto left_tag, auto b_tag, int kt) {
-        step(left_tag, b_tag, c0, kt);
-        step(left_tag, b_tag, c1, kt);
-        if constexpr (H == 2) { step(left_tag, b_tag, c2, kt); step(left_tag, b_tag, c3, kt); }
-    };
-    wait_vm_and_barrier<NTW + (D - 1) * PER>();
-    fetch(c0, fa[0]);
-    const auto all = std::make_integer_sequence<int, D>();
-    for (int kt = 0; kt + D < KT; kt += D) each_index([&](auto b) { stage(std::integral_constant<int, D>(), b, kt + b); }, all);
-    each_index([&](auto b) { stage(std::integral_constant<int, D - 1 - decltype(b)::value>(), b, 0); }, all);
-    __syncthreads();                                              // the ring is idle from here on
+        },
+        [&](int t, int i, const v4i &w, const v4i &f) { acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, f, acc[t][i], 0, 0, 0); });
 
     constexpr int STRIDE = Tile::STRIDE, CHUNKS = BN / 16, PASSES = (BM * CHUNKS + 255) / 256;
     constexpr bool EVEN = BM * CHUNKS % 256 == 0;

@@ -194,6 +194,10 @@ hipError_t launch_attention_i8(const int8_t *qkv, const int *cu, int B, int max_
 hipError_t launch_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int *cu, int B,
                                    int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
                                    hipStream_t st, const Timing *tm);
+// on weights in the order of launch_pack_weight; hipErrorNotSupported: more than 128 tokens, or H is no multiple of 256
+hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const float *m, const float *b, const int *cu, int B,
+                                          int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
+                                          hipStream_t st, const Timing *tm);
 hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const float *bias, const int *cu, int B, int max_len,
                                     int H, float scale, bool small_ring, __half *ctx, hipStream_t st, const Timing *tm);
 hipError_t launch_code_histogram(const int8_t *codes, size_t n, unsigned long long *hist, hipStream_t st);

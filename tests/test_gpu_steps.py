@@ -410,6 +410,29 @@ def test_qkv_gemm_and_attention_in_one_kernel_bit_exact(P, lens, heads, offsets)
     assert np.array_equal(no_bias, oracle.attention_i8(oracle.epilogue_requant(oracle.gemm_i8_i32(x, w), m, np.zeros(3 * H, np.float32)), cu, heads, *sc))
 
 
+@pytest.mark.parametrize("lens,heads", [([128, 113, 112, 64, 16, 1], 4), ([128, 128], 12), ([33, 97, 17], 16)])
+@pytest.mark.parametrize("unsigned", [False, True])
+def test_qkv_attention_on_packed_weights_gives_the_same_codes(P, lens, heads, unsigned):
+    """Sequences on both sides of a token tile's edge and of the copy of the loop that tests for dead tiles; four, six and eight stages
+    of K pairs; with and without offsets in the epilogue, with explicit sequence offsets and without."""
+    rng = np.random.default_rng(heads + len(lens))
+    cu = _cu(lens)
+    H, T = heads * 64, int(cu[-1])
+    x, w = rng.integers(-127, 128, (T, H), dtype=np.int8), rng.integers(-127, 128, (3 * H, H), dtype=np.int8)
+    m = (26.0 / (73.3 * 73.3 * np.sqrt(H)) * (0.8 + 0.4 * rng.random(3 * H))).astype(np.float32)
+    b = (rng.standard_normal(3 * H) * 3).astype(np.float32)
+    sc = (0.0209, 0.0249, 0.021, 0.0003 * (0.5 if unsigned else 1.0), 0.0021)
+    packed = P.pack_weight_i8(dev(w))
+    acc = oracle.gemm_i8_i32(x, w)
+    for offsets in (b, None):
+        qkv = oracle.epilogue_requant(acc, m, np.zeros_like(m) if offsets is None else b)
+        want = oracle.attention_i8(qkv, cu, heads, *sc, p_unsigned=unsigned)
+        assert np.abs(want).max() > 20
+        run = lambda c: host(P.qkv_attention_i8_packed(dev(x), packed, dev(m), None if offsets is None else dev(b), c, max(lens), heads, *sc, p_unsigned=unsigned))
+        assert np.array_equal(run(dev(cu)), want)
+        if len(set(lens)) == 1: assert np.array_equal(run(None), want)
+
+
 @pytest.mark.parametrize("M,N,K", [(130, 384, 384), (65, 192 * 2, 640)])
 def test_tables_that_arrive_with_the_last_stage_of_an_odd_number(P, M, N, K):
     """128 x 192 tiles (configuration 6): the epilogue's tables take the ring stage that the last one but one leaves free,
