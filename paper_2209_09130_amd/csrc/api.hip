@@ -241,7 +241,7 @@ int check_forward_args(const samp_encoder_t *enc, const void *hidden, int B, int
 
 // The kernel sequence.  calib: FP16-only run that also records each tensor's absmax.
 int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int B, int S, void *out, void *workspace,
-        hipStream_t st, bool calib, bool beside)
+        hipStream_t st, bool calib, bool beside, bool prefetch)
 {
     const samp_config_t &c = enc->cfg;
     const int H = c.hidden, F = c.ffn, heads = c.heads, Lc = c.layers;
@@ -284,6 +284,13 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     void *ybuf[2] = {w.y, w.x};                     // layer outputs alternate; w.x is free after layer 0's LN-1
     int yi = 0;
 
+    // From 256 rows to 3.2 million values the LayerNorm steps ask for the weights that come next (the first of several groups does it for
+    // all).  Below, a layer is over before they arrive (forward without / with it: 19 rows 326 / 331 us); above, a GEMM lasts long enough to
+    // fetch its own (width 768, two groups of 4096 rows 1286 / 1254, of 8192 rows 2014 / 2040; width 1024, two of 4096 rows 3783 / 3798).
+    const bool fetch_ahead = prefetch && Tmax >= 256 && (long)Tmax * H <= 3200000;
+    auto ahead = [&](const void *W, const int8_t *Wp, int N, int K, bool i8) {
+        return Prefetch{i8 && Wp && !gemm_i8_reads_rows(rows, N) ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};
+    };
     for (int l = 0; l < Lc; l++) {
         const Layer &Y = enc->L[l];
         const bool mha8 = Y.mode & 1, ffn8 = Y.mode & 2, last = (l == Lc - 1);
@@ -350,7 +357,8 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
         {   // bias + residual + LayerNorm (+ quantise for an INT8 FFN); residual = the block's own input tensor
             AddLnArgs a{w.ao, mha8, Y.s.attn_out, Y.b_o, x, mha8, Y.s.x, Y.g1, Y.be1, c.ln_eps,
                         w.h1, ffn8, Y.s.ffn_in, nullptr, am ? am + 7 : nullptr, rows, H};
-            HIP_TRY(launch_add_ln(a, st, timing(enc, SAMP_PROF_LN1)));
+            const Prefetch next[2] = {ahead(Y.w_f1, Y.p_f1, F, H, ffn8), ahead(Y.w_f2, Y.p_f2, H, F, ffn8)};
+            HIP_TRY(launch_add_ln(a, fetch_ahead ? next : nullptr, st, timing(enc, SAMP_PROF_LN1)));
         }
         if (ffn8) {
             HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, Y.p_f1, w.f1, Y.m_f1, Y.b_f1,
@@ -369,7 +377,9 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             void *dst = last ? (calib ? ybuf[yi] : out) : ybuf[yi];
             AddLnArgs a{w.f2, ffn8, Y.s.ffn_out, Y.b_f2, w.h1, ffn8, Y.s.ffn_in, Y.g2, Y.be2, c.ln_eps,
                         dst, next8, next8 ? enc->L[l + 1].s.x : 1.0f, (last && !calib) ? row_map : nullptr, nullptr, rows, H};
-            HIP_TRY(launch_add_ln(a, st, timing(enc, SAMP_PROF_LN2)));
+            const Layer &X = enc->L[last ? l : l + 1];
+            const Prefetch next[2] = {ahead(X.w_qkv, X.p_qkv, 3 * H, H, X.mode & 1), ahead(X.w_o, X.p_o, H, H, X.mode & 1)};
+            HIP_TRY(launch_add_ln(a, fetch_ahead && !last ? next : nullptr, st, timing(enc, SAMP_PROF_LN2)));
             x = dst;
             yi ^= 1;
         }
@@ -553,7 +563,7 @@ static int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids
                          void *out, void *workspace, hipStream_t st)
 {
     const int G = choose_groups(enc, B, S);
-    if (G == 1) return run(enc, hidden, ids, mask, B, S, out, workspace, st, false, false);
+    if (G == 1) return run(enc, hidden, ids, mask, B, S, out, workspace, st, false, false, true);
     if (!enc->streams_ready) {
         for (int i = 0; i < MAX_GROUPS - 1; i++) {
             HIP_TRY(hipStreamCreateWithFlags(&enc->side[i], hipStreamNonBlocking));
@@ -579,7 +589,7 @@ static int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids
         if (ids) part = Ids{ids->emb, ids->token_ids + (size_t)b0 * S, ids->segment_ids ? ids->segment_ids + (size_t)b0 * S : nullptr};
         const int rc = run(enc, ids ? nullptr : (const __half *)hidden + b0 * seq_elems, ids ? &part : nullptr,
                            mask ? mask + (size_t)b0 * S : nullptr, nb, S,
-                           (__half *)out + b0 * seq_elems, (char *)workspace + g * piece, gs, false, true);
+                           (__half *)out + b0 * seq_elems, (char *)workspace + g * piece, gs, false, true, g == 0);
         if (rc != SAMP_OK) return rc;
         if (g > 0 && !serial) {
             HIP_TRY(hipEventRecord(enc->join[g - 1], gs));
@@ -621,7 +631,7 @@ int samp_encoder_forward_noalloc(samp_encoder_t *enc, const void *hidden, const 
     void *ws = nullptr;
     if (int rc = noalloc_scratch(&ws)) return rc;
     // one group, plain launches on the caller's stream: no side streams, events or graphs are created on this path
-    return run(enc, hidden, nullptr, mask, B, S, out, ws, static_cast<hipStream_t>(stream), false, false);
+    return run(enc, hidden, nullptr, mask, B, S, out, ws, static_cast<hipStream_t>(stream), false, false, true);
 }
 
 static int check_embedding(const samp_embedding_t *e, int H, int S)
@@ -729,7 +739,7 @@ int samp_encoder_calibrate(samp_encoder_t *enc, const void *hidden, const int32_
     if (!aligned(hidden, 16)) return fail(SAMP_ERR_ARG, "hidden must be 16-byte aligned");
     if (!enc->all_fp16) return fail(SAMP_ERR_ARG, "calibration needs an encoder whose layers are all SAMP_FP16");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (int rc = run(enc, hidden, nullptr, mask, B, S, nullptr, workspace, st, true, false)) return rc;
+    if (int rc = run(enc, hidden, nullptr, mask, B, S, nullptr, workspace, st, true, false, false)) return rc;
     const int n = enc->cfg.layers * 10;
     std::vector<float> am(n);
     Workspace w = carve(enc->cfg, B, S, workspace);
@@ -993,7 +1003,7 @@ int samp_add_ln(const void *in, int32_t in_i8, float s_in, const float *bias, co
         return fail(SAMP_ERR_SCALE, "a step of an int8 operand is not finite and positive");
     AddLnArgs a{in, in_i8 != 0, s_in, bias, res, res_i8 != 0, s_res, gamma, beta, eps, out, out_i8 != 0, s_out,
                 nullptr, nullptr, Rows{M, nullptr}, H};
-    HIP_TRY(launch_add_ln(a, (hipStream_t)stream, nullptr));
+    HIP_TRY(launch_add_ln(a, nullptr, (hipStream_t)stream, nullptr));
     return SAMP_OK;
 }
 

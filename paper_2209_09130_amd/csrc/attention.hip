@@ -761,6 +761,8 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
 // each of the three parts, so a lane's query and key results are four channels of one token per 16 x 16 tile and its value results, formed
 // with the operands the other way round, four tokens of one channel.  Its multipliers and offsets fit 18 registers.  50 KB of LDS for two stages
 // of token rows (the row-major kernel: 80 KB).  Every value is formed by the same operations as there.
+// Forwards, row-major / packed: BERT-base 32 x 128 Fully-Quant 848 / 822 us, 64 x 16..128 with six Fully-Quant layers 1404 / 1392; three stages
+// in flight instead of two: the same.
 template <bool PU, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__restrict__ Wp, const float *__restrict__ m_tab,

@@ -1450,12 +1450,12 @@ std::atomic<int> gemm_config_override{-1};                    // tuning aid: for
 // split / packed weights: 768 x 768 at 128 rows 2.95 / 3.4, at 256 3.4 / 3.6, at 427 3.8 / 3.5; 768 x 3072 at 256 rows 5.1 / 6.3, at 512 6.25 / 6.25;
 // 1024 x 4096 at 256 rows 5.9 / 6.3, at 427 7.25 / 6.4; 1024 x 1024 at 256 rows 3.9 / 4.3, at 768 5.5 / 5.2; 2304 x 768 at 32 rows 3.25 / 3.4, at 64
 // 3.7 / 3.5; 3072 x 768 at 32 rows 3.7 / 3.8, at 64 4.05 / 3.8; 4096 x 1024 at 32 rows 4.0 / 4.1, at 64 4.6 / 4.15)
-static bool k_split_is_faster(Rows rows, int N) { return (long)rows.host_rows * N <= (N <= 1024 ? 300000 : 128000); }
+bool gemm_i8_reads_rows(Rows rows, int N) { return (long)rows.host_rows * N <= (N <= 1024 ? 300000 : 128000); }
 
 hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, const int8_t *Wp, void *out, const float *m, const float *b,
                           float inv_s_out, const GeluTable *gt, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
 {
-    if (Wp && gemm_config_override.load(std::memory_order_relaxed) < 0 && !k_split_is_faster(rows, N)) {
+    if (Wp && gemm_config_override.load(std::memory_order_relaxed) < 0 && !gemm_i8_reads_rows(rows, N)) {
         const hipError_t e = launch_gemm_i8_packed(epi, A, Wp, out, m, b, gt, rows, N, K, -1, st, tm);
         if (e != hipErrorNotSupported) return e;
     }

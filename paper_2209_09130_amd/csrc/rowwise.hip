@@ -3,6 +3,8 @@
 // and epilogue-table folding at create time, and the absmax taps of the min-max calibration.
 // All of them move each byte once with coalesced 4..16-byte accesses; reductions stay inside a wave.
 #include "samp_common.h"
+
+#include <type_traits>
 #include <hip/hip_ext.h>
 #include <algorithm>
 
@@ -127,9 +129,41 @@ __device__ __forceinline__ void ln_finish(const float (&z)[NJ][16], double sum, 
     }
 }
 
-template <int NJ, bool IN_I8, bool RES_I8, bool OUT_I8, bool WHOLE>
-__global__ __launch_bounds__(16 * LN_ROWS) void add_ln_kernel(AddLnArgs a)
+// The weights of a whole model come from beyond the memory-side cache when another model (or much else) ran in between, and then the
+// first loads of every GEMM take one to two microseconds longer.  The LayerNorm step leaves most of the memory system idle: the last
+// PREFETCH_BLOCKS blocks of its grid (a multiple of 8) read the weights of the GEMMs that come next, XCD x the x-th eighth of them, so that
+// these find them in the memory-side cache.  True if this is such a block.  Forwards of three models in turn, without / with, us: BERT-base
+// Fully-Quant 8 x 128 487 / 454, 16 x 128 603 / 576, 32 x 128 798 / 773, 64 x 128 1286 / 1254, 8 x 512 1094 / 1064; Quant-FFN-Only 32 x 128
+// 935 / 912; FP16 16 x 128 977 / 935, 64 x 128 2270 / 2200, 32 x 128 1320 / 1341.  (Every XCD reading all of them into its own L2: the
+// LayerNorm step gets too long, 7 x 61 424 / 449.)
+// (Kernels of their own: a test in every block costs a launch of few rows 1 %.)
+constexpr int PREFETCH_BLOCKS = 256;
+struct AddLnPrefetchArgs : AddLnArgs { Prefetch prefetch[2]; };
+__device__ __forceinline__ bool prefetch_block(const AddLnArgs &) { return false; }
+__device__ __forceinline__ bool prefetch_block(const AddLnPrefetchArgs &a)
 {
+    const int first = (int)gridDim.x - PREFETCH_BLOCKS, block = (int)blockIdx.x;
+    if (block < first) return false;
+    const int xcd = block & 7, index = (block - first) >> 3, count = PREFETCH_BLOCKS >> 3;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const unsigned eighth = a.prefetch[k].bytes >> 7, step = count * blockDim.x;            // in units of 16 bytes
+        const v4i *from = reinterpret_cast<const v4i *>(a.prefetch[k].from) + (size_t)xcd * eighth;
+        for (unsigned i = index * blockDim.x + threadIdx.x; i < eighth; i += 8 * step) {
+            v4i d[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) d[u] = from[min(i + u * step, eighth - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; u++) asm volatile("" ::"v"(d[u]));
+        }
+    }
+    return true;
+}
+
+template <int NJ, bool IN_I8, bool RES_I8, bool OUT_I8, bool WHOLE, class Args>
+__global__ __launch_bounds__(16 * LN_ROWS) void add_ln_kernel(Args a)
+{
+    if (prefetch_block(a)) return;
     const int M = a.rows.dev_rows ? *a.rows.dev_rows : a.rows.host_rows;
     const int nblk = (M + LN_ROWS - 1) / LN_ROWS;
     if ((int)blockIdx.x >= nblk) return;
@@ -230,9 +264,10 @@ __device__ __forceinline__ void ln_finish_wave(const float (&z)[CPL], double sum
     }
 }
 
-template <int CPL, bool IN_I8, bool RES_I8, bool OUT_I8>
-__global__ __launch_bounds__(256) void add_ln_wave_kernel(AddLnArgs a)
+template <int CPL, bool IN_I8, bool RES_I8, bool OUT_I8, class Args>
+__global__ __launch_bounds__(256) void add_ln_wave_kernel(Args a)
 {
+    if (prefetch_block(a)) return;
     constexpr int H = 64 * CPL;
     const int M = a.rows.dev_rows ? *a.rows.dev_rows : a.rows.host_rows;
     const int nblk = (M + 3) / 4;
@@ -257,8 +292,8 @@ __global__ __launch_bounds__(256) void add_ln_wave_kernel(AddLnArgs a)
     ln_finish_wave<CPL, OUT_I8>(z, sum, gamma, beta, a.eps, a.s_out, a.out, (size_t)out_row * H + c);
 }
 
-template <int NJ>
-hipError_t launch_add_ln_nj(const AddLnArgs &a, hipStream_t st, const Timing *tm)
+template <int NJ, class Args>
+hipError_t launch_add_ln_nj(const Args &a, hipStream_t st, const Timing *tm)
 {
     // one wave per row at widths of 256, 512, 768 and 1024 (calibration, which also wants the absmax of the output, keeps the other
     // form), as long as a launch lasts no longer than a row's chain: forward of 6 layers, one batch group, us, four rows / one row per
@@ -280,12 +315,12 @@ hipError_t launch_add_ln_nj(const AddLnArgs &a, hipStream_t st, const Timing *tm
                       (a.rows.beside ? (long)a.rows.host_rows * a.H / (a.rows.dev_rows ? 2 : 1) < ln_wave_max_values_beside(256 * NJ)
                                      : a.rows.host_rows < LN_WAVE_MAX_ROWS);
     const int per_block = wave ? 4 : LN_ROWS;
-    dim3 grid((a.rows.host_rows + per_block - 1) / per_block), block(wave ? 256 : 16 * LN_ROWS);
+    dim3 grid((a.rows.host_rows + per_block - 1) / per_block + (std::is_same<Args, AddLnPrefetchArgs>::value ? PREFETCH_BLOCKS : 0)), block(wave ? 256 : 16 * LN_ROWS);
 #define SAMP_LN_CASE(I, R, O)                                                                              \
     if (a.in_i8 == I && a.res_i8 == R && a.out_i8 == O) {                                                  \
-        if (wave) launch_kernel(add_ln_wave_kernel<WAVE ? 4 * NJ : 4, I, R, O>, grid, block, 0, st, tm, a); \
-        else if (WHOLE_WIDTHS && a.H == 256 * NJ) launch_kernel(add_ln_kernel<NJ, I, R, O, WHOLE_WIDTHS>, grid, block, 0, st, tm, a); \
-        else launch_kernel(add_ln_kernel<NJ, I, R, O, false>, grid, block, 0, st, tm, a);                  \
+        if (wave) launch_kernel(add_ln_wave_kernel<WAVE ? 4 * NJ : 4, I, R, O, Args>, grid, block, 0, st, tm, a); \
+        else if (WHOLE_WIDTHS && a.H == 256 * NJ) launch_kernel(add_ln_kernel<NJ, I, R, O, WHOLE_WIDTHS, Args>, grid, block, 0, st, tm, a); \
+        else launch_kernel(add_ln_kernel<NJ, I, R, O, false, Args>, grid, block, 0, st, tm, a);                  \
         return hipGetLastError();                                                                          \
     }
     SAMP_LN_CASE(true, true, true) SAMP_LN_CASE(true, true, false) SAMP_LN_CASE(false, false, true)
@@ -583,9 +618,21 @@ __global__ void fill_f32_kernel(float *p, int n, float v)
 
 }  // namespace
 
-hipError_t launch_add_ln(const AddLnArgs &a, hipStream_t st, const Timing *tm)
+hipError_t launch_add_ln(const AddLnArgs &a, const Prefetch *prefetch, hipStream_t st, const Timing *tm)
 {
     const int nj = (a.H + 255) / 256;
+    if (prefetch && nj <= 4) {
+        AddLnPrefetchArgs p;
+        static_cast<AddLnArgs &>(p) = a;
+        p.prefetch[0] = prefetch[0];
+        p.prefetch[1] = prefetch[1];
+        switch (nj) {
+        case 1: return launch_add_ln_nj<1>(p, st, tm);
+        case 2: return launch_add_ln_nj<2>(p, st, tm);
+        case 3: return launch_add_ln_nj<3>(p, st, tm);
+        case 4: return launch_add_ln_nj<4>(p, st, tm);
+        }
+    }
     switch (nj) {
     case 1: return launch_add_ln_nj<1>(a, st, tm);
     case 2: return launch_add_ln_nj<2>(a, st, tm);

@@ -179,6 +179,8 @@ extern std::atomic<int> gemm_config_override;                           // < 0: 
 hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, const int8_t *Wp, void *out, const float *m, const float *b,
                           float inv_s_out, const GeluTable *gelu_table, Rows rows, int N, int K, hipStream_t st,
                           const Timing *tm);
+// whether launch_gemm_i8 reads W although it is given Wp
+bool gemm_i8_reads_rows(Rows rows, int N);
 // on packed weights alone; tile: -1 by size, or a number of stream_tile's list (hipErrorInvalidValue where it does not divide N).
 // hipErrorNotSupported: K is no multiple of 256, N none of 64, or the epilogue is another
 hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t *Wp, void *out, const float *m, const float *b,
@@ -206,6 +208,8 @@ hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int 
 hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max_len, int H, int heads, float scale,
                                 __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm);
 
+// Weights that the next kernels will read: extra blocks of the launch ask for them (prefetch_block)
+struct Prefetch { const void *from; unsigned bytes; };
 struct AddLnArgs {
     const void *in; bool in_i8; float s_in; const float *bias;
     const void *res; bool res_i8; float s_res;
@@ -215,7 +219,8 @@ struct AddLnArgs {
     float *absmax_out;                                     // optional: running absmax of y (calibration)
     Rows rows; int H;
 };
-hipError_t launch_add_ln(const AddLnArgs &a, hipStream_t st, const Timing *tm);
+// prefetch: null, or two ranges (of 0 bytes or more); widths above 1024 leave it out
+hipError_t launch_add_ln(const AddLnArgs &a, const Prefetch *prefetch, hipStream_t st, const Timing *tm);
 
 struct EmbedArgs {
     const int *token_ids, *segment_ids;                    // [B*S]; segment_ids may be null (segment 0)
