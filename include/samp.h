@@ -327,6 +327,13 @@ SAMP_API int samp_gemm_i8_gelu_quant_packed(const int8_t *A, const int8_t *Wp, c
  * gelu != 0 applies GELU.  N % 128 == 0, K % 32 == 0.                                             */
 SAMP_API int samp_gemm_f16(const uint16_t *A, const uint16_t *W, const float *bias, int32_t gelu, uint16_t *out,
                            int32_t M, int32_t N, int32_t K, void *stream);
+/* FP16 weights in the order in which the encoder's FP16 GEMMs read them (1 KB blocks of 32 rows x 32 bytes, row blocks outermost;
+ * inside a block two 16-byte columns of 32 rows each; N % 32 == 0, K % 16 == 0), and those GEMMs on their own: K % 128 == 0.
+ * tile: -1 by size, or 0..3 for tiles of 32 x 128, 64 x 128, 64 x 256, 128 x 256 rows x channels
+ * (SAMP_ERR_SHAPE if its width does not divide N); the results do not depend on it and are samp_gemm_f16's. */
+SAMP_API int samp_pack_weight_f16(const uint16_t *W, int32_t N, int32_t K, uint16_t *Wp, void *stream);
+SAMP_API int samp_gemm_f16_packed(const uint16_t *A, const uint16_t *Wp, const float *bias, int32_t gelu, uint16_t *out,
+                                  int32_t M, int32_t N, int32_t K, int32_t tile, void *stream);
 
 /* Softmax attention over packed rows.  qkv: dev [T,3H] (int8 or fp16), columns [0,H) Q, [H,2H) K,
  * [2H,3H) V.  cu_seqlens: dev int32 [B+1], sequence b owns rows cu[b]..cu[b+1); max_len >= every

@@ -313,6 +313,23 @@ def gemm_f16(A, W, bias, gelu: bool) -> torch.Tensor:
     return out
 
 
+def pack_weight_f16(W) -> torch.Tensor:
+    """The fp16 matrix [N, K] in the order in which the encoder's FP16 GEMMs read it (samp_pack_weight_f16)."""
+    N, K = W.shape
+    out = torch.empty(N * K, dtype=torch.float16, device=W.device)
+    _check(lib().samp_pack_weight_f16(_dp(W), N, K, _dp(out), _stream()))
+    return out
+
+
+def gemm_f16_packed(A, Wp, bias, gelu: bool, tile: int = -1) -> torch.Tensor:
+    """gemm_f16 on packed weights; tile: -1 by size, or one of the tiles that samp.h lists."""
+    M, K = A.shape
+    N = Wp.numel() // K
+    out = torch.empty((M, N), dtype=torch.float16, device=A.device)
+    _check(lib().samp_gemm_f16_packed(_dp(A), _dp(Wp), _dp(bias), int(gelu), _dp(out), M, N, K, tile, _stream()))
+    return out
+
+
 def _batch_of(cu, T: int, max_len: int) -> int:
     if cu is not None:
         return cu.numel() - 1

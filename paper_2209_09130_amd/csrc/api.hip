@@ -45,7 +45,7 @@ struct Layer {
     samp_layer_scales_t s;
     // INT8 blocks: int8 weights and folded epilogue tables; FP16 blocks: fp16 weights
     void *w_qkv, *w_o, *w_f1, *w_f2;
-    int8_t *p_qkv, *p_o, *p_f1, *p_f2;              // the int8 weights once more, packed (nullptr where no kernel reads them so)
+    void *p_qkv, *p_o, *p_f1, *p_f2;                // the same weights packed (nullptr where no kernel reads them so)
     float *m_qkv, *bq_qkv, *m_o, *m_f1, *m_f2;
     float *b_qkv, *b_o, *b_f1, *b_f2, *g1, *be1, *g2, *be2;
     float m_sc, inv_sp, m_ctx;                      // attention multipliers of an INT8 MHA block
@@ -86,8 +86,8 @@ int check_config(const samp_config_t *c)
     return SAMP_OK;
 }
 
-// INT8 matrices of rows that are whole pairs of 128-byte stages are kept packed too
-bool packs(size_t K) { return K % 256 == 0; }
+// matrices of rows that are whole pairs of 128-byte stages are kept packed too
+bool packs(size_t Kbytes) { return Kbytes % 256 == 0; }
 
 size_t layer_arena_bytes(const samp_config_t &c, int mode)
 {
@@ -105,10 +105,11 @@ size_t layer_arena_bytes(const samp_config_t &c, int mode)
 size_t layer_packed_bytes(const samp_config_t &c, int mode)
 {
     const size_t H = c.hidden, F = c.ffn;
+    const size_t e_mha = (mode & 1) ? 1 : 2, e_ffn = (mode & 2) ? 1 : 2;
     size_t n = 0;
-    if ((mode & 1) && packs(H)) n += up(3 * H * H) + up(H * H);
-    if ((mode & 2) && packs(H)) n += up(F * H);
-    if ((mode & 2) && packs(F)) n += up(H * F);
+    if (packs(H * e_mha)) n += up(3 * H * H * e_mha) + up(H * H * e_mha);
+    if (packs(H * e_ffn)) n += up(F * H * e_ffn);
+    if (packs(F * e_ffn)) n += up(H * F * e_ffn);
     return n;
 }
 
@@ -288,8 +289,9 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     // all).  Below, a layer is over before they arrive (forward without / with it: 19 rows 326 / 331 us); above, a GEMM lasts long enough to
     // fetch its own (width 768, two groups of 4096 rows 1286 / 1254, of 8192 rows 2014 / 2040; width 1024, two of 4096 rows 3783 / 3798).
     const bool fetch_ahead = prefetch && Tmax >= 256 && (long)Tmax * H <= 3200000;
-    auto ahead = [&](const void *W, const int8_t *Wp, int N, int K, bool i8) {
-        return Prefetch{i8 && Wp && !gemm_i8_reads_rows(rows, N) ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};
+    auto ahead = [&](const void *W, const void *Wp, int N, int K, bool i8) {
+        const bool packed = Wp && !(i8 ? gemm_i8_reads_rows(rows, N) : gemm_f16_reads_rows(rows, N, K));
+        return Prefetch{packed ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};
     };
     for (int l = 0; l < Lc; l++) {
         const Layer &Y = enc->L[l];
@@ -308,14 +310,14 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                 const bool p_unsigned = (Y.mode & SAMP_P_UNSIGNED) != 0;
                 const Timing *tm = timing(enc, SAMP_PROF_QKV_ATTN);
                 hipError_t e = !Y.p_qkv ? hipErrorNotSupported
-                                        : launch_qkv_attention_i8_packed((const int8_t *)x, Y.p_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
+                                        : launch_qkv_attention_i8_packed((const int8_t *)x, (const int8_t *)Y.p_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
                                                                          Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
                 if (e == hipErrorNotSupported)
                     e = launch_qkv_attention_i8((const int8_t *)x, (const int8_t *)Y.w_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
                                                 Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
                 HIP_TRY(e);
             } else {
-                HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, Y.p_qkv, w.qkv, Y.m_qkv, Y.bq_qkv, 0.f,
+                HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, (const int8_t *)Y.p_qkv, w.qkv, Y.m_qkv, Y.bq_qkv, 0.f,
                                        nullptr, rows, 3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
                 if (Y.mode & SAMP_P_FP16)
                     HIP_TRY(launch_attention_i8_p16((const int8_t *)w.qkv, cu, B, S, H, heads, Y.m_sc, Y.m_ctx, (int8_t *)w.ctx,
@@ -325,7 +327,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                                 (Y.mode & SAMP_P_UNSIGNED) != 0, (int8_t *)w.ctx, nullptr, st,
                                                 timing(enc, SAMP_PROF_ATTN)));
             }
-            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.ctx, (const int8_t *)Y.w_o, Y.p_o, w.ao, Y.m_o, nullptr, 0.f,
+            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.ctx, (const int8_t *)Y.w_o, (const int8_t *)Y.p_o, w.ao, Y.m_o, nullptr, 0.f,
                                    nullptr, rows, H, H, st, timing(enc, SAMP_PROF_ATTN_OUT)));
         } else {
             if (am) HIP_TRY(launch_absmax_f16((const __half *)x, rows, H, H, am + 0, st));
@@ -341,7 +343,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                 HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, cu, B, S, H, 0.125f, small_ring,
                                                  (__half *)w.ctx, st, timing(enc, SAMP_PROF_QKV_ATTN)));
             } else {
-                HIP_TRY(launch_gemm_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, false, (__half *)w.qkv, rows,
+                HIP_TRY(launch_gemm_f16((const __half *)x, (const __half *)Y.w_qkv, (const __half *)Y.p_qkv, Y.b_qkv, false, (__half *)w.qkv, rows,
                                         3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
                 if (am)
                     for (int part = 0; part < 3; part++)
@@ -350,7 +352,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                              am ? am + 4 : nullptr, st, timing(enc, SAMP_PROF_ATTN)));
             }
             if (am) HIP_TRY(launch_absmax_f16((const __half *)w.ctx, rows, H, H, am + 5, st));
-            HIP_TRY(launch_gemm_f16((const __half *)w.ctx, (const __half *)Y.w_o, nullptr, false, (__half *)w.ao, rows, H, H,
+            HIP_TRY(launch_gemm_f16((const __half *)w.ctx, (const __half *)Y.w_o, (const __half *)Y.p_o, nullptr, false, (__half *)w.ao, rows, H, H,
                                     st, timing(enc, SAMP_PROF_ATTN_OUT)));
             if (am) HIP_TRY(launch_absmax_f16((const __half *)w.ao, rows, H, H, am + 6, st));
         }
@@ -361,15 +363,15 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             HIP_TRY(launch_add_ln(a, fetch_ahead ? next : nullptr, st, timing(enc, SAMP_PROF_LN1)));
         }
         if (ffn8) {
-            HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, Y.p_f1, w.f1, Y.m_f1, Y.b_f1,
+            HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, (const int8_t *)Y.p_f1, w.f1, Y.m_f1, Y.b_f1,
                                    1.0f / Y.s.ffn_mid, &Y.gelu, rows, F, H, st, timing(enc, SAMP_PROF_FFN1)));
-            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.f1, (const int8_t *)Y.w_f2, Y.p_f2, w.f2, Y.m_f2, nullptr, 0.f,
+            HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.f1, (const int8_t *)Y.w_f2, (const int8_t *)Y.p_f2, w.f2, Y.m_f2, nullptr, 0.f,
                                    nullptr, rows, H, F, st, timing(enc, SAMP_PROF_FFN2)));
         } else {
-            HIP_TRY(launch_gemm_f16((const __half *)w.h1, (const __half *)Y.w_f1, Y.b_f1, true, (__half *)w.f1, rows, F, H,
+            HIP_TRY(launch_gemm_f16((const __half *)w.h1, (const __half *)Y.w_f1, (const __half *)Y.p_f1, Y.b_f1, true, (__half *)w.f1, rows, F, H,
                                     st, timing(enc, SAMP_PROF_FFN1)));
             if (am) HIP_TRY(launch_absmax_f16((const __half *)w.f1, rows, F, F, am + 8, st));
-            HIP_TRY(launch_gemm_f16((const __half *)w.f1, (const __half *)Y.w_f2, nullptr, false, (__half *)w.f2, rows, H, F,
+            HIP_TRY(launch_gemm_f16((const __half *)w.f1, (const __half *)Y.w_f2, (const __half *)Y.p_f2, nullptr, false, (__half *)w.f2, rows, H, F,
                                     st, timing(enc, SAMP_PROF_FFN2)));
             if (am) HIP_TRY(launch_absmax_f16((const __half *)w.f2, rows, H, H, am + 9, st));
         }
@@ -475,7 +477,7 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
             Y.m_o = cv.take<float>(H); Y.m_f1 = cv.take<float>(F); Y.m_f2 = cv.take<float>(H);
 
             // fp16 matrix -> either kept as fp16 or quantised per output channel into int8
-            auto matrix = [&](const uint16_t *src, size_t N, size_t K, bool q8, void **dst, int8_t **packed) -> int {
+            auto matrix = [&](const uint16_t *src, size_t N, size_t K, bool q8, void **dst, void **packed) -> int {
                 *packed = nullptr;
                 if (!q8) {
                     *dst = cv.take<__half>(N * K);
@@ -484,10 +486,11 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
                     *dst = cv.take<int8_t>(N * K);
                     HIP_TRY(hipMemcpyAsync(stage, src, N * K * 2, hipMemcpyHostToDevice, st));
                     HIP_TRY(launch_quantize_weight(stage, (int)N, (int)K, (int8_t *)*dst, s_w, st));
-                    if (packs(K)) {
-                        *packed = cvp.take<int8_t>(N * K);
-                        HIP_TRY(launch_pack_weight((const int8_t *)*dst, (int)N, (int)K, *packed, st));
-                    }
+                }
+                const size_t e = q8 ? 1 : 2;
+                if (packs(K * e)) {
+                    *packed = cvp.take<char>(N * K * e);
+                    HIP_TRY(launch_pack_weight(*dst, (int)N, (int)(K * e), !q8, *packed, st));
                 }
                 return SAMP_OK;
             };
@@ -848,7 +851,7 @@ int samp_pack_weight_i8(const int8_t *W, int32_t N, int32_t K, int8_t *Wp, void 
         return fail(SAMP_ERR_SHAPE, "packing needs N %% 16 == 0, K %% 64 == 0, N * K < 2^31 (N=%d K=%d)", N, K);
     if (!aligned(W, 16) || !aligned(Wp, 16)) return fail(SAMP_ERR_ARG, "matrices must be 16-byte aligned");
     if (W == Wp) return fail(SAMP_ERR_ARG, "a matrix cannot be packed in place");
-    HIP_TRY(launch_pack_weight(W, N, K, Wp, (hipStream_t)stream));
+    HIP_TRY(launch_pack_weight(W, N, K, false, Wp, (hipStream_t)stream));
     return SAMP_OK;
 }
 
@@ -899,8 +902,31 @@ int samp_gemm_f16(const uint16_t *A, const uint16_t *W, const float *bias, int32
                   int32_t K, void *stream)
 {
     if (int rc = check_gemm(A, W, out, M, N, K, 32)) return rc;
-    HIP_TRY(launch_gemm_f16((const __half *)A, (const __half *)W, bias, gelu != 0, (__half *)out, Rows{M, nullptr}, N, K,
+    HIP_TRY(launch_gemm_f16((const __half *)A, (const __half *)W, nullptr, bias, gelu != 0, (__half *)out, Rows{M, nullptr}, N, K,
                             (hipStream_t)stream, nullptr));
+    return SAMP_OK;
+}
+
+int samp_pack_weight_f16(const uint16_t *W, int32_t N, int32_t K, uint16_t *Wp, void *stream)
+{
+    if (!W || !Wp) return fail(SAMP_ERR_ARG, "NULL matrix pointer");
+    if (N < 32 || N % 32 || K < 16 || K % 16 || (long long)N * K > INT32_MAX)
+        return fail(SAMP_ERR_SHAPE, "packing needs N %% 32 == 0, K %% 16 == 0, N * K < 2^31 (N=%d K=%d)", N, K);
+    if (!aligned(W, 16) || !aligned(Wp, 16)) return fail(SAMP_ERR_ARG, "matrices must be 16-byte aligned");
+    if (W == Wp) return fail(SAMP_ERR_ARG, "a matrix cannot be packed in place");
+    HIP_TRY(launch_pack_weight(W, N, 2 * K, true, Wp, (hipStream_t)stream));
+    return SAMP_OK;
+}
+
+int samp_gemm_f16_packed(const uint16_t *A, const uint16_t *Wp, const float *bias, int32_t gelu, uint16_t *out, int32_t M, int32_t N,
+                         int32_t K, int32_t tile, void *stream)
+{
+    if (int rc = check_gemm(A, Wp, out, M, N, K, 128)) return rc;
+    if (bias && !aligned(bias, 16)) return fail(SAMP_ERR_ARG, "bias must be 16-byte aligned");
+    if (tile < -1 || tile > 3) return fail(SAMP_ERR_ARG, "tile must be in [-1, 3]");
+    if (tile >= 2 && N % 256) return fail(SAMP_ERR_SHAPE, "tile %d needs N %% 256 == 0 (N=%d)", tile, N);
+    HIP_TRY(launch_gemm_f16_packed((const __half *)A, (const __half *)Wp, bias, gelu != 0, (__half *)out, Rows{M, nullptr}, N, K, tile,
+                                   (hipStream_t)stream, nullptr));
     return SAMP_OK;
 }
 

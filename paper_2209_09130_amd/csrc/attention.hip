@@ -769,7 +769,7 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
                                     const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, float m_sc,
                                     float inv_sp, float m_ctx, int8_t *__restrict__ ctx)
 {
-    constexpr int MT = 8, BM = 16 * MT, RING = stream_ring_bytes<MT, D>();
+    constexpr int MT = 8, BM = 16 * MT, RING = stream_ring_bytes<false, MT, D>();
     constexpr int K_OFF = BM * QK_STRIDE_I8, VT_OFF = 2 * K_OFF;
     static_assert(VT_OFF + 64 * VT_ROW_I8<1> <= RING, "q, k and V^T take the place of the ring");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -811,7 +811,7 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
         bv = b_tab ? b_tab[2 * H + c0 + r] : 0.0f;
     };
     auto loop = [&](auto live) {                                  // live(i): token tile i holds tokens
-        stream_tile_loop<MT, 3, D>(X + (size_t)sq.t0 * H, offa, wbase, H / 128, lds, wave, lane, started,
+        stream_tile_loop<false, MT, 3, D>(X + (size_t)sq.t0 * H, offa, wbase, H / 128, lds, wave, lane, started,
             [&](int t, int i, const v4i &w, const v4i &f) {
                 if (live(i)) acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(t < 2 ? w : f, t < 2 ? f : w, acc[t][i], 0, 0, 0);
             });
@@ -1772,7 +1772,7 @@ hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packe
 {
     if (max_len > 128 || H % 256 || B <= 0) return hipErrorNotSupported;
     auto go = [&](auto kern) {
-        launch_kernel(kern, dim3((unsigned)(B * (H / 64))), dim3(256), stream_ring_bytes<8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
+        launch_kernel(kern, dim3((unsigned)(B * (H / 64))), dim3(256), stream_ring_bytes<false, 8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
                       (const char *)w_packed, m, b, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx);
         return hipGetLastError();
     };

@@ -18,6 +18,9 @@
 // lane i's 16 bytes at LDS position i of a 1 KiB run; the XOR swizzle that keeps the operand
 // fetches (ds_read_b128) conflict-free is therefore applied to the global address instead.
 // Work-groups are renumbered so that each XCD (own L2) owns a contiguous range of tiles.
+// That is the row-major kernels.  An encoder keeps its weights packed as well and runs most of its GEMMs on those (gemm_nt_stream_kernel):
+// the row-major ones are left with few rows, INT8 rows that are no whole pairs of 128-byte stages, GELU without a table, the step
+// entries and forced configurations.
 #include "samp_common.h"
 #include "mfma_tile.h"
 
@@ -753,7 +756,7 @@ hipError_t launch_big(const void *A, const void *W, void *out, const Epi &epi, R
 }
 
 
-// ---- packed weights, straight into registers (INT8) --------------------------------------------------
+// ---- packed weights, straight into registers ---------------------------------------------------
 // The tile loops above move both operands through LDS, and LDS is what the large ones run out of: a 128 x 192 tile of four 64 x 96
 // wave tiles reads 20 KB of fragments and writes 10 KB for every 192 clocks of matrix work, and its ring holds one stage in flight
 // (40 KB per block).  Here the block's four waves stand side by side, each with all 16 MT tokens and 16 NTW channels of its own: no
@@ -765,18 +768,23 @@ hipError_t launch_big(const void *A, const void *W, void *out, const Epi &epi, R
 // of 128 bytes into LDS get 125.
 // A lane's results are four channels of one token per 16 x 16 tile, the same four for all its tokens: its entries of the epilogue's
 // vectors are loaded once, into registers, and a wave's table lookups are the only LDS reads of the epilogue beside the output tile's.
-template <int MT, int NTW, int D> struct StreamTile {
-    static constexpr int BM = 16 * MT, BN = 64 * NTW, RING = stream_ring_bytes<MT, D>(), STRIDE = BN + 16;
-    static constexpr int OUT = BM * STRIDE, LUT_OFF = RING > OUT ? RING : OUT;       // the output tile takes the ring's place
+// FP16: 32 x 32 x 16 products, as in the row-major kernels and so with their bytes; blocks of 32 rows x 32 bytes; four products' weights
+// per 128-byte stage.  The bias goes to LDS: in registers (16 NTW) it makes the 128 x 256 tile spill.
+template <class T, class Epi, int MT, int NTW, int D> struct StreamTile {
+    static constexpr bool HALF = std::is_same<T, F16>::value;
+    static constexpr int ROWS = StreamGeometry<HALF>::ROWS, BM = ROWS * MT, BN = 4 * ROWS * NTW;
+    static constexpr int RING = stream_ring_bytes<HALF, MT, D>(), STRIDE = BN * Epi::OUT_BYTES + 16, OUT = BM * STRIDE;
+    static constexpr int LUT_OFF = RING > OUT ? RING : OUT;       // the output tile takes the ring's place
 };
 
-template <class Epi, int MT, int NTW, int D>
+template <class T, class Epi, int MT, int NTW, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ Wp, char *__restrict__ out, Epi epi, int host_rows,
                            const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n, bool channels_first)
 {
-    typedef StreamTile<MT, NTW, D> Tile;
-    constexpr int BM = Tile::BM, BN = Tile::BN, G = MT < 4 ? MT : 4, H = MT / G;
+    typedef StreamTile<T, Epi, MT, NTW, D> Tile;
+    constexpr bool HALF = Tile::HALF;
+    constexpr int ROWS = Tile::ROWS, BM = Tile::BM, BN = Tile::BN, G = MT < 4 ? MT : 4, H = MT / G, NLDA = stream_loads<HALF, MT>();
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     v2i *lut = reinterpret_cast<v2i *>(lds + Tile::LUT_OFF);
 
@@ -786,71 +794,98 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
     const int tile = xcd_contiguous(blockIdx.x, tiles);
     const int m0 = (channels_first ? tile % tiles_m : tile / tiles_n) * BM, n0 = (channels_first ? tile / tiles_m : tile % tiles_n) * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r = lane & 15, q = lane >> 4;
+    const int r = lane & (ROWS - 1), q = lane / ROWS;
 
-    unsigned offa[MT / 2];
+    unsigned offa[NLDA];
 #pragma unroll
-    for (int j = 0; j < MT / 2; j++) {
+    for (int j = 0; j < NLDA; j++) {
         const int srow = 8 * (wave + 4 * j) + (lane >> 3);
         offa[j] = (unsigned)min(srow, M - 1 - m0) * (unsigned)Kbytes + (((lane & 7) ^ swz<128>(srow)) << 4);
     }
     const char *wbase[NTW];
 #pragma unroll
-    for (int t = 0; t < NTW; t++) wbase[t] = Wp + (size_t)(n0 + 16 * (NTW * wave + t)) * Kbytes;
-    v4i acc[NTW][MT];
+    for (int t = 0; t < NTW; t++) wbase[t] = Wp + (size_t)(n0 + ROWS * (NTW * wave + t)) * Kbytes;
+    typedef typename std::conditional<HALF, v16f, v4i>::type Acc;
+    Acc acc[NTW][MT];
 #pragma unroll
     for (int t = 0; t < NTW; t++)
 #pragma unroll
-        for (int i = 0; i < MT; i++) acc[t][i] = v4i{0, 0, 0, 0};
-    v4f mm[NTW], bb[NTW];
-    stream_tile_loop<MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, Kbytes / 128, lds, wave, lane,
-        [&]() {
-            epi.load_lut_direct(lut, wave, 4, lane);
+        for (int i = 0; i < MT; i++)
 #pragma unroll
-            for (int t = 0; t < NTW; t++) {
-                const int n = n0 + 16 * (NTW * wave + t) + 4 * q;
-                mm[t] = *reinterpret_cast<const v4f *>(epi.m + n);
-                bb[t] = epi.offsets() ? *reinterpret_cast<const v4f *>(epi.offsets() + n) : v4f{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < (HALF ? 16 : 4); e++) acc[t][i][e] = 0;
+    constexpr int OB = Epi::OUT_BYTES, STRIDE = Tile::STRIDE;
+    if constexpr (HALF) {
+        float *tab = reinterpret_cast<float *>(lds + Tile::LUT_OFF);
+        stream_tile_loop<HALF, MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, Kbytes / 128, lds, wave, lane,
+            [&]() { epi.load_tables_direct(tab, n0, BN, wave, 4, lane); },
+            [&](int t, int i, const v4i &w, const v4i &f) { acc[t][i] = T::mma(w, f, acc[t][i]); });
+#pragma unroll
+        for (int t = 0; t < NTW; t++) {
+            const typename Epi::Tab b = epi.load_tab(tab, BN, 32 * (NTW * wave + t), q);
+#pragma unroll
+            for (int i = 0; i < MT; i++) {
+                v2i pk[4];
+                epi.tile(acc[t][i], b, nullptr, BN, 0, q, pk);
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    *reinterpret_cast<v2i *>(lds + (32 * i + r) * STRIDE + (32 * (NTW * wave + t) + 8 * u + 4 * q) * OB) = pk[u];
             }
-        },
-        [&](int t, int i, const v4i &w, const v4i &f) { acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, f, acc[t][i], 0, 0, 0); });
-
-    constexpr int STRIDE = Tile::STRIDE, CHUNKS = BN / 16, PASSES = (BM * CHUNKS + 255) / 256;
-    constexpr bool EVEN = BM * CHUNKS % 256 == 0;
-#pragma unroll
-    for (int t = 0; t < NTW; t++)
-#pragma unroll
-        for (int h = 0; h < H; h++) {
-            v4i group[G];
-            int pk[G];
-#pragma unroll
-            for (int i = 0; i < G; i++) group[i] = acc[t][G * h + i];
-            epi.quads(group, mm[t], bb[t], lut, pk);
-#pragma unroll
-            for (int i = 0; i < G; i++)
-                *reinterpret_cast<int *>(lds + (16 * (G * h + i) + r) * STRIDE + 16 * (NTW * wave + t) + 4 * q) = pk[i];
         }
-    __syncthreads();
-    v4i v[PASSES];
+    } else {
+        v4f mm[NTW], bb[NTW];
+        stream_tile_loop<HALF, MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, Kbytes / 128, lds, wave, lane,
+            [&]() {
+                epi.load_lut_direct(lut, wave, 4, lane);
 #pragma unroll
-    for (int p = 0; p < PASSES; p++) {
-        const int idx = EVEN ? p * 256 + tid : min(p * 256 + tid, BM * CHUNKS - 1);
-        v[p] = *reinterpret_cast<const v4i *>(lds + (idx / CHUNKS) * STRIDE + (idx % CHUNKS) * 16);
+                for (int t = 0; t < NTW; t++) {
+                    const int n = n0 + 16 * (NTW * wave + t) + 4 * q;
+                    mm[t] = *reinterpret_cast<const v4f *>(epi.m + n);
+                    bb[t] = epi.offsets() ? *reinterpret_cast<const v4f *>(epi.offsets() + n) : v4f{0.f, 0.f, 0.f, 0.f};
+                }
+            },
+            [&](int t, int i, const v4i &w, const v4i &f) { acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, f, acc[t][i], 0, 0, 0); });
+#pragma unroll
+        for (int t = 0; t < NTW; t++)
+#pragma unroll
+            for (int h = 0; h < H; h++) {
+                v4i group[G];
+                int pk[G];
+#pragma unroll
+                for (int i = 0; i < G; i++) group[i] = acc[t][G * h + i];
+                epi.quads(group, mm[t], bb[t], lut, pk);
+#pragma unroll
+                for (int i = 0; i < G; i++)
+                    *reinterpret_cast<int *>(lds + (16 * (G * h + i) + r) * STRIDE + 16 * (NTW * wave + t) + 4 * q) = pk[i];
+            }
     }
+    __syncthreads();
+    constexpr int CHUNKS = BN * OB / 16, PASSES = (BM * CHUNKS + 255) / 256;
+    constexpr bool EVEN = BM * CHUNKS % 256 == 0;
+    constexpr int BATCH = PASSES < 8 ? PASSES : 8;                // all reads of a batch, then its stores
+    static_assert(PASSES % BATCH == 0, "whole batches");
 #pragma unroll
-    for (int p = 0; p < PASSES; p++) {
-        const int idx = p * 256 + tid, row = m0 + idx / CHUNKS;
-        if (row < M && (EVEN || idx < BM * CHUNKS)) *reinterpret_cast<v4i *>(out + (size_t)row * N + n0 + (idx % CHUNKS) * 16) = v[p];
+    for (int p0 = 0; p0 < PASSES; p0 += BATCH) {
+        v4i v[BATCH];
+#pragma unroll
+        for (int p = 0; p < BATCH; p++) {
+            const int idx = EVEN ? (p0 + p) * 256 + tid : min((p0 + p) * 256 + tid, BM * CHUNKS - 1);
+            v[p] = *reinterpret_cast<const v4i *>(lds + (idx / CHUNKS) * STRIDE + (idx % CHUNKS) * 16);
+        }
+#pragma unroll
+        for (int p = 0; p < BATCH; p++) {
+            const int idx = (p0 + p) * 256 + tid, row = m0 + idx / CHUNKS;
+            if (row < M && (EVEN || idx < BM * CHUNKS)) *reinterpret_cast<v4i *>(out + ((size_t)row * N + n0) * OB + (idx % CHUNKS) * 16) = v[p];
+        }
     }
 }
 
-template <class Epi, int MT, int NTW, int D>
+template <class T, class Epi, int MT, int NTW, int D>
 hipError_t launch_stream(const void *A, const void *Wp, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
 {
-    typedef StreamTile<MT, NTW, D> Tile;
-    const size_t LDS = Tile::LUT_OFF + extra_lds_of(epi, 0);
-    if (N % Tile::BN || K % (128 * D)) return hipErrorInvalidValue;
-    auto kern = gemm_nt_stream_kernel<Epi, MT, NTW, D>;
+    typedef StreamTile<T, Epi, MT, NTW, D> Tile;
+    const size_t LDS = Tile::LUT_OFF + (Tile::HALF ? Tile::BN * 4 : extra_lds_of(epi, 0));
+    if (N % Tile::BN || K * T::ELEM % (128 * D)) return hipErrorInvalidValue;
+    auto kern = gemm_nt_stream_kernel<T, Epi, MT, NTW, D>;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -862,10 +897,10 @@ hipError_t launch_stream(const void *A, const void *Wp, void *out, const Epi &ep
     // are more than its L2 holds beside them and the rows are few: then it takes an eighth of the channels and all of the rows (us, token
     // rows first / channels first: 1024 x 4096, 256 rows 7.8 / 6.4, 512 rows 10.6 / 7.1, 1024 rows 11.3 / 11.6, 2048 rows 13.9 / 14.5;
     // 4096 x 1024, 512 rows 6.9 / 6.1, 1024 rows 10.6 / 8.6; 768 x 3072 and 3072 x 768 +-2 % up to 1024 rows)
-    const bool channels_first = (long)N * K >= 3 << 20 && rows.host_rows <= 1024;
+    const bool channels_first = (long)N * K * T::ELEM >= 3 << 20 && rows.host_rows <= 1024;
     const int tiles_n = N / Tile::BN, tiles_m = (rows.host_rows + Tile::BM - 1) / Tile::BM;
     launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)Wp, (char *)out, epi,
-                  rows.host_rows, rows.dev_rows, N, K, tiles_n, channels_first);
+                  rows.host_rows, rows.dev_rows, N, K * T::ELEM, tiles_n, channels_first);
     return hipGetLastError();
 }
 
@@ -900,23 +935,58 @@ hipError_t launch_packed(const void *A, const void *Wp, void *out, const Epi &ep
     if (K % 256 || N % 64) return hipErrorNotSupported;
     switch (tile < 0 ? stream_tile(rows, N, K) : tile) {
     case 0:
-        if (K % 512 == 0) return launch_stream<Epi, 2, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
-        if (K % 768 == 0) return launch_stream<Epi, 2, 1, 6>(A, Wp, out, epi, rows, N, K, st, tm);
-        return launch_stream<Epi, 2, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 512 == 0) return launch_stream<I8, Epi, 2, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 768 == 0) return launch_stream<I8, Epi, 2, 1, 6>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<I8, Epi, 2, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
     case 1:
-        if (K % 512 == 0) return launch_stream<Epi, 4, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
-        if (K % 384 == 0) return launch_stream<Epi, 4, 1, 3>(A, Wp, out, epi, rows, N, K, st, tm);
-        return launch_stream<Epi, 4, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 512 == 0) return launch_stream<I8, Epi, 4, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 384 == 0) return launch_stream<I8, Epi, 4, 1, 3>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<I8, Epi, 4, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
     case 2:
-        if (K % 512 == 0) return launch_stream<Epi, 4, 2, 4>(A, Wp, out, epi, rows, N, K, st, tm);
-        if (K % 384 == 0) return launch_stream<Epi, 4, 2, 3>(A, Wp, out, epi, rows, N, K, st, tm);
-        return launch_stream<Epi, 4, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 512 == 0) return launch_stream<I8, Epi, 4, 2, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 384 == 0) return launch_stream<I8, Epi, 4, 2, 3>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<I8, Epi, 4, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
     case 3:
-        if (K % 384 == 0) return launch_stream<Epi, 4, 3, 3>(A, Wp, out, epi, rows, N, K, st, tm);
-        return launch_stream<Epi, 4, 3, 2>(A, Wp, out, epi, rows, N, K, st, tm);
-    case 4: return launch_stream<Epi, 4, 4, 2>(A, Wp, out, epi, rows, N, K, st, tm);
-    case 5: return launch_stream<Epi, 8, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
-    case 6: return launch_stream<Epi, 8, 3, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+        if (K % 384 == 0) return launch_stream<I8, Epi, 4, 3, 3>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<I8, Epi, 4, 3, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 4: return launch_stream<I8, Epi, 4, 4, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 5: return launch_stream<I8, Epi, 8, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 6: return launch_stream<I8, Epi, 8, 3, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    }
+    return hipErrorInvalidValue;
+}
+
+// The same for FP16: tiles of 32 mt tokens x 128 ntw channels.  Here the operand bytes alone decide (a fit gives the other terms no weight;
+// the choice costs 0.3 % on average over the best of the four).
+constexpr StreamShape STREAM_TILES_F16[] = {{1, 1}, {2, 1}, {2, 2}, {4, 2}};
+constexpr int STREAM_TILE_F16_COUNT = sizeof(STREAM_TILES_F16) / sizeof(STREAM_TILES_F16[0]);
+int stream_tile_f16(Rows rows, int N, int K)
+{
+    int best = -1;
+    long best_cost = 0;
+    for (int i = 0; i < STREAM_TILE_F16_COUNT; i++) {
+        const int bm = 32 * STREAM_TILES_F16[i].mt, bn = 128 * STREAM_TILES_F16[i].ntw;
+        if (N % bn) continue;
+        const long tiles = (long)(N / bn) * ((rows.host_rows + bm - 1) / bm), cost = (tiles + 255) / 256 * (bm + bn);
+        if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+    }
+    return best;
+}
+hipError_t launch_packed_f16(const void *A, const void *Wp, void *out, const EpiF16 &epi, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm)
+{
+    if (K % 128 || N % 128) return hipErrorNotSupported;
+    // four stages in flight (two where K is no multiple): 32 x 128 tiles 768 x 3072 at 1024 rows 14.8 / 13.1, 128 x 128 4096 x 1024 at 4096
+    // rows 58.0 / 50.7, 3072 x 768 there 34.1 / 31.0.  The wide tiles have no registers for more than two.
+    const bool deep = K % 256 == 0;
+    switch (tile < 0 ? stream_tile_f16(rows, N, K) : tile) {
+    case 0:
+        if (deep) return launch_stream<F16, EpiF16, 1, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<F16, EpiF16, 1, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 1:
+        if (deep) return launch_stream<F16, EpiF16, 2, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
+        return launch_stream<F16, EpiF16, 2, 1, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 2: return launch_stream<F16, EpiF16, 2, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
+    case 3: return launch_stream<F16, EpiF16, 4, 2, 2>(A, Wp, out, epi, rows, N, K, st, tm);
     }
     return hipErrorInvalidValue;
 }
@@ -1398,17 +1468,7 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
     case 3: return launch_big<T, Epi, 4, 4, 128, 2>(A, W, out, epi, rows, N, K, st, tm);      // 256 x 256, two 128-byte stages
     case 4: return launch_big<T, Epi, 2, 4, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 128 tokens x 256 channels, two blocks per CU
     case 5: return launch_big<T, Epi, 4, 2, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);    // 256 tokens x 128 channels, two blocks per CU
-    case 6:                                                                                    // 128 x 192, two 128-byte stages, two blocks per CU
-        // FP16 beside another batch group, with more than one block for most CUs and not two for all: three 64-byte stages, which leave
-        // that group a quarter of the LDS (us, 6 layers of width 768, 128-byte / 64-byte stages by rows per group: FP16, sequences of 128
-        // tokens 3072 970 / 926, 3328 1033 / 1013, 3584 1084 / 1049, 4096 1134 / 1143, 5120 1363 / 1415, of 512 tokens 3072 1259 / 1185, 3584
-        // 1354 / 1332, of 350 tokens 3500 1259 / 1211, of 256 tokens 3072 1062 / 1079, 3584 1187 / 1179; MHA-only at 3584 rows 1003 / 980 (128
-        // tokens), 1113 / 1036 (256), 1204 / 1147 (512).  Below it is one or the other: 2816 rows of 128 tokens FP16 945 / 902, MHA-only
-        // 825 / 864; 2560 rows of 256 tokens FP16 889 / 920.  A ragged batch of 3328 padded rows per group: 757 / 768)
-        if constexpr (std::is_same<T, F16>::value)
-            if (!forced && rows.beside && !rows.dev_rows && rows.host_rows >= 3072 && rows.host_rows < 4096)
-                return launch_big<T, Epi, 2, 3, 64, 3, 2>(A, W, out, epi, rows, N, K, st, tm);
-        return launch_big<T, Epi, 2, 3, 128, 2, 2>(A, W, out, epi, rows, N, K, st, tm);
+    case 6: return launch_big<T, Epi, 2, 3, 128, 2, 2>(A, W, out, epi, rows, N, K, st, tm);   // 128 x 192, two 128-byte stages, two blocks per CU
     case 7: return launch_big<T, Epi, 4, 4, 64, 4>(A, W, out, epi, rows, N, K, st, tm);       // 256 x 256, four 64-byte stages
     case 1:
         // the GELU epilogue is as much vector work as the main loop is matrix work: 64-byte stages leave room
@@ -1481,9 +1541,23 @@ hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t
     return hipErrorNotSupported;
 }
 
-hipError_t launch_gemm_f16(const __half *A, const __half *W, const float *bias, bool gelu, __half *out, Rows rows,
+hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows, int N, int K,
+                                  int tile, hipStream_t st, const Timing *tm)
+{
+    return launch_packed_f16(A, Wp, out, EpiF16{bias, gelu}, rows, N, K, tile, st, tm);
+}
+
+// Few rows of few channels: as for INT8 (us, K split / packed weights: 768 x 768 at 128 rows 4.94 / 5.01, at 256 5.00 / 5.27, at 427 5.5 / 5.3;
+// 1024 x 1024 at 256 rows 5.7 / 6.1, at 427 6.35 / 6.15; 768 x 3072 at 256 rows 11.6 / 11.4; 1024 x 4096 at 128 rows 14.7 / 14.0)
+bool gemm_f16_reads_rows(Rows rows, int N, int K) { return N <= 1024 && K <= 1024 && (long)rows.host_rows * N <= 270000; }
+
+hipError_t launch_gemm_f16(const __half *A, const __half *W, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows,
                            int N, int K, hipStream_t st, const Timing *tm)
 {
+    if (Wp && gemm_config_override.load(std::memory_order_relaxed) < 0 && !gemm_f16_reads_rows(rows, N, K)) {
+        const hipError_t e = launch_gemm_f16_packed(A, Wp, bias, gelu, out, rows, N, K, -1, st, tm);
+        if (e != hipErrorNotSupported) return e;
+    }
     return launch<F16>(A, W, out, EpiF16{bias, gelu}, rows, N, K, st, tm);
 }
 

@@ -65,28 +65,36 @@ template <int N> __device__ __forceinline__ void wait_lds_reads()
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// ---- tile loop on packed weights (INT8) ----------------------------------------------------------
-// A block's four waves stand side by side: each multiplies all 16 MT token rows of the block by 16 NTW weight rows of its own.  The token rows
-// travel through LDS (a ring of D + 1 stages of 128 bytes a row, direct loads); the weight rows, which no other wave wants, come straight
-// into registers, D stages ahead, in the order of the 16 x 16 x 64 product (pack_weight_kernel: 1 KB per 16 rows x 64 bytes).
+// ---- tile loop on packed weights -----------------------------------------------------------------
+// A block's four waves stand side by side: each multiplies all token rows of the block by weight rows of its own.  The token rows travel
+// through LDS (a ring of D + 1 stages of 128 bytes a row, direct loads); the weight rows, which no other wave wants, come straight into
+// registers, D stages ahead, in the order of the matrix product (pack_weight_kernel: 1 KB per 16 rows x 64 bytes for the 16 x 16 x 64 product
+// of INT8, per 32 rows x 32 bytes for the 32 x 32 x 16 product of FP16, whose sums are formed in the order of every other FP16 kernel).
 template <class F, int... I> __device__ __forceinline__ void each_index(F f, std::integer_sequence<int, I...>)
 {
     (f(std::integral_constant<int, I>()), ...);
 }
-template <int MT, int D> constexpr int stream_ring_bytes() { return (D + 1) * 16 * MT * 128; }
+template <bool HALF> struct StreamGeometry {
+    static constexpr int ROWS = HALF ? 32 : 16;                   // token rows of a product, and weight rows
+    static constexpr int KS = HALF ? 4 : 2;                       // products along a stage
+};
+template <bool HALF, int MT, int D> constexpr int stream_ring_bytes() { return (D + 1) * StreamGeometry<HALF>::ROWS * MT * 128; }
+template <bool HALF, int MT> constexpr int stream_loads() { return StreamGeometry<HALF>::ROWS * MT / 32; }     // token-row loads of a wave and stage
 
-// abase: first token row; offa: this lane's offsets into the rows of its pieces (8 rows x 128 bytes, swizzled); wbase: the wave's packed
-// row blocks; KT: stages of 128 bytes, a multiple of D.  started() runs once the first stage is requested (what it loads has arrived when
-// the first product runs); mma(t, i, w, f) adds the product of weight block t and token tile i.  On return the ring is idle.
-template <int MT, int NTW, int D, class Started, class Mma>
-__device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[MT / 2], const char *const (&wbase)[NTW], int KT, char *lds,
-                                                 int wave, int lane, Started started, Mma mma)
+// MT token tiles, NTW weight blocks per wave.  abase: first token row; offa: this lane's offsets into the rows of its pieces (8 rows x 128
+// bytes, swizzled); wbase: the wave's packed row blocks; KT: stages of 128 bytes, a multiple of D.  started() runs once the first stage is
+// requested (what it loads has arrived when the first product runs); mma(t, i, w, f) adds the product of weight block t and token tile i.
+// On return the ring is idle.
+template <bool HALF, int MT, int NTW, int D, class Started, class Mma>
+__device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[stream_loads<HALF, MT>()], const char *const (&wbase)[NTW],
+                                                 int KT, char *lds, int wave, int lane, Started started, Mma mma)
 {
-    constexpr int SLOT = 16 * MT * 128, RING = stream_ring_bytes<MT, D>();
-    constexpr int G = MT < 4 ? MT : 4, H = MT / G, STEPS = 2 * H;          // token tiles per step; steps per 64 bytes of K
-    constexpr int NLDA = MT / 2, PER = NLDA + 2 * NTW;                     // loads of a wave and stage: token rows; all
-    static_assert(MT % G == 0 && H <= 2 && D >= 2, "whole steps");
-    const int r = lane & 15, q = lane >> 4;
+    constexpr int ROWS = StreamGeometry<HALF>::ROWS, KS = StreamGeometry<HALF>::KS, TILE = ROWS * 128;
+    constexpr int SLOT = TILE * MT, RING = stream_ring_bytes<HALF, MT, D>();
+    constexpr int G = MT < 4 ? MT : 4, H = MT / G, STEPS = KS * H;         // token tiles per step; steps of a stage
+    constexpr int NLDA = stream_loads<HALF, MT>(), PER = NLDA + KS * NTW;  // loads of a wave and stage: token rows; all
+    static_assert(MT % G == 0 && H <= 2 && D >= 2 && NLDA >= 1, "whole steps, whole pieces per wave");
+    const int r = lane & (ROWS - 1), q = lane / ROWS;
     const unsigned offw = 16 * lane;
     int fill = 0;                                                 // ring position of the next stage to request
     auto issue_a = [&](int kt, int first, int last) {
@@ -102,22 +110,22 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
         if (last == NLDA) fill = fill + SLOT == RING ? 0 : fill + SLOT;
     };
     // (written out so that the compiler does not wait for them: step() does, and ties the registers to its wait)
-    v4i w[D][2][NTW];
+    v4i w[D][KS][NTW];
     auto load_w = [&](int kt, int ks, v4i (&d)[NTW]) {
 #pragma unroll
         for (int t = 0; t < NTW; t++)
-            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(d[t]) : "v"(offw), "s"(wbase[t] + (size_t)(2 * kt + ks) * 1024));
+            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(d[t]) : "v"(offw), "s"(wbase[t] + (size_t)(KS * kt + ks) * 1024));
     };
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
-    unsigned addr[2];
+    unsigned addr[KS];
 #pragma unroll
-    for (int ks = 0; ks < 2; ks++) addr[ks] = lds_base + r * 128 + (((4 * ks + q) ^ swz<128>(r)) << 4);
+    for (int ks = 0; ks < KS; ks++) addr[ks] = lds_base + r * 128 + (((8 / KS * ks + q) ^ swz<128>(r)) << 4);
 
 #pragma unroll
     for (int s = 0; s < D; s++) {
         issue_a(s, 0, NLDA);
-        load_w(s, 0, w[s][0]);
-        load_w(s, 1, w[s][1]);
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) load_w(s, ks, w[s][ks]);
         if (s == 0) {
             started();
             __builtin_amdgcn_sched_barrier(0);
@@ -126,33 +134,32 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
     v4i fa[2][G];
     int slot = 0;
     auto fetch = [&](auto idx_tag, v4i (&f)[G]) {
-        constexpr int OFF = (decltype(idx_tag)::value % H) * G * 2048;
-        lds_read_frags<2048>(addr[decltype(idx_tag)::value / H] + slot + OFF, f, std::make_integer_sequence<int, G>());
+        constexpr int OFF = (decltype(idx_tag)::value % H) * G * TILE;
+        lds_read_frags<TILE>(addr[decltype(idx_tag)::value / H] + slot + OFF, f, std::make_integer_sequence<int, G>());
     };
     constexpr std::integral_constant<int, 0> c0;
-    constexpr std::integral_constant<int, 1> c1;
-    constexpr std::integral_constant<int, 2> c2;
-    constexpr std::integral_constant<int, 3> c3;
-    // One step multiplies G token tiles by the wave's channels over 64 bytes of K, with the token fragments of the step after it on
+    // One step multiplies G token tiles by the wave's channels along one product's K, with the token fragments of the step after it on
     // their way from LDS.  The loads of the stage D further on are dealt out over the steps (a burst of them would hold the wave up
     // at its issue, with the matrix cores idle): token rows in each, weights into the registers that the step before has read last.
     // LEFT: stages after this one, D where there are that many or more (copies of the code instead of tests: the waits are constants).
+    // The waits let stay in flight what was requested behind the loads they are for, counted from the order below.
     auto step = [&](auto left_tag, auto b_tag, auto idx_tag, int kt) {
         constexpr int LEFT = decltype(left_tag)::value, B = decltype(b_tag)::value, IDX = decltype(idx_tag)::value, ks = IDX / H, h = IDX % H;
         constexpr bool MORE = LEFT == D;
-        if constexpr (IDX == H) {                                 // the second half of this stage's weights has landed
-            wait_vm<MORE ? (D - 1) * PER + NLDA * H / STEPS : LEFT * PER>();
-            tie(w[B][1], std::make_integer_sequence<int, NTW>());
+        if constexpr (ks > 0 && h == 0) {                         // this product's weights have landed
+            wait_vm<(KS - 1 - ks) * NTW + (MORE ? (D - 1) * PER + NLDA * IDX / STEPS + (ks - 1) * NTW : LEFT * PER)>();
+            tie(w[B][ks], std::make_integer_sequence<int, NTW>());
         }
         if constexpr (MORE) {
             issue_a(kt + D, NLDA * IDX / STEPS, NLDA * (IDX + 1) / STEPS);
-            if constexpr (IDX == H) load_w(kt + D, 0, w[B][0]);
+            if constexpr (ks > 0 && h == 0) load_w(kt + D, ks - 1, w[B][ks - 1]);
         }
         if constexpr (IDX + 1 < STEPS) {
             fetch(std::integral_constant<int, IDX + 1>(), fa[(IDX + 1) & 1]);
             wait_lds_reads<G>();
-        } else if constexpr (LEFT > 0) {                          // so have the next stage's token rows and the first half of its weights
-            wait_vm_and_barrier<MORE ? (D - 1) * PER : NTW + (LEFT - 1) * PER>();
+        } else if constexpr (LEFT > 0) {                          // so have the next stage's token rows and its first product's weights
+            constexpr int AFTER = (H == 1 && KS > 2 ? 2 : 1) * NTW;
+            wait_vm_and_barrier<AFTER + (MORE ? (D - 2) * PER + NLDA + (KS - 1) * NTW : (LEFT - 1) * PER)>();
             slot = slot + SLOT == RING ? 0 : slot + SLOT;
             fetch(c0, fa[0]);
         } else {
@@ -166,14 +173,12 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
 #pragma unroll
             for (int i = 0; i < G; i++) mma(t, G * h + i, w[B][ks][t], fa[IDX & 1][i]);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (MORE && IDX + 1 == STEPS) load_w(kt + D, 1, w[B][1]);
+        if constexpr (MORE && IDX + 1 == STEPS) load_w(kt + D, KS - 1, w[B][KS - 1]);
     };
     auto stage = [&](auto left_tag, auto b_tag, int kt) {
-        step(left_tag, b_tag, c0, kt);
-        step(left_tag, b_tag, c1, kt);
-        if constexpr (H == 2) { step(left_tag, b_tag, c2, kt); step(left_tag, b_tag, c3, kt); }
+        each_index([&](auto idx) { step(left_tag, b_tag, idx, kt); }, std::make_integer_sequence<int, STEPS>());
     };
-    wait_vm_and_barrier<NTW + (D - 1) * PER>();
+    wait_vm_and_barrier<(KS - 1) * NTW + (D - 1) * PER>();
     fetch(c0, fa[0]);
     const auto all = std::make_integer_sequence<int, D>();
     for (int kt = 0; kt + D < KT; kt += D) each_index([&](auto b) { stage(std::integral_constant<int, D>(), b, kt + b); }, all);

@@ -538,14 +538,17 @@ __global__ __launch_bounds__(256) void quantize_weight_kernel(const __half *__re
     for (int k = threadIdx.x; k < K; k += 256) Wq[(size_t)n * K + k] = (int8_t)qcode(__fdiv_rn((float)row[k], s));
 }
 
-// Weights in the order in which a wave takes them as the operand of a 16 x 16 x 64 product (create time): one thread per 16 bytes.
-__global__ __launch_bounds__(256) void pack_weight_kernel(const int8_t *__restrict__ W, int K, int chunks, int8_t *__restrict__ Wp)
+// Weights in the order in which a wave takes them as the operand of a matrix product (create time): one thread per 16 bytes.  1 KB blocks of
+// ROWS rows, row blocks outermost, inside a block 16-byte columns of ROWS rows one after the other (INT8 16, FP16 32 rows).
+template <int ROWS>
+__global__ __launch_bounds__(256) void pack_weight_kernel(const char *__restrict__ W, int Kbytes, size_t chunks, char *__restrict__ Wp)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;                  // chunk of the result: [row block][64-byte group][column][row]
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;       // chunk of the result: [row block][column group][column][row]
     if (i >= chunks) return;
-    const int r = i & 15, q = (i >> 4) & 3, block = i >> 6, groups = K >> 6;
-    const size_t row = (size_t)(block / groups) * 16 + r, col = (size_t)(block % groups) * 64 + 16 * q;
-    reinterpret_cast<v4i *>(Wp)[i] = *reinterpret_cast<const v4i *>(W + row * K + col);
+    constexpr int COLS = 64 / ROWS;
+    const size_t block = i >> 6, groups = Kbytes / (16 * COLS);
+    const size_t row = block / groups * ROWS + i % ROWS, col = block % groups * (16 * COLS) + i / ROWS % COLS * 16;
+    reinterpret_cast<v4i *>(Wp)[i] = *reinterpret_cast<const v4i *>(W + row * Kbytes + col);
 }
 
 // Epilogue tables: m[n] = s_in * s_w[n] / s_out, b[n] = bias[n] / s_out, formed in binary64 and
@@ -652,10 +655,11 @@ hipError_t launch_quantize_weight(const __half *W, int N, int K, int8_t *Wq, flo
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weight(const int8_t *W, int N, int K, int8_t *Wp, hipStream_t st)
+hipError_t launch_pack_weight(const void *W, int N, int Kbytes, bool half, void *Wp, hipStream_t st)
 {
-    const int chunks = (int)((size_t)N * K / 16);
-    hipLaunchKernelGGL(pack_weight_kernel, dim3((chunks + 255) / 256), dim3(256), 0, st, W, K, chunks, Wp);
+    const size_t chunks = (size_t)N * Kbytes / 16;
+    hipLaunchKernelGGL(half ? pack_weight_kernel<32> : pack_weight_kernel<16>, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st,
+                       (const char *)W, Kbytes, chunks, (char *)Wp);
     return hipGetLastError();
 }
 

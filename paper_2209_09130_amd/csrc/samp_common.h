@@ -185,8 +185,12 @@ bool gemm_i8_reads_rows(Rows rows, int N);
 // hipErrorNotSupported: K is no multiple of 256, N none of 64, or the epilogue is another
 hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t *Wp, void *out, const float *m, const float *b,
                                  const GeluTable *gelu_table, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm);
-hipError_t launch_gemm_f16(const __half *A, const __half *W, const float *bias, bool gelu, __half *out, Rows rows,
+hipError_t launch_gemm_f16(const __half *A, const __half *W, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows,
                            int N, int K, hipStream_t st, const Timing *tm);
+bool gemm_f16_reads_rows(Rows rows, int N, int K);
+// as launch_gemm_i8_packed, K and N multiples of 128
+hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows, int N, int K,
+                                  int tile, hipStream_t st, const Timing *tm);
 
 // cu == nullptr: every sequence has exactly max_len rows (row b*max_len is its first).
 // p_unsigned: softmax codes 0..255 instead of -127..127; p_hist (optional): 256 counters of the codes used
@@ -236,8 +240,9 @@ hipError_t launch_embed_ln(const EmbedArgs &a, hipStream_t st, const Timing *tm)
 
 hipError_t launch_quantize_weight(const __half *W, int N, int K, int8_t *Wq, float *s_w, hipStream_t st);
 // W [N,K] in the order of the 16 x 16 x 64 matrix product: 1 KB blocks of 16 rows x 64 bytes, row blocks outermost, inside a block the
-// four 16-byte columns one after the other, 16 rows each.  N % 16 == 0, K % 64 == 0
-hipError_t launch_pack_weight(const int8_t *W, int N, int K, int8_t *Wp, hipStream_t st);
+// four 16-byte columns one after the other, 16 rows each (INT8; FP16: 32 rows x 32 bytes, two columns of 32 rows).  N % 16 (32) == 0,
+// Kbytes % 64 (32) == 0
+hipError_t launch_pack_weight(const void *W, int N, int Kbytes, bool half, void *Wp, hipStream_t st);
 hipError_t launch_fold(const float *s_in_dev_or_null, float s_in, const float *s_w, const float *bias, float s_out, int N,
                        float *m, float *b, hipStream_t st);
 hipError_t launch_seq_offsets(const int *mask, int B, int S, int *cu, hipStream_t st);

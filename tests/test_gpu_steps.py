@@ -177,6 +177,31 @@ def test_gemms_on_packed_weights_give_the_same_codes(P, tile, M, N, K):
                           oracle.epilogue_gelu_quant(acc, md, bias, s_out))
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3])
+@pytest.mark.parametrize("M,N,K", [(1, 768, 128), (130, 768, 768), (257, 384, 1024), (33, 768, 3072), (1100, 512, 640)])
+def test_fp16_gemm_on_packed_weights_gives_the_same_values(P, tile, M, N, K):
+    """Every tile with one row, a last row tile that is not full, two to forty-eight stages of K, two and four of them in flight: the bytes
+    of the row-major kernels, which add in the same order.  The packed bytes against the definition."""
+    width = {0: 128, 1: 128, 2: 256, 3: 256}
+    rng = np.random.default_rng(M + N + K)
+    A = rng.standard_normal((M, K)).astype(np.float16)
+    W = (rng.standard_normal((N, K)) / np.sqrt(K)).astype(np.float16)
+    bias = (0.1 * rng.standard_normal(N)).astype(np.float32)
+    packed = P.pack_weight_f16(dev(W))
+    assert np.array_equal(host(packed), W.reshape(N // 32, 32, K // 16, 2, 8).transpose(0, 2, 3, 1, 4).ravel())
+    if tile >= 0 and N % width[tile]:
+        with pytest.raises(P.SampError):
+            P.gemm_f16_packed(dev(A), packed, dev(bias), True, tile)
+        return
+    for b, gelu in ((bias, True), (bias, False), (None, False)):
+        b = None if b is None else dev(b)
+        got = host(P.gemm_f16_packed(dev(A), packed, b, gelu, tile))
+        assert np.array_equal(got, host(P.gemm_f16(dev(A), dev(W), b, gelu)))
+        # one rounding to 16 bits, and 32-bit sums of K terms, against the oracle's
+        want = oracle.gemm_f16(A, W, bias if b is not None else np.zeros(N, np.float32), gelu).astype(np.float64)
+        assert (np.abs(got - want) <= np.maximum(np.abs(want), 2.0 ** -14) * 2.0 ** -10 + K * 2.0 ** -24).all()
+
+
 @pytest.mark.parametrize("config", [-1, 0, 1, 2])
 def test_table_lookup_gelu_epilogue_in_the_small_tile_configurations(P, config):
     rng = np.random.default_rng(5 + config)
