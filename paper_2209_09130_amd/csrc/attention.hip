@@ -530,9 +530,9 @@ __device__ __forceinline__ void qkv_tile_gemm_any(const char *__restrict__ X, co
 // `words` dwords into LDS by one wave, 64 per direct load; the caller waits for them (vmcnt) before its next barrier
 __device__ __forceinline__ void load_direct(float *dst, const void *src, int words, int lane)
 {
+    const auto from = buffer_of(src);
     for (int i = 0; i < words; i += 64)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((const int *)src + i + lane),
-                                         (__attribute__((address_space(3))) void *)(dst + i), 4, 0, 0);
+        buffer_to_lds32(from, 4 * (i + lane), (int *)dst + i);
 }
 
 // q and k as token rows of 64 codes, v transposed (a channel's codes of all keys in a row): strides of the LDS copies
@@ -789,10 +789,9 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
         const int srow = 8 * (wave + 4 * j) + (lane >> 3);
         offa[j] = (unsigned)min(srow, n - 1) * (unsigned)H + (((lane & 7) ^ swz<128>(srow)) << 4);
     }
-    const char *wbase[3];
     const int c0 = head * 64 + 16 * wave;                         // the wave's channels in each part
-#pragma unroll
-    for (int t = 0; t < 3; t++) wbase[t] = Wp + (size_t)(t * H + c0) * H;
+    const char *wbase = Wp + (size_t)c0 * H;
+    const unsigned woff[3] = {0, (unsigned)(H * H), (unsigned)(2 * H * H)};
     v4i acc[3][MT];
 #pragma unroll
     for (int t = 0; t < 3; t++)
@@ -811,7 +810,7 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
         bv = b_tab ? b_tab[2 * H + c0 + r] : 0.0f;
     };
     auto loop = [&](auto live) {                                  // live(i): token tile i holds tokens
-        stream_tile_loop<false, MT, 3, D>(X + (size_t)sq.t0 * H, offa, wbase, H / 128, lds, wave, lane, started,
+        stream_tile_loop<false, MT, 3, D>(X + (size_t)sq.t0 * H, offa, wbase, woff, H / 128, lds, wave, lane, started,
             [&](int t, int i, const v4i &w, const v4i &f) {
                 if (live(i)) acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(t < 2 ? w : f, t < 2 ? f : w, acc[t][i], 0, 0, 0);
             });

@@ -76,10 +76,10 @@ __device__ __forceinline__ void copy_table(float *dst, const float *src, int n0,
 // instruction, the instructions dealt out over the waves.
 __device__ __forceinline__ void copy_direct(void *dst, const void *src, int words, int wave, int nwaves, int lane)
 {
+    const auto from = buffer_of(src);
     for (int i = wave * 64; i < words; i += nwaves * 64)             // wave-uniform
         if (i + lane < words)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((const int *)src + i + lane),
-                                             (__attribute__((address_space(3))) void *)((int *)dst + i), 4, 0, 0);
+            buffer_to_lds32(from, 4 * (i + lane), (int *)dst + i);
 }
 __device__ __forceinline__ void copy_table_direct(float *dst, const float *src, int n0, int bn, int wave, int nwaves, int lane)
 {
@@ -802,9 +802,10 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
         const int srow = 8 * (wave + 4 * j) + (lane >> 3);
         offa[j] = (unsigned)min(srow, M - 1 - m0) * (unsigned)Kbytes + (((lane & 7) ^ swz<128>(srow)) << 4);
     }
-    const char *wbase[NTW];
+    const char *wbase = Wp + (size_t)(n0 + ROWS * NTW * wave) * Kbytes;
+    unsigned woff[NTW];
 #pragma unroll
-    for (int t = 0; t < NTW; t++) wbase[t] = Wp + (size_t)(n0 + ROWS * (NTW * wave + t)) * Kbytes;
+    for (int t = 0; t < NTW; t++) woff[t] = ROWS * t * Kbytes;
     typedef typename std::conditional<HALF, v16f, v4i>::type Acc;
     Acc acc[NTW][MT];
 #pragma unroll
@@ -816,7 +817,7 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
     constexpr int OB = Epi::OUT_BYTES, STRIDE = Tile::STRIDE;
     if constexpr (HALF) {
         float *tab = reinterpret_cast<float *>(lds + Tile::LUT_OFF);
-        stream_tile_loop<HALF, MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, Kbytes / 128, lds, wave, lane,
+        stream_tile_loop<HALF, MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, woff, Kbytes / 128, lds, wave, lane,
             [&]() { epi.load_tables_direct(tab, n0, BN, wave, 4, lane); },
             [&](int t, int i, const v4i &w, const v4i &f) { acc[t][i] = T::mma(w, f, acc[t][i]); });
 #pragma unroll
@@ -833,19 +834,20 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
         }
     } else {
         v4f mm[NTW], bb[NTW];
-        stream_tile_loop<HALF, MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, Kbytes / 128, lds, wave, lane,
+        stream_tile_loop<HALF, MT, NTW, D>(A + (size_t)m0 * Kbytes, offa, wbase, woff, Kbytes / 128, lds, wave, lane,
             [&]() {
                 epi.load_lut_direct(lut, wave, 4, lane);
 #pragma unroll
                 for (int t = 0; t < NTW; t++) {
                     const int n = n0 + 16 * (NTW * wave + t) + 4 * q;
                     mm[t] = *reinterpret_cast<const v4f *>(epi.m + n);
-                    bb[t] = epi.offsets() ? *reinterpret_cast<const v4f *>(epi.offsets() + n) : v4f{0.f, 0.f, 0.f, 0.f};
+                    bb[t] = *reinterpret_cast<const v4f *>((epi.offsets() ? epi.offsets() : epi.m) + n);
                 }
             },
             [&](int t, int i, const v4i &w, const v4i &f) { acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, f, acc[t][i], 0, 0, 0); });
 #pragma unroll
-        for (int t = 0; t < NTW; t++)
+        for (int t = 0; t < NTW; t++) {
+            if (!epi.offsets()) bb[t] = v4f{0.f, 0.f, 0.f, 0.f};   // (here: a choice before the loop would wait for the loads)
 #pragma unroll
             for (int h = 0; h < H; h++) {
                 v4i group[G];
@@ -857,6 +859,7 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
                 for (int i = 0; i < G; i++)
                     *reinterpret_cast<int *>(lds + (16 * (G * h + i) + r) * STRIDE + 16 * (NTW * wave + t) + 4 * q) = pk[i];
             }
+        }
     }
     __syncthreads();
     constexpr int CHUNKS = BN * OB / 16, PASSES = (BM * CHUNKS + 255) / 256;

@@ -34,6 +34,17 @@ template <int N> __device__ __forceinline__ void wait_vm()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Loads through a buffer descriptor: scalar base + 32-bit vector offset + scalar offset, so no address arithmetic in vector registers.  The
+// compiler counts such loads one by one when it waits for a register; after a direct load of the global_load_lds kind, which it takes for
+// one that may return out of order, it waits for all that are in flight.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base)          // no bounds check
+{ return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0xffffffffu, 0x00027000); }
+// 16 or 4 bytes per lane, one lane's behind the other's in LDS
+__device__ __forceinline__ void buffer_to_lds128(__amdgpu_buffer_rsrc_t from, unsigned offset, unsigned scalar_offset, void *lds)
+{ __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void *)lds, 16, offset, scalar_offset, 0, 0); }
+__device__ __forceinline__ void buffer_to_lds32(__amdgpu_buffer_rsrc_t from, unsigned offset, void *lds)
+{ __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void *)lds, 4, offset, 0, 0, 0); }
+
 // Fragment fetches of the large-tile kernel are written as ds_read_b128 instructions of its own, with
 // explicit waits: left to the compiler, every group of MFMAs is preceded by a wait for ALL outstanding
 // LDS reads, including the ones just issued for the step after it, which puts the LDS latency in front
@@ -86,8 +97,8 @@ template <bool HALF, int MT> constexpr int stream_loads() { return StreamGeometr
 // requested (what it loads has arrived when the first product runs); mma(t, i, w, f) adds the product of weight block t and token tile i.
 // On return the ring is idle.
 template <bool HALF, int MT, int NTW, int D, class Started, class Mma>
-__device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[stream_loads<HALF, MT>()], const char *const (&wbase)[NTW],
-                                                 int KT, char *lds, int wave, int lane, Started started, Mma mma)
+__device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[stream_loads<HALF, MT>()], const char *wbase,
+                                                 const unsigned (&woff)[NTW], int KT, char *lds, int wave, int lane, Started started, Mma mma)
 {
     constexpr int ROWS = StreamGeometry<HALF>::ROWS, KS = StreamGeometry<HALF>::KS, TILE = ROWS * 128;
     constexpr int SLOT = TILE * MT, RING = stream_ring_bytes<HALF, MT, D>();
@@ -97,24 +108,16 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
     const int r = lane & (ROWS - 1), q = lane / ROWS;
     const unsigned offw = 16 * lane;
     int fill = 0;                                                 // ring position of the next stage to request
+    const auto rows = buffer_of(abase), weights = buffer_of(wbase);
     auto issue_a = [&](int kt, int first, int last) {
-        const char *from = abase + (size_t)kt * 128;
-        asm volatile("" : "+s"(from));
 #pragma unroll
-        for (int j = first; j < last; j++) {
-            unsigned o = offa[j];
-            asm volatile("" : "+v"(o));                            // keeps the offset a 32-bit one: scalar base + vector offset
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + o),
-                                             (__attribute__((address_space(3))) void *)(lds + fill + (wave + 4 * j) * 1024), 16, 0, 0);
-        }
+        for (int j = first; j < last; j++) buffer_to_lds128(rows, offa[j], kt * 128, lds + fill + (wave + 4 * j) * 1024);
         if (last == NLDA) fill = fill + SLOT == RING ? 0 : fill + SLOT;
     };
-    // (written out so that the compiler does not wait for them: step() does, and ties the registers to its wait)
     v4i w[D][KS][NTW];
     auto load_w = [&](int kt, int ks, v4i (&d)[NTW]) {
 #pragma unroll
-        for (int t = 0; t < NTW; t++)
-            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(d[t]) : "v"(offw), "s"(wbase[t] + (size_t)(KS * kt + ks) * 1024));
+        for (int t = 0; t < NTW; t++) d[t] = __builtin_amdgcn_raw_buffer_load_b128(weights, offw, woff[t] + (KS * kt + ks) * 1024, 0);
     };
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     unsigned addr[KS];
@@ -124,6 +127,7 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
 #pragma unroll
     for (int s = 0; s < D; s++) {
         issue_a(s, 0, NLDA);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) load_w(s, ks, w[s][ks]);
         if (s == 0) {
@@ -142,14 +146,12 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
     // their way from LDS.  The loads of the stage D further on are dealt out over the steps (a burst of them would hold the wave up
     // at its issue, with the matrix cores idle): token rows in each, weights into the registers that the step before has read last.
     // LEFT: stages after this one, D where there are that many or more (copies of the code instead of tests: the waits are constants).
-    // The waits let stay in flight what was requested behind the loads they are for, counted from the order below.
+    // The compiler waits for the weights.  For the token rows, which it does not see in LDS, each stage lets stay in flight what was
+    // requested behind them: no less than this stage's loads so far, those of the stages in between, and the next stage's last weights
+    // (load order inside a step is the compiler's; across the scheduling barriers it stays).
     auto step = [&](auto left_tag, auto b_tag, auto idx_tag, int kt) {
         constexpr int LEFT = decltype(left_tag)::value, B = decltype(b_tag)::value, IDX = decltype(idx_tag)::value, ks = IDX / H, h = IDX % H;
         constexpr bool MORE = LEFT == D;
-        if constexpr (ks > 0 && h == 0) {                         // this product's weights have landed
-            wait_vm<(KS - 1 - ks) * NTW + (MORE ? (D - 1) * PER + NLDA * IDX / STEPS + (ks - 1) * NTW : LEFT * PER)>();
-            tie(w[B][ks], std::make_integer_sequence<int, NTW>());
-        }
         if constexpr (MORE) {
             issue_a(kt + D, NLDA * IDX / STEPS, NLDA * (IDX + 1) / STEPS);
             if constexpr (ks > 0 && h == 0) load_w(kt + D, ks - 1, w[B][ks - 1]);
@@ -157,16 +159,14 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
         if constexpr (IDX + 1 < STEPS) {
             fetch(std::integral_constant<int, IDX + 1>(), fa[(IDX + 1) & 1]);
             wait_lds_reads<G>();
-        } else if constexpr (LEFT > 0) {                          // so have the next stage's token rows and its first product's weights
-            constexpr int AFTER = (H == 1 && KS > 2 ? 2 : 1) * NTW;
-            wait_vm_and_barrier<AFTER + (MORE ? (D - 2) * PER + NLDA + (KS - 1) * NTW : (LEFT - 1) * PER)>();
+        } else if constexpr (LEFT > 0) {                          // the next stage's token rows have landed
+            wait_vm_and_barrier<NTW + (MORE ? (D - 2) * PER + NLDA + (KS - 1) * NTW : (LEFT - 1) * PER)>();
             slot = slot + SLOT == RING ? 0 : slot + SLOT;
             fetch(c0, fa[0]);
         } else {
             wait_lds_reads<0>();
         }
         tie(fa[IDX & 1], std::make_integer_sequence<int, G>());
-        if constexpr (IDX == 0) tie(w[B][0], std::make_integer_sequence<int, NTW>());
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < NTW; t++)
