@@ -262,6 +262,12 @@ SAMP_API int samp_classify(const uint16_t *hidden, int32_t B, int32_t S, int32_t
                            const float *b_pool, const uint16_t *w_cls, const float *b_cls, int32_t classes,
                            float *logits, void *stream);
 
+/* The same logits (the same bits) in less time: pooled dev float [B, H], 16-byte aligned, is a workspace for the pooled vectors
+ * tanh(W_p . hidden[b, 0, :] + b_p), so that the chip shares the work of few sequences.               */
+SAMP_API int samp_classify_workspace(const uint16_t *hidden, int32_t B, int32_t S, int32_t H, const uint16_t *w_pool,
+                                     const float *b_pool, const uint16_t *w_cls, const float *b_cls, int32_t classes,
+                                     float *pooled, float *logits, void *stream);
+
 /* Code-usage statistic of any int8 tensor (Appendix B compares the softmax codes with the codes of
  * the attention output): ADDS to hist[256] (dev uint64, zeroed by the caller; index = the code as
  * an unsigned byte) the number of occurrences of each code among codes[0..n).                     */

@@ -383,11 +383,13 @@ def qkv_attention_f16(x, w_qkv, bias, cu, max_len: int, heads: int):
 
 
 def classify(hidden: torch.Tensor, w_pool, b_pool, w_cls, b_cls) -> torch.Tensor:
-    """samp_classify: float32 logits [B, classes] from the first token of each sequence."""
+    """samp_classify_workspace: float32 logits [B, classes] from the first token of each sequence."""
     B, S, H = hidden.shape
     Cn = w_cls.shape[0]
     logits = torch.empty((B, Cn), dtype=torch.float32, device=hidden.device)
-    _check(lib().samp_classify(_dp(hidden), B, S, H, _dp(w_pool), _dp(b_pool), _dp(w_cls), _dp(b_cls), Cn, _dp(logits), _stream()))
+    pooled = torch.empty((B, H), dtype=torch.float32, device=hidden.device)
+    _check(lib().samp_classify_workspace(_dp(hidden), B, S, H, _dp(w_pool), _dp(b_pool), _dp(w_cls), _dp(b_cls), Cn, _dp(pooled), _dp(logits),
+                                         _stream()))
     return logits
 
 

@@ -1090,8 +1090,8 @@ int samp_recommend(const double *accuracy, const double *latency, int32_t n, dou
     return SAMP_OK;
 }
 
-int samp_classify(const uint16_t *hidden, int32_t B, int32_t S, int32_t H, const uint16_t *w_pool, const float *b_pool,
-                  const uint16_t *w_cls, const float *b_cls, int32_t classes, float *logits, void *stream)
+static int classify(const uint16_t *hidden, int32_t B, int32_t S, int32_t H, const uint16_t *w_pool, const float *b_pool,
+                    const uint16_t *w_cls, const float *b_cls, int32_t classes, float *pooled, float *logits, void *stream)
 {
     if (!hidden || !w_pool || !b_pool || !w_cls || !b_cls || !logits) return fail(SAMP_ERR_ARG, "NULL pointer");
     if (B < 1 || S < 1 || classes < 1) return fail(SAMP_ERR_SHAPE, "B, S and classes must be >= 1");
@@ -1099,8 +1099,22 @@ int samp_classify(const uint16_t *hidden, int32_t B, int32_t S, int32_t H, const
     if (!aligned(hidden, 16) || !aligned(w_pool, 16) || !aligned(w_cls, 16))
         return fail(SAMP_ERR_ARG, "hidden and the weight matrices must be 16-byte aligned");
     HIP_TRY(launch_classify((const __half *)hidden, B, S, H, (const __half *)w_pool, b_pool, (const __half *)w_cls, b_cls,
-                            classes, logits, (hipStream_t)stream));
+                            classes, pooled, logits, (hipStream_t)stream));
     return SAMP_OK;
+}
+
+int samp_classify(const uint16_t *hidden, int32_t B, int32_t S, int32_t H, const uint16_t *w_pool, const float *b_pool,
+                  const uint16_t *w_cls, const float *b_cls, int32_t classes, float *logits, void *stream)
+{
+    return classify(hidden, B, S, H, w_pool, b_pool, w_cls, b_cls, classes, nullptr, logits, stream);
+}
+
+int samp_classify_workspace(const uint16_t *hidden, int32_t B, int32_t S, int32_t H, const uint16_t *w_pool, const float *b_pool,
+                            const uint16_t *w_cls, const float *b_cls, int32_t classes, float *pooled, float *logits, void *stream)
+{
+    if (!pooled) return fail(SAMP_ERR_ARG, "NULL pointer");
+    if (!aligned(pooled, 16)) return fail(SAMP_ERR_ARG, "the workspace must be 16-byte aligned");
+    return classify(hidden, B, S, H, w_pool, b_pool, w_cls, b_cls, classes, pooled, logits, stream);
 }
 
 int samp_probe_mfma_rate(int32_t fp16, int32_t random_operands, int32_t iters, void *dev_sink, void *stream, double *ops_per_s)

@@ -254,7 +254,7 @@ hipError_t launch_fill_f32(float *p, int n, float v, hipStream_t st);
 hipError_t launch_gelu_quant(const float *y, size_t n, float inv_s, int8_t *codes, float *fast, hipStream_t st);
 
 hipError_t launch_classify(const __half *hidden, int B, int S, int H, const __half *w_pool, const float *b_pool,
-                           const __half *w_cls, const float *b_cls, int C, float *logits, hipStream_t st);
+                           const __half *w_cls, const float *b_cls, int C, float *pooled, float *logits, hipStream_t st);
 
 // measured ceilings (probe.hip); both synchronise the stream
 hipError_t probe_mfma_rate(bool f16, bool random_operands, int iters, int *sink, hipStream_t st, double *ops_per_s);

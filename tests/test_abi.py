@@ -92,6 +92,7 @@ def test_later_entry_points_reject_bad_arguments_on_the_host(L):
     assert L.samp_classify(None, 1, 4, 128, buf, buf, buf, buf, 3, buf, None) == -1
     assert L.samp_classify(buf, 1, 4, 100, buf, buf, buf, buf, 3, buf, None) == -2          # H % 8
     assert L.samp_classify(buf, 1, 4, 128, buf, buf, buf, buf, 0, buf, None) == -2          # no classes
+    assert L.samp_classify_workspace(buf, 1, 4, 128, buf, buf, buf, buf, 3, None, buf, None) == -1
     assert L.samp_code_histogram(None, C.c_size_t(16), buf, None) == -1
     assert L.samp_code_histogram(buf, C.c_size_t(0), buf, None) == -2
     assert L.samp_set_gemm_config(9) == -1

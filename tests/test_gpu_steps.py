@@ -5,6 +5,8 @@ arithmetic is a fixed sequence of binary32 operations must be bit-exact too; fp1
 attention (binary32 accumulation in hardware order against binary64 in the oracle) are compared
 with a tolerance derived from that difference.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -830,6 +832,16 @@ def test_padding_removal_packs_valid_rows(P, quant):
     assert np.array_equal(row_map[:T], np.concatenate([b * S + np.arange(lens[b]) for b in range(B)]))
 
 
+@pytest.mark.parametrize("B,S", [(1, 1), (3, 63), (63, 65), (64, 2), (65, 1023), (17, 1024), (2, 1025), (130, 1100), (5, 2048)])
+def test_sequence_offsets_at_the_edges_of_pieces_and_scans(P, B, S):
+    """Pieces of 1024 mask entries, sixteen waves, prefix sums of 64 sequences at a time."""
+    lens = np.random.default_rng(B + S).integers(1, S + 1, B).astype(np.int32)
+    lens[0], lens[-1] = S, max(1, S // 2)
+    mask = (np.arange(S)[None, :] < lens[:, None]).astype(np.int32)
+    _, cu, _ = P.pack_rows(dev(np.zeros((B, S, 8), np.float16)), dev(mask))
+    assert np.array_equal(host(cu), _cu(lens))
+
+
 # ------------------------------------------------------------------ embedding kernel
 @pytest.mark.parametrize("H", [128, 768, 1024])
 def test_embedding_kernel_bit_exact(P, H):
@@ -890,6 +902,18 @@ def test_classification_target_at_ragged_widths(P, B, S, H, Cn):
     """Widths that leave part of the last 256-channel section (or almost all of the first) empty, and class counts on
     either side of the eight rows a wave takes at a time."""
     test_classification_target_within_accumulation_tolerance(P, B, S, H, Cn)
+
+
+@pytest.mark.parametrize("B,S,H,Cn", [(1, 1, 8, 1), (3, 2, 776, 9), (4, 1, 768, 8), (5, 3, 1024, 119), (33, 2, 264, 17)])
+def test_classification_target_without_a_workspace_gives_the_same_bits(P, B, S, H, Cn):
+    import torch
+    rng = np.random.default_rng(B + H)
+    t = [dev(rng.standard_normal(shape).astype(dtype)) for shape, dtype in (((B, S, H), np.float16), ((H, H), np.float16), (H, np.float32),
+                                                                           ((Cn, H), np.float16), (Cn, np.float32))]
+    logits = torch.empty((B, Cn), dtype=torch.float32, device="cuda")
+    ptr = [ctypes.c_void_p(x.data_ptr()) for x in t + [logits]]
+    assert P.lib().samp_classify(ptr[0], B, S, H, *ptr[1:5], Cn, ptr[5], ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert np.array_equal(host(logits), host(P.classify(*t)))
 
 
 @pytest.mark.parametrize("H", [8, 256, 264, 768, 1024, 1288, 4096])
