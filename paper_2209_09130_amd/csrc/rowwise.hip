@@ -446,25 +446,45 @@ hipError_t launch_embed_ln_nj(const EmbedArgs &a, hipStream_t st, const Timing *
 
 // ---------------------------------------------------------------------------------------------
 // Sequence offsets: cu[b] = number of valid tokens before sequence b (exclusive prefix sum of the
-// mask's row sums), cu[B] = T.  One block; wave w sums the rows w, w+16, ...
+// mask's row sums), cu[B] = T.  One block; what bounds it is latency, so a wave's item is up to 1024 entries of a row, whose
+// sixteen loads a lane has outstanding at once (three rows of 1100 entries by one wave each, 64 entries at a time: 8.8 us).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void seq_offsets_kernel(const int *__restrict__ mask, int B, int S, int *__restrict__ cu)
 {
     extern __shared__ int len[];                    // [B]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int b = wave; b < B; b += 16) {
-        int s = 0;
-        if (mask) { for (int i = lane; i < S; i += 64) s += mask[(size_t)b * S + i] != 0; }
-        else s = (lane == 0) ? S : 0;
+    for (int b = threadIdx.x; b < B; b += 1024) len[b] = mask ? 0 : S;
+    if (mask) {
+        __syncthreads();
+        const int pieces = (S + 1023) / 1024;       // of a row
+        for (int item = wave; item < B * pieces; item += 16) {
+            const int b = item / pieces, i0 = item % pieces * 1024 + lane;
+            const int *row = mask + (size_t)b * S;
+            int v[16], s = 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (lane == 0) len[b] = s;
+            for (int u = 0; u < 16; u++) v[u] = row[min(i0 + 64 * u, S - 1)];
+#pragma unroll
+            for (int u = 0; u < 16; u++) s += i0 + 64 * u < S && v[u] != 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+            if (lane == 0) atomicAdd(&len[b], s);
+        }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0) {                                // 64 sequences at a time
         int run = 0;
-        for (int b = 0; b < B; b++) { cu[b] = run; run += len[b]; }
-        cu[B] = run;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            const int b = b0 + lane, n = b < B ? len[b] : 0;
+            int upto = n;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int below = __shfl_up(upto, o, 64);
+                if (lane >= o) upto += below;
+            }
+            if (b < B) cu[b] = run + upto - n;
+            run += __shfl(upto, 63, 64);
+        }
+        if (lane == 0) cu[B] = run;
     }
 }
 
@@ -562,7 +582,8 @@ __global__ void fold_kernel(float s_in, const float *__restrict__ s_w, const flo
     if (b) b[n] = bias ? (float)((double)bias[n] / (double)s_out) : 0.0f;
 }
 
-// Calibration tap: running absmax of an fp16 [rows, cols] view with leading dimension ld.
+// Calibration tap: running absmax of an fp16 [rows, cols] view with leading dimension ld.  One atomic per block, and only where it would
+// raise the slot: with one per wave the 1536 of 1024 rows x 3072 took their turns at the one address for 25 us.
 __global__ __launch_bounds__(256) void absmax_f16_kernel(const __half *__restrict__ x, int host_rows,
                                                          const int *__restrict__ dev_rows, int cols, int ld,
                                                          float *__restrict__ slot)
@@ -576,8 +597,17 @@ __global__ __launch_bounds__(256) void absmax_f16_kernel(const __half *__restric
 #pragma unroll
         for (int e = 0; e < 8; e++) amax = __builtin_fmaxf(amax, __builtin_fabsf((float)v[e]));
     }
+    __shared__ float wave_amax[4];
     amax = wave_max(amax);
-    if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<int *>(slot), __float_as_int(amax));
+    if ((threadIdx.x & 63) == 0) wave_amax[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < 4; w++) amax = __builtin_fmaxf(amax, wave_amax[w]);
+        int *p = reinterpret_cast<int *>(slot);
+        const int bits = __float_as_int(amax);
+        if (bits > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, bits);
+    }
 }
 
 // The FFN1 epilogue's decision step on its own: codes = rne(GELU(y) / s_out); optionally also the
