@@ -375,6 +375,9 @@ SAMP_API int samp_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packe
  * byte for byte.  x dev fp16 [T,hidden], w_qkv dev fp16 [3 hidden, hidden], bias dev float [3 hidden] or NULL.  */
 SAMP_API int samp_qkv_attention_f16(const uint16_t *x, const uint16_t *w_qkv, const float *bias, const int32_t *cu_seqlens,
                                     int32_t B, int32_t max_len, int32_t hidden, int32_t heads, uint16_t *ctx, void *stream);
+/* The same on w_qkv packed by samp_pack_weight_f16, for sequences of at most 128 tokens; hidden % 128 == 0. */
+SAMP_API int samp_qkv_attention_f16_packed(const uint16_t *x, const uint16_t *w_packed, const float *bias, const int32_t *cu_seqlens,
+                                    int32_t B, int32_t max_len, int32_t hidden, int32_t heads, uint16_t *ctx, void *stream);
 SAMP_API int samp_attention_f16(const uint16_t *qkv, const int32_t *cu_seqlens, int32_t B, int32_t max_len, int32_t hidden,
                                 int32_t heads, uint16_t *ctx, void *stream);
 

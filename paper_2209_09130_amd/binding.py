@@ -382,6 +382,15 @@ def qkv_attention_f16(x, w_qkv, bias, cu, max_len: int, heads: int):
     return ctx
 
 
+def qkv_attention_f16_packed(x, w_packed, bias, cu, max_len: int, heads: int):
+    """qkv_attention_f16 on weights that pack_weight_f16 packed, for sequences of at most 128 tokens."""
+    T, H = x.shape
+    B = _batch_of(cu, T, max_len)
+    ctx = torch.zeros((T, H), dtype=torch.float16, device=x.device)
+    _check(lib().samp_qkv_attention_f16_packed(_dp(x), _dp(w_packed), _dp(bias), _dp(cu), B, max_len, H, heads, _dp(ctx), _stream()))
+    return ctx
+
+
 def classify(hidden: torch.Tensor, w_pool, b_pool, w_cls, b_cls) -> torch.Tensor:
     """samp_classify_workspace: float32 logits [B, classes] from the first token of each sequence."""
     B, S, H = hidden.shape

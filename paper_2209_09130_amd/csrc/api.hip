@@ -293,6 +293,18 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
         const bool packed = Wp && !(i8 ? gemm_i8_reads_rows(rows, N) : gemm_f16_reads_rows(rows, N, K));
         return Prefetch{packed ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};
     };
+    // Attention blocks whose QKV GEMM and attention run as one kernel.  Its block is one (sequence, head) and a tile of 128 tokens: from 49 to 128
+    // tokens, and about 128 such blocks per launch.  Shorter sequences leave most of the tile empty, and every sequence reads all of the
+    // weights; longer ones do better with the QKV GEMM on packed weights and the attention kernel.  Forward, us, one kernel / two, by sequences x
+    // tokens: BERT-base Fully-Quant 256 x 16 1191 / 877, 128 x 32 924 / 827, 24 x 40 471 / 451, 64 x 64 813 / 831, 32 x 128 788 / 845; FP16
+    // 256 x 16 2060 / 1314, 24 x 40 686 / 671, 64 x 64 1269 / 1320, 32 x 128 1202 / 1319, 64 x 144 3060 / 2521, 32 x 40..200 1683 / 1548, 16 x 256
+    // 1347 / 1347; BERT-large Fully-Quant 128 x 32 2683 / 2266, 64 x 64 2290 / 2281, 16 x 64 1069 / 1109, 32 x 128 2114 / 2305, FP16 64 x 64 3776 /
+    // 3659, 32 x 128 3300 / 3638, Quant-FFN-Only 8 x 160 2010 / 1650, 32 x 256 4880 / 4841 (BERT-base there 1589 / 1623).  By blocks, 128 tokens,
+    // before the weights were packed: batch 4 +12 %, 8 +-0, 16 -1.6 %, 32 -4.9 %, 256 -6.8 %.
+    auto one_qkv_kernel = [&](const Layer &Y) {
+        if (Y.mode & SAMP_P_FP16) return false;
+        return enc->fusion_wanted == 2 ? S <= 256 : enc->fusion_wanted == 0 && S > 48 && S <= 128 && B * heads >= 128;
+    };
     for (int l = 0; l < Lc; l++) {
         const Layer &Y = enc->L[l];
         const bool mha8 = Y.mode & 1, ffn8 = Y.mode & 2, last = (l == Lc - 1);
@@ -300,13 +312,9 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
         float *am = calib ? w.absmax + l * 10 : nullptr;
 
         if (mha8) {
-            // sequences of at most 128 tokens: the QKV tile of a (sequence, head) is one block tile and all that head's
-            // attention needs, so one kernel does both.  It pays from about 128 such blocks per launch (BERT-base, 128
-            // tokens: batch 4 +12 %, 8 +-0, 16 -1.6 %, 32 -4.9 %, 256 -6.8 % on the forward).  The 256-token flavour
-            // (one block per CU, a wave's 64 queries one after the other) loses against the two kernels, whose exact
-            // exponentials run four blocks to a CU (BERT-large 32 x 256: +6 %); it runs only when forced.
-            const bool can_fuse = S <= (enc->fusion_wanted == 2 ? 256 : 128) && !(Y.mode & SAMP_P_FP16);
-            if (can_fuse && (enc->fusion_wanted == 2 || (enc->fusion_wanted == 0 && B * heads >= 128))) {
+            // (of 129 to 256 tokens only when forced: one block per CU, a wave's 64 queries one after the other, loses against the two
+            // kernels, whose exact exponentials run four blocks to a CU: BERT-large 32 x 256 +6 %)
+            if (one_qkv_kernel(Y)) {
                 const bool p_unsigned = (Y.mode & SAMP_P_UNSIGNED) != 0;
                 const Timing *tm = timing(enc, SAMP_PROF_QKV_ATTN);
                 hipError_t e = !Y.p_qkv ? hipErrorNotSupported
@@ -331,16 +339,9 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                    nullptr, rows, H, H, st, timing(enc, SAMP_PROF_ATTN_OUT)));
         } else {
             if (am) HIP_TRY(launch_absmax_f16((const __half *)x, rows, H, H, am + 0, st));
-            // (calibration taps q, k, v and the softmax output, so it keeps the two kernels; with binary32 exponentials
-            //  the 256-token flavour pays as well: BERT-large 32 x 256 with FP16 attention blocks -12.7 %)
-            if (!am && S <= 256 && (enc->fusion_wanted == 2 || (enc->fusion_wanted == 0 && B * heads >= 128))) {
-                // up to about one block per CU the INT8 feed-forward kernels of the other batch group need the LDS more than
-                // this kernel needs 128-byte stages (Quant-FFN-Only, 6 layers, us, smaller / larger ring by blocks per launch: width
-                // 768 in two groups 192: 492 / 501, 240: 580 / 582, 252: 597 / 594, 264: 683 / 686, 312: 750 / 741, 384: 862 / 845,
-                // 576: 1149 / 1100; in one group 192: 355 / 359, 240: 407 / 413; width 1024 in two groups 192: 632 / 636, 240: 686 / 681,
-                // 256: 715 / 708, in one 192: 489 / 499)
-                const bool small_ring = ffn8 && B * heads < 256;
-                HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, Y.b_qkv, cu, B, S, H, 0.125f, small_ring,
+            // (calibration taps q, k, v and the softmax output, so it keeps the two kernels)
+            if (!am && one_qkv_kernel(Y)) {
+                HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, (const __half *)Y.p_qkv, Y.b_qkv, cu, B, S, H, 0.125f,
                                                  (__half *)w.ctx, st, timing(enc, SAMP_PROF_QKV_ATTN)));
             } else {
                 HIP_TRY(launch_gemm_f16((const __half *)x, (const __half *)Y.w_qkv, (const __half *)Y.p_qkv, Y.b_qkv, false, (__half *)w.qkv, rows,
@@ -998,16 +999,30 @@ int samp_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const 
     return qkv_attention_i8(x, w_packed, m, b, cu, B, max_len, hidden, heads, s_q, s_k, s_v, s_p, s_ctx, p_kind, ctx, stream, true);
 }
 
+static int qkv_attention_f16(const uint16_t *x, const uint16_t *w, const float *bias, const int32_t *cu, int32_t B, int32_t max_len,
+                             int32_t hidden, int32_t heads, uint16_t *ctx, void *stream, bool packed)
+{
+    if (!x || !w || !ctx) return fail(SAMP_ERR_ARG, "NULL pointer");
+    const int longest = packed ? 128 : 256;
+    if (B < 1 || max_len < 1 || max_len > longest) return fail(SAMP_ERR_SHAPE, "B >= 1 and 1 <= max_len <= %d required", longest);
+    if (heads < 1 || hidden != heads * 64) return fail(SAMP_ERR_SHAPE, "head size must be 64");
+    if (packed && heads % 2) return fail(SAMP_ERR_SHAPE, "an even number of heads required");
+    if (!aligned(x, 16) || !aligned(w, 16) || !aligned(ctx, 16)) return fail(SAMP_ERR_ARG, "tensors must be 16-byte aligned");
+    HIP_TRY(launch_qkv_attention_f16((const __half *)x, packed ? nullptr : (const __half *)w, packed ? (const __half *)w : nullptr, bias, cu, B,
+                                     max_len, hidden, 0.125f, (__half *)ctx, (hipStream_t)stream, nullptr));
+    return SAMP_OK;
+}
+
 int samp_qkv_attention_f16(const uint16_t *x, const uint16_t *w_qkv, const float *bias, const int32_t *cu, int32_t B,
                            int32_t max_len, int32_t hidden, int32_t heads, uint16_t *ctx, void *stream)
 {
-    if (!x || !w_qkv || !ctx) return fail(SAMP_ERR_ARG, "NULL pointer");
-    if (B < 1 || max_len < 1 || max_len > 256) return fail(SAMP_ERR_SHAPE, "B >= 1 and 1 <= max_len <= 256 required");
-    if (heads < 1 || hidden != heads * 64) return fail(SAMP_ERR_SHAPE, "head size must be 64");
-    if (!aligned(x, 16) || !aligned(w_qkv, 16) || !aligned(ctx, 16)) return fail(SAMP_ERR_ARG, "tensors must be 16-byte aligned");
-    HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)w_qkv, bias, cu, B, max_len, hidden, 0.125f, false, (__half *)ctx,
-                                     (hipStream_t)stream, nullptr));
-    return SAMP_OK;
+    return qkv_attention_f16(x, w_qkv, bias, cu, B, max_len, hidden, heads, ctx, stream, false);
+}
+
+int samp_qkv_attention_f16_packed(const uint16_t *x, const uint16_t *w_packed, const float *bias, const int32_t *cu, int32_t B,
+                                  int32_t max_len, int32_t hidden, int32_t heads, uint16_t *ctx, void *stream)
+{
+    return qkv_attention_f16(x, w_packed, bias, cu, B, max_len, hidden, heads, ctx, stream, true);
 }
 
 int samp_attention_f16(const uint16_t *qkv, const int32_t *cu, int32_t B, int32_t max_len, int32_t hidden, int32_t heads,

@@ -374,8 +374,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
 // come last, into the stage that the last one but one leaves free (LATE).  A stand-in that only loads the stages pulls 35 to 41
 // bytes per clock and CU like this, 24 with 64-byte stages; forward, three 64-byte stages against two of 128: BERT-base 256 x 128
 // Fully-Quant 4.43 / 4.21 ms, 32 x 128 FP16 1.380 / 1.324, BERT-large 64 x 128 Fully-Quant 3.94 / 3.78, Quant-FFN-Only 4.73 / 4.48.  Three 64-byte stages are kept for rows that are no
-// multiple of 128 bytes (an odd number of heads in INT8) and for QT = 2, whose registers do not hold 128-byte stages' offsets,
-// and where the caller asks for the smaller ring (62 KB).
+// multiple of 128 bytes (an odd number of heads in INT8) and for QT = 2, whose registers do not hold 128-byte stages' offsets.
 template <int QT, int STAGE>                               // QT 32-query tiles per wave: sequences of at most 128 QT tokens
 struct QkvTile {                                           // the block tile both flavours of the kernel share
     static constexpr int TM = 2 * QT, TN = 3, BKB = STAGE, NSTAGE = STAGE == 128 ? 2 : 3, NWAVES = 4, CH = BKB / 16, RPI = 64 / CH, KS = BKB / 32;
@@ -838,25 +837,33 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
     attend_i8<1, PU>(lds, lds + K_OFF, lds + VT_OFF, exp_table, n, sq.t0, head, H, m_sc, inv_sp, m_ctx, ctx, wave, lane);
 }
 
+constexpr int QKV_F16_PACKED_D = 2, QKV_F16_PACKED_RING = stream_ring_bytes<true, 4, QKV_F16_PACKED_D>();
+
 // The FP16 flavour of the kernel above: fp16 QKV GEMM with its bias, q, k, v rounded to fp16 into LDS, then the
 // arithmetic of attention_f16_kernel.  The products P.V of the four key tiles are formed from zero one by one and
 // added in the order in which that kernel adds its four waves' partial contexts (tiles past the end add +0), and the
 // row sums likewise, so the context is the same bytes as from the two kernels.
-template <int QT, int STAGE>
+// PACKED (at most 128 tokens, weights in the order of the 32 x 32 x 16 product): the tile loop of the GEMMs on packed weights, in the same
+// 2 x 2 arrangement of waves (six channel blocks do not deal out over four waves), so two waves each load the same weight rows.  55 KB of
+// LDS instead of 80, two stages in flight instead of one; BERT-base 32 x 128 forward, us, row-major / packed: FP16 1240 / 1196, Quant-FFN-Only
+// 941 / 891.
+template <int QT, int STAGE, bool PACKED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ bias,
                               const int *__restrict__ cu, int max_len, int H, float scale, __half *__restrict__ ctx)
 {
     typedef QkvTile<QT, STAGE> Tile;
-    constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, RING_BYTES = Tile::RING_BYTES, NKT = 4 * QT;
+    constexpr bool LATE = Tile::LATE && !PACKED;
+    constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, NKT = 4 * QT;
+    constexpr int RING_BYTES = PACKED ? QKV_F16_PACKED_RING : Tile::RING_BYTES;
     constexpr int QK_STRIDE = 144, VT_STRIDE = 2 * BM + 8;        // bytes per token row of q / k (64 fp16 + pad), per channel row of V^T (all keys + pad)
     constexpr int TAB_BYTES = 1024;                               // bias of the 192 columns
-    constexpr int Q_OFF = Tile::LATE ? TAB_BYTES : 0, K_OFF = Q_OFF + BM * QK_STRIDE, VT_OFF = K_OFF + BM * QK_STRIDE;
+    constexpr int Q_OFF = LATE ? TAB_BYTES : 0, K_OFF = Q_OFF + BM * QK_STRIDE, VT_OFF = K_OFF + BM * QK_STRIDE;
     constexpr int QKV_BYTES = VT_OFF + 64 * VT_STRIDE;            // q, k and V^T take the place of the ring (and more, for 256 tokens)
     constexpr int TAB_OFF = QKV_BYTES > RING_BYTES ? QKV_BYTES : RING_BYTES;
-    static_assert(!Tile::LATE || QKV_BYTES + TAB_BYTES <= RING_BYTES, "clear of a table at either end of the ring");
+    static_assert(!LATE || QKV_BYTES + TAB_BYTES <= RING_BYTES, "clear of a table at either end of the ring");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    float *tab = reinterpret_cast<float *>(lds + (!Tile::LATE ? TAB_OFF : (H / 64) & 1 ? RING_BYTES - TAB_BYTES : 0));
+    float *tab = reinterpret_cast<float *>(lds + (!LATE ? TAB_OFF : (H / 64) & 1 ? RING_BYTES - TAB_BYTES : 0));
 
     const int heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -869,8 +876,8 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     const int r = lane & 31, g = lane >> 5;
 
     v16f acc[TN][TM];
-    qkv_tile_gemm_any<QT, STAGE, true>(X, W, sq.t0, n, head, H, 2 * H, lds, wave, lane, acc, [&]() {
-        if constexpr (Tile::LATE) {
+    auto load_tables = [&]() {
+        if constexpr (LATE || PACKED) {
             if (wave < 3) {
                 if (bias) load_direct(tab + wave * 64, bias + wave * H + head * 64, 64, lane);
                 else tab[wave * 64 + lane] = 0.0f;
@@ -878,7 +885,44 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
             return;
         }
         for (int c = tid; c < BN; c += 256) tab[c] = bias ? bias[(c >> 6) * H + head * 64 + (c & 63)] : 0.0f;
-    });
+    };
+    if constexpr (PACKED) {
+        unsigned offa[stream_loads<true, 4>()];
+#pragma unroll
+        for (int j = 0; j < stream_loads<true, 4>(); j++) {
+            const int srow = 8 * (wave + 4 * j) + (lane >> 3);
+            offa[j] = (unsigned)min(srow, n - 1) * (unsigned)(2 * H) + (((lane & 7) ^ swz<128>(srow)) << 4);
+        }
+        unsigned woff[TN];
+#pragma unroll
+        for (int io = 0; io < TN; io++) {
+            const int nl = wn + 32 * io;
+            woff[io] = (unsigned)((nl >> 6) * H + head * 64 + (nl & 63)) * (unsigned)(2 * H);
+        }
+#pragma unroll
+        for (int io = 0; io < TN; io++)
+#pragma unroll
+            for (int j = 0; j < TM; j++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[io][j][e] = 0.0f;
+        // values (the last two channel blocks of odd waves): token rows first, as in qkv_tile_gemm()
+        auto loop = [&](auto vwave, auto live) {
+            stream_tile_loop<true, TM, TN, QKV_F16_PACKED_D, 2>(X + (size_t)sq.t0 * (2 * H), offa, W, woff, H / 64, lds, wave, lane, load_tables,
+                [&](int t, int i, const v4i &w, const v4i &f) {
+                    const bool swap = decltype(vwave)::value && t > 0;
+                    if (live(i)) acc[t][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, swap ? f : w),
+                                                                                   __builtin_bit_cast(v8h, swap ? w : f), acc[t][i], 0, 0, 0);
+                }, wave >> 1);
+        };
+        auto either = [&](auto vwave) {
+            if (n > BM - 32) loop(vwave, [](int) { return true; });
+            else loop(vwave, [&](int i) { return wm + 32 * i < n; });
+        };
+        if (wave & 1) either(std::true_type());
+        else either(std::false_type());
+    } else {
+        qkv_tile_gemm_any<QT, STAGE, true>(X, W, sq.t0, n, head, H, 2 * H, lds, wave, lane, acc, load_tables);
+    }
 
     // fp16(acc + bias) into LDS: q and k as token rows, v transposed (lane layouts as in the INT8 flavour)
 #pragma unroll
@@ -1778,10 +1822,12 @@ hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packe
     return p_unsigned ? go(qkv_attention_i8_packed_kernel<true, 2>) : go(qkv_attention_i8_packed_kernel<false, 2>);
 }
 
-hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const float *bias, const int *cu, int B, int max_len,
-                                    int H, float scale, bool small_ring, __half *ctx, hipStream_t st, const Timing *tm)
+hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const __half *w_packed, const float *bias, const int *cu, int B,
+                                    int max_len, int H, float scale, __half *ctx, hipStream_t st, const Timing *tm)
 {
     if (max_len > 256 || H % 64 || B <= 0) return hipErrorInvalidValue;
+    const bool packed = w_packed && max_len <= 128 && H % 128 == 0;
+    if (!packed && !w_qkv) return hipErrorNotSupported;
     const dim3 grid((unsigned)(B * (H / 64)));
     auto go = [&](auto kern, size_t lds, std::atomic<bool> &attr_set) {
         if (!attr_set.load(std::memory_order_acquire)) {
@@ -1789,14 +1835,15 @@ hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const 
             if (e != hipSuccess) return e;
             attr_set.store(true, std::memory_order_release);
         }
-        launch_kernel(kern, grid, dim3(256), lds, st, tm, (const char *)x, (const char *)w_qkv, bias, cu, max_len, H, scale, ctx);
+        launch_kernel(kern, grid, dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, scale, ctx);
         return hipGetLastError();
     };
     static std::atomic<bool> attr_set[3];
-    constexpr size_t tab = 192 * sizeof(float), qkv_bytes = 2 * 256 * 144 + 64 * (2 * 256 + 8);
-    if (max_len > 128) return go(qkv_attention_f16_kernel<2, 64>, std::max<size_t>(qkv_bytes, QkvTile<2, 64>::RING_BYTES) + tab, attr_set[2]);
-    if (small_ring) return go(qkv_attention_f16_kernel<1, 64>, QkvTile<1, 64>::RING_BYTES + tab, attr_set[1]);
-    return go(qkv_attention_f16_kernel<1, 128>, QkvTile<1, 128>::RING_BYTES, attr_set[0]);
+    constexpr size_t tab = 192 * sizeof(float);
+    constexpr auto qkv_bytes = [](size_t BM) { return 2 * BM * 144 + 64 * (2 * BM + 8); };
+    if (packed) return go(qkv_attention_f16_kernel<1, 128, true>, std::max<size_t>(qkv_bytes(128), QKV_F16_PACKED_RING) + tab, attr_set[1]);
+    if (max_len > 128) return go(qkv_attention_f16_kernel<2, 64, false>, std::max<size_t>(qkv_bytes(256), QkvTile<2, 64>::RING_BYTES) + tab, attr_set[2]);
+    return go(qkv_attention_f16_kernel<1, 128, false>, QkvTile<1, 128>::RING_BYTES, attr_set[0]);
 }
 
 hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,

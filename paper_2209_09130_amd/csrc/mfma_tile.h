@@ -92,18 +92,20 @@ template <bool HALF> struct StreamGeometry {
 template <bool HALF, int MT, int D> constexpr int stream_ring_bytes() { return (D + 1) * StreamGeometry<HALF>::ROWS * MT * 128; }
 template <bool HALF, int MT> constexpr int stream_loads() { return StreamGeometry<HALF>::ROWS * MT / 32; }     // token-row loads of a wave and stage
 
-// MT token tiles, NTW weight blocks per wave.  abase: first token row; offa: this lane's offsets into the rows of its pieces (8 rows x 128
+// MT token tiles, NTW weight blocks per wave.  SPLIT: the block's token rows are split over that many groups of waves (this wave's: part), so
+// that waves of different groups load the same weights.  abase: first token row; offa: this lane's offsets into the rows of its pieces (8 rows x 128
 // bytes, swizzled); wbase: the wave's packed row blocks; KT: stages of 128 bytes, a multiple of D.  started() runs once the first stage is
 // requested (what it loads has arrived when the first product runs); mma(t, i, w, f) adds the product of weight block t and token tile i.
 // On return the ring is idle.
-template <bool HALF, int MT, int NTW, int D, class Started, class Mma>
-__device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[stream_loads<HALF, MT>()], const char *wbase,
-                                                 const unsigned (&woff)[NTW], int KT, char *lds, int wave, int lane, Started started, Mma mma)
+template <bool HALF, int MT, int NTW, int D, int SPLIT = 1, class Started, class Mma>
+__device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[stream_loads<HALF, MT * SPLIT>()], const char *wbase,
+                                                 const unsigned (&woff)[NTW], int KT, char *lds, int wave, int lane, Started started, Mma mma,
+                                                 int part = 0)
 {
     constexpr int ROWS = StreamGeometry<HALF>::ROWS, KS = StreamGeometry<HALF>::KS, TILE = ROWS * 128;
-    constexpr int SLOT = TILE * MT, RING = stream_ring_bytes<HALF, MT, D>();
+    constexpr int SLOT = TILE * MT * SPLIT, RING = stream_ring_bytes<HALF, MT * SPLIT, D>();
     constexpr int G = MT < 4 ? MT : 4, H = MT / G, STEPS = KS * H;         // token tiles per step; steps of a stage
-    constexpr int NLDA = stream_loads<HALF, MT>(), PER = NLDA + KS * NTW;  // loads of a wave and stage: token rows; all
+    constexpr int NLDA = stream_loads<HALF, MT * SPLIT>(), PER = NLDA + KS * NTW;  // loads of a wave and stage: token rows; all
     static_assert(MT % G == 0 && H <= 2 && D >= 2 && NLDA >= 1, "whole steps, whole pieces per wave");
     const int r = lane & (ROWS - 1), q = lane / ROWS;
     const unsigned offw = 16 * lane;
@@ -122,7 +124,7 @@ __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsign
     const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     unsigned addr[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) addr[ks] = lds_base + r * 128 + (((8 / KS * ks + q) ^ swz<128>(r)) << 4);
+    for (int ks = 0; ks < KS; ks++) addr[ks] = lds_base + part * (MT * TILE) + r * 128 + (((8 / KS * ks + q) ^ swz<128>(r)) << 4);
 
 #pragma unroll
     for (int s = 0; s < D; s++) {

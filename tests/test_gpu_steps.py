@@ -460,6 +460,23 @@ def test_qkv_attention_on_packed_weights_gives_the_same_codes(P, lens, heads, un
         if len(set(lens)) == 1: assert np.array_equal(run(None), want)
 
 
+@pytest.mark.parametrize("lens,heads", [([128, 113, 97, 96, 65, 64, 33, 32, 1], 4), ([128, 128], 12), ([33, 97, 17], 2), ([70], 16)])
+def test_fp16_qkv_attention_on_packed_weights_gives_the_same_bytes(P, lens, heads):
+    """Sequences on both sides of the edges of 32-token tiles and of the two halves of the waves; two to sixteen stages of K."""
+    rng = np.random.default_rng(heads + len(lens))
+    cu = _cu(lens)
+    H, T = heads * 64, int(cu[-1])
+    x = dev(rng.standard_normal((T, H)).astype(np.float16))
+    w = (rng.standard_normal((3 * H, H)) * 0.05).astype(np.float16)
+    packed, w = P.pack_weight_f16(dev(w)), dev(w)
+    for bias in (dev((rng.standard_normal(3 * H) * 0.1).astype(np.float32)), None):
+        want = host(P.qkv_attention_f16(x, w, bias, dev(cu), max(lens), heads))
+        assert np.abs(want).max() > 0.1
+        assert np.array_equal(host(P.qkv_attention_f16_packed(x, packed, bias, dev(cu), max(lens), heads)), want)
+        if len(set(lens)) == 1:
+            assert np.array_equal(host(P.qkv_attention_f16_packed(x, packed, bias, None, max(lens), heads)), want)
+
+
 @pytest.mark.parametrize("M,N,K", [(130, 384, 384), (65, 192 * 2, 640)])
 def test_tables_that_arrive_with_the_last_stage_of_an_odd_number(P, M, N, K):
     """128 x 192 tiles (configuration 6): the epilogue's tables take the ring stage that the last one but one leaves free,
