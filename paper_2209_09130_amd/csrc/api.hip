@@ -305,6 +305,18 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
         if (Y.mode & SAMP_P_FP16) return false;
         return enc->fusion_wanted == 2 ? S <= 256 : enc->fusion_wanted == 0 && S > 48 && S <= 128 && B * heads >= 128;
     };
+    // a LayerNorm step of few rows and the GEMM behind it as one launch (a launch that is timed stays apart); true: done
+    auto ln_and_gemm = [&](const AddLnArgs &a, GemmEpilogue epi, const void *Wp, void *to, const float *m, const float *b, const GeluTable *gt, int N,
+                           bool *done) -> int {
+        *done = false;
+        if (enc->prof_which != SAMP_PROF_OFF) return SAMP_OK;
+        const hipError_t e = launch_ln_gemm_i8(a, epi, (const int8_t *)Wp, to, m, b, gt, N, st);
+        if (e == hipErrorNotSupported) return SAMP_OK;
+        HIP_TRY(e);
+        *done = true;
+        return SAMP_OK;
+    };
+    bool qkv_done = false;                          // this layer's QKV GEMM ran with the LayerNorm step before it
     for (int l = 0; l < Lc; l++) {
         const Layer &Y = enc->L[l];
         const bool mha8 = Y.mode & 1, ffn8 = Y.mode & 2, last = (l == Lc - 1);
@@ -325,8 +337,9 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                                 Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
                 HIP_TRY(e);
             } else {
-                HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, (const int8_t *)Y.p_qkv, w.qkv, Y.m_qkv, Y.bq_qkv, 0.f,
-                                       nullptr, rows, 3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
+                if (!qkv_done)
+                    HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)x, (const int8_t *)Y.w_qkv, (const int8_t *)Y.p_qkv, w.qkv, Y.m_qkv, Y.bq_qkv,
+                                           0.f, nullptr, rows, 3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
                 if (Y.mode & SAMP_P_FP16)
                     HIP_TRY(launch_attention_i8_p16((const int8_t *)w.qkv, cu, B, S, H, heads, Y.m_sc, Y.m_ctx, (int8_t *)w.ctx,
                                                     st, timing(enc, SAMP_PROF_ATTN)));
@@ -357,15 +370,18 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                     st, timing(enc, SAMP_PROF_ATTN_OUT)));
             if (am) HIP_TRY(launch_absmax_f16((const __half *)w.ao, rows, H, H, am + 6, st));
         }
+        bool ffn1_done = false;
         {   // bias + residual + LayerNorm (+ quantise for an INT8 FFN); residual = the block's own input tensor
             AddLnArgs a{w.ao, mha8, Y.s.attn_out, Y.b_o, x, mha8, Y.s.x, Y.g1, Y.be1, c.ln_eps,
                         w.h1, ffn8, Y.s.ffn_in, nullptr, am ? am + 7 : nullptr, rows, H};
+            if (int rc = ln_and_gemm(a, EPI_GELU_QUANT, Y.p_f1, w.f1, Y.m_f1, Y.b_f1, &Y.gelu, F, &ffn1_done)) return rc;
             const Prefetch next[2] = {ahead(Y.w_f1, Y.p_f1, F, H, ffn8), ahead(Y.w_f2, Y.p_f2, H, F, ffn8)};
-            HIP_TRY(launch_add_ln(a, fetch_ahead ? next : nullptr, st, timing(enc, SAMP_PROF_LN1)));
+            if (!ffn1_done) HIP_TRY(launch_add_ln(a, fetch_ahead ? next : nullptr, st, timing(enc, SAMP_PROF_LN1)));
         }
         if (ffn8) {
-            HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, (const int8_t *)Y.p_f1, w.f1, Y.m_f1, Y.b_f1,
-                                   1.0f / Y.s.ffn_mid, &Y.gelu, rows, F, H, st, timing(enc, SAMP_PROF_FFN1)));
+            if (!ffn1_done)
+                HIP_TRY(launch_gemm_i8(EPI_GELU_QUANT, (const int8_t *)w.h1, (const int8_t *)Y.w_f1, (const int8_t *)Y.p_f1, w.f1, Y.m_f1, Y.b_f1,
+                                       1.0f / Y.s.ffn_mid, &Y.gelu, rows, F, H, st, timing(enc, SAMP_PROF_FFN1)));
             HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.f1, (const int8_t *)Y.w_f2, (const int8_t *)Y.p_f2, w.f2, Y.m_f2, nullptr, 0.f,
                                    nullptr, rows, H, F, st, timing(enc, SAMP_PROF_FFN2)));
         } else {
@@ -382,7 +398,10 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                         dst, next8, next8 ? enc->L[l + 1].s.x : 1.0f, (last && !calib) ? row_map : nullptr, nullptr, rows, H};
             const Layer &X = enc->L[last ? l : l + 1];
             const Prefetch next[2] = {ahead(X.w_qkv, X.p_qkv, 3 * H, H, X.mode & 1), ahead(X.w_o, X.p_o, H, H, X.mode & 1)};
-            HIP_TRY(launch_add_ln(a, fetch_ahead && !last ? next : nullptr, st, timing(enc, SAMP_PROF_LN2)));
+            qkv_done = false;
+            if (next8 && !one_qkv_kernel(X))
+                if (int rc = ln_and_gemm(a, EPI_REQUANT, X.p_qkv, w.qkv, X.m_qkv, X.bq_qkv, nullptr, 3 * H, &qkv_done)) return rc;
+            if (!qkv_done) HIP_TRY(launch_add_ln(a, fetch_ahead && !last ? next : nullptr, st, timing(enc, SAMP_PROF_LN2)));
             x = dst;
             yi ^= 1;
         }

@@ -23,6 +23,7 @@
 // entries and forced configurations.
 #include "samp_common.h"
 #include "mfma_tile.h"
+#include "ln_wave.h"
 
 #include <atomic>
 #include <type_traits>
@@ -1285,6 +1286,92 @@ hipError_t launch_small_any(const void *A, const void *W, void *out, const Epi &
     return hipErrorNotSupported;
 }
 
+// ---- LayerNorm step and the GEMM behind it, few rows -------------------------------------------------------------
+// Up to some dozens of tokens a layer is a chain of launches, each 3.6 us long whatever it does.  Here every block forms the LayerNorm rows
+// that it multiplies by itself: a wave one row (int8 in, residual and out; the arithmetic of add_ln_wave_kernel), its codes into LDS, then the
+// wave's 128 channels of K times 64 channels of packed weights, which were requested before the row was; the waves' partial sums meet in
+// LDS.  K = 128 NW.  The blocks of the first 64 channels store the codes for the next residual.  What a launch and its gap cost (3.9 us) is
+// replaced by the row's arithmetic (0.7 us), done again by every block of its row.
+template <class Epi, int NW>
+struct LnGemm {
+    static constexpr int K = 128 * NW, STRIDE = K + 16, A_OFF = NW * 4096, TAB_OFF = A_OFF + NW * STRIDE;
+};
+
+template <class Epi, int NW>
+__global__ __launch_bounds__(64 * NW)
+void gemm_nt_ln_kernel(AddLnArgs a, const char *__restrict__ Wp, char *__restrict__ out, Epi epi, int N, int tiles_n)
+{
+    typedef LnGemm<Epi, NW> G;
+    constexpr int K = G::K, CPL = K / 64;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    float *tab = reinterpret_cast<float *>(lds + G::TAB_OFF);
+    const int M = a.rows.dev_rows ? *a.rows.dev_rows : a.rows.host_rows;
+    const int tiles_m = (M + NW - 1) / NW, tiles = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= tiles) return;
+    const int tile = xcd_contiguous(blockIdx.x, tiles);
+    const int m0 = (tile % tiles_m) * NW, n0 = (tile / tiles_m) * 64;          // channels outermost: an XCD reads an eighth of the weights
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, q = lane >> 4;
+
+    const auto weights = buffer_of(Wp);
+    v4i w[2][4];
+#pragma unroll
+    for (int t = 0; t < 4; t++)
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++)
+            w[ks][t] = __builtin_amdgcn_raw_buffer_load_b128(weights, 16 * lane, ((n0 / 16 + t) * (K / 64) + 2 * wave + ks) * 1024, 0);
+    epi.load_tables_direct(tab, n0, 64, wave, NW, lane);
+
+    const int row = m0 + wave, c = lane * CPL;
+    float z[CPL], gamma[CPL], beta[CPL], y[CPL];
+    const double sum = ln_row_wave<CPL, true, true>(a, min(row, M - 1), c, z, gamma, beta);
+    ln_normalise_wave<CPL>(z, sum, gamma, beta, a.eps, y);
+    const float inv_s = 1.0f / a.s_out;
+#pragma unroll
+    for (int d = 0; d < CPL / 4; d++) {
+        const int codes = pack_row_codes(y + 4 * d, inv_s);
+        *reinterpret_cast<int *>(lds + G::A_OFF + wave * G::STRIDE + c + 4 * d) = codes;
+        if (n0 == 0 && row < M) *reinterpret_cast<int *>((int8_t *)a.out + (size_t)row * K + c + 4 * d) = codes;
+    }
+    wait_vm_and_barrier<0>();                                     // the rows and the direct loads of the tables are in LDS
+
+    v4i acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; t++) acc[t] = v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) {                              // (a product has sixteen rows; those past the block's NW repeat the last one)
+        const v4i f = *reinterpret_cast<const v4i *>(lds + G::A_OFF + min(r, NW - 1) * G::STRIDE + wave * 128 + ks * 64 + q * 16);
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[ks][t], f, acc[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; t++) *reinterpret_cast<v4i *>(lds + (wave * 4 + t) * 1024 + lane * 16) = acc[t];
+    __syncthreads();
+    if (wave >= 4) return;                                        // lane: token r, channels 16 wave + 4 q .. + 3
+    v4i total = {0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < NW; u++) total += *reinterpret_cast<const v4i *>(lds + (u * 4 + wave) * 1024 + lane * 16);
+    const int nl = 16 * wave + 4 * q, pk = epi.four(total, tab, 64, nl);
+    if (r < NW && m0 + r < M) *reinterpret_cast<int *>(out + (size_t)(m0 + r) * N + n0 + nl) = pk;
+}
+
+template <class Epi, int NW>
+hipError_t launch_ln_gemm(const AddLnArgs &a, const void *Wp, void *out, const Epi &epi, int N, hipStream_t st)
+{
+    typedef LnGemm<Epi, NW> G;
+    const size_t LDS = G::TAB_OFF + 2 * 64 * sizeof(float) + extra_lds_of(epi, 0);     // at most 50 KB (1024 channels, 2048 bins)
+    const int tiles_n = N / 64, tiles_m = (a.rows.host_rows + NW - 1) / NW;
+    launch_kernel(gemm_nt_ln_kernel<Epi, NW>, dim3(tiles_n * tiles_m), dim3(64 * NW), LDS, st, nullptr, a, (const char *)Wp, (char *)out, epi, N,
+                  tiles_n);
+    return hipGetLastError();
+}
+template <class Epi>
+hipError_t launch_ln_gemm_width(const AddLnArgs &a, const void *Wp, void *out, const Epi &epi, int N, hipStream_t st)
+{
+    if (a.H == 768) return launch_ln_gemm<Epi, 6>(a, Wp, out, epi, N, st);
+    if (a.H == 1024) return launch_ln_gemm<Epi, 8>(a, Wp, out, epi, N, st);
+    return hipErrorNotSupported;
+}
+
 // The FP16 counterpart.  Binary32 sums are formed in K order whatever the tile, so K is not split; what four waves share is the
 // issue of the loads (one wave that loads and multiplies spends most of its time issuing loads: 768 x 3072, 19 rows, 13 us).
 // A block of four waves computes 32 tokens x 32 CW channels: all waves stream the operands through an R-deep ring of stages of
@@ -1541,6 +1628,22 @@ hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t
     if (epi == EPI_GELU_QUANT && gt && gt->entries)
         return launch_packed(A, Wp, out, EpiGeluTable{m, b, gt->entries, gt->spec.rate, gt->spec.offset, gt->spec.t_max, gt->spec.bins},
                              rows, N, K, tile, st, tm);
+    return hipErrorNotSupported;
+}
+
+// Beyond, the two launches are faster: the rows' arithmetic is done once per 64 channels of the result.  One sequence, Fully-Quant, us per
+// forward, two launches / one: BERT-base 1 token 289 / 265, 19 302 / 275, 32 307 / 293, 48 317 / 304, 64 328 / 328; BERT-large 1 660 / 597, 19 707 / 621,
+// 32 747 / 644, 48 739 / 724, 64 761 / 755
+constexpr int LN_GEMM_MAX_ROWS = 64;
+hipError_t launch_ln_gemm_i8(const AddLnArgs &a, GemmEpilogue epi, const int8_t *Wp, void *out, const float *m, const float *b, const GeluTable *gt,
+                             int N, hipStream_t st)
+{
+    if (a.rows.host_rows > LN_GEMM_MAX_ROWS || !Wp || N % 64 || !a.in_i8 || !a.res_i8 || !a.out_i8 || a.row_map || a.absmax_out ||
+        gemm_config_override.load(std::memory_order_relaxed) >= 0)
+        return hipErrorNotSupported;
+    if (epi == EPI_REQUANT) return launch_ln_gemm_width(a, Wp, out, EpiRequant{m, b}, N, st);
+    if (epi == EPI_GELU_QUANT && gt && gt->entries)
+        return launch_ln_gemm_width(a, Wp, out, EpiGeluTable{m, b, gt->entries, gt->spec.rate, gt->spec.offset, gt->spec.t_max, gt->spec.bins}, N, st);
     return hipErrorNotSupported;
 }
 

@@ -3,6 +3,7 @@
 // and epilogue-table folding at create time, and the absmax taps of the min-max calibration.
 // All of them move each byte once with coalesced 4..16-byte accesses; reductions stay inside a wave.
 #include "samp_common.h"
+#include "ln_wave.h"
 
 #include <type_traits>
 #include <hip/hip_ext.h>
@@ -24,25 +25,6 @@ constexpr int LN_WAVE_MAX_ROWS = 4096;             // below: one wave per row, i
 constexpr long ln_wave_max_values_beside(int width) { return width == 1024 ? 1650000 : 1450000; }
 constexpr int LN_ROWS = 8;               // token rows per block of the LayerNorm step (16 lanes each): small blocks slot in beside the other group's kernels
 
-template <int CTRL> __device__ __forceinline__ int dpp_mov(int v)
-{ return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
-
-template <int CTRL> __device__ __forceinline__ double dpp_mov(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = dpp_mov<CTRL>((int)b), hi = dpp_mov<CTRL>((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// sum over the 16 lanes of a DPP row; every lane ends with the same bits (the adds commute)
-__device__ __forceinline__ double row16_sum(double v)
-{
-    v += dpp_mov<0xB1>(v);            // quad_perm [1,0,3,2]
-    v += dpp_mov<0x4E>(v);            // quad_perm [2,3,0,1]
-    v += dpp_mov<0x141>(v);           // row_half_mirror
-    v += dpp_mov<0x140>(v);           // row_mirror
-    return v;
-}
 __device__ __forceinline__ float row16_max(float v)
 {
     v = __builtin_fmaxf(v, __int_as_float(dpp_mov<0xB1>(__float_as_int(v))));
@@ -205,62 +187,20 @@ __global__ __launch_bounds__(16 * LN_ROWS) void add_ln_kernel(Args a)
 // The same step with one wave per row, for the widths that 64 lanes divide into whole dwords of channels (H = 64 CPL).  A
 // launch of a few thousand rows lasts as long as one row's chain of vector arithmetic: 800 instructions of a wave that holds four
 // rows, 300 of one that holds one.  Us per launch in a chain, int8 in and out, H = 768: 19 rows 3.6 -> 2.3, 2048 rows 3.9 -> 3.1; H = 1024: 4.7 -> 2.4, 5.1 -> 3.4.
-template <bool I8, int CPL> __device__ __forceinline__ void load_lane(const void *p, size_t elem, float (&v)[CPL])
-{
-    static_assert(CPL % 4 == 0, "whole dwords of int8 channels per lane");
-#pragma unroll
-    for (int d = 0; d < CPL / 4; d++) {
-        if (I8) {
-            const int q = *reinterpret_cast<const int *>((const int8_t *)p + elem + 4 * d);
-#pragma unroll
-            for (int e = 0; e < 4; e++) v[4 * d + e] = (float)(int8_t)(q >> (8 * e));
-        } else {
-            const v4h h = *reinterpret_cast<const v4h *>((const __half *)p + elem + 4 * d);
-#pragma unroll
-            for (int e = 0; e < 4; e++) v[4 * d + e] = (float)h[e];
-        }
-    }
-}
-template <int CPL> __device__ __forceinline__ void load_lane_f32(const float *p, float (&v)[CPL])
-{
-#pragma unroll
-    for (int q = 0; q < CPL / 4; q++) *reinterpret_cast<v4f *>(v + 4 * q) = *reinterpret_cast<const v4f *>(p + 4 * q);
-}
-
-__device__ __forceinline__ double lane_double(double v, int lane)
-{
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | lo);
-}
-__device__ __forceinline__ double row64_sum(double v)
-{
-    v = row16_sum(v);
-    return (lane_double(v, 0) + lane_double(v, 16)) + (lane_double(v, 32) + lane_double(v, 48));
-}
-
 // second half of a row held by a wave, as ln_finish()
 template <int CPL, bool OUT_I8>
 __device__ __forceinline__ void ln_finish_wave(const float (&z)[CPL], double sum, const float (&gamma)[CPL], const float (&beta)[CPL], float eps,
                                                float s_out, void *out, size_t obase)
 {
-    constexpr int H = 64 * CPL;
-    const double mu = row64_sum(sum) / (double)H;
-    double sq = 0.0;
-#pragma unroll
-    for (int e = 0; e < CPL; e++) { const double d = (double)z[e] - mu; sq = __builtin_fma(d, d, sq); }
-    const double var = row64_sum(sq) / (double)H;
-    const float mu32 = (float)mu, rstd32 = (float)(1.0 / sqrt(var + (double)eps)), inv_s = OUT_I8 ? 1.0f / s_out : 0.0f;
+    float y[CPL];
+    ln_normalise_wave<CPL>(z, sum, gamma, beta, eps, y);
+    const float inv_s = OUT_I8 ? 1.0f / s_out : 0.0f;
 #pragma unroll
     for (int q = 0; q < CPL / 4; q++) {
-        float y[4];
-#pragma unroll
-        for (int t = 0; t < 4; t++) y[t] = __builtin_fmaf((z[4 * q + t] - mu32) * rstd32, gamma[4 * q + t], beta[4 * q + t]);
-        if (OUT_I8)
-            *reinterpret_cast<int *>((int8_t *)out + obase + 4 * q) =
-                pack_codes(code_bits(y[0] * inv_s), code_bits(y[1] * inv_s), code_bits(y[2] * inv_s), code_bits(y[3] * inv_s));
+        if (OUT_I8) *reinterpret_cast<int *>((int8_t *)out + obase + 4 * q) = pack_row_codes(y + 4 * q, inv_s);
         else
-            *reinterpret_cast<v4h *>((__half *)out + obase + 4 * q) = v4h{to_half(y[0]), to_half(y[1]), to_half(y[2]), to_half(y[3])};
+            *reinterpret_cast<v4h *>((__half *)out + obase + 4 * q) =
+                v4h{to_half(y[4 * q]), to_half(y[4 * q + 1]), to_half(y[4 * q + 2]), to_half(y[4 * q + 3])};
     }
 }
 
@@ -276,19 +216,8 @@ __global__ __launch_bounds__(256) void add_ln_wave_kernel(Args a)
     if (row >= M) return;
     const int c = (threadIdx.x & 63) * CPL;
     const int out_row = a.row_map ? a.row_map[row] : row;
-    float x[CPL], r[CPL], z[CPL], gamma[CPL], beta[CPL];
-    load_lane<IN_I8>(a.in, (size_t)row * H + c, x);
-    load_lane<RES_I8>(a.res, (size_t)row * H + c, r);
-    load_lane_f32(a.bias + c, z);
-    load_lane_f32(a.gamma + c, gamma);
-    load_lane_f32(a.beta + c, beta);
-    double sum = 0.0;
-#pragma unroll
-    for (int e = 0; e < CPL; e++) {
-        const float u = IN_I8 ? __builtin_fmaf(x[e], a.s_in, z[e]) : x[e] + z[e];
-        z[e] = RES_I8 ? __builtin_fmaf(r[e], a.s_res, u) : u + r[e];
-        sum += (double)z[e];
-    }
+    float z[CPL], gamma[CPL], beta[CPL];
+    const double sum = ln_row_wave<CPL, IN_I8, RES_I8>(a, row, c, z, gamma, beta);
     ln_finish_wave<CPL, OUT_I8>(z, sum, gamma, beta, a.eps, a.s_out, a.out, (size_t)out_row * H + c);
 }
 

@@ -225,6 +225,10 @@ struct AddLnArgs {
 };
 // prefetch: null, or two ranges (of 0 bytes or more); widths above 1024 leave it out
 hipError_t launch_add_ln(const AddLnArgs &a, const Prefetch *prefetch, hipStream_t st, const Timing *tm);
+// launch_add_ln and launch_gemm_i8 on its int8 output (N channels, packed weights) in one launch, for few rows; hipErrorNotSupported, and
+// nothing launched, where it is no gain or the step is of another form.  Same bytes, in a.out too.
+hipError_t launch_ln_gemm_i8(const AddLnArgs &a, GemmEpilogue epi, const int8_t *Wp, void *out, const float *m, const float *b, const GeluTable *gt,
+                             int N, hipStream_t st);
 
 struct EmbedArgs {
     const int *token_ids, *segment_ids;                    // [B*S]; segment_ids may be null (segment 0)

@@ -705,3 +705,25 @@ def test_error_paths_on_the_device_side(P):
         enc.calibrate(hid[:2])
     assert e.value.code == -1
     enc.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,B,S,varlen", [(768, 3072, 1, 1, False), (768, 3072, 1, 6, False), (768, 768, 1, 7, False), (768, 3072, 3, 9, True),
+                                                   (768, 3072, 1, 64, False), (768, 3072, 5, 13, True), (1024, 4096, 1, 8, False), (1024, 1024, 3, 17, True)])
+def test_layernorm_and_gemm_in_one_launch_gives_the_same_bytes(P, hidden, ffn, B, S, varlen):
+    """Few rows of a Fully-Quant stack: blocks of six (768) or eight (1024) rows, whole and not, up to the last row count that takes the
+    path and the first that does not; against the oracle, and against the steps apart (a timed step is a launch of its own)."""
+    import torch
+    w = W.Workload("few", 3, hidden, hidden // 64, ffn, B, S, (FULL_INT8, FULL_INT8 | P_UNSIGNED, FULL_INT8), varlen=varlen, min_len=1,
+                   plain_params=False)
+    wts = W.make_weights(w)
+    hid, lens, mask = W.make_hidden(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    want = oracle.Encoder(*args(w), w.modes, wts, sc).forward(hid, lens)
+    got = run_gpu(P, w, wts, sc, hid, mask if varlen else None)
+    assert np.array_equal(got.view(np.uint16), want.view(np.uint16))
+    enc = P.Encoder(*args(w), w.modes, wts, sc, max_batch=B, max_seq=S)
+    enc.profile(4)
+    apart = enc.forward(torch.from_numpy(hid).cuda(), torch.from_numpy(mask).cuda() if varlen else None)
+    torch.cuda.synchronize()
+    enc.close()
+    assert np.array_equal(got.view(np.uint16), apart.cpu().numpy().view(np.uint16))
