@@ -322,7 +322,7 @@ SAMP_API int samp_gemm_i8_gelu_quant(const int8_t *A, const int8_t *W, const flo
 SAMP_API int samp_pack_weight_i8(const int8_t *W, int32_t N, int32_t K, int8_t *Wp, void *stream);
 /* As samp_gemm_i8_requant and (with a table) samp_gemm_i8_gelu_quant, on packed weights; K % 256 == 0.  tile: -1 by size,
  * or 0..6 for tiles of 32 x 64, 64 x 64, 64 x 128, 64 x 192, 64 x 256, 128 x 128, 128 x 192 rows x channels (SAMP_ERR_SHAPE
- * if its width does not divide N); the results do not depend on it.                                */
+ * if its width does not divide N); the results do not depend on it.  m, b 16-byte aligned.       */
 SAMP_API int samp_gemm_i8_requant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *b, int8_t *out,
                                          int32_t M, int32_t N, int32_t K, int32_t tile, void *stream);
 SAMP_API int samp_gemm_i8_gelu_quant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *bias,

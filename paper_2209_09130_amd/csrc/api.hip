@@ -875,10 +875,11 @@ int samp_pack_weight_i8(const int8_t *W, int32_t N, int32_t K, int8_t *Wp, void 
     return SAMP_OK;
 }
 
-static int check_packed(const void *A, const void *Wp, const void *out, int M, int N, int K, int tile)
+static int check_packed(const void *A, const void *Wp, const float *m, const float *b, const void *out, int M, int N, int K, int tile)
 {
     static const int width[] = {64, 64, 128, 192, 256, 128, 192};
     if (int rc = check_gemm(A, Wp, out, M, N, K, 256)) return rc;
+    if (!aligned(m, 16) || !aligned(b, 16)) return fail(SAMP_ERR_ARG, "tables must be 16-byte aligned");
     if (tile < -1 || tile > 6) return fail(SAMP_ERR_ARG, "tile must be in [-1, 6]");
     if (tile >= 0 && N % width[tile]) return fail(SAMP_ERR_SHAPE, "tile %d needs N %% %d == 0 (N=%d)", tile, width[tile], N);
     return SAMP_OK;
@@ -887,7 +888,7 @@ static int check_packed(const void *A, const void *Wp, const void *out, int M, i
 int samp_gemm_i8_requant_packed(const int8_t *A, const int8_t *Wp, const float *m, const float *b, int8_t *out, int32_t M,
                                 int32_t N, int32_t K, int32_t tile, void *stream)
 {
-    if (int rc = check_packed(A, Wp, out, M, N, K, tile)) return rc;
+    if (int rc = check_packed(A, Wp, m, b, out, M, N, K, tile)) return rc;
     if (!m) return fail(SAMP_ERR_ARG, "multiplier table is NULL");
     HIP_TRY(launch_gemm_i8_packed(EPI_REQUANT, A, Wp, out, m, b, nullptr, Rows{M, nullptr}, N, K, tile, (hipStream_t)stream, nullptr));
     return SAMP_OK;
@@ -897,7 +898,7 @@ int samp_gemm_i8_gelu_quant_packed(const int8_t *A, const int8_t *Wp, const floa
                                    const samp_gelu_table_t *table, const void *table_entries, int8_t *out, int32_t M, int32_t N,
                                    int32_t K, int32_t tile, void *stream)
 {
-    if (int rc = check_packed(A, Wp, out, M, N, K, tile)) return rc;
+    if (int rc = check_packed(A, Wp, m, bias, out, M, N, K, tile)) return rc;
     if (!m || !bias) return fail(SAMP_ERR_ARG, "multiplier or bias table is NULL");
     GeluTable gt;
     if (int rc = check_gelu_table(table, table_entries, &gt)) return rc;

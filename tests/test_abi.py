@@ -93,6 +93,13 @@ def test_later_entry_points_reject_bad_arguments_on_the_host(L):
     assert L.samp_classify(buf, 1, 4, 100, buf, buf, buf, buf, 3, buf, None) == -2          # H % 8
     assert L.samp_classify(buf, 1, 4, 128, buf, buf, buf, buf, 0, buf, None) == -2          # no classes
     assert L.samp_classify_workspace(buf, 1, 4, 128, buf, buf, buf, buf, 3, None, buf, None) == -1
+    many = (C.c_char * 320)()
+    at = lambda n: C.c_void_p(((C.addressof(many) + 15) & ~15) + n)                          # n bytes past a 16-byte boundary
+    assert L.samp_gemm_i8_requant_packed(at(0), at(0), at(4), at(0), at(0), 1, 128, 256, -1, None) == -1      # tables are read 16 bytes at a time
+    assert b"aligned" in L.samp_last_error()
+    assert L.samp_gemm_i8_requant_packed(at(0), at(0), at(0), at(4), at(0), 1, 128, 256, -1, None) == -1
+    assert L.samp_gemm_i8_gelu_quant_packed(at(0), at(0), at(0), at(4), None, None, at(0), 1, 128, 256, -1, None) == -1
+    assert b"tables" in L.samp_last_error()
     assert L.samp_code_histogram(None, C.c_size_t(16), buf, None) == -1
     assert L.samp_code_histogram(buf, C.c_size_t(0), buf, None) == -2
     assert L.samp_set_gemm_config(9) == -1
