@@ -2,6 +2,7 @@
 // per-layer kernel sequence of Section 3.2 (seven kernels per layer plus entry / exit handling).
 #include "../../include/samp.h"
 #include "samp_common.h"
+#include "gemm_rules.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -288,7 +289,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     // From 256 rows to 3.2 million values the LayerNorm steps ask for the weights that come next (the first of several groups does it for
     // all).  Below, a layer is over before they arrive (forward without / with it: 19 rows 326 / 331 us); above, a GEMM lasts long enough to
     // fetch its own (width 768, two groups of 4096 rows 1286 / 1254, of 8192 rows 2014 / 2040; width 1024, two of 4096 rows 3783 / 3798).
-    const bool fetch_ahead = prefetch && Tmax >= 256 && (long)Tmax * H <= 3200000;
+    const bool fetch_ahead = prefetch && Tmax >= FETCH_AHEAD_MIN_ROWS && (long)Tmax * H <= 3200000;
     auto ahead = [&](const void *W, const void *Wp, int N, int K, bool i8) {
         const bool packed = Wp && !(i8 ? gemm_i8_reads_rows(rows, N) : gemm_f16_reads_rows(rows, N, K));
         return Prefetch{packed ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};

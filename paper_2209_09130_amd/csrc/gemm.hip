@@ -24,6 +24,7 @@
 #include "samp_common.h"
 #include "mfma_tile.h"
 #include "ln_wave.h"
+#include "gemm_rules.h"
 
 #include <atomic>
 #include <type_traits>
@@ -1483,7 +1484,7 @@ hipError_t launch_small_f16_any(const void *A, const void *W, void *out, const E
 {
     if (K % 256) return hipErrorNotSupported;
     const long tiles_m = (rows.host_rows + 31) / 32;
-    if (N % 32 == 0 && tiles_m * (N / 32) <= 2 * cus_for(rows)) return launch_small_f16<1, 2>(A, W, out, epi, rows, N, K, st, tm);      // two blocks per CU
+    if (N % 32 == 0 && f16_small_tiles(rows.host_rows, N) <= 2 * cus_for(rows)) return launch_small_f16<1, 2>(A, W, out, epi, rows, N, K, st, tm);      // two blocks per CU
     if (N % 64 == 0 && tiles_m * (N / 64) <= cus_for(rows)) return launch_small_f16<2, 2>(A, W, out, epi, rows, N, K, st, tm);
     if (N % 128 == 0 && K <= 1024 && tiles_m * (N / 128) <= cus_for(rows)) return launch_small_f16<4, 2>(A, W, out, epi, rows, N, K, st, tm);
     return hipErrorNotSupported;
@@ -1654,9 +1655,7 @@ hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float
     return launch_packed_f16(A, Wp, out, EpiF16{bias, gelu}, rows, N, K, tile, st, tm);
 }
 
-// Few rows of few channels: as for INT8 (us, K split / packed weights: 768 x 768 at 128 rows 4.94 / 5.01, at 256 5.00 / 5.27, at 427 5.5 / 5.3;
-// 1024 x 1024 at 256 rows 5.7 / 6.1, at 427 6.35 / 6.15; 768 x 3072 at 256 rows 11.6 / 11.4; 1024 x 4096 at 128 rows 14.7 / 14.0)
-bool gemm_f16_reads_rows(Rows rows, int N, int K) { return N <= 1024 && K <= 1024 && (long)rows.host_rows * N <= 270000; }
+bool gemm_f16_reads_rows(Rows rows, int N, int K) { return f16_reads_rows(rows.host_rows, N, K, cus_for(rows)); }
 
 hipError_t launch_gemm_f16(const __half *A, const __half *W, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows,
                            int N, int K, hipStream_t st, const Timing *tm)

@@ -187,7 +187,7 @@ hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t
                                  const GeluTable *gelu_table, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm);
 hipError_t launch_gemm_f16(const __half *A, const __half *W, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows,
                            int N, int K, hipStream_t st, const Timing *tm);
-bool gemm_f16_reads_rows(Rows rows, int N, int K);
+bool gemm_f16_reads_rows(Rows rows, int N, int K);                       // (the rules: gemm_rules.h)
 // as launch_gemm_i8_packed, K and N multiples of 128
 hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows, int N, int K,
                                   int tile, hipStream_t st, const Timing *tm);

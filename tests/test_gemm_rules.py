@@ -1,0 +1,54 @@
+"""The rules that choose between the two copies of a matrix (csrc/gemm_rules.h), compiled for the host: which GEMMs of few token rows
+read the weights as they lie."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(__file__), "..", "paper_2209_09130_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text('#include "gemm_rules.h"\n'
+                                 'extern "C" int f16(long rows, int N, int K, long cus) { return samp::f16_reads_rows(rows, N, K, cus); }\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "rules.so"), str(d / "rules.cpp")], check=True)
+    lib = C.CDLL(str(d / "rules.so"))
+    lib.f16.argtypes = [C.c_long, C.c_int, C.c_int, C.c_long]
+    return lib
+
+
+@pytest.mark.parametrize("H,F", [(256, 1024), (512, 2048), (768, 3072), (1024, 4096), (1280, 5120), (2048, 8192)])
+def test_fp16_gemms_of_a_few_dozen_rows_spread_over_the_chip(rules, H, F):
+    """A packed tile is at least 128 channels wide; up to 64 rows it would leave most CUs without a block wherever tiles of 32 channels
+    fit the chip.  From 2048 rows on nothing reads rows as they lie; K without a small kernel never does."""
+    for N, K in ((3 * H, H), (H, H), (F, H), (H, F)):
+        for rows in (1, 8, 19, 32, 48, 64):
+            small = -(-rows // 32) * (N // 32)
+            assert bool(rules.f16(rows, N, K, 256)) == (small <= 512), (rows, N, K)
+        assert not rules.f16(2048 * 2048 // H, N, K, 256)
+        assert not rules.f16(19, N, 640, 256) and not rules.f16(19, N, 384, 256)
+    # the last rows that two 32 x 32 tiles per CU hold, and one per CU from 256 rows on
+    assert rules.f16(224, 2304, 768, 256) and not rules.f16(225, 2304, 768, 256)
+    assert rules.f16(128, 4096, 1024, 256) and not rules.f16(129, 4096, 1024, 256)
+    assert rules.f16(320, 768, 3072, 256) and not rules.f16(321, 768, 3072, 256)
+    assert rules.f16(255, 1536, 512, 256) and not rules.f16(256, 1536, 512, 256)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(1, 2304, 768), (97, 3072, 768), (224, 2304, 768), (33, 1024, 4096), (128, 4096, 1024), (255, 512, 2048)])
+def test_few_rows_of_both_copies_give_the_same_bytes(M, N, K):
+    import torch
+    import paper_2209_09130_amd as P
+    rng = np.random.default_rng(M + N)
+    A = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float16)).cuda()
+    W = torch.from_numpy((rng.standard_normal((N, K)) / np.sqrt(K)).astype(np.float16)).cuda()
+    bias = torch.from_numpy((0.1 * rng.standard_normal(N)).astype(np.float32)).cuda()
+    rows, packed = P.gemm_f16(A, W, bias, True), P.gemm_f16_packed(A, P.pack_weight_f16(W), bias, True)
+    assert torch.equal(rows, packed)
+    want = torch.nn.functional.gelu(A.cpu().double() @ W.cpu().double().T + bias.cpu().double())
+    # one rounding to 16 bits, and 32-bit sums of K terms
+    assert ((rows.cpu().double() - want).abs() <= want.abs().clamp(min=2.0 ** -14) * 2.0 ** -10 + K * 2.0 ** -24).all()
