@@ -291,7 +291,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     // fetch its own (width 768, two groups of 4096 rows 1286 / 1254, of 8192 rows 2014 / 2040; width 1024, two of 4096 rows 3783 / 3798).
     const bool fetch_ahead = prefetch && Tmax >= FETCH_AHEAD_MIN_ROWS && (long)Tmax * H <= 3200000;
     auto ahead = [&](const void *W, const void *Wp, int N, int K, bool i8) {
-        const bool packed = Wp && !(i8 ? gemm_i8_reads_rows(rows, N) : gemm_f16_reads_rows(rows, N, K));
+        const bool packed = Wp && !(i8 ? gemm_i8_reads_rows(rows, N, K) : gemm_f16_reads_rows(rows, N, K));
         return Prefetch{packed ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};
     };
     // Attention blocks whose QKV GEMM and attention run as one kernel.  Its block is one (sequence, head) and a tile of 128 tokens: from 49 to 128

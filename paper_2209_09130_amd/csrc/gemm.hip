@@ -1279,12 +1279,12 @@ hipError_t launch_small_waves(const void *A, const void *W, void *out, const Epi
 template <class Epi>
 hipError_t launch_small_any(const void *A, const void *W, void *out, const Epi &epi, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
 {
-    if (K % 1024 == 0) {                                          // eight waves; rings as deep as LDS allows where a wave has more than one slab
+    if (i8_small_waves(K) == 8) {                                 // eight waves; rings as deep as LDS allows where a wave has more than one slab
         if (K > 1024) return launch_small_waves<Epi, 8, 3, 2>(A, W, out, epi, rows, N, K, st, tm);
         return launch_small_waves<Epi, 8, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
     }
-    // (whole slabs for other numbers of waves are not instantiated: K of 256, 384, 512, 640 and 1280 take the kernels above)
-    if (K % 768 == 0) return launch_small_waves<Epi, 6, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
+    // (other numbers of waves are not instantiated: i8_small_waves)
+    if (i8_small_waves(K) == 6) return launch_small_waves<Epi, 6, 1, 1>(A, W, out, epi, rows, N, K, st, tm);
     return hipErrorNotSupported;
 }
 
@@ -1598,16 +1598,12 @@ hipError_t launch(const void *A, const void *W, void *out, const Epi &epi, Rows 
 
 std::atomic<int> gemm_config_override{-1};                    // tuning aid: force one tile configuration (see launch())
 
-// Few rows: the kernel that splits K over a block's waves asks for the whole of K at once and has smaller tiles for narrow matrices (us, K
-// split / packed weights: 768 x 768 at 128 rows 2.95 / 3.4, at 256 3.4 / 3.6, at 427 3.8 / 3.5; 768 x 3072 at 256 rows 5.1 / 6.3, at 512 6.25 / 6.25;
-// 1024 x 4096 at 256 rows 5.9 / 6.3, at 427 7.25 / 6.4; 1024 x 1024 at 256 rows 3.9 / 4.3, at 768 5.5 / 5.2; 2304 x 768 at 32 rows 3.25 / 3.4, at 64
-// 3.7 / 3.5; 3072 x 768 at 32 rows 3.7 / 3.8, at 64 4.05 / 3.8; 4096 x 1024 at 32 rows 4.0 / 4.1, at 64 4.6 / 4.15)
-bool gemm_i8_reads_rows(Rows rows, int N) { return (long)rows.host_rows * N <= (N <= 1024 ? 300000 : 128000); }
+bool gemm_i8_reads_rows(Rows rows, int N, int K) { return i8_reads_rows(rows.host_rows, N, K); }
 
 hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, const int8_t *Wp, void *out, const float *m, const float *b,
                           float inv_s_out, const GeluTable *gt, Rows rows, int N, int K, hipStream_t st, const Timing *tm)
 {
-    if (Wp && gemm_config_override.load(std::memory_order_relaxed) < 0 && !gemm_i8_reads_rows(rows, N)) {
+    if (Wp && gemm_config_override.load(std::memory_order_relaxed) < 0 && !gemm_i8_reads_rows(rows, N, K)) {
         const hipError_t e = launch_gemm_i8_packed(epi, A, Wp, out, m, b, gt, rows, N, K, -1, st, tm);
         if (e != hipErrorNotSupported) return e;
     }

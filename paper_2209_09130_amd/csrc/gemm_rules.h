@@ -25,4 +25,20 @@ inline bool f16_reads_rows(long rows, int N, int K, long cus)
     return K % 256 == 0 && f16_small_tiles(rows, N) <= (rows < FETCH_AHEAD_MIN_ROWS ? 2 : 1) * cus;
 }
 
+// INT8: the rows as they lie where the kernel that splits K over a block's waves (gemm_nt_small_kernel) is the faster one: it asks for the whole of K at once
+// and has tiles of 16 channels.  It exists for K of whole slabs of eight or of six waves (128 bytes each) and for no other: those are always faster
+// packed than on what is left for them (us, 19 rows: 512 x 512 5.07 / 2.95, 1024 x 512 5.24 / 3.03, 640 x 2560 13.2 / 4.8, 1280 x 1280 11.0 / 6.0).
+// Us per launch, K split / packed weights, at most 1024 channels: 768 x 768 at 128 rows 3.05 / 3.29, 255 3.50 / 3.36, 400 3.89 / 3.41; 768 x 3072 at 128 rows
+// 5.43 / 7.27, 320 5.15 / 6.33, 400 6.13 / 6.32; 1024 x 1024 at 255 rows 4.20 / 5.06, 448 4.33 / 4.64; 1024 x 4096 at 128 rows 6.03 / 8.52, 256 5.91 / 6.36, 320
+// 7.15 / 6.38.  Up to 2048 channels, long K: 1280 x 5120 at 128 rows 8.6 / 10.5, 192 8.4 / 10.4, 256 11.0 / 10.4; 1536 x 6144 at 160 rows 9.5 / 11.8, 192
+// 12.4 / 11.8; 2048 x 8192 at 64 rows 9.6 / 15.5, 160 13.3 / 15.2, 192 15.0 / 15.2; K no longer than N: 2048 x 2048 at 128 rows 5.47 / 5.71, 160
+// 6.05 / 5.65; 1536 x 1536 at 64 rows 4.39 / 5.13, 128 5.27 / 5.20, 192 5.94 / 5.35.  Wider: 2304 x 768 at 32 rows 3.55 / 4.20, 40 4.05 / 3.91; 3072 x 768
+// at 32 rows 3.61 / 4.23, 40 4.08 / 3.90; 4096 x 1024 at 32 rows 4.00 / 4.47, 40 4.37 / 4.34; 6144 x 2048 at 32 rows 6.07 / 6.19, 64 7.09 / 6.17.
+// (from 256 rows weights in the memory-side cache, below from memory)
+inline int i8_small_waves(int K) { return K % 1024 == 0 ? 8 : K % 768 == 0 ? 6 : 0; }
+inline bool i8_reads_rows(long rows, int N, int K)
+{
+    return i8_small_waves(K) && rows * N <= (N <= 1024 ? 300000 : N > 2048 ? 128000 : K > N ? 330000 : 262144);
+}
+
 }  // namespace samp

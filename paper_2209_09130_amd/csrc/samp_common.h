@@ -179,15 +179,15 @@ extern std::atomic<int> gemm_config_override;                           // < 0: 
 hipError_t launch_gemm_i8(GemmEpilogue epi, const int8_t *A, const int8_t *W, const int8_t *Wp, void *out, const float *m, const float *b,
                           float inv_s_out, const GeluTable *gelu_table, Rows rows, int N, int K, hipStream_t st,
                           const Timing *tm);
-// whether launch_gemm_i8 reads W although it is given Wp
-bool gemm_i8_reads_rows(Rows rows, int N);
+// whether launch_gemm_i8 reads W although it is given Wp (the rules: gemm_rules.h)
+bool gemm_i8_reads_rows(Rows rows, int N, int K);
 // on packed weights alone; tile: -1 by size, or a number of stream_tile's list (hipErrorInvalidValue where it does not divide N).
 // hipErrorNotSupported: K is no multiple of 256, N none of 64, or the epilogue is another
 hipError_t launch_gemm_i8_packed(GemmEpilogue epi, const int8_t *A, const int8_t *Wp, void *out, const float *m, const float *b,
                                  const GeluTable *gelu_table, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm);
 hipError_t launch_gemm_f16(const __half *A, const __half *W, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows,
                            int N, int K, hipStream_t st, const Timing *tm);
-bool gemm_f16_reads_rows(Rows rows, int N, int K);                       // (the rules: gemm_rules.h)
+bool gemm_f16_reads_rows(Rows rows, int N, int K);
 // as launch_gemm_i8_packed, K and N multiples of 128
 hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float *bias, bool gelu, __half *out, Rows rows, int N, int K,
                                   int tile, hipStream_t st, const Timing *tm);

@@ -14,10 +14,12 @@ CSRC = os.path.join(os.path.dirname(__file__), "..", "paper_2209_09130_amd", "cs
 def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text('#include "gemm_rules.h"\n'
-                                 'extern "C" int f16(long rows, int N, int K, long cus) { return samp::f16_reads_rows(rows, N, K, cus); }\n')
+                                 'extern "C" int f16(long rows, int N, int K, long cus) { return samp::f16_reads_rows(rows, N, K, cus); }\n'
+                                 'extern "C" int i8(long rows, int N, int K) { return samp::i8_reads_rows(rows, N, K); }\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "rules.so"), str(d / "rules.cpp")], check=True)
     lib = C.CDLL(str(d / "rules.so"))
     lib.f16.argtypes = [C.c_long, C.c_int, C.c_int, C.c_long]
+    lib.i8.argtypes = [C.c_long, C.c_int, C.c_int]
     return lib
 
 
@@ -38,6 +40,22 @@ def test_fp16_gemms_of_a_few_dozen_rows_spread_over_the_chip(rules, H, F):
     assert rules.f16(255, 1536, 512, 256) and not rules.f16(256, 1536, 512, 256)
 
 
+@pytest.mark.parametrize("H,F", [(256, 1024), (512, 2048), (640, 2560), (768, 3072), (1024, 4096), (1280, 5120), (1536, 6144), (1792, 7168), (2048, 8192)])
+def test_int8_gemms_read_rows_only_where_a_kernel_splits_k(rules, H, F):
+    """K has to be whole slabs of eight or six waves; where it is, a few dozen rows read the weights as they lie, up to 2048 channels, and
+    thousands of rows never do."""
+    for N, K in ((3 * H, H), (H, H), (F, H), (H, F)):
+        exists = K % 1024 == 0 or K % 768 == 0
+        for rows in (1, 19, 64, 100, 128):
+            if N <= 2048: assert bool(rules.i8(rows, N, K)) == exists, (rows, N, K)
+            if rows * N > 128000 and N > 2048: assert not rules.i8(rows, N, K)
+        assert not rules.i8(2048, N, K)
+    assert rules.i8(390, 768, 3072) and not rules.i8(391, 768, 3072)
+    assert rules.i8(160, 2048, 8192) and not rules.i8(192, 2048, 8192)
+    assert rules.i8(128, 2048, 2048) and not rules.i8(129, 2048, 2048)
+    assert rules.i8(32, 3072, 768) and not rules.i8(42, 3072, 768)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(1, 2304, 768), (97, 3072, 768), (224, 2304, 768), (33, 1024, 4096), (128, 4096, 1024), (255, 512, 2048)])
 def test_few_rows_of_both_copies_give_the_same_bytes(M, N, K):
@@ -52,3 +70,19 @@ def test_few_rows_of_both_copies_give_the_same_bytes(M, N, K):
     want = torch.nn.functional.gelu(A.cpu().double() @ W.cpu().double().T + bias.cpu().double())
     # one rounding to 16 bits, and 32-bit sums of K terms
     assert ((rows.cpu().double() - want).abs() <= want.abs().clamp(min=2.0 ** -14) * 2.0 ** -10 + K * 2.0 ** -24).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(19, 512, 512), (257, 256, 1024), (100, 1280, 5120), (70, 1280, 1280)])
+def test_few_int8_rows_of_both_copies_give_the_same_codes(M, N, K):
+    """Sizes on both sides of the rule; the encoder takes one of the two."""
+    import torch
+    import oracle
+    import paper_2209_09130_amd as P
+    rng = np.random.default_rng(M + K)
+    A, W = (rng.integers(-127, 128, shape, dtype=np.int8) for shape in ((M, K), (N, K)))
+    m, b = (0.5 + rng.random(N, dtype=np.float32)) * np.float32(40 / (5400 * np.sqrt(K))), rng.standard_normal(N).astype(np.float32)
+    t = [torch.from_numpy(x).cuda() for x in (A, W, m, b)]
+    want = oracle.epilogue_requant(oracle.gemm_i8_i32(A, W), m, b)
+    assert np.array_equal(P.gemm_i8_requant(*t).cpu().numpy(), want)
+    assert np.array_equal(P.gemm_i8_requant_packed(t[0], P.pack_weight_i8(t[1]), t[2], t[3]).cpu().numpy(), want)
