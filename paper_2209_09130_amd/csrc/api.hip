@@ -455,8 +455,11 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
             return fail(SAMP_ERR_SCALE, "layer %d: a feed-forward-block scale is not finite and positive", l);
     }
     if (!aligned(dev_arena, ALIGN)) return fail(SAMP_ERR_SPACE, "arena must be 256-byte aligned");
-    const size_t need = samp_encoder_arena_bytes(cfg, modes);
+    const size_t whole = samp_encoder_arena_bytes(cfg, modes);
+    size_t need = whole;                                          // without room for the packed copies every GEMM reads rows
+    for (int l = 0; l < cfg->layers; l++) need -= layer_packed_bytes(*cfg, modes[l]);
     if (arena_bytes < need) return fail(SAMP_ERR_SPACE, "arena has %zu bytes, %zu needed", arena_bytes, need);
+    const bool pack = arena_bytes >= whole;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     samp_encoder *E = new (std::nothrow) samp_encoder();
@@ -509,7 +512,7 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
                     HIP_TRY(launch_quantize_weight(stage, (int)N, (int)K, (int8_t *)*dst, s_w, st));
                 }
                 const size_t e = q8 ? 1 : 2;
-                if (packs(K * e)) {
+                if (pack && packs(K * e)) {
                     *packed = cvp.take<char>(N * K * e);
                     HIP_TRY(launch_pack_weight(*dst, (int)N, (int)(K * e), !q8, *packed, st));
                 }

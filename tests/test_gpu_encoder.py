@@ -727,3 +727,26 @@ def test_layernorm_and_gemm_in_one_launch_gives_the_same_bytes(P, hidden, ffn, B
     torch.cuda.synchronize()
     enc.close()
     assert np.array_equal(got.view(np.uint16), apart.cpu().numpy().view(np.uint16))
+
+
+@pytest.mark.parametrize("hidden,ffn,B,S,modes", [(768, 3072, 2, 40, (FULL_INT8, FP16)), (256, 1024, 3, 100, (FULL_INT8 | P_UNSIGNED, FFN_INT8)),
+                                                  (256, 1024, 40, 64, (MHA_INT8, FULL_INT8))])
+def test_an_arena_without_room_for_the_packed_copies(P, monkeypatch, hidden, ffn, B, S, modes):
+    """The size that an encoder without packed copies needs is accepted, and gives the same bytes; one byte less is refused."""
+    import torch
+    w = W.Workload("rows", len(modes), hidden, hidden // 64, ffn, B, S, modes, plain_params=False)
+    wts = W.make_weights(w)
+    hid, _, _ = W.make_hidden(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    want = run_gpu(P, w, wts, sc, hid, None)
+    up = lambda n: (n + 255) // 256 * 256
+    whole = P.lib().samp_encoder_arena_bytes
+    matrices = ((3 * hidden, hidden, 1), (hidden, hidden, 1), (ffn, hidden, 2), (hidden, ffn, 2))
+    packed = sum(up(N * K * (1 if m & bit else 2)) for m in modes for N, K, bit in matrices)
+    for less in (1, packed):
+        monkeypatch.setattr(P.lib(), "samp_encoder_arena_bytes", lambda c, m: whole(c, m) - less)
+        assert np.array_equal(run_gpu(P, w, wts, sc, hid, None).view(np.uint16), want.view(np.uint16))
+    monkeypatch.setattr(P.lib(), "samp_encoder_arena_bytes", lambda c, m: whole(c, m) - packed - 1)
+    with pytest.raises(P.SampError) as e:
+        P.Encoder(*args(w), w.modes, wts, sc, max_batch=B, max_seq=S)
+    assert e.value.code == -3
