@@ -1360,7 +1360,9 @@ template <class Epi, int NW>
 hipError_t launch_ln_gemm(const AddLnArgs &a, const void *Wp, void *out, const Epi &epi, int N, hipStream_t st)
 {
     typedef LnGemm<Epi, NW> G;
-    const size_t LDS = G::TAB_OFF + 2 * 64 * sizeof(float) + extra_lds_of(epi, 0);     // at most 50 KB (1024 channels, 2048 bins)
+    // 57984 bytes at most (1024 channels, 2048 bins); a launch gets 64 KB without asking for more
+    static_assert(G::TAB_OFF + 2 * 64 * sizeof(float) + GELU_TABLE_MAX_BINS * 8 <= 64 * 1024, "");
+    const size_t LDS = G::TAB_OFF + 2 * 64 * sizeof(float) + extra_lds_of(epi, 0);
     const int tiles_n = N / 64, tiles_m = (a.rows.host_rows + NW - 1) / NW;
     launch_kernel(gemm_nt_ln_kernel<Epi, NW>, dim3(tiles_n * tiles_m), dim3(64 * NW), LDS, st, nullptr, a, (const char *)Wp, (char *)out, epi, N,
                   tiles_n);
