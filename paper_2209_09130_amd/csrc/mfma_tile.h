@@ -95,7 +95,8 @@ template <bool HALF, int MT> constexpr int stream_loads() { return StreamGeometr
 // MT token tiles, NTW weight blocks per wave.  SPLIT: the block's token rows are split over that many groups of waves (this wave's: part), so
 // that waves of different groups load the same weights.  abase: first token row; offa: this lane's offsets into the rows of its pieces (8 rows x 128
 // bytes, swizzled); wbase: the wave's packed row blocks; KT: stages of 128 bytes, a multiple of D.  started() runs once the first stage is
-// requested (what it loads has arrived when the first product runs); mma(t, i, w, f) adds the product of weight block t and token tile i.
+// requested; what it loads into LDS is there for all waves behind the barrier that ends the first stage, so it is for use after the loop, not in
+// mma (KT >= 2); mma(t, i, w, f) adds the product of weight block t and token tile i.
 // On return the ring is idle.
 template <bool HALF, int MT, int NTW, int D, int SPLIT = 1, class Started, class Mma>
 __device__ __forceinline__ void stream_tile_loop(const char *abase, const unsigned (&offa)[stream_loads<HALF, MT * SPLIT>()], const char *wbase,
