@@ -182,9 +182,9 @@ SAMP_API int samp_encoder_set_groups(samp_encoder_t *enc, int32_t groups);
 /* Section 3.2 hands the QKV GEMM's requantised int8 output straight to the attention; for sequences of at
  * most 256 tokens one kernel can do both per (sequence, head), so that q, k, v never reach memory and a layer
  * has one launch less (INT8 blocks with int8 softmax codes, signed or unsigned, and FP16 blocks outside calibration).
- * mode 0 (default): used where it measured faster (at least 128 (sequence, head) pairs per launch; INT8 blocks
- * up to 128 tokens, FP16 blocks up to 256); 1: never; 2: whenever the shape allows.  The context is the same
- * bytes either way.                                                                                       */
+ * mode 0 (default): used where it measured faster, for S (the padded length of the call) of 49 to 128 tokens and at least 128
+ * (sequence, head) pairs per launch (a launch has the sequences of one group of the batch); 1: never; 2: for every S of at most 256.  A binary16 softmax
+ * output (SAMP_P_FP16) always takes two kernels.  The context is the same bytes either way.         */
 SAMP_API int samp_encoder_set_qkv_fusion(samp_encoder_t *enc, int32_t mode);
 
 /* A forward is a few hundred short kernels, so by default the library records them once per distinct

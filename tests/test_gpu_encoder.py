@@ -750,3 +750,22 @@ def test_an_arena_without_room_for_the_packed_copies(P, monkeypatch, hidden, ffn
     with pytest.raises(P.SampError) as e:
         P.Encoder(*args(w), w.modes, wts, sc, max_batch=B, max_seq=S)
     assert e.value.code == -3
+
+
+@pytest.mark.parametrize("mode", [FULL_INT8, FP16, MHA_INT8 | P_UNSIGNED, FULL_INT8 | P_FP16])
+def test_qkv_and_attention_are_one_kernel_where_the_header_says(P, mode):
+    """samp_encoder_set_qkv_fusion, mode 0: padded lengths of 49 to 128 tokens and 128 (sequence, head) pairs; mode 2: up to 256 tokens.  A timed
+    forward counts the launches of the kernel."""
+    import torch
+    w = W.Workload("fusion", 2, 128, 2, 128, 64, 257, (mode,) * 2, plain_params=False)
+    wts = W.make_weights(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    enc = P.Encoder(*args(w), w.modes, wts, sc, max_batch=64, max_seq=257)
+    for wanted, shapes in ((0, {(64, 48): 0, (64, 49): 2, (63, 49): 0, (64, 128): 2, (64, 129): 0}), (1, {(64, 128): 0}),
+                           (2, {(1, 1): 2, (2, 256): 2, (2, 257): 0})):
+        enc.set_qkv_fusion(wanted)
+        for (B, S), launches in shapes.items():
+            enc.profile(P.PROF_QKV_ATTN)
+            enc.forward(torch.zeros((B, S, 128), dtype=torch.float16, device="cuda"))
+            assert enc.profile_read()[1] == (0 if mode & P_FP16 else launches), (wanted, B, S)
+    enc.close()
