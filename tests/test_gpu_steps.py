@@ -179,6 +179,32 @@ def test_gemms_on_packed_weights_give_the_same_codes(P, tile, M, N, K):
                           oracle.epilogue_gelu_quant(acc, md, bias, s_out))
 
 
+@pytest.mark.parametrize("M,tile", [(1, -1), (70, 2), (129, 5), (257, 0), (1024, -1), (1024, 4), (1025, -1)])
+@pytest.mark.parametrize("N,K", [(1024, 3072), (4096, 1024)])
+def test_gemm_on_packed_weights_with_channels_outermost(P, M, tile, N, K):
+    """Weights of 3 MB and more, at most 1024 rows: blocks are numbered with the channels outermost (1025 rows: as everywhere else)."""
+    rng = np.random.default_rng(M + N)
+    A = rng.integers(-127, 128, (M, K), dtype=np.int8)
+    W = rng.integers(-127, 128, (N, K), dtype=np.int8)
+    s_w, bias = _tables(rng, N)
+    m, b = oracle.fold_requant(0.037, s_w, bias, 0.021 * np.sqrt(K / 768))
+    want = oracle.epilogue_requant(oracle.gemm_i8_i32(A, W), m, b)
+    assert np.abs(want).max() > 20
+    assert np.array_equal(host(P.gemm_i8_requant_packed(dev(A), P.pack_weight_i8(dev(W)), dev(m), dev(b), tile)), want)
+
+
+@pytest.mark.parametrize("M,tile", [(1, -1), (70, 0), (257, 2), (1024, 3), (1025, -1)])
+def test_fp16_gemm_on_packed_weights_with_channels_outermost(P, M, tile):
+    rng = np.random.default_rng(M)
+    N, K = 2048, 768
+    A = dev(rng.standard_normal((M, K)).astype(np.float16))
+    W = dev((rng.standard_normal((N, K)) / np.sqrt(K)).astype(np.float16))
+    bias = dev((0.1 * rng.standard_normal(N)).astype(np.float32))
+    want = host(P.gemm_f16(A, W, bias, True))                  # compared with the oracle at other sizes; the same order of sums
+    assert np.abs(want).max() > 0.5
+    assert np.array_equal(host(P.gemm_f16_packed(A, P.pack_weight_f16(W), bias, True, tile)), want)
+
+
 @pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3])
 @pytest.mark.parametrize("M,N,K", [(1, 768, 128), (130, 768, 768), (257, 384, 1024), (33, 768, 3072), (1100, 512, 640)])
 def test_fp16_gemm_on_packed_weights_gives_the_same_values(P, tile, M, N, K):

@@ -45,3 +45,12 @@ def test_kernels_use_no_scratch_memory(kernel, tmp_path):
     found = [(name, scratch) for name, scratch in kernels(tmp_path) if kernel in name]
     assert len(found) >= 4, found
     assert not [k for k in found if k[1]]
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf is not installed")
+@pytest.mark.parametrize("kernel,least", [("qkv_attention_i8_packed_kernel", 2), ("gemm_nt_ln_kernel", 4), ("gemm_nt_small_kernel", 4),
+                                          ("gemm_nt_small_f16_kernel", 3)])
+def test_kernels_of_few_instances_use_no_scratch_memory(kernel, least, tmp_path):
+    found = [(name, scratch) for name, scratch in kernels(tmp_path) if kernel in name]
+    assert len(found) >= least, found
+    assert not [k for k in found if k[1]]
