@@ -187,12 +187,14 @@ const Timing *timing(samp_encoder *e, int which)
 int choose_groups(const samp_encoder *e, int B, int S)
 {
     int g = e->groups_wanted;
-    // Measured: below about two million values (token rows x hidden) one chain is faster, from there on two are.  Forwards of 6 layers
-    // on sequences of 128 tokens, Fully-Quant / FP16, us, one group / two groups, width 768: 20 sequences 355 / 378 and 503 / 594, 22
-    // 402 / 375 and 570 / 560, 26 430 / 388 and 617 / 589; width 1024: 15 405 / 442 and 597 / 700, 17 499 / 450 and 759 / 678; width 512: 28
-    // 313 / 346 and 380 / 470, 32 336 / 329 and 413 / 413; narrow widths, whose chains are launches and little else, a little later,
-    // width 256: 52 253 / 346 and 299 / 351, 64 257 / 297 and 318 / 327, 96 337 / 309 and 405 / 389; width 128: 128 245 / 262 and 263 / 292,
-    // 192 338 / 294 and 336 / 321.  BERT-base 128 x 512 -4 %; three or four groups never beat two
+    // Below about two million values (token rows x hidden) one chain is faster.  From there on two are, at first only where there are FP16 blocks:
+    // Fully-Quant stacks break even between 2.4 and 3.2 million, narrow widths a little later.  Forwards of 6 layers on sequences of 128 tokens,
+    // us, one group / two groups: width 768 Fully-Quant 20 sequences 284 / 334, 22 343 / 366, 24 346 / 367, 28 370 / 374; FP16 20 435 / 508, 22
+    // 560 / 532, 28 590 / 558; Quant-FFN-Only 20 326 / 401, 22 403 / 404, 28 435 / 416; width 1024 Fully-Quant 8 268 / 335, 10 336 / 342, 16
+    // 352 / 378, 18 450 / 449, 24 478 / 481; FP16 14 506 / 598, 16 531 / 598, 18 713 / 678, 24 753 / 743; Quant-FFN-Only 16 398 / 435, 18 527 / 520;
+    // width 512 Fully-Quant 28 247 / 314, 32 263 / 279, 40 340 / 355, FP16 32 372 / 377, 40 480 / 434; width 256 Fully-Quant 64 221 / 282, 96
+    // 301 / 320, FP16 64 283 / 301, 96 377 / 383; width 128 Fully-Quant 128 247 / 282, 192 306 / 306, FP16 128 259 / 271, 192 333 / 342.  (Before the
+    // GEMMs read packed weights: BERT-base 128 x 512 -4 %; three or four groups never beat two.)
     if (g <= 0) g = ((long)B * S * e->cfg.hidden >= 2000000) ? 2 : 1;
     if (g > MAX_GROUPS) g = MAX_GROUPS;
     if (g > B) g = B;

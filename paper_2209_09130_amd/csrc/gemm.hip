@@ -19,8 +19,8 @@
 // fetches (ds_read_b128) conflict-free is therefore applied to the global address instead.
 // Work-groups are renumbered so that each XCD (own L2) owns a contiguous range of tiles.
 // That is the row-major kernels.  An encoder keeps its weights packed as well and runs most of its GEMMs on those (gemm_nt_stream_kernel):
-// the row-major ones are left with few rows, INT8 rows that are no whole pairs of 128-byte stages, GELU without a table, the step
-// entries and forced configurations.
+// the row-major ones are left with few rows (gemm_rules.h), INT8 rows that are no whole pairs of 128-byte stages (widths 384, 640, 896, ...), GELU
+// without a table, the step entries, forced configurations and encoders whose arena has no room for packed copies.
 #include "samp_common.h"
 #include "mfma_tile.h"
 #include "ln_wave.h"
@@ -963,7 +963,7 @@ hipError_t launch_packed(const void *A, const void *Wp, void *out, const Epi &ep
 }
 
 // The same for FP16: tiles of 32 mt tokens x 128 ntw channels.  Here the operand bytes alone decide (a fit gives the other terms no weight;
-// the choice costs 0.3 % on average over the best of the four).
+// the choice costs 0.3 % on average over the best of the four, from 256 rows on; fewer rows read the weights as they lie, gemm_rules.h).
 constexpr StreamShape STREAM_TILES_F16[] = {{1, 1}, {2, 1}, {2, 2}, {4, 2}};
 constexpr int STREAM_TILE_F16_COUNT = sizeof(STREAM_TILES_F16) / sizeof(STREAM_TILES_F16[0]);
 int stream_tile_f16(Rows rows, int N, int K)
@@ -1254,7 +1254,7 @@ hipError_t launch_small(const void *A, const void *W, void *out, const Epi &epi,
 // Measured, us per launch in a chain (before: the 64 x 96 and 64 x 128 tiles of configuration 2): N x K = 768 x 3072, 19 rows
 // 9.9 -> 3.7, 256 rows 10.7 -> 4.7, 1024 rows 10.7 -> 7.7; 768 x 768, 19 rows 4.3 -> 2.5, 1024 rows 5.3 -> 4.1; 2304 x 768,
 // 128 rows 5.2 -> 3.4.
-// Beside another batch group half of the chip is there for it (us, forward of 6 layers of width 512, counting on the whole chip / on
+// Beside another batch group half of the chip is there for it (few rows beside another group: forced groups, or no packed copies; us, forward of 6 layers of width 512, counting on the whole chip / on
 // half of it: FP16 at 2048 and 1920 rows 540 / 486, Fully-Quant at 2 x 2048 rows 386 / 372).
 constexpr int CUS = 256;
 long cus_for(Rows rows) { return rows.beside ? CUS / 2 : CUS; }
@@ -1292,7 +1292,8 @@ hipError_t launch_small_any(const void *A, const void *W, void *out, const Epi &
 // Up to some dozens of tokens a layer is a chain of launches, each 3.6 us long whatever it does.  Here every block forms the LayerNorm rows
 // that it multiplies by itself: a wave one row (int8 in, residual and out; the arithmetic of add_ln_wave_kernel), its codes into LDS, then the
 // wave's 128 channels of K times 64 channels of packed weights, which were requested before the row was; the waves' partial sums meet in
-// LDS.  K = 128 NW.  The blocks of the first 64 channels store the codes for the next residual.  What a launch and its gap cost (3.9 us) is
+// LDS.  K = 128 NW: six and eight waves, the widths of the two BERT models; two and four (256, 512) are not built, nor is an FP16 input or
+// output (Quant-FFN-Only layers take the two launches).  The blocks of the first 64 channels store the codes for the next residual.  What a launch and its gap cost (3.9 us) is
 // replaced by the row's arithmetic (0.7 us), done again by every block of its row.
 template <class Epi, int NW>
 struct LnGemm {
@@ -1492,7 +1493,8 @@ hipError_t launch_small_f16_any(const void *A, const void *W, void *out, const E
     return hipErrorNotSupported;
 }
 
-// Tile configuration per problem shape.  What bounds the main loop on this chip is the rate at which
+// Tile configuration per problem shape, for weights as they lie (who comes here: the top of this file; figures of the widths 768 and 1024 were
+// taken when every encoder did).  What bounds the main loop on this chip is the rate at which
 // a CU pulls operand stages out of L2 (20 to 40 bytes per clock per CU, whichever way they are loaded),
 // so small problems want many small tiles (more CUs pulling), large ones the larger tile (less traffic):
 //   0: 128 x 128 tile, 64-byte stages, 4-deep ring  (any K that is a multiple of 64 bytes)
