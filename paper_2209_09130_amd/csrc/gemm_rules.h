@@ -8,21 +8,25 @@ namespace samp {
 // memory-side cache; below, a GEMM waits for memory beyond it.
 constexpr int FETCH_AHEAD_MIN_ROWS = 256;
 
-// FP16: the rows as they lie while the 32 x 32 tiles of gemm_nt_small_f16_kernel are all on the chip at once, two to a CU, and one to a CU where the
-// weights have been fetched ahead.  The packed kernel's narrowest tile is 128 channels wide: 32 rows of 1024 x 4096 are 8 blocks of it, 32 of the small
-// one, and what bounds such a GEMM is how many CUs ask for its weights.  Us per launch, rows as they lie / packed, weights from memory:
-// 2304 x 768 at 19 rows 5.70 / 6.63, 96 5.72 / 6.65, 224 6.43 / 6.60, 240 (no longer two to a CU) 8.63 / 6.47; 4096 x 1024 at 19 rows 6.62 / 7.93, 64
-// 6.78 / 8.08, 128 7.70 / 7.97, 144 10.20 / 7.83; 768 x 3072 at 19 rows 13.3 / 18.1, 255 13.3 / 18.0; 1024 x 4096 at 32 rows 16.4 / 24.4, 255
-// 16.5 / 22.8; 2048 x 8192 at 19 rows 29.8 / 46.0.  Weights in the memory-side cache: 768 x 3072 at 256 rows 11.45 / 12.21, 320 (240 tiles) 11.68 / 12.55,
-// 384 12.92 / 12.41; 1024 x 4096 at 256 rows 14.66 / 15.50, 320 16.01 / 15.63; 768 x 768 at 320 rows 4.90 / 5.09, 384 5.25 / 5.08.  (Below 256 rows the wide
-// matrices are faster packed when a single model keeps its weights cached: 2304 x 768 at 19 rows 5.04 / 4.87, 192 5.66 / 5.13.)  Forward of
-// BERT-large FP16, one sequence, all packed / one to a CU / two to a CU below 256 rows: 19 tokens 1404 / 1178 / 1178, 96 tokens - / 1267 / 1234, 144
-// 1442 / 1268 / 1257; from 256 rows on two to a CU loses: 512 tokens 1386 / 1386 / 1407.
+// FP16: the rows as they lie while the 32 x 32 tiles of gemm_nt_small_f16_kernel are all on the chip at once.  The packed kernel's narrowest tile is
+// 128 channels wide: 32 rows of 1024 x 4096 are 8 blocks of it, 32 of the small one, and what bounds such a GEMM is how many CUs ask for its weights.
+// One small tile per CU is always worth it, two where the weights come from memory and the packed kernel waits longest for them: up to 96 rows (of
+// its 64 x 128 tiles, at most two in a column), and with the longer chain of loads of K from 1024 on (models of that width do not fit the memory-side
+// cache).  Us per launch, rows as they lie / packed, weights from memory: 2304 x 768 at 19 rows 5.70 / 6.63, 96 5.72 / 6.65, 128 (288 small tiles)
+// 6.53 / 6.59, 240 (576) 8.63 / 6.47; 3072 x 768 at 96 rows (288) 6.20 / 6.71, 97 (384) 6.19 / 6.34; 3072 x 1024 at 96 rows (288) 7.08 / 7.93, 160 (480)
+// 7.34 / 7.93, 192 (576) 10.22 / 7.95; 4096 x 1024 at 19 rows 6.62 / 7.93, 96 (384) 7.38 / 8.00, 128 (512) 7.70 / 7.97, 144 (640) 10.20 / 7.83; 768 x 3072
+// at 19 rows 13.3 / 18.1, 255 13.3 / 18.0; 1024 x 4096 at 32 rows 16.4 / 24.4, 255 16.5 / 22.8; 2048 x 8192 at 19 rows 29.8 / 46.0, 255 (512) 35 / 46.
+// Weights in the memory-side cache: 2304 x 768 at 19 rows 5.04 / 4.87, 96 5.18 / 5.01, 128 5.62 / 5.08, 192 (432) 5.66 / 5.13; 768 x 3072 at 256 rows
+// 11.45 / 12.21, 320 (240) 11.68 / 12.55, 384 (288) 12.92 / 12.41; 1024 x 4096 at 256 rows 14.66 / 15.50, 320 (320) 16.01 / 15.63; 768 x 768 at 320 rows 4.90 / 5.09,
+// 384 5.25 / 5.08.  Forward, one sequence, all packed / one tile per CU / two below 256 rows: BERT-large FP16 19 tokens 1408 / 1178 / 1176, 96
+// tokens - / 1267 / 1234, 144 1442 / 1268 / 1257, 512 (two there as well) 1386 / 1386 / 1407; BERT-base FP16 96 tokens - / 540 / 538, 128 609 / 552 / 557, and
+// with its weights in the memory-side cache 128 474 / 462 / 472, 192 - / 478 / 499; one layer of 128 rows, Quant-FFN-Only, 33.4 / 33.4 / 33.9.
 // K that is no multiple of 256 has no small kernel: 384 x 384 at 128 rows 4.82 / 3.99, 640 x 640 10.5 / 6.2.
 inline long f16_small_tiles(long rows, int N) { return (rows + 31) / 32 * (N / 32); }
 inline bool f16_reads_rows(long rows, int N, int K, long cus)
 {
-    return K % 256 == 0 && f16_small_tiles(rows, N) <= (rows < FETCH_AHEAD_MIN_ROWS ? 2 : 1) * cus;
+    const bool from_memory = rows <= 96 || (rows < FETCH_AHEAD_MIN_ROWS && K >= 1024);
+    return K % 256 == 0 && f16_small_tiles(rows, N) <= (from_memory ? 2 : 1) * cus;
 }
 
 // INT8: the rows as they lie where the kernel that splits K over a block's waves (gemm_nt_small_kernel) is the faster one: it asks for the whole of K at once

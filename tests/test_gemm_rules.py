@@ -33,11 +33,13 @@ def test_fp16_gemms_of_a_few_dozen_rows_spread_over_the_chip(rules, H, F):
             assert bool(rules.f16(rows, N, K, 256)) == (small <= 512), (rows, N, K)
         assert not rules.f16(2048 * 2048 // H, N, K, 256)
         assert not rules.f16(19, N, 640, 256) and not rules.f16(19, N, 384, 256)
-    # the last rows that two 32 x 32 tiles per CU hold, and one per CU from 256 rows on
-    assert rules.f16(224, 2304, 768, 256) and not rules.f16(225, 2304, 768, 256)
+    # the last rows with two 32 x 32 tiles per CU and with one, the step from the one to the other, and the weights fetched ahead from 256 rows on
+    assert rules.f16(96, 3072, 768, 256) and not rules.f16(97, 3072, 768, 256)
+    assert rules.f16(96, 2304, 768, 256) and not rules.f16(97, 2304, 768, 256)
     assert rules.f16(128, 4096, 1024, 256) and not rules.f16(129, 4096, 1024, 256)
     assert rules.f16(320, 768, 3072, 256) and not rules.f16(321, 768, 3072, 256)
-    assert rules.f16(255, 1536, 512, 256) and not rules.f16(256, 1536, 512, 256)
+    assert rules.f16(255, 2048, 8192, 256) and not rules.f16(256, 2048, 8192, 256)
+    assert rules.f16(160, 1536, 512, 256) and not rules.f16(161, 1536, 512, 256)
 
 
 @pytest.mark.parametrize("H,F", [(256, 1024), (512, 2048), (640, 2560), (768, 3072), (1024, 4096), (1280, 5120), (1536, 6144), (1792, 7168), (2048, 8192)])
