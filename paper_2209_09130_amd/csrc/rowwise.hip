@@ -375,16 +375,19 @@ hipError_t launch_embed_ln_nj(const EmbedArgs &a, hipStream_t st, const Timing *
 
 // ---------------------------------------------------------------------------------------------
 // Sequence offsets: cu[b] = number of valid tokens before sequence b (exclusive prefix sum of the
-// mask's row sums), cu[B] = T.  One block; what bounds it is latency, so a wave's item is up to 1024 entries of a row, whose
-// sixteen loads a lane has outstanding at once (three rows of 1100 entries by one wave each, 64 entries at a time: 8.8 us).
+// mask's row sums), cu[B] = T.  One block; what bounds it is latency, so a wave has sixteen loads outstanding: of rows of more than 512 entries up to
+// 1024 of one row, whose sums stay in their lanes; of shorter ones sixteen chunks of up to 64 entries, in whatever rows they lie.  Us per launch,
+// one row per wave at a time / items of up to 1024 entries of one row for all / now: 7 x 61 1.8 / 2.5 / 2.6, 32 x 128 2.6 / 4.1 / 2.7, 64 x 128 3.8 / 6.4 /
+// 3.0, 33 x 301 3.8 / 4.3 / 3.5, 300 x 40 11 / 24 / 5.6, 1024 x 64 35 / 78 / 15.5, 8192 x 4 261 / 612 / 110; 6 x 1100 3.6 / 2.8 / 2.8, 32 x 2048 9.1 / 6.4 / 6.4
+// (in chunks 11.0).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void seq_offsets_kernel(const int *__restrict__ mask, int B, int S, int *__restrict__ cu)
 {
     extern __shared__ int len[];                    // [B]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int b = threadIdx.x; b < B; b += 1024) len[b] = mask ? 0 : S;
-    if (mask) {
-        __syncthreads();
+    if (mask) __syncthreads();
+    if (mask && S > 512) {
         const int pieces = (S + 1023) / 1024;       // of a row
         for (int item = wave; item < B * pieces; item += 16) {
             const int b = item / pieces, i0 = item % pieces * 1024 + lane;
@@ -397,6 +400,26 @@ __global__ __launch_bounds__(1024) void seq_offsets_kernel(const int *__restrict
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
             if (lane == 0) atomicAdd(&len[b], s);
+        }
+    } else if (mask) {
+        const int row_chunks = (S + 63) / 64, chunks = B * row_chunks;
+        for (int first = 16 * wave; first < chunks; first += 256) {
+            int b = first / row_chunks, at = (first - b * row_chunks) * 64;
+            int v[16], live[16], row = 0, count = 0;
+#pragma unroll
+            for (int u = 0; u < 16; u++) {          // (chunks past the last repeat a row of the last sequence, and are not counted)
+                v[u] = mask[(size_t)min(b, B - 1) * S + min(at + lane, S - 1)];
+                live[u] = S - at;
+                if (lane == u) row = b;
+                at += 64;
+                if (at >= S) { at = 0; b++; }
+            }
+#pragma unroll
+            for (int u = 0; u < 16; u++) {
+                const int n = __popcll(__ballot(lane < live[u] && v[u] != 0));
+                if (lane == u) count = n;
+            }
+            if (lane < 16 && first + lane < chunks) atomicAdd(&len[row], count);
         }
     }
     __syncthreads();
