@@ -375,19 +375,64 @@ hipError_t launch_embed_ln_nj(const EmbedArgs &a, hipStream_t st, const Timing *
 
 // ---------------------------------------------------------------------------------------------
 // Sequence offsets: cu[b] = number of valid tokens before sequence b (exclusive prefix sum of the
-// mask's row sums), cu[B] = T.  One block; what bounds it is latency, so a wave has sixteen loads outstanding: of rows of more than 512 entries up to
-// 1024 of one row, whose sums stay in their lanes; of shorter ones sixteen chunks of up to 64 entries, in whatever rows they lie.  Us per launch,
-// one row per wave at a time / items of up to 1024 entries of one row for all / now: 7 x 61 1.8 / 2.5 / 2.6, 32 x 128 2.6 / 4.1 / 2.7, 64 x 128 3.8 / 6.4 /
-// 3.0, 33 x 301 3.8 / 4.3 / 3.5, 300 x 40 11 / 24 / 5.6, 1024 x 64 35 / 78 / 15.5, 8192 x 4 261 / 612 / 110; 6 x 1100 3.6 / 2.8 / 2.8, 32 x 2048 9.1 / 6.4 / 6.4
-// (in chunks 11.0).
+// mask's row sums), cu[B] = T.  One block; what bounds it is latency.  Of rows of more than 512 entries a wave has sixteen loads outstanding, up to
+// 1024 entries of one row, whose sums stay in their lanes; of shorter ones chunks of up to 64 entries, in whatever rows they lie: one or four
+// where the block's sixteen waves have no more to do than that, else sixteen (of which a few rows would leave most past the end, and their code
+// alone takes 1 us).  The sums are cleared while the first loads are on their way.  Us per launch, one row per wave at a time / items of up to 1024
+// entries of one row for all / sixteen chunks for all shorter rows / now: 2 x 8 1.6 / 2.3 / 2.7 / 1.5, 7 x 61 1.8 / 2.5 / 2.7 / 1.6, 20 x 20 2.2 / 3.2 /
+// 2.8 / 2.0, 32 x 128 2.6 / 4.2 / 2.8 / 2.2, 64 x 128 3.9 / 6.4 / 3.0 / 2.9, 33 x 301 3.9 / 4.4 / 3.6 / 3.4, 300 x 40 11.2 / 24 / 5.7 / 4.7, 1024 x 64 35 /
+// 78 / 15.5 / 12.2, 8192 x 4 260 / 612 / 110 / 86; 6 x 1100 3.4 / 2.6 / 2.7 / 2.6, 32 x 2048 9.1 / 6.4 / 6.3 / 6.1 (in chunks 11.0).
 // ---------------------------------------------------------------------------------------------
+// Chunks first, .. first + U - 1, a wave's: adds the valid entries of each to its row's sum.  started() runs when the loads are on their way.
+template <int U, class Started>
+__device__ __forceinline__ void count_chunks(const int *__restrict__ mask, int B, int S, int row_chunks, int first, int chunks, int *len, int lane,
+                                             Started started)
+{
+    int b = row_chunks == 1 ? first : first / row_chunks, at = (first - b * row_chunks) * 64;
+    int v[U], live[U], row = 0, count = 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {                   // (chunks past the last repeat a row of the last sequence, and are not counted)
+        v[u] = mask[(size_t)min(b, B - 1) * S + min(at + lane, S - 1)];
+        live[u] = S - at;
+        if (lane == u) row = b;
+        at += 64;
+        if (at >= S) { at = 0; b++; }
+    }
+    started();
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int n = __popcll(__ballot(lane < live[u] && v[u] != 0));
+        if (lane == u) count = n;
+    }
+    if (lane < U && first + lane < chunks) atomicAdd(&len[row], count);
+}
+__device__ __forceinline__ int wave_inclusive_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);          // row_shr 1, 2, 4, 8: sums inside 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);         // lane 15 of a row of 16 to the next row (rows 1 and 3)
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);         // lane 31 to the upper half
+    return v;
+}
 __global__ __launch_bounds__(1024) void seq_offsets_kernel(const int *__restrict__ mask, int B, int S, int *__restrict__ cu)
 {
     extern __shared__ int len[];                    // [B]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (int b = threadIdx.x; b < B; b += 1024) len[b] = mask ? 0 : S;
-    if (mask) __syncthreads();
-    if (mask && S > 512) {
+    const int row_chunks = (S + 63) / 64, chunks = B * row_chunks;
+    auto clear = [&]() {
+        for (int b = threadIdx.x; b < B; b += 1024) len[b] = 0;
+        __syncthreads();
+    };
+    if (!mask) {
+        for (int b = threadIdx.x; b < B; b += 1024) len[b] = S;
+    } else if (chunks <= 16) {
+        count_chunks<1>(mask, B, S, row_chunks, wave, chunks, len, lane, clear);
+    } else if (chunks <= 64) {
+        count_chunks<4>(mask, B, S, row_chunks, 4 * wave, chunks, len, lane, clear);
+    } else if (S > 512) {
+        clear();
         const int pieces = (S + 1023) / 1024;       // of a row
         for (int item = wave; item < B * pieces; item += 16) {
             const int b = item / pieces, i0 = item % pieces * 1024 + lane;
@@ -401,40 +446,19 @@ __global__ __launch_bounds__(1024) void seq_offsets_kernel(const int *__restrict
             for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
             if (lane == 0) atomicAdd(&len[b], s);
         }
-    } else if (mask) {
-        const int row_chunks = (S + 63) / 64, chunks = B * row_chunks;
-        for (int first = 16 * wave; first < chunks; first += 256) {
-            int b = first / row_chunks, at = (first - b * row_chunks) * 64;
-            int v[16], live[16], row = 0, count = 0;
-#pragma unroll
-            for (int u = 0; u < 16; u++) {          // (chunks past the last repeat a row of the last sequence, and are not counted)
-                v[u] = mask[(size_t)min(b, B - 1) * S + min(at + lane, S - 1)];
-                live[u] = S - at;
-                if (lane == u) row = b;
-                at += 64;
-                if (at >= S) { at = 0; b++; }
-            }
-#pragma unroll
-            for (int u = 0; u < 16; u++) {
-                const int n = __popcll(__ballot(lane < live[u] && v[u] != 0));
-                if (lane == u) count = n;
-            }
-            if (lane < 16 && first + lane < chunks) atomicAdd(&len[row], count);
-        }
+    } else {
+        clear();
+        for (int first = 16 * wave; first < chunks; first += 256)
+            count_chunks<16>(mask, B, S, row_chunks, first, chunks, len, lane, []() {});
     }
     __syncthreads();
     if (wave == 0) {                                // 64 sequences at a time
         int run = 0;
         for (int b0 = 0; b0 < B; b0 += 64) {
             const int b = b0 + lane, n = b < B ? len[b] : 0;
-            int upto = n;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int below = __shfl_up(upto, o, 64);
-                if (lane >= o) upto += below;
-            }
+            const int upto = wave_inclusive_sum(n);
             if (b < B) cu[b] = run + upto - n;
-            run += __shfl(upto, 63, 64);
+            run += __builtin_amdgcn_readlane(upto, 63);
         }
         if (lane == 0) cu[B] = run;
     }

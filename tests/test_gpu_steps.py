@@ -1050,9 +1050,10 @@ def _us_per_call(f, calls=50):
     return best
 
 
-@pytest.mark.parametrize("B,S", [(8192, 1), (8192, 4), (1024, 64), (1023, 65), (15, 64), (16, 64), (17, 63), (257, 128), (33, 512), (33, 513), (1, 1025), (3, 4096)])
+@pytest.mark.parametrize("B,S", [(8192, 1), (8192, 4), (1024, 64), (1023, 65), (15, 64), (16, 64), (17, 63), (257, 128), (33, 512), (33, 513), (1, 1025), (3, 4096),
+                                 (1, 1), (2, 8), (16, 1), (17, 1), (5, 192), (5, 193), (4, 256), (64, 64), (65, 64), (64, 65), (1, 1024), (1, 4096), (1, 4097), (20, 192)])
 def test_sequence_offsets_of_many_short_rows(P, B, S):
-    """Sixteen chunks of 64 entries per wave and round, over row ends and past the last row; with entries behind a zero, and other values than one."""
+    """One, four or sixteen chunks of 64 entries per wave and round, over row ends and past the last row; with entries behind a zero, and other values than one."""
     rng = np.random.default_rng(B + S)
     mask = (rng.random((B, S)) < 0.7).astype(np.int32) * rng.integers(-3, 4, (B, S)).astype(np.int32)
     mask[:, 0] = 1
@@ -1062,9 +1063,47 @@ def test_sequence_offsets_of_many_short_rows(P, B, S):
 
 def test_sequence_offsets_do_not_wait_for_every_short_row(P):
     """8192 rows of four entries against 32 rows of 1024, the same number of entries: the rows' latencies overlap.  (One row or less per wave and
-    round: 354 and 633 us against 25; now 132.)"""
+    round: 354 and 633 us against 25; now about 110.)"""
     run = {}
     for B, S in ((8192, 4), (32, 1024)):
         hidden, mask = dev(np.zeros((B, S, 8), np.float16)), dev(np.ones((B, S), np.int32))
         run[S] = _us_per_call(lambda: P.pack_rows(hidden, mask))
     assert run[4] < 9 * run[1024], run
+
+
+def _us_in_a_graph(f, calls=50):
+    """Per call, of `calls` calls in one graph: no host time between them.  The fastest of ten replays."""
+    import torch
+    f()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(calls):
+            f()
+    best = np.inf
+    for _ in range(10):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+def test_sequence_offsets_of_few_rows_take_no_longer_than_their_launch(P):
+    """Offsets and packing of two rows of eight tokens against two launches that fill one value each: 3.7 against 3.3 us (4.8 where every wave
+    has the loads of sixteen chunks)."""
+    import torch
+    from paper_2209_09130_amd import binding
+    B, S, H = 2, 8, 8
+    hidden, mask = dev(np.zeros((B, S, H), np.float16)), dev(np.ones((B, S), np.int32))
+    packed, cu, row_map = torch.zeros_like(hidden), dev(np.zeros(B + 1, np.int32)), dev(np.zeros(B * S, np.int32))
+
+    def pack():
+        dp = binding._dp
+        binding._check(P.lib().samp_pack_rows(dp(hidden), dp(mask), B, S, H, binding._f(0.0), dp(packed), dp(cu), dp(row_map), binding._stream()))
+
+    one = torch.zeros(1, device="cuda")
+    took, launches = _us_in_a_graph(pack), _us_in_a_graph(lambda: (one.zero_(), one.zero_()))
+    assert took < 1.3 * launches, (took, launches)
