@@ -176,7 +176,8 @@ SAMP_API int samp_encoder_forward_ids(samp_encoder_t *enc, const samp_embedding_
 /* Sequences are independent (all scales are static, Appendix B), so a forward may cut a batch
  * into up to 4 groups of sequences that run concurrently on streams owned by the encoder, forked
  * from and joined back into the caller's stream; results do not depend on the split.  groups = 0
- * (default) chooses by size (two groups from two million token rows x hidden on), 1 disables the split, 2..4 force it. */
+ * (default) chooses by size (two groups from two million token rows x hidden on, if that times the layers is at least 3.2 million,
+ * in Fully-Quant stacks 6.5 million), 1 disables the split, 2..4 force it.                       */
 SAMP_API int samp_encoder_set_groups(samp_encoder_t *enc, int32_t groups);
 
 /* Section 3.2 hands the QKV GEMM's requantised int8 output straight to the attention; for sequences of at

@@ -152,7 +152,7 @@ constexpr int MAX_GROUPS = 4;
 struct samp_encoder {
     samp_config_t cfg;
     std::vector<Layer> L;
-    bool all_fp16;
+    bool all_fp16, all_int8;                        // every block of every layer
     int prof_which = SAMP_PROF_OFF;
     int fusion_wanted = 0;                          // QKV GEMM + attention in one kernel: 0 by size, 1 never, 2 whenever the shape allows
     std::vector<Timing> events;                     // pool, created on first use
@@ -187,15 +187,21 @@ const Timing *timing(samp_encoder *e, int which)
 int choose_groups(const samp_encoder *e, int B, int S)
 {
     int g = e->groups_wanted;
-    // Below about two million values (token rows x hidden) one chain is faster.  From there on two are, at first only where there are FP16 blocks:
-    // Fully-Quant stacks break even between 2.4 and 3.2 million, narrow widths a little later.  Forwards of 6 layers on sequences of 128 tokens,
-    // us, one group / two groups: width 768 Fully-Quant 20 sequences 284 / 334, 22 343 / 366, 24 346 / 367, 28 370 / 374; FP16 20 435 / 508, 22
-    // 560 / 532, 28 590 / 558; Quant-FFN-Only 20 326 / 401, 22 403 / 404, 28 435 / 416; width 1024 Fully-Quant 8 268 / 335, 10 336 / 342, 16
-    // 352 / 378, 18 450 / 449, 24 478 / 481; FP16 14 506 / 598, 16 531 / 598, 18 713 / 678, 24 753 / 743; Quant-FFN-Only 16 398 / 435, 18 527 / 520;
-    // width 512 Fully-Quant 28 247 / 314, 32 263 / 279, 40 340 / 355, FP16 32 372 / 377, 40 480 / 434; width 256 Fully-Quant 64 221 / 282, 96
-    // 301 / 320, FP16 64 283 / 301, 96 377 / 383; width 128 Fully-Quant 128 247 / 282, 192 306 / 306, FP16 128 259 / 271, 192 333 / 342.  (Before the
-    // GEMMs read packed weights: BERT-base 128 x 512 -4 %; three or four groups never beat two.)
-    if (g <= 0) g = ((long)B * S * e->cfg.hidden >= 2000000) ? 2 : 1;
+    // Two groups from two million values (token rows x hidden) on, if the layers are many enough: forking to another stream and joining again costs a
+    // forward some 40 us, which every layer pays back in part by hiding one group's launches and tails behind the other's kernels, a layer with FP16
+    // blocks more of it.  Below, one chain is faster.  Forwards on sequences of 128 tokens, us, one group / two groups, by number of layers and
+    // sequences: width 768 Fully-Quant 1 layer 22 sequences 65 / 108, 47 96 / 110, 61 105 / 118, 102 159 / 163, 132 207 / 196; 2 layers 41 151 /
+    // 161, 81 250 / 242; 4 layers 22 230 / 238, 35 284 / 267; 6 layers 22 343 / 333; 12 layers 18 544 / 616, 22 673 / 639, 31 714 / 686; Quant-FFN-Only
+    // 1 layer 22 67 / 95, 47 106 / 111, 81 147 / 147, 132 231 / 219; 2 layers 41 168 / 179, 61 228 / 226; 4 layers 22 255 / 252; 12 layers 18 588 / 667, 22
+    // 755 / 718; FP16 1 layer 22 92 / 100, 35 105 / 114, 47 143 / 140, 61 158 / 166, 102 254 / 248; 2 layers 102 504 / 477; 4 layers 22 357 / 336; 12
+    // layers 18 781 / 943, 22 1066 / 973.  Width 1024 Fully-Quant 1 layer 46 131 / 134, 99 244 / 234; 3 layers 17 220 / 209, 24 231 / 235; 24 layers 14
+    // 1333 / 1318, 17 1729 / 1557; FP16 3 layers 17 336 / 314; 24 layers 14 1946 / 2308, 17 2749 / 2483.  Width 512, 4 layers Fully-Quant 34 231 /
+    // 215; width 256 4 layers 67 196 / 207, 98 213 / 211.  Where three such encoders and their buffers take turns, so that less is in the caches, two
+    // groups pay earlier: 1 layer of width 768, FP16 35 x 128 108 / 115, 9 x 490 154 / 150, 4 x 1024 154 / 154, 44 x 128 158 / 144, 61 x 128 182 / 179, Fully-Quant
+    // 60 x 128 106 / 119, 65 x 128 - / 123, 90 x 128 159 / 164.  Ragged batches (16 to 100 % of the tokens, which only the device knows) break even
+    // where the others do.  (Before the GEMMs read packed weights three or four groups never beat two.)
+    const long values = (long)B * S * e->cfg.hidden;
+    if (g <= 0) g = values >= 2000000 && values * e->cfg.layers >= (e->all_int8 ? 6500000 : 3200000) ? 2 : 1;
     if (g > MAX_GROUPS) g = MAX_GROUPS;
     if (g > B) g = B;
     return g;
@@ -468,6 +474,7 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
     if (!E) return fail(SAMP_ERR_ARG, "out of host memory");
     E->cfg = *cfg;
     E->all_fp16 = !any8;
+    E->all_int8 = std::all_of(modes, modes + cfg->layers, [](uint8_t m) { return (m & SAMP_FULL_INT8) == SAMP_FULL_INT8; });
     E->L.resize(cfg->layers);
     const size_t H = cfg->hidden, F = cfg->ffn;
     Carver cv{static_cast<char *>(dev_arena), 0};

@@ -652,6 +652,29 @@ def test_a_batch_in_two_groups_is_the_same_bytes_at_the_bounds_of_the_kernel_cho
     assert torch.equal(*outs)
 
 
+@pytest.mark.parametrize("modes,batch,groups", [((FP16,), 195, 1), ((FP16,), 196, 2), ((FP16,) * 3, 122, 1), ((FP16,) * 2, 128, 2), ((MHA_INT8,), 195, 1),
+                                                ((FULL_INT8,), 275, 1), ((FULL_INT8,), 397, 2), ((FULL_INT8 | P_UNSIGNED,) * 3, 128, 1),
+                                                ((FULL_INT8,) * 4, 128, 2), ((FULL_INT8, FULL_INT8, FFN_INT8), 128, 2)])
+def test_a_batch_is_split_where_its_layers_pay_for_the_fork(P, modes, batch, groups):
+    """Two groups need two million values (rows x width) and 3.2 million over all layers, 6.5 where all blocks are INT8: one layer of 22 x 128 tokens,
+    width 768, takes 65 us in one group and 108 in two.  A timed forward counts the LayerNorm launches of all groups; the bytes are those of
+    one group."""
+    import torch
+    w = W.Workload("fork", len(modes), 128, 2, 128, batch, 128, modes, plain_params=False, calib_batch=1, calib_seq=32)
+    wts = W.make_weights(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w)) if any(modes) else None
+    enc = P.Encoder(*args(w), w.modes, wts, sc, max_batch=batch, max_seq=128)
+    h = torch.randn((batch, 128, 128), device="cuda", generator=torch.Generator("cuda").manual_seed(batch)).half()
+    out = enc.forward(h).clone()
+    enc.profile(P.PROF_LN1)
+    enc.forward(h)
+    assert enc.profile_read()[1] == groups * len(modes)
+    enc.profile(P.PROF_OFF)
+    enc.set_groups(1)
+    assert torch.equal(enc.forward(h), out)
+    enc.close()
+
+
 @pytest.mark.parametrize("varlen", [False, True])
 def test_forward_captured_into_a_graph_of_the_caller(P, varlen):
     """A caller that records the forward into a HIP graph of its own switches the library's graph cache off; the plain
