@@ -11,7 +11,7 @@
 // One block = (sequence, head, 32 queries), 4 waves (8 for INT8 beyond 512 keys); wave w owns key
 // tiles w, w+4, ... (32 keys each).  S^T = K.Q^T is computed so that in the 32x32 MFMA result a lane holds ONE query and 16
 // keys: after the softmax those 16 values are, as they stand, the lane's operand of the P.V MFMA.
-// Its other operand is V^T, staged per wave through LDS.  Row maxima, row sums and the partial
+// Its other operand is V^T: V rows lie in the wave's LDS as they come and are transposed by the read.  Row maxima, row sums and the partial
 // P.V products are combined across the waves through LDS (integer partial sums: exact).
 // Every floating-point value that decides an int8 code follows one fixed sequence of binary32
 // operations; exp and the row sum are evaluated in binary64 and rounded once.
@@ -74,16 +74,20 @@ __device__ __forceinline__ double exp_nonpos(double x)
 // beside them (2.4 clocks of LDS time per wave and read where many entries are equal; those are broadcast).  Forward with the
 // polynomial and with this: BERT-base 128 x 512 Fully-Quant 12104 / 11603 us, 6 x 500..1100 1933 / 1860, 33 x 40..301 binary16
 // softmax 1709 / 1685 (the second part of the constant is 1.1, 1.5 and 0.7 % of that).
-// The result underflows to a binary32 zero below -103.98, so the argument is clamped at -104, also that of a masked key.
+// The result underflows to a binary32 zero below -103.98, so the argument may be clamped at -104 or below, also that of a masked key.
+// UNIT: the argument is given as its UNIT-th part, a power of two that goes into the constants: with -128 the subtraction of a score from the row's
+// maximum (both divided by 128, which is exact) clamps its own result to [0, 1] and no operation is spent on the bound.  Below -128 is 0 like below -104.
 typedef uint64_t ExpTable[256];
+template <int UNIT> __device__ __forceinline__ float exp_units(double xd, const ExpTable &table);
 __device__ __forceinline__ float exp_nonpos(float x, const ExpTable &table)
+{ return exp_units<1>((double)__builtin_fmaxf(x, -104.0f), table); }
+template <int UNIT> __device__ __forceinline__ float exp_units(double xd, const ExpTable &table)
 {
-    const double xd = (double)__builtin_fmaxf(x, -104.0f);
-    const double shifted = __builtin_fma(xd, 0x1.71547652b82fep+8, 6755399441055744.0);
+    const double shifted = __builtin_fma(xd, UNIT * 0x1.71547652b82fep+8, 6755399441055744.0);
     const unsigned k = (unsigned)__double_as_longlong(shifted);
     const uint64_t entry = table[k & 255];
-    double f = __builtin_fma(xd, 0x1.71547652b82fep+8, -(shifted - 6755399441055744.0));
-    f = __builtin_fma(xd, 0x1.777d0ffda0d24p-48, f);
+    double f = __builtin_fma(xd, UNIT * 0x1.71547652b82fep+8, -(shifted - 6755399441055744.0));
+    f = __builtin_fma(xd, UNIT * 0x1.777d0ffda0d24p-48, f);
     double q = 0x1.3b2ab83ecf101p-39;
     q = __builtin_fma(q, f, 0x1.c6b0902ba1a20p-29);
     q = __builtin_fma(q, f, 0x1.ebfbdff82c585p-19);
@@ -91,6 +95,10 @@ __device__ __forceinline__ float exp_nonpos(float x, const ExpTable &table)
     const double scale = __hiloint2double((int)((unsigned)(entry >> 32) + (k << 12)), (int)(unsigned)entry);
     return (float)__builtin_fma(scale, f * q, scale);
 }
+constexpr float SCORE_UNIT = 0x1p-7f;
+// exp(128 (score - max)), score <= max
+__device__ __forceinline__ float exp_below(float score, float max, const ExpTable &table)
+{ return exp_units<-128>((double)__builtin_amdgcn_fmed3f(max - score, 0.0f, 1.0f), table); }
 
 // The wave's number inside its block, as a scalar: every test on it (does this wave own key tile j?) then is a
 // scalar branch instead of a lane mask with copies of the live registers where the paths join.
@@ -155,6 +163,58 @@ __device__ __forceinline__ void store_vt_tile(const unsigned (&d)[2][4], int lan
     }
 }
 
+// V rows of a key tile as they lie (32 keys x 64 codes) in LDS, and V^T operands out of it: ds_read_b64_tr_b8 hands lane i of sixteen the byte
+// i & 7 of the eight bytes that each lane of parity i >> 3 points at, so that with lanes 2 j and 2 j + 1 at 16 channels of key j a lane gets one
+// channel of eight keys.  No transposition in registers (16 byte permutes and eight dword loads per tile), and the rows can come as direct loads.
+// 16-byte chunk c of key k lies at position c ^ 2 ((k >> 3) & 1): the 32 lanes of a read's phase hit 64 different banks.
+constexpr int V_TILE = 32 * 64;
+struct VLane {                                            // what a lane loads and reads of every tile
+    unsigned from, at;                                    // offset of its 16 bytes in the first 16 rows; of its first read in a tile
+    __device__ __forceinline__ VLane(unsigned ld, int lane)
+    {
+        from = (unsigned)(lane >> 2) * ld + (((lane & 3) ^ ((lane >> 5) << 1)) << 4);
+        const int pair = (lane >> 1) & 7;                 // keys 4 g + (0..3, 8..11) of the half, channels 16 ((lane >> 4) & 1) + 8 (lane & 1) ..
+        at = (4 * (lane >> 5) + (pair & 3) + 8 * (pair >> 2)) * 64 + ((((lane >> 4) & 1) ^ (pair >> 2 << 1)) << 4) + 8 * (lane & 1);
+    }
+};
+// channels 32 cb + (lane & 31), keys 4 (lane >> 5) + (0..3, 8..11, 16..19, 24..27)
+__device__ __forceinline__ v4i read_vt(const int8_t *tile, unsigned at, int cb)
+{
+    typedef __attribute__((address_space(3))) v2i *Lds;
+    const int8_t *p = tile + (at ^ (cb << 5));
+    const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((Lds)p), hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((Lds)(p + 1024));
+    return v4i{lo.x, lo.y, hi.x, hi.y};
+}
+__device__ __forceinline__ void request_v_tile(__amdgpu_buffer_rsrc_t rows, unsigned from, unsigned ld, int8_t *tile)
+{
+    buffer_to_lds128(rows, from, 0, tile);
+    buffer_to_lds128(rows, from + 16 * ld, 0, tile + 1024);
+}
+
+// Four softmax codes, rne((e rS) inv_sp): the conversion rounds to the nearest integer, ties to even, saturates to [0, 255] (probabilities are not
+// negative) and puts the byte into its place, one operation where clamp, rounding add and byte permutes were 2.75.
+__device__ __forceinline__ int softmax_codes(const float (&e)[16], int first, float rS, float inv_sp)
+{
+    unsigned pk = 0;
+#pragma unroll
+    for (int t = 0; t < 4; t++) pk = __builtin_amdgcn_cvt_pk_u8_f32((e[first + t] * rS) * inv_sp, t, pk);
+    return (int)pk;
+}
+// Signed codes end at 127.  A row's largest code is that of exp(0) = 1, so as long as no row of the wave (or of the lanes that share its scores) has a
+// probability beyond the calibrated range nothing is to be done; otherwise the products are formed and bounded here, and the factors become 1.
+template <int NT, class Live>
+__device__ __forceinline__ void bound_codes(float (&e)[NT][16], float &rS, float &inv_sp, Live live)
+{
+    if (__builtin_amdgcn_ballot_w64(rS * inv_sp > 127.0f) == 0) return;
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+        if (live(i)) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) e[i][k] = __builtin_fminf((e[i][k] * rS) * inv_sp, 127.0f);
+        }
+    rS = inv_sp = 1.0f;
+}
+
 struct SeqInfo { int t0, n; };
 __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 {
@@ -167,6 +227,10 @@ __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 //     bit) and the missing 128 * sum_k V[k] of the same V tiles is added back; both are exact in int32.
 // HIST: also counts every softmax code of a valid (query, key) pair into p_hist[256] (a diagnostic:
 //     which of the 256 integers the softmax output uses, as Appendix B tabulates).
+// What bounds it beyond a few hundred keys is vector arithmetic, all of it at four clocks per operation and wave: 20.5 operations per score, and
+// per tile of 16 scores some 25 for addresses, loads and V (it was 24 and 65 with V transposed by byte permutes on the way to LDS, row numbers
+// clamped per load, an exponential that clamps its argument and codes packed from rounding adds).  All loads of up to four tiles are requested at
+// once.  Forward, us, before / now: BERT-base 128 x 512 10850 / 10370, 6 x 500..1100 1690 / 1590, BERT-large 32 x 256 3780 / 3728, 7 x 61 397 / 393.
 // At least two waves per SIMD are asked for so that the register budget is one the matrix-core results fit
 // without the accumulation registers: the products then land where the vector ALU reads them.
 // NW: waves of the block.  Four up to 512 keys; eight up to 2048 (NT = 3 to 8 key tiles per wave), so that the strip of scores of a
@@ -179,13 +243,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
                                                            int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist)
 {
     __shared__ unsigned hist[HIST ? 256 : 1];
-    // One slab per wave: first its V^T tiles (written and read by that wave alone), then, once its last P.V
-    // product has read them, its partial context for the other waves; sharing the bytes lets a third block fit a CU.
-    // It holds at most four tiles: a fifth one (and so on) takes the place of a tile that has been multiplied, two steps before it
-    // is used itself (three steps before, one more tile of scores is alive: five tiles of unsigned codes then took scratch).
-    constexpr int VT_TILE = 64 * VT_STRIDE_I8, SO_BYTES = QB * 64 * 4, VT_TILES = NT < 4 ? NT : 4;
-    constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
-    __shared__ __attribute__((aligned(16))) int8_t slab[NW][SLAB];
+    // One slab per wave: first its V tiles (written and read by that wave alone), then, once its last P.V
+    // product has read them, its partial context for the other waves; sharing the bytes lets a fourth block fit a CU.
+    // It holds at most four tiles, requested at the start: a fifth one (and so on) takes the place of a tile that has been multiplied, through
+    // registers and two steps before it is used itself.
+    constexpr int SO_BYTES = QB * 64 * 4, V_TILES = NT < 4 ? NT : 4;
+    constexpr int SLAB = V_TILES * V_TILE > SO_BYTES ? V_TILES * V_TILE : SO_BYTES;
+    constexpr int K_AHEAD = NT <= 4 ? NT : NT == 5 && PU ? 1 : 2;   // key tiles whose rows are requested before the first product (as many as registers hold)
+    __shared__ __attribute__((aligned(1024))) int8_t slab[NW][SLAB];
     auto so = [&](int wave) { return reinterpret_cast<int(*)[64]>(slab[wave]); };
     __shared__ float smax[NW][QB];
     __shared__ double ssum[NW][QB];
@@ -202,56 +267,65 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;                          // row offsets inside a sequence fit 32 bits
-    const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64, *vp = base + 2 * H;
+    const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64;
+    // rows from j0 to the end of the sequence; a row past it reads as zeros, so no load needs a test or an address of its own
+    auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, max((n - j0) * (int)ld - head * 64, 0)); };
+    auto first_key = [&](int i) { return (w + NW * i) * 32; };
     const uint64_t table_entry = EXP2_TABLE[tid & 255];
     if (HIST && tid < 256) hist[tid] = 0;                                      // ordered before its use by the barriers below
 
-    // Q strip: second MFMA operand, lane (query r, half g) holds 16 consecutive bytes of the head dim
-    const int qrow = min(q0 + r, n - 1);
-    v4i qf[2];
+    // lane (row r, half g) holds 16 consecutive bytes of the head dim of a query row (second MFMA operand) or a key row (first)
+    const unsigned row_at = (unsigned)r * ld + g * 16, key_at = row_at + H;
+    const VLane vl(ld, lane);
+    v4i qf[2], kf[K_AHEAD][2];
+    auto request_keys = [&](int i) {
+        const auto rows = rows_from(first_key(i));
 #pragma unroll
-    for (int ks = 0; ks < 2; ks++) qf[ks] = *reinterpret_cast<const v4i *>(base + (unsigned)qrow * ld + ks * 32 + g * 16);
+        for (int ks = 0; ks < 2; ks++) kf[i % K_AHEAD][ks] = __builtin_amdgcn_raw_buffer_load_b128(rows, key_at + ks * 32, 0, 0);
+    };
+    {
+        const auto rows = rows_from(q0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) qf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rows, row_at + ks * 32, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < K_AHEAD; i++) request_keys(i);
+#pragma unroll
+    for (int i = 0; i < V_TILES; i++) request_v_tile(rows_from(first_key(i)), vl.from + 2 * H, ld, &slab[w][i * V_TILE]);
 
-    float sc[NT][16];
+    float sc[NT][16];                                             // scores / 128, then exponentials
+    const float m_unit = m_sc * SCORE_UNIT;
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + NW * i) * 32;
+        const int j0 = first_key(i);
         if (j0 < n) {                                           // wave-uniform
-            // the K rows are requested first, then the V rows: the first product then waits for the K rows only
-            const int krow = min(j0 + r, n - 1);
-            const int8_t *kp = base + (unsigned)krow * ld + H;
-            v4i kf[2];
-#pragma unroll
-            for (int ks = 0; ks < 2; ks++) kf[ks] = *reinterpret_cast<const v4i *>(kp + ks * 32 + g * 16);
-            const bool full = j0 + 32 <= n;                      // wave-uniform
-            unsigned d[2][4];                                    // all eight loads are issued before the first is used
-            if (i < VT_TILES) load_v_tile(vp, ld, j0, n, lane, d);
             v16i acc;
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[e] = 0;
 #pragma unroll
-            for (int ks = 0; ks < 2; ks++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[ks], qf[ks], acc, 0, 0, 0);
-            if (i < VT_TILES) store_vt_tile(d, lane, &slab[w][i * VT_TILE]);
-            if (full) {                                          // a full tile needs no masking
+            for (int ks = 0; ks < 2; ks++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[i % K_AHEAD][ks], qf[ks], acc, 0, 0, 0);
+            if (j0 + 32 <= n) {                                  // a full tile needs no masking
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
-                    sc[i][e] = (float)acc[e] * m_sc;
+                    sc[i][e] = (float)acc[e] * m_unit;
                     mx = __builtin_fmaxf(mx, sc[i][e]);
                 }
             } else {
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
                     const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
-                    sc[i][e] = key < n ? (float)acc[e] * m_sc : -INFINITY;
+                    sc[i][e] = key < n ? (float)acc[e] * m_unit : -INFINITY;
                     mx = __builtin_fmaxf(mx, sc[i][e]);
                 }
             }
         }                                                        // the scores of a tile past the end are never read
+        if (i + K_AHEAD < NT) request_keys(i + K_AHEAD);
     }
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
     if (NW == 4 || tid < 256) exp_table[tid] = table_entry;
+    wait_vm<0>();                                                 // the wave's V tiles are in its slab
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
@@ -260,10 +334,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     double part = 0.0;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        if ((w + NW * i) * 32 < n) {
+        if (first_key(i) < n) {
 #pragma unroll
             for (int e = 0; e < 16; e++) {
-                sc[i][e] = exp_nonpos(sc[i][e] - mx, exp_table);
+                sc[i][e] = exp_below(sc[i][e], mx, exp_table);
                 part += (double)sc[i][e];
             }
         }
@@ -275,7 +349,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
 #pragma unroll
     for (int u = 1; u < NW; u++) total += ssum[u][r];
     const float S = (float)total;
-    const float rS = __fdiv_rn(1.0f, S);
+    float rS = __fdiv_rn(1.0f, S);
+    if (!PU) bound_codes(sc, rS, inv_sp, [&](int i) { return first_key(i) < n; });
 
     // Every accumulator register starts from a zero of its own that the compiler cannot see through: with literal
     // zeros it gives the first product of each path registers of its own and copies all 32 accumulators where the
@@ -286,38 +361,39 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     for (int cb = 0; cb < 2; cb++)
 #pragma unroll
         for (int e = 0; e < 16; e++) o[cb][e] = opaque_zero();
-    const float lo = PU ? 0.0f : -127.0f, hi = PU ? 255.0f : 127.0f;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + NW * i) * 32;
-        const int j2 = j0 + 2 * 32 * NW;                          // the tile that takes the place of the one before the last
-        unsigned d[2][4];
-        if (i > 1 && i + 2 < NT && j2 < n) load_v_tile(vp, ld, j2, n, lane_again(), d);
+        const int j0 = first_key(i);
+        v4i late[2];                                          // tile i + 2 takes the place of tile i - 2
+        const bool refill = i > 1 && i + 2 < NT && first_key(i + 2) < n;
+        if (refill) {
+            const auto rows = rows_from(first_key(i + 2));
+#pragma unroll
+            for (int u = 0; u < 2; u++) late[u] = __builtin_amdgcn_raw_buffer_load_b128(rows, vl.from + 2 * H + u * 16 * ld, 0, 0);
+        }
         if (j0 < n) {
             v4i pf;
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                float f[4];
+                pf[q] = softmax_codes(sc[i], 4 * q, rS, inv_sp);
+                if (HIST) {
 #pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    // clamp, then round half to even in the adder: the code is the low byte of f
-                    f[t] = __builtin_amdgcn_fmed3f((sc[i][4 * q + t] * rS) * inv_sp, lo, hi) + SAMP_RNE_MAGIC;
-                    if (HIST && q0 + r < n && j0 + 8 * q + 4 * g + t < n) atomicAdd(&hist[__float_as_uint(f[t]) & 0xffu], 1u);
+                    for (int t = 0; t < 4; t++)
+                        if (q0 + r < n && j0 + 8 * q + 4 * g + t < n) atomicAdd(&hist[((unsigned)pf[q] >> (8 * t)) & 0xffu], 1u);
                 }
-                pf[q] = pack_codes(f[0], f[1], f[2], f[3]);
-                if (PU) pf[q] ^= (int)0x80808080u;                 // code - 128 as a signed byte
+                if (PU) pf[q] ^= (int)0x80808080u;             // code - 128 as a signed byte
             }
 #pragma unroll
             for (int cb = 0; cb < 2; cb++) {
-                v4i vf;
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-                    vf[q] = *reinterpret_cast<const int *>(&slab[w][(i & 3) * VT_TILE + (cb * 32 + r) * VT_STRIDE_I8 + 8 * q + 4 * g]);
+                const v4i vf = read_vt(&slab[w][(i & 3) * V_TILE], vl.at, cb);
                 o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf, vf, o[cb], 0, 0, 0);
                 if (PU) vsum[cb] = add_codes(vf, vsum[cb]);
             }
         }
-        if (i > 1 && i + 2 < NT && j2 < n) store_vt_tile(d, lane_again(), &slab[w][((i + 2) & 3) * VT_TILE]);
+        if (refill) {
+#pragma unroll
+            for (int u = 0; u < 2; u++) *reinterpret_cast<v4i *>(&slab[w][((i + 2) & 3) * V_TILE + u * 1024 + lane_again() * 16]) = late[u];
+        }
     }
     if (PU) {
 #pragma unroll
@@ -340,15 +416,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
         int pk[CPT / 4];
 #pragma unroll
         for (int d = 0; d < CPT / 4; d++) {
-            int codes[4];
+            float codes[4];
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 int O = 0;
 #pragma unroll
                 for (int u = 0; u < NW; u++) O += so(u)[query][c0 + 4 * d + e];
-                codes[e] = qcode((float)O * m_ctx);
+                codes[e] = code_bits((float)O * m_ctx);
             }
-            pk[d] = pack4(codes[0], codes[1], codes[2], codes[3]);
+            pk[d] = pack_codes(codes[0], codes[1], codes[2], codes[3]);
         }
         int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0;
         if constexpr (CPT == 8) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
@@ -553,7 +629,8 @@ __device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *
         v4i qf[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ks++) qf[ks] = *reinterpret_cast<const v4i *>(lq + (q0 + r) * QK_STRIDE + ks * 32 + g * 16);
-        float sc[NKT][16];
+        float sc[NKT][16];                                        // scores / 128, then exponentials
+        const float m_unit = m_sc * SCORE_UNIT;
         float mx = -INFINITY;
 #pragma unroll
         for (int i = 0; i < NKT; i++) {
@@ -570,14 +647,14 @@ __device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *
                 if (j0 + 32 <= n) {
 #pragma unroll
                     for (int e = 0; e < 16; e++) {
-                        sc[i][e] = (float)s[e] * m_sc;
+                        sc[i][e] = (float)s[e] * m_unit;
                         mx = __builtin_fmaxf(mx, sc[i][e]);
                     }
                 } else {
 #pragma unroll
                     for (int e = 0; e < 16; e++) {
                         const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
-                        sc[i][e] = key < n ? (float)s[e] * m_sc : -INFINITY;
+                        sc[i][e] = key < n ? (float)s[e] * m_unit : -INFINITY;
                         mx = __builtin_fmaxf(mx, sc[i][e]);
                     }
                 }
@@ -592,7 +669,7 @@ __device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *
             if (32 * i < n) {
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
-                    sc[i][e] = exp_nonpos(sc[i][e] - mx, exp_table);
+                    sc[i][e] = exp_below(sc[i][e], mx, exp_table);
                     part[i & 3] += (double)sc[i][e];
                 }
             }
@@ -600,14 +677,14 @@ __device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *
 #pragma unroll
         for (int u = 0; u < 4; u++) part[u] += __shfl_xor(part[u], 32, 64);
         const float S = (float)(((part[0] + part[1]) + part[2]) + part[3]);
-        const float rS = __fdiv_rn(1.0f, S);
+        float rS = __fdiv_rn(1.0f, S), per_code = inv_sp;
+        if (!PU) bound_codes(sc, rS, per_code, [&](int i) { return 32 * i < n; });
 
         v16i o[2], o1[PU ? 2 : 1];
 #pragma unroll
         for (int cb = 0; cb < 2; cb++)
 #pragma unroll
             for (int e = 0; e < 16; e++) { o[cb][e] = opaque_zero(); if (PU) o1[cb][e] = opaque_zero(); }
-        const float lo = PU ? 0.0f : -127.0f, hi = PU ? 255.0f : 127.0f;
         const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 #pragma unroll
         for (int i = 0; i < NKT; i++) {
@@ -616,10 +693,7 @@ __device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *
                 v4i pf;
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    float f[4];
-#pragma unroll
-                    for (int t = 0; t < 4; t++) f[t] = __builtin_amdgcn_fmed3f((sc[i][4 * q + t] * rS) * inv_sp, lo, hi) + SAMP_RNE_MAGIC;
-                    pf[q] = pack_codes(f[0], f[1], f[2], f[3]);
+                    pf[q] = softmax_codes(sc[i], 4 * q, rS, per_code);
                     if (PU) pf[q] ^= (int)0x80808080u;             // code - 128 as a signed byte
                 }
 #pragma unroll
@@ -649,8 +723,8 @@ __device__ __forceinline__ void attend_i8(char *lq, const char *lk, const char *
 #pragma unroll
             for (int q = 0; q < 4; q++)
                 *reinterpret_cast<int *>(slab + r * QK_STRIDE + cb * 32 + 8 * q + 4 * g) =
-                    pack4(qcode((float)o[cb][4 * q] * m_ctx), qcode((float)o[cb][4 * q + 1] * m_ctx), qcode((float)o[cb][4 * q + 2] * m_ctx),
-                          qcode((float)o[cb][4 * q + 3] * m_ctx));
+                    pack_codes(code_bits((float)o[cb][4 * q] * m_ctx), code_bits((float)o[cb][4 * q + 1] * m_ctx),
+                               code_bits((float)o[cb][4 * q + 2] * m_ctx), code_bits((float)o[cb][4 * q + 3] * m_ctx));
         __builtin_amdgcn_wave_barrier();
         const int query = lane >> 1, half = lane & 1;
         if (q0 + query < n) {

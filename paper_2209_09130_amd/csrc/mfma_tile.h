@@ -39,6 +39,9 @@ template <int N> __device__ __forceinline__ void wait_vm()
 // one that may return out of order, it waits for all that are in flight.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base)          // no bounds check
 { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0xffffffffu, 0x00027000); }
+// `bytes` of it are there: beyond, loads return zeros
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, int bytes)
+{ return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00027000); }
 // 16 or 4 bytes per lane, one lane's behind the other's in LDS
 __device__ __forceinline__ void buffer_to_lds128(__amdgpu_buffer_rsrc_t from, unsigned offset, unsigned scalar_offset, void *lds)
 { __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void *)lds, 16, offset, scalar_offset, 0, 0); }

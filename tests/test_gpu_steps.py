@@ -612,6 +612,26 @@ def test_int8_attention_unsigned_softmax_codes_bit_exact(P, lens, heads):
         assert np.abs(want).max() > 20
 
 
+@pytest.mark.parametrize("lens", [[32, 1, 31], [130, 256, 97], [385, 512, 5], [513, 1100, 64], [2048, 1793]])
+@pytest.mark.parametrize("unsigned", [False, True])
+def test_int8_attention_where_some_rows_pass_the_calibrated_range(P, lens, unsigned):
+    """Codes end at 127 (255): the kernel bounds them only where a row of the wave needs it.  Half of the sequences have scores of
+    zero (no code near the end), in the others every third query sees one key far above the rest, whose code is beyond it."""
+    rng = np.random.default_rng(sum(lens))
+    heads = 2
+    cu = _cu(lens)
+    qkv = np.clip(np.rint(rng.standard_normal((int(cu[-1]), 3, heads, 64)) * 30), -127, 127).astype(np.int8)
+    for i in range(len(lens)):
+        rows = qkv[cu[i]:cu[i + 1]]
+        rows[:, 0] = 0
+        if i % 2 == 0:
+            rows[::3, 0], rows[lens[i] // 2, 1] = 100, 100
+    qkv = qkv.reshape(int(cu[-1]), -1)
+    sc = (0.02, 0.02, 0.021, 0.6 / 127, 0.0021)
+    want = oracle.attention_i8(qkv, cu, heads, *sc, p_unsigned=unsigned)
+    assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), max(lens), heads, *sc, p_unsigned=unsigned)), want)
+
+
 @pytest.mark.parametrize("lens,heads", [([128], 2), ([1, 5, 32, 33, 64, 17, 2], 3), ([300, 512, 129], 1), ([700, 1, 1030], 1)])
 def test_int8_attention_with_binary16_softmax_output_bit_exact(P, lens, heads):
     """P rounded to binary16 times integer V: the kernel splits P16 * 2^24 into four 7-bit digit planes for the int8
