@@ -1459,7 +1459,8 @@ __global__ __launch_bounds__(256) void attention_i8_long_kernel(const int8_t *__
 // exactly: a binary16 value in [0, 1] is an integer multiple of 2^-24, so P16 * 2^24 is an integer below
 // 2^25 that splits into four bytes; each byte plane is one more int8 operand for the matrix core (the lower
 // three as byte - 128, with 128 times the sum of V added back; the top byte is 0 or 1), the int32
-// products recombine in 64-bit integers, and one conversion rounds the true sum to binary32.
+// products recombine in 64-bit integers, and one conversion rounds the true sum to binary32.  That is the kernel for any length;
+// up to 1536 keys two binary16 parts do it with less arithmetic (below).
 
 // V^T of key tile j0 into a wave's own LDS slab
 __device__ __forceinline__ void stage_vt_i8(const int8_t *vp, unsigned ld, int j0, int n, int lane, int8_t *slab)
@@ -1510,41 +1511,217 @@ __device__ __forceinline__ void p16_add(const v16i (&o)[4], int vsum, long long 
 }
 
 // The block's sums, complete after a barrier: scaled back (exact) and rounded once to binary32.
-template <int NW>
 __device__ __forceinline__ void p16_store(const long long (&so)[2][QB][32], float m_ctx, int8_t *ctx_rows, int H, int rows_left, int tid)
 {
+    const int query = tid >> 3, c0 = (tid & 7) * 8;
+    if (query >= rows_left) return;
+    int codes[8];
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const int c = c0 + e;
+        codes[e] = qcode((float)((double)so[c >> 5][query][c & 31] * 5.9604644775390625e-08) * m_ctx);      // * 2^-24
+    }
+    *reinterpret_cast<v2i *>(ctx_rows + (size_t)query * H + c0) =
+        v2i{pack4(codes[0], codes[1], codes[2], codes[3]), pack4(codes[4], codes[5], codes[6], codes[7])};
+}
+
+// Up to 1536 keys the strip of scores stays in registers (one pass, as attention_i8_kernel), and the exact sum needs no digits: P16 splits into two
+// binary16 numbers, hi = (P16 + C) - C with C = 1.5 / 16 and lo = P16 - hi, both exact, whose products with the V codes (as binary16) the FP16 matrix
+// instruction adds up exactly in binary32, whatever its order:
+//     hi is a multiple of 2^-14 and sum |hi V| <= 127 (1.001 + 2^-15 keys) < 2^24 2^-14;
+//     lo is a multiple of 2^-24 with |lo| <= 2^-15 (P16 below 2^-5) or P16 / 2^9, so sum |lo V| <= 127 (2^-15 keys + 1.01 / 2^9) < 2^24 2^-24 as long as a
+//     wave has at most 192 keys.
+// In units of 2^-24 the whole sum is below 127 (1 + 2^-7) 2^24 < 2^31, so the waves' parts meet in an array of int32.
+// What bounds the kernel is vector arithmetic: 19 operations of the softmax per score, then 3 for the parts and 2.5 for V as binary16, where the
+// digits took 9.3 and the recombination of the waves' sums twice the operations; it also fits four blocks to a CU instead of two.  Forward,
+// BERT-base 33 x 40..301, us, digits / parts: 1458 / 1265.
+constexpr int P16_WAVE_KEYS = 192;
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+// one key tile's operands, from ev[e] = fl32(exp(score - max)): keys 16 u + 8 q + 4 g + t of half u
+__device__ __forceinline__ void p16_split(const float (&ev)[16], float rS, v8h (&hi)[2], v8h (&lo)[2])
+{
+    const v2h c = {(_Float16)0.09375f, (_Float16)0.09375f};
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        v2f v = {ev[2 * k] * rS, ev[2 * k + 1] * rS};
+        asm("" : "+v"(v));                                        // (binary32 first, as to_half)
+        const v2h p = __builtin_convertvector(v, v2h), h = (p + c) - c, l = p - h;
+#pragma unroll
+        for (int t = 0; t < 2; t++) { hi[k >> 2][2 * (k & 3) + t] = h[t]; lo[k >> 2][2 * (k & 3) + t] = l[t]; }
+    }
+}
+// eight codes as binary16: byte u = code + 128 under the exponent of 1024 is 1024 + u
+__device__ __forceinline__ v8h codes_to_half(int d0, int d1)
+{
+    const v2h bias = {(_Float16)1152.0f, (_Float16)1152.0f};
+    v4i raw;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const unsigned x = (unsigned)(k ? d1 : d0) ^ 0x80808080u;
+        raw[2 * k] = (int)__builtin_amdgcn_perm(0x64646464u, x, 0x04010400u);
+        raw[2 * k + 1] = (int)__builtin_amdgcn_perm(0x64646464u, x, 0x04030402u);
+    }
+    v4i out;
+#pragma unroll
+    for (int k = 0; k < 4; k++) out[k] = __builtin_bit_cast(int, __builtin_bit_cast(v2h, (int)raw[k]) - bias);
+    return __builtin_bit_cast(v8h, out);
+}
+
+template <int NT, int NW = 4>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 3 ? 4 : 2))) void
+attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, float m_sc, float m_ctx,
+                        int8_t *__restrict__ ctx)
+{
+    static_assert(32 * NT <= P16_WAVE_KEYS, "the bound on the sum of the low parts");
+    constexpr int K_AHEAD = NT <= 4 ? NT : 2;
+    __shared__ __attribute__((aligned(1024))) int8_t slab[NW][NT * V_TILE];
+    __shared__ __attribute__((aligned(16))) int so[QB][64];
+    __shared__ float smax[NW][QB];
+    __shared__ double ssum[NW][QB];
+    __shared__ ExpTable exp_table;
+
+    const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
+    const int item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int seq = item / (nqb * heads), head = (item / nqb) % heads;
+    const SeqInfo sq = seq_info(cu, seq, max_len);
+    const int q0 = (item % nqb) * QB;
+    if (q0 >= sq.n) return;
+    const int n = sq.n;
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
+    const unsigned ld = 3u * (unsigned)H;
+    const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64;
+    auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, max((n - j0) * (int)ld - head * 64, 0)); };     // as in attention_i8_kernel
+    auto first_key = [&](int i) { return (w + NW * i) * 32; };
+    const uint64_t table_entry = EXP2_TABLE[tid & 255];
+
+    const unsigned row_at = (unsigned)r * ld + g * 16, key_at = row_at + H;
+    const VLane vl(ld, lane);
+    v4i qf[2], kf[K_AHEAD][2];
+    auto request_keys = [&](int i) {
+        const auto rows = rows_from(first_key(i));
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) kf[i % K_AHEAD][ks] = __builtin_amdgcn_raw_buffer_load_b128(rows, key_at + ks * 32, 0, 0);
+    };
+    {
+        const auto rows = rows_from(q0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) qf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rows, row_at + ks * 32, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < K_AHEAD; i++) request_keys(i);
+#pragma unroll
+    for (int i = 0; i < NT; i++) request_v_tile(rows_from(first_key(i)), vl.from + 2 * H, ld, &slab[w][i * V_TILE]);
+#pragma unroll
+    for (int i = 0; i < QB * 64 / 4 / (64 * NW); i++) reinterpret_cast<v4i *>(&so[0][0])[i * 64 * NW + tid] = v4i{0, 0, 0, 0};      // used after two barriers
+
+    float sc[NT][16];                                             // scores / 128, then exponentials
+    const float m_unit = m_sc * SCORE_UNIT;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+        const int j0 = first_key(i);
+        if (j0 < n) {
+            v16i acc;
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[e] = 0;
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[i % K_AHEAD][ks], qf[ks], acc, 0, 0, 0);
+            if (j0 + 32 <= n) {
+#pragma unroll
+                for (int e = 0; e < 16; e++) sc[i][e] = (float)acc[e] * m_unit;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; e++) sc[i][e] = j0 + 8 * (e >> 2) + 4 * g + (e & 3) < n ? (float)acc[e] * m_unit : -INFINITY;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, sc[i][e]);
+        }
+        if (i + K_AHEAD < NT) request_keys(i + K_AHEAD);
+    }
+    mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (g == 0) smax[w][r] = mx;
+    if (NW == 4 || tid < 256) exp_table[tid] = table_entry;
+    wait_vm<0>();                                                 // the wave's V tiles are in its slab
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
+
+    double part = 0.0;
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+        if (first_key(i) < n) {
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                sc[i][e] = exp_below(sc[i][e], mx, exp_table);
+                part += (double)sc[i][e];
+            }
+        }
+    part += __shfl_xor(part, 32, 64);
+    if (g == 0) ssum[w][r] = part;
+    __syncthreads();
+    double total = ssum[0][r];
+#pragma unroll
+    for (int u = 1; u < NW; u++) total += ssum[u][r];
+    const float S = (float)total;
+    const float rS = __fdiv_rn(1.0f, S);
+
+    // the operands of all tiles take the exponentials' registers; one channel block at a time halves the accumulators
+    v8h hi[NT][2], lo[NT][2];
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+        if (first_key(i) < n) p16_split(sc[i], rS, hi[i], lo[i]);
+    if (w * 32 < n) {
+#pragma unroll
+        for (int cb = 0; cb < 2; cb++) {
+            v16f o[2];
+#pragma unroll
+            for (int k = 0; k < 2; k++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) o[k][e] = __int_as_float(opaque_zero());
+#pragma unroll
+            for (int i = 0; i < NT; i++)
+                if (first_key(i) < n) {
+                    const v4i vf = read_vt(&slab[w][i * V_TILE], vl.at, cb);
+#pragma unroll
+                    for (int u = 0; u < 2; u++) {
+                        const v8h v = codes_to_half(vf[2 * u], vf[2 * u + 1]);
+                        o[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hi[i][u], v, o[0], 0, 0, 0);
+                        o[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(lo[i][u], v, o[1], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+                atomicAdd(&so[8 * (e >> 2) + 4 * g + (e & 3)][cb * 32 + r], (int)(o[0][e] * 16777216.0f) + (int)(o[1][e] * 16777216.0f));
+        }
+    }
+    __syncthreads();
+
+    // the block's sums: scaled back (exact) and rounded once to binary32
     constexpr int CPT = 32 / NW;
     const int query = tid / (64 / CPT), c0 = tid % (64 / CPT) * CPT;
-    if (query >= rows_left) return;
+    if (q0 + query >= n) return;
     int pk[CPT / 4];
 #pragma unroll
     for (int d = 0; d < CPT / 4; d++) {
-        int codes[4];
+        float codes[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const int c = c0 + 4 * d + e;
-            codes[e] = qcode((float)((double)so[c >> 5][query][c & 31] * 5.9604644775390625e-08) * m_ctx);      // * 2^-24
-        }
-        pk[d] = pack4(codes[0], codes[1], codes[2], codes[3]);
+        for (int e = 0; e < 4; e++) codes[e] = code_bits((float)so[query][c0 + 4 * d + e] * 0x1p-24f * m_ctx);
+        pk[d] = pack_codes(codes[0], codes[1], codes[2], codes[3]);
     }
-    int8_t *dst = ctx_rows + (size_t)query * H + c0;
+    int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0;
     if constexpr (CPT == 8) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
     else *reinterpret_cast<int *>(dst) = pk[0];
 }
 
-// NT > 0: up to 32 NT NW keys, the strip of scores stays in registers (one pass, as attention_i8_kernel);
-// NT == 0: any length, three sweeps (as attention_i8_long_kernel).
-// What bounds it is vector arithmetic, 28 operations of the softmax and 12 of the digits per score, and how many blocks a
-// CU holds: key tiles past a sequence's end cost nothing, the waves' partial contexts meet in one 16 KB array of 64-bit
-// sums instead of an array per wave, and digits are whole bytes (three byte permutes for four keys and a plane).  17
-// sequences of 301 tokens (twelve heads) 51 -> 40 us, three of 1100 110 -> 75 us.
-template <int NT, int NW = 4>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void
-attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, float m_sc, float m_ctx,
-                        int8_t *__restrict__ ctx)
+// Any length: three sweeps (as attention_i8_long_kernel), digit planes.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void
+attention_i8_p16_long_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, float m_sc, float m_ctx,
+                             int8_t *__restrict__ ctx)
 {
-    constexpr int NSLAB = NT > 0 ? NT : 1;
-    __shared__ __attribute__((aligned(16))) int8_t vt[NW][NSLAB][64 * VT_STRIDE_I8];
+    constexpr int NW = 4;
+    __shared__ __attribute__((aligned(16))) int8_t vt[NW][64 * VT_STRIDE_I8];
     __shared__ long long so[2][QB][32];
     __shared__ float smax[NW][QB];
     __shared__ double ssum[NW][QB];
@@ -1570,53 +1747,25 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
 #pragma unroll
     for (int i = 0; i < 2 * QB * 32 / (64 * NW); i++) (&so[0][0][0])[i * 64 * NW + tid] = 0;      // used after two barriers
 
-    float scr[NSLAB][16];
     float sc[16];
     float mx = -INFINITY;
-    if constexpr (NT > 0) {
+    for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
+        score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
 #pragma unroll
-        for (int i = 0; i < NT; i++) {
-            const int j0 = (w + NW * i) * 32;
-            if (j0 < n) {
-                unsigned d[2][4];
-                load_v_tile(vp, ld, j0, n, lane, d);             // requested with the keys, not after them
-                score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, scr[i]);
-                store_vt_tile(d, lane, vt[w][i]);
-#pragma unroll
-                for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, scr[i][e]);
-            }
-        }
-    } else {
-        for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
-            score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
-#pragma unroll
-            for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, sc[e]);
-        }
+        for (int e = 0; e < 16; e++) mx = __builtin_fmaxf(mx, sc[e]);
     }
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
-    if (NW == 4 || tid < 256) exp_table[tid] = table_entry;
+    exp_table[tid] = table_entry;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
 
     double part = 0.0;
-    if constexpr (NT > 0) {
+    for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
+        score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
 #pragma unroll
-        for (int i = 0; i < NT; i++)
-            if ((w + NW * i) * 32 < n) {
-#pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    scr[i][e] = exp_nonpos(scr[i][e] - mx, exp_table);
-                    part += (double)scr[i][e];
-                }
-            }
-    } else {
-        for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
-            score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
-#pragma unroll
-            for (int e = 0; e < 16; e++) part += (double)exp_nonpos(sc[e] - mx, exp_table);
-        }
+        for (int e = 0; e < 16; e++) part += (double)exp_nonpos(sc[e] - mx, exp_table);
     }
     part += __shfl_xor(part, 32, 64);
     if (g == 0) ssum[w][r] = part;
@@ -1627,52 +1776,31 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     const float S = (float)total;
     const float rS = __fdiv_rn(1.0f, S);
 
-    if constexpr (NT > 0) {
-        // the digit planes of all tiles stay in registers; one channel block at a time halves the accumulators
-        v4i pf[NT][4];
+    v16i o[2][4];                                         // [channel block][digit plane]
+    int vsum[2] = {0, 0};
 #pragma unroll
-        for (int i = 0; i < NT; i++)
-            if ((w + NW * i) * 32 < n) p16_digits(scr[i], rS, pf[i]);
+    for (int cb = 0; cb < 2; cb++)
 #pragma unroll
-        for (int cb = 0; cb < 2; cb++) {
-            v16i o[4];
-            int vsum = 0;
+        for (int k = 0; k < 4; k++)
 #pragma unroll
-            for (int k = 0; k < 4; k++)
+            for (int e = 0; e < 16; e++) o[cb][k][e] = 0;
+    for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
+        score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
+        // the slab is written and read by this wave only, in program order
+        __builtin_amdgcn_wave_barrier();
+        stage_vt_i8(vp, ld, j0, n, lane, vt[w]);
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int e = 0; e < 16; e++) o[k][e] = opaque_zero();
-#pragma unroll
-            for (int i = 0; i < NT; i++)
-                if ((w + NW * i) * 32 < n) p16_mfma(pf[i], vt[w][i], cb, r, g, o, vsum);
-            if (w * 32 < n) p16_add(o, vsum, so[cb], r, g);
-        }
-    } else {
-        v16i o[2][4];                                         // [channel block][digit plane]
-        int vsum[2] = {0, 0};
-#pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-            for (int k = 0; k < 4; k++)
-#pragma unroll
-                for (int e = 0; e < 16; e++) o[cb][k][e] = 0;
-        for (int j0 = w * 32; j0 < n; j0 += 32 * NW) {
-            score_tile_i8(base, ld, H, j0, n, r, g, qf, m_sc, sc);
-            // the slab is written and read by this wave only, in program order
-            __builtin_amdgcn_wave_barrier();
-            stage_vt_i8(vp, ld, j0, n, lane, vt[w][0]);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int e = 0; e < 16; e++) sc[e] = exp_nonpos(sc[e] - mx, exp_table);
-            v4i pf[4];
-            p16_digits(sc, rS, pf);
-            p16_mfma(pf, vt[w][0], 0, r, g, o[0], vsum[0]);
-            p16_mfma(pf, vt[w][0], 1, r, g, o[1], vsum[1]);
-        }
-        p16_add(o[0], vsum[0], so[0], r, g);
-        p16_add(o[1], vsum[1], so[1], r, g);
+        for (int e = 0; e < 16; e++) sc[e] = exp_nonpos(sc[e] - mx, exp_table);
+        v4i pf[4];
+        p16_digits(sc, rS, pf);
+        p16_mfma(pf, vt[w], 0, r, g, o[0], vsum[0]);
+        p16_mfma(pf, vt[w], 1, r, g, o[1], vsum[1]);
     }
+    p16_add(o[0], vsum[0], so[0], r, g);
+    p16_add(o[1], vsum[1], so[1], r, g);
     __syncthreads();
-    p16_store<NW>(so, m_ctx, ctx + (size_t)(sq.t0 + q0) * H + head * 64, H, n - q0, tid);
+    p16_store(so, m_ctx, ctx + (size_t)(sq.t0 + q0) * H + head * 64, H, n - q0, tid);
 }
 
 __device__ __forceinline__ void score_tile_f16(const __half *base, unsigned ld, int H, int j0, int n, int r, int g,
@@ -1931,7 +2059,7 @@ hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int 
     else if (max_len <= ONE_PASS_MAX_LEN) go(attention_i8_p16_kernel<4>, 4);
     else if (max_len <= 1024) go(attention_i8_p16_kernel<4, 8>, 8);
     else if (max_len <= 1536) go(attention_i8_p16_kernel<6, 8>, 8);      // (beyond, V^T and the sums do not fit LDS together)
-    else go(attention_i8_p16_kernel<0>, 4);
+    else go(attention_i8_p16_long_kernel, 4);
     return hipGetLastError();
 }
 

@@ -648,6 +648,25 @@ def test_int8_attention_with_binary16_softmax_output_bit_exact(P, lens, heads):
     assert np.abs(want).max() > 20
 
 
+@pytest.mark.parametrize("n", [1, 31, 127, 128, 129, 343, 381, 511, 513, 1024, 1191, 1425, 1536])
+def test_binary16_softmax_output_at_the_bounds_of_its_exact_sum(P, n):
+    """The kernel splits P16 into a multiple of 2^-14 and a rest and adds the products with V up in binary32, which is exact as long as
+    the sums stay below 2^24 units.  Largest sums: V codes of 127 throughout, with equal probabilities (1 / n; near an odd multiple of
+    2^-15 at 343, 381, 1191 and 1425, where the rests are largest) and with one key that has nearly all of it; both signs."""
+    heads = 2
+    qkv = np.zeros((n, 3, heads, 64), np.int8)
+    qkv[:, 2, 0, :32], qkv[:, 2, 0, 32:] = 127, -127
+    qkv[:, 2, 1] = np.where(np.arange(n) % 2, -127, 127)[:, None]
+    qkv[n // 2:, 0], qkv[n // 3, 1] = 60, 60
+    qkv = qkv.reshape(n, -1)
+    cu = _cu([n])
+    for step in (0.02, 0.05):
+        for s_ctx in (0.021, 0.021 / 64):                         # the whole range of codes; the last bits of small sums
+            want = oracle.attention_i8_p16(qkv, cu, heads, step, step, 0.021, s_ctx)
+            got = host(P.attention_i8(dev(qkv), dev(cu), n, heads, step, step, 0.021, float("nan"), s_ctx, p_fp16=True))
+            assert np.array_equal(got, want)
+
+
 def test_softmax_code_usage_histogram(P):
     """The statistic of Appendix B (how many of the 256 integers a tensor's codes use) on synthetic data: the
     kernel's count of the softmax codes equals the count of the oracle's dumped codes, and samp_code_histogram of the
