@@ -8,6 +8,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -149,6 +151,20 @@ int noalloc_scratch(void **out)
 
 constexpr int MAX_GROUPS = 4;
 
+// The streams on which batch groups run beside a caller's stream.  Encoders that are used on the same stream share them: a forward that takes up a
+// stream which has been idle starts some 60 us late (three BERT-base encoders in turn, 32 x 128 Fully-Quant, streams of their own / shared: 740 /
+// 680 us), and the streams of one caller have one order anyway.  Different streams never share, so that none waits for another.  The last
+// encoder that holds them gives them back.
+struct SideStreams {
+    int device = -1;
+    hipStream_t caller = nullptr, side[MAX_GROUPS - 1] = {};
+    ~SideStreams()
+    {
+        for (hipStream_t s : side)
+            if (s) (void)hipStreamDestroy(s);
+    }
+};
+
 struct samp_encoder {
     samp_config_t cfg;
     std::vector<Layer> L;
@@ -160,12 +176,13 @@ struct samp_encoder {
     // batch-group concurrency: sequences are independent, so a batch is cut into groups that run on side
     // streams at the same time (one chain's kernels leave the chip idle while they start up and drain)
     int groups_wanted = 0;                          // 0 = choose by size
-    hipStream_t side[MAX_GROUPS - 1] = {};
+    std::vector<std::shared_ptr<SideStreams>> sides;   // of the streams it was used on last, the latest first
     hipEvent_t fork = nullptr, join[MAX_GROUPS - 1] = {};
-    bool streams_ready = false;
+    bool events_ready = false;
     // whole-forward HIP graphs, one per distinct argument set (the forward is launch-bound: a few
-    // hundred kernels of 5..30 microseconds); captured on an internal stream, replayed on the caller's
-    struct Graph { const void *hidden, *mask, *out, *ws; int B, S, G; int seen; hipGraphExec_t exec; const void *seg; samp_embedding_t emb; int tuning; };
+    // hundred kernels of 5..30 microseconds); captured on an internal stream, replayed on the caller's.  A graph per batch group: one of two
+    // branches takes the host 500 us to launch (BERT-base), two of one branch 130
+    struct Graph { const void *hidden, *mask, *out, *ws; int B, S, G; int seen; hipGraphExec_t exec[MAX_GROUPS]; const void *seg; samp_embedding_t emb; int tuning; };
     std::vector<Graph> graphs;
     bool graphs_enabled = true;
     hipStream_t cap = nullptr;
@@ -200,6 +217,10 @@ int choose_groups(const samp_encoder *e, int B, int S)
     // groups pay earlier: 1 layer of width 768, FP16 35 x 128 108 / 115, 9 x 490 154 / 150, 4 x 1024 154 / 154, 44 x 128 158 / 144, 61 x 128 182 / 179, Fully-Quant
     // 60 x 128 106 / 119, 65 x 128 - / 123, 90 x 128 159 / 164.  Ragged batches (16 to 100 % of the tokens, which only the device knows) break even
     // where the others do.  (Before the GEMMs read packed weights three or four groups never beat two.)
+    // (All of that with each encoder's groups on streams of its own.  With the streams shared, three encoders in turn, one group / two: width 768
+    // Fully-Quant 1 layer 102 sequences 162 / 167, 132 210 / 201; 2 layers 61 205 / 210, 90 286 / 275; 4 layers 22 230 / 233, 35 290 / 267; 12 layers 20 577 /
+    // 592, 24 701 / 661; Quant-FFN-Only 1 layer 61 120 / 126, 102 186 / 188; 2 layers 41 171 / 176, 61 243 / 228; 4 layers 22 253 / 254; FP16 1 layer 61 173 /
+    // 170 and 152 / 164 for one encoder, 102 265 / 261; 2 layers 24 184 / 185; 4 layers 22 368 / 357: the same bounds.)
     const long values = (long)B * S * e->cfg.hidden;
     if (g <= 0) g = values >= 2000000 && values * e->cfg.layers >= (e->all_int8 ? 6500000 : 3200000) ? 2 : 1;
     if (g > MAX_GROUPS) g = MAX_GROUPS;
@@ -418,6 +439,99 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     return SAMP_OK;
 }
 
+constexpr size_t MAX_SIDES = 4;
+std::mutex g_sides_mutex;
+std::vector<std::weak_ptr<SideStreams>> g_sides;
+
+// The side streams that go with the caller's stream, `count` of them, created on first use.
+int side_streams(samp_encoder_t *enc, hipStream_t st, int count, std::shared_ptr<SideStreams> *out)
+{
+    int device = -1;
+    HIP_TRY(hipGetDevice(&device));
+    const std::lock_guard<std::mutex> lock(g_sides_mutex);
+    std::shared_ptr<SideStreams> found;
+    for (size_t i = 0; i < enc->sides.size() && !found; i++)
+        if (enc->sides[i]->caller == st && enc->sides[i]->device == device) {
+            found = enc->sides[i];
+            enc->sides.erase(enc->sides.begin() + (long)i);
+        }
+    if (!found) {
+        for (size_t i = 0; i < g_sides.size();) {
+            const std::shared_ptr<SideStreams> s = g_sides[i].lock();
+            // (one handle, a stream of its own for each thread: not shared)
+            if (s && s->caller == st && s->device == device && st != hipStreamPerThread) found = s;
+            if (s) i++;
+            else g_sides.erase(g_sides.begin() + i);
+        }
+        if (!found) {
+            found = std::make_shared<SideStreams>();
+            found->device = device;
+            found->caller = st;
+            g_sides.push_back(found);
+        }
+        if (enc->sides.size() >= MAX_SIDES) enc->sides.pop_back();
+    }
+    enc->sides.insert(enc->sides.begin(), found);
+    for (int i = 0; i < count; i++)
+        if (!found->side[i]) HIP_TRY(hipStreamCreateWithFlags(&found->side[i], hipStreamNonBlocking));
+    *out = found;
+    return SAMP_OK;
+}
+
+// Runs each(g, stream) for every group, group 0 on the caller's stream and the others beside it.
+template <class F>
+int fork_join(samp_encoder_t *enc, int groups, hipStream_t st, F each)
+{
+    std::shared_ptr<SideStreams> streams;
+    if (int rc = side_streams(enc, st, groups - 1, &streams)) return rc;
+    if (!enc->events_ready) {
+        for (hipEvent_t &e : enc->join)
+            if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        if (!enc->fork) HIP_TRY(hipEventCreateWithFlags(&enc->fork, hipEventDisableTiming));
+        enc->events_ready = true;
+    }
+    HIP_TRY(hipEventRecord(enc->fork, st));
+    for (int g = 0; g < groups; g++) {
+        hipStream_t gs = g ? streams->side[g - 1] : st;
+        if (g) HIP_TRY(hipStreamWaitEvent(gs, enc->fork, 0));
+        if (int rc = each(g, gs)) return rc;
+    }
+    for (int g = 1; g < groups; g++) {
+        HIP_TRY(hipEventRecord(enc->join[g - 1], streams->side[g - 1]));
+        HIP_TRY(hipStreamWaitEvent(st, enc->join[g - 1], 0));
+    }
+    return SAMP_OK;
+}
+
+// Group g of G: its slice of the input and of the output, and its own workspace piece.
+int run_group(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int B, int S, void *out, void *workspace,
+                     int G, int g, hipStream_t st)
+{
+    if (G == 1) return run(enc, hidden, ids, mask, B, S, out, workspace, st, false, false, true);
+    const int Bg = (B + G - 1) / G, b0 = g * Bg, nb = std::min(Bg, B - b0);
+    const size_t piece = carve(enc->cfg, Bg, S, nullptr).bytes, seq_elems = (size_t)S * enc->cfg.hidden;
+    Ids part;
+    if (ids) part = Ids{ids->emb, ids->token_ids + (size_t)b0 * S, ids->segment_ids ? ids->segment_ids + (size_t)b0 * S : nullptr};
+    return run(enc, ids ? nullptr : (const __half *)hidden + b0 * seq_elems, ids ? &part : nullptr, mask ? mask + (size_t)b0 * S : nullptr, nb, S,
+               (__half *)out + b0 * seq_elems, (char *)workspace + g * piece, st, false, true, g == 0);
+}
+// groups that hold sequences (five sequences in four groups are 2, 2 and 1)
+int filled_groups(int B, int G) { const int Bg = (B + G - 1) / G; return (B + Bg - 1) / Bg; }
+
+int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int32_t B, int32_t S,
+                         void *out, void *workspace, hipStream_t st)
+{
+    const int G = choose_groups(enc, B, S), filled = filled_groups(B, G);
+    auto each = [&](int g, hipStream_t gs) { return run_group(enc, hidden, ids, mask, B, S, out, workspace, G, g, gs); };
+    if (G == 1) return each(0, st);
+    if (enc->prof_which == SAMP_PROF_OFF) return fork_join(enc, filled, st, each);
+    // while a kernel is being timed the groups run one after another on the caller's stream, so that
+    // each timed launch has the device to itself (same launch shapes, no overlap in the figures)
+    for (int g = 0; g < filled; g++)
+        if (int rc = each(g, st)) return rc;
+    return SAMP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -595,46 +709,6 @@ int samp_encoder_set_qkv_fusion(samp_encoder_t *enc, int32_t mode)
     return SAMP_OK;
 }
 
-static int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int32_t B, int32_t S,
-                         void *out, void *workspace, hipStream_t st)
-{
-    const int G = choose_groups(enc, B, S);
-    if (G == 1) return run(enc, hidden, ids, mask, B, S, out, workspace, st, false, false, true);
-    if (!enc->streams_ready) {
-        for (int i = 0; i < MAX_GROUPS - 1; i++) {
-            HIP_TRY(hipStreamCreateWithFlags(&enc->side[i], hipStreamNonBlocking));
-            HIP_TRY(hipEventCreateWithFlags(&enc->join[i], hipEventDisableTiming));
-        }
-        HIP_TRY(hipEventCreateWithFlags(&enc->fork, hipEventDisableTiming));
-        enc->streams_ready = true;
-    }
-    // group g owns sequences [g*Bg, ...): its slice of hidden / mask / out and its own workspace piece
-    const int Bg = (B + G - 1) / G;
-    const size_t piece = carve(enc->cfg, Bg, S, nullptr).bytes;
-    const size_t seq_elems = (size_t)S * enc->cfg.hidden;
-    // while a kernel is being timed the groups run one after another on the caller's stream, so that
-    // each timed launch has the device to itself (same launch shapes, no overlap in the figures)
-    const bool serial = enc->prof_which != SAMP_PROF_OFF;
-    if (!serial) HIP_TRY(hipEventRecord(enc->fork, st));
-    for (int g = 0; g < G; g++) {
-        const int b0 = g * Bg, nb = std::min(Bg, B - b0);
-        if (nb <= 0) break;
-        hipStream_t gs = (g == 0 || serial) ? st : enc->side[g - 1];
-        if (g > 0 && !serial) HIP_TRY(hipStreamWaitEvent(gs, enc->fork, 0));
-        Ids part;
-        if (ids) part = Ids{ids->emb, ids->token_ids + (size_t)b0 * S, ids->segment_ids ? ids->segment_ids + (size_t)b0 * S : nullptr};
-        const int rc = run(enc, ids ? nullptr : (const __half *)hidden + b0 * seq_elems, ids ? &part : nullptr,
-                           mask ? mask + (size_t)b0 * S : nullptr, nb, S,
-                           (__half *)out + b0 * seq_elems, (char *)workspace + g * piece, gs, false, true, g == 0);
-        if (rc != SAMP_OK) return rc;
-        if (g > 0 && !serial) {
-            HIP_TRY(hipEventRecord(enc->join[g - 1], gs));
-            HIP_TRY(hipStreamWaitEvent(st, enc->join[g - 1], 0));
-        }
-    }
-    return SAMP_OK;
-}
-
 // forward from a hidden state (ids == nullptr) or from ids (hidden == nullptr), with the graph cache
 static int forward_common(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int32_t B, int32_t S,
                           void *out, void *workspace, hipStream_t st);
@@ -712,6 +786,14 @@ int samp_embed_ln(const samp_embedding_t *emb, const int32_t *token_ids, const i
     return SAMP_OK;
 }
 
+static void destroy_graph(samp_encoder::Graph &g)
+{
+    for (hipGraphExec_t &exec : g.exec) {
+        if (exec) (void)hipGraphExecDestroy(exec);
+        exec = nullptr;
+    }
+}
+
 static int forward_common(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *mask, int32_t B, int32_t S,
                           void *out, void *workspace, hipStream_t st)
 {
@@ -730,34 +812,41 @@ static int forward_common(samp_encoder_t *enc, const void *hidden, const Ids *id
     for (auto &e : enc->graphs)
         if (e.hidden == key && e.seg == key_seg && std::memcmp(&e.emb, &key_emb, sizeof(key_emb)) == 0 && e.mask == mask && e.out == out && e.ws == workspace &&
             e.B == B && e.S == S && e.G == G && e.tuning == tuning) g = &e;
-    if (g && g->exec) { HIP_TRY(hipGraphLaunch(g->exec, st)); return SAMP_OK; }
+    const int filled = filled_groups(B, G);
+    auto replay = [&]() -> int {
+        auto each = [&](int i, hipStream_t gs) -> int { HIP_TRY(hipGraphLaunch(g->exec[i], gs)); return SAMP_OK; };
+        return filled == 1 ? each(0, st) : fork_join(enc, filled, st, each);
+    };
+    if (g && g->exec[0]) return replay();
     if (!g) {                                       // first sight of these arguments: run eagerly (one-off set-up happens here)
         if (enc->graphs.size() >= 8) {
-            if (enc->graphs.front().exec) (void)hipGraphExecDestroy(enc->graphs.front().exec);
+            destroy_graph(enc->graphs.front());
             enc->graphs.erase(enc->graphs.begin());
         }
-        enc->graphs.push_back({key, mask, out, workspace, B, S, G, 1, nullptr, key_seg, key_emb, tuning});
+        enc->graphs.push_back({key, mask, out, workspace, B, S, G, 1, {}, key_seg, key_emb, tuning});
         return forward_eager(enc, hidden, ids, mask, B, S, out, workspace, st);
     }
-    // second sight: record the same launches into a graph on an internal stream, then replay it
+    // second sight: record the same launches, each group's into a graph of its own, on an internal stream, then replay them
     if (!enc->cap) HIP_TRY(hipStreamCreateWithFlags(&enc->cap, hipStreamNonBlocking));
-    hipGraph_t graph = nullptr;
-    hipError_t e = hipStreamBeginCapture(enc->cap, hipStreamCaptureModeRelaxed);
+    hipError_t e = hipSuccess;
     int rc = SAMP_OK;
-    if (e == hipSuccess) {
-        rc = forward_eager(enc, hidden, ids, mask, B, S, out, workspace, enc->cap);
-        e = hipStreamEndCapture(enc->cap, &graph);
+    for (int i = 0; i < filled && e == hipSuccess && rc == SAMP_OK; i++) {
+        hipGraph_t graph = nullptr;
+        e = hipStreamBeginCapture(enc->cap, hipStreamCaptureModeRelaxed);
+        if (e == hipSuccess) {
+            rc = run_group(enc, hidden, ids, mask, B, S, out, workspace, G, i, enc->cap);
+            e = hipStreamEndCapture(enc->cap, &graph);
+        }
+        if (e == hipSuccess && rc == SAMP_OK) e = hipGraphInstantiate(&g->exec[i], graph, nullptr, nullptr, 0);
+        if (graph) (void)hipGraphDestroy(graph);
     }
-    if (e == hipSuccess && rc == SAMP_OK) e = hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0);
-    if (graph) (void)hipGraphDestroy(graph);
-    if (e != hipSuccess || rc != SAMP_OK || !g->exec) {  // capture not possible here: stay with plain launches
+    if (e != hipSuccess || rc != SAMP_OK || !g->exec[filled - 1]) {  // capture not possible here: stay with plain launches
         (void)hipGetLastError();
-        g->exec = nullptr;
+        destroy_graph(*g);
         enc->graphs_enabled = false;
         return forward_eager(enc, hidden, ids, mask, B, S, out, workspace, st);
     }
-    HIP_TRY(hipGraphLaunch(g->exec, st));
-    return SAMP_OK;
+    return replay();
 }
 
 int samp_encoder_set_graph(samp_encoder_t *enc, int32_t enabled)
@@ -790,12 +879,15 @@ int samp_encoder_destroy(samp_encoder_t *enc)
 {
     if (!enc) return SAMP_OK;
     for (Timing &t : enc->events) { (void)hipEventDestroy(t.start); (void)hipEventDestroy(t.stop); }
-    if (enc->streams_ready) {
-        for (int i = 0; i < MAX_GROUPS - 1; i++) { (void)hipStreamDestroy(enc->side[i]); (void)hipEventDestroy(enc->join[i]); }
-        (void)hipEventDestroy(enc->fork);
-    }
-    for (auto &g : enc->graphs) if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    for (hipEvent_t e : enc->join)
+        if (e) (void)hipEventDestroy(e);
+    if (enc->fork) (void)hipEventDestroy(enc->fork);
+    for (auto &g : enc->graphs) destroy_graph(g);
     if (enc->cap) (void)hipStreamDestroy(enc->cap);
+    {
+        const std::lock_guard<std::mutex> lock(g_sides_mutex);
+        enc->sides.clear();
+    }
     delete enc;
     return SAMP_OK;
 }

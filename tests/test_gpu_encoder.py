@@ -675,6 +675,60 @@ def test_a_batch_is_split_where_its_layers_pay_for_the_fork(P, modes, batch, gro
     enc.close()
 
 
+@pytest.mark.parametrize("groups", [2, 4])
+def test_encoders_that_share_the_streams_of_their_groups(P, groups):
+    """Encoders used on one caller's stream run their batch groups on the same side streams.  Three encoders in turn on two streams and from
+    two threads, without synchronisation in between (eager, capture, replays), one of them closed and another opened on the way;
+    five sequences leave a fourth group without any."""
+    import threading
+    import torch
+    w = small((FULL_INT8, FULL_INT8), batch=5, seq=64, varlen=True)
+    wts = W.make_weights(w)
+    hid, lens, mask = W.make_hidden(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    h, m = torch.from_numpy(hid).cuda(), torch.from_numpy(mask).cuda()
+    make = lambda: P.Encoder(*args(w), w.modes, wts, sc, max_batch=w.batch, max_seq=w.seq)
+    single = make()
+    single.set_groups(1)
+    want = single.forward(h, m).clone()
+    single.close()
+    torch.cuda.synchronize()
+
+    def work(failed):
+        encs = [make() for _ in range(3)]
+        for e in encs:
+            e.set_groups(groups)
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        outs = [torch.full_like(h, 3.0) for _ in range(6)]
+        torch.cuda.synchronize()
+        for rnd in range(5):
+            for i, e in enumerate(encs):
+                for k, st in enumerate(streams):
+                    if k:
+                        st.wait_stream(streams[0])                # an encoder's workspace serves one forward at a time
+                    with torch.cuda.stream(st):
+                        e.forward(h, m, outs[2 * i + k])
+                    streams[0].wait_stream(st)
+            if rnd == 2:
+                torch.cuda.synchronize()
+                encs[0].close()
+                encs[0] = make()
+                encs[0].set_groups(groups)
+        torch.cuda.synchronize()
+        if not all(torch.equal(o, want) for o in outs):
+            failed.append(1)
+        for e in encs:
+            e.close()
+
+    failed = []
+    threads = [threading.Thread(target=work, args=(failed,)) for _ in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
+
+
 @pytest.mark.parametrize("varlen", [False, True])
 def test_forward_captured_into_a_graph_of_the_caller(P, varlen):
     """A caller that records the forward into a HIP graph of its own switches the library's graph cache off; the plain
