@@ -677,9 +677,9 @@ def test_a_batch_is_split_where_its_layers_pay_for_the_fork(P, modes, batch, gro
 
 @pytest.mark.parametrize("groups", [2, 4])
 def test_encoders_that_share_the_streams_of_their_groups(P, groups):
-    """Encoders used on one caller's stream run their batch groups on the same side streams.  Three encoders in turn on two streams and from
-    two threads, without synchronisation in between (eager, capture, replays), one of them closed and another opened on the way;
-    five sequences leave a fourth group without any."""
+    """Encoders used on one caller's stream run their batch groups on the same side streams.  Two threads, each with three encoders in turn on
+    two streams and no synchronisation in between (eager, capture, replays); then one encoder is closed and another opened, and the first
+    thread's go on.  Five sequences leave a fourth group without any."""
     import threading
     import torch
     w = small((FULL_INT8, FULL_INT8), batch=5, seq=64, varlen=True)
@@ -687,46 +687,54 @@ def test_encoders_that_share_the_streams_of_their_groups(P, groups):
     hid, lens, mask = W.make_hidden(w)
     sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
     h, m = torch.from_numpy(hid).cuda(), torch.from_numpy(mask).cuda()
-    make = lambda: P.Encoder(*args(w), w.modes, wts, sc, max_batch=w.batch, max_seq=w.seq)
-    single = make()
-    single.set_groups(1)
+
+    def make(g=groups):
+        e = P.Encoder(*args(w), w.modes, wts, sc, max_batch=w.batch, max_seq=w.seq)
+        e.set_groups(g)
+        e._workspace(w.batch, w.seq)
+        return e
+
+    single = make(1)
     want = single.forward(h, m).clone()
-    single.close()
+    encs = [[make() for _ in range(3)] for _ in range(2)]
+    streams = [[torch.cuda.Stream(), torch.cuda.Stream()] for _ in range(2)]
+    outs = [[torch.full_like(h, 3.0) for _ in range(6)] for _ in range(2)]
     torch.cuda.synchronize()
+    raised = []
 
-    def work(failed):
-        encs = [make() for _ in range(3)]
-        for e in encs:
-            e.set_groups(groups)
-        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
-        outs = [torch.full_like(h, 3.0) for _ in range(6)]
-        torch.cuda.synchronize()
-        for rnd in range(5):
-            for i, e in enumerate(encs):
-                for k, st in enumerate(streams):
-                    if k:
-                        st.wait_stream(streams[0])                # an encoder's workspace serves one forward at a time
-                    with torch.cuda.stream(st):
-                        e.forward(h, m, outs[2 * i + k])
-                    streams[0].wait_stream(st)
-            if rnd == 2:
-                torch.cuda.synchronize()
-                encs[0].close()
-                encs[0] = make()
-                encs[0].set_groups(groups)
-        torch.cuda.synchronize()
-        if not all(torch.equal(o, want) for o in outs):
-            failed.append(1)
-        for e in encs:
-            e.close()
+    def work(t):
+        try:
+            for _ in range(4):
+                for i, e in enumerate(encs[t]):
+                    for k, st in enumerate(streams[t]):
+                        if k:
+                            st.wait_stream(streams[t][0])         # an encoder's workspace serves one forward at a time
+                        with torch.cuda.stream(st):
+                            e.forward(h, m, outs[t][2 * i + k])
+                    streams[t][0].wait_stream(streams[t][1])
+            streams[t][0].synchronize()
+        except Exception as e:
+            raised.append(e)
 
-    failed = []
-    threads = [threading.Thread(target=work, args=(failed,)) for _ in range(2)]
-    for t in threads:
-        t.start()
-    for t in threads:
-        t.join()
-    assert not failed
+    def together(*ts):
+        threads = [threading.Thread(target=work, args=(t,)) for t in ts]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not raised, raised
+        assert all(torch.equal(o, want) for o in outs[0] + outs[1])
+
+    together(0, 1)
+    encs[0][0].close()
+    encs[0][0] = make()
+    for o in outs[0]:
+        o.fill_(3.0)
+    torch.cuda.synchronize()
+    together(0)
+    for e in encs[0] + encs[1] + [single]:
+        e.close()
 
 
 @pytest.mark.parametrize("varlen", [False, True])
