@@ -315,10 +315,22 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     void *ybuf[2] = {w.y, w.x};                     // layer outputs alternate; w.x is free after layer 0's LN-1
     int yi = 0;
 
-    // From 256 rows to 3.2 million values the LayerNorm steps ask for the weights that come next (the first of several groups does it for
-    // all).  Below, a layer is over before they arrive (forward without / with it: 19 rows 326 / 331 us); above, a GEMM lasts long enough to
-    // fetch its own (width 768, two groups of 4096 rows 1286 / 1254, of 8192 rows 2014 / 2040; width 1024, two of 4096 rows 3783 / 3798).
-    const bool fetch_ahead = prefetch && Tmax >= FETCH_AHEAD_MIN_ROWS && (long)Tmax * H <= 3200000;
+    // Up to 3.2 million values extra blocks of a launch ask for the weights that come next, which come from beyond the caches when other models ran in
+    // between; above, a GEMM lasts long enough to fetch its own (width 768, two groups of 4096 rows 1286 / 1254 us, of 8192 rows 2014 / 2040; width 1024,
+    // two of 4096 rows 3783 / 3798).  One group lets its attention kernels ask for the next four matrices (they exist with such blocks up to 256
+    // tokens): they leave most of the chip idle, and every GEMM of the layer profits.  Beside another group the attention kernels are what fills
+    // the chip, and the LayerNorm steps of the first group ask, from 256 rows, each for two matrices.  Forwards of three encoders in turn, us, LayerNorm
+    // (from 256 rows) / attention: BERT-base Fully-Quant 1 x 64 329 / 313, 1 x 128 340 / 327, 7 x 61 368 / 362, 8 x 128 462 / 453, 16 x 128 557 / 553, two groups
+    // of 16 x 128 697 / 748; FP16 1 x 19 511 / 474, 1 x 64 527 / 483, 1 x 200 559 / 504, 8 x 128 672 / 661, two groups of 16 x 128 1120 / 1158; Quant-FFN-Only 1 x
+    // 128 412 / 380; BERT-large 1 x 64 Fully-Quant 752 / 705, FP16 1208 / 1117.  One encoder alone: 1 x 19 260 / 262, 1 x 64 312 / 312, FP16 1 x 200 493 / 467.  A
+    // single layer's weights are in the caches anyway (1 x 128 33.5 / 33.7).
+    const bool fetches = prefetch && (long)Tmax * H <= 3200000;
+    const bool attention_fetches = fetches && !beside && Lc > 1 && S <= ATTENTION_FETCH_MAX_LEN;
+    const bool fetch_ahead = fetches && !attention_fetches && Tmax >= FETCH_AHEAD_MIN_ROWS;
+    // A GEMM that forms the LayerNorm rows it multiplies waits for them longer than for its weights, as long as the rows are few: BERT-base 1 x 8, 19,
+    // 32, 40, 48, 56, 64 tokens, none / all but those / all: 269 / 266 / 293, 274 / 268 / 286, 295 / 284 / 311, 288 / 287 / 305, 304 / 300 / 301, 307 / 301 / 295, 327 /
+    // 319 / 316; BERT-large 1 x 19 621 / 608 / 626, 32 645 / 613 / 623, 48 723 / 714 / 695
+    constexpr int FETCH_LN_GEMM_MIN_ROWS = 48;
     auto ahead = [&](const void *W, const void *Wp, int N, int K, bool i8) {
         const bool packed = Wp && !(i8 ? gemm_i8_reads_rows(rows, N, K) : gemm_f16_reads_rows(rows, N, K));
         return Prefetch{packed ? Wp : W, (unsigned)N * K * (i8 ? 1 : 2)};
@@ -352,6 +364,22 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
         const bool mha8 = Y.mode & 1, ffn8 = Y.mode & 2, last = (l == Lc - 1);
         const bool next8 = !last && (enc->L[l + 1].mode & 1);
         float *am = calib ? w.absmax + l * 10 : nullptr;
+        const Layer &X = enc->L[last ? l : l + 1];      // the layer that comes next
+        FetchAhead next_weights = {};
+        const FetchAhead *fetch = nullptr;
+        if (attention_fetches) {
+            const bool few = Tmax < FETCH_LN_GEMM_MIN_ROWS;
+            next_weights.part[0] = ahead(Y.w_o, Y.p_o, H, H, mha8);
+            if (!(few && mha8 && ffn8)) next_weights.part[1] = ahead(Y.w_f1, Y.p_f1, F, H, ffn8);
+            next_weights.part[2] = ahead(Y.w_f2, Y.p_f2, H, F, ffn8);
+            if (!last && !(few && ffn8 && next8)) next_weights.part[3] = ahead(X.w_qkv, X.p_qkv, 3 * H, H, X.mode & 1);
+            // enough of them that the loads are on their way at once, and no more than that (128 / 256 blocks, in turn and alone: Fully-Quant 1 x 19 267 / 271
+            // and 262 / 264, 1 x 64 313 / 316, FP16 1 x 19 487 / 473, BERT-large FP16 1 x 64 1134 / 1114)
+            size_t bytes = 0;
+            for (const Prefetch &p : next_weights.part) bytes += p.bytes;
+            next_weights.blocks = bytes > 8 << 20 ? 256 : 128;
+            fetch = &next_weights;
+        }
 
         if (mha8) {
             // (of 129 to 256 tokens only when forced: one block per CU, a wave's 64 queries one after the other, loses against the two
@@ -361,7 +389,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                 const Timing *tm = timing(enc, SAMP_PROF_QKV_ATTN);
                 hipError_t e = !Y.p_qkv ? hipErrorNotSupported
                                         : launch_qkv_attention_i8_packed((const int8_t *)x, (const int8_t *)Y.p_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
-                                                                         Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
+                                                                         Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm, fetch);
                 if (e == hipErrorNotSupported)
                     e = launch_qkv_attention_i8((const int8_t *)x, (const int8_t *)Y.w_qkv, Y.m_qkv, Y.bq_qkv, cu, B, S, H, Y.m_sc, Y.inv_sp,
                                                 Y.m_ctx, p_unsigned, (int8_t *)w.ctx, st, tm);
@@ -372,11 +400,11 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                                            0.f, nullptr, rows, 3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
                 if (Y.mode & SAMP_P_FP16)
                     HIP_TRY(launch_attention_i8_p16((const int8_t *)w.qkv, cu, B, S, H, heads, Y.m_sc, Y.m_ctx, (int8_t *)w.ctx,
-                                                    st, timing(enc, SAMP_PROF_ATTN)));
+                                                    st, timing(enc, SAMP_PROF_ATTN), fetch));
                 else
                     HIP_TRY(launch_attention_i8((const int8_t *)w.qkv, cu, B, S, H, heads, Y.m_sc, Y.inv_sp, Y.m_ctx,
                                                 (Y.mode & SAMP_P_UNSIGNED) != 0, (int8_t *)w.ctx, nullptr, st,
-                                                timing(enc, SAMP_PROF_ATTN)));
+                                                timing(enc, SAMP_PROF_ATTN), fetch));
             }
             HIP_TRY(launch_gemm_i8(EPI_REQUANT, (const int8_t *)w.ctx, (const int8_t *)Y.w_o, (const int8_t *)Y.p_o, w.ao, Y.m_o, nullptr, 0.f,
                                    nullptr, rows, H, H, st, timing(enc, SAMP_PROF_ATTN_OUT)));
@@ -385,7 +413,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             // (calibration taps q, k, v and the softmax output, so it keeps the two kernels)
             if (!am && one_qkv_kernel(Y)) {
                 HIP_TRY(launch_qkv_attention_f16((const __half *)x, (const __half *)Y.w_qkv, (const __half *)Y.p_qkv, Y.b_qkv, cu, B, S, H, 0.125f,
-                                                 (__half *)w.ctx, st, timing(enc, SAMP_PROF_QKV_ATTN)));
+                                                 (__half *)w.ctx, st, timing(enc, SAMP_PROF_QKV_ATTN), fetch));
             } else {
                 HIP_TRY(launch_gemm_f16((const __half *)x, (const __half *)Y.w_qkv, (const __half *)Y.p_qkv, Y.b_qkv, false, (__half *)w.qkv, rows,
                                         3 * H, H, st, timing(enc, SAMP_PROF_QKV)));
@@ -393,7 +421,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                     for (int part = 0; part < 3; part++)
                         HIP_TRY(launch_absmax_f16((const __half *)w.qkv + part * H, rows, H, 3 * H, am + 1 + part, st));
                 HIP_TRY(launch_attention_f16((const __half *)w.qkv, cu, B, S, H, heads, 0.125f, (__half *)w.ctx,
-                                             am ? am + 4 : nullptr, st, timing(enc, SAMP_PROF_ATTN)));
+                                             am ? am + 4 : nullptr, st, timing(enc, SAMP_PROF_ATTN), fetch));
             }
             if (am) HIP_TRY(launch_absmax_f16((const __half *)w.ctx, rows, H, H, am + 5, st));
             HIP_TRY(launch_gemm_f16((const __half *)w.ctx, (const __half *)Y.w_o, (const __half *)Y.p_o, nullptr, false, (__half *)w.ao, rows, H, H,
@@ -426,7 +454,6 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             void *dst = last ? (calib ? ybuf[yi] : out) : ybuf[yi];
             AddLnArgs a{w.f2, ffn8, Y.s.ffn_out, Y.b_f2, w.h1, ffn8, Y.s.ffn_in, Y.g2, Y.be2, c.ln_eps,
                         dst, next8, next8 ? enc->L[l + 1].s.x : 1.0f, (last && !calib) ? row_map : nullptr, nullptr, rows, H};
-            const Layer &X = enc->L[last ? l : l + 1];
             const Prefetch next[2] = {ahead(X.w_qkv, X.p_qkv, 3 * H, H, X.mode & 1), ahead(X.w_o, X.p_o, H, H, X.mode & 1)};
             qkv_done = false;
             if (next8 && !one_qkv_kernel(X))
@@ -1105,7 +1132,9 @@ static int qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m
     const float m_sc = (float)((double)s_q * (double)s_k / std::sqrt(64.0));
     if (!good_score_multiplier(m_sc)) return fail(SAMP_ERR_SCALE, "s_q * s_k / 8 must not exceed %g", (double)MAX_SCORE_MULTIPLIER);
     const float m_ctx = (float)((double)s_p * (double)s_v / (double)s_ctx);
-    HIP_TRY((packed ? launch_qkv_attention_i8_packed : launch_qkv_attention_i8)(x, w_qkv, m, b, cu, B, max_len, hidden, m_sc, 1.0f / s_p, m_ctx,
+    HIP_TRY(packed ? launch_qkv_attention_i8_packed(x, w_qkv, m, b, cu, B, max_len, hidden, m_sc, 1.0f / s_p, m_ctx,
+                                                                                p_kind == 1, ctx, (hipStream_t)stream, nullptr)
+                   : launch_qkv_attention_i8(x, w_qkv, m, b, cu, B, max_len, hidden, m_sc, 1.0f / s_p, m_ctx,
                                                                                 p_kind == 1, ctx, (hipStream_t)stream, nullptr));
     return SAMP_OK;
 }

@@ -215,6 +215,21 @@ __device__ __forceinline__ void bound_codes(float (&e)[NT][16], float &rS, float
     rS = inv_sp = 1.0f;
 }
 
+// FETCH: the grid's last blocks ask for the weights of the kernels that follow.
+struct NoFetch {};
+template <bool FETCH> struct FetchArg { typedef NoFetch type; };
+template <> struct FetchArg<true> { typedef FetchAhead type; };
+__device__ __forceinline__ int work_blocks(const NoFetch &) { return (int)gridDim.x; }
+__device__ __forceinline__ int work_blocks(const FetchAhead &f) { return (int)gridDim.x - f.blocks; }
+__device__ __forceinline__ bool fetch_instead(const NoFetch &) { return false; }
+__device__ __forceinline__ bool fetch_instead(const FetchAhead &f)
+{
+    const int index = (int)blockIdx.x - work_blocks(f);
+    if (index < 0) return false;
+    fetch_block(f.part, (int)blockIdx.x & 7, (unsigned)index >> 3, (unsigned)f.blocks >> 3);
+    return true;
+}
+
 struct SeqInfo { int t0, n; };
 __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 {
@@ -237,11 +252,12 @@ __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 // long sequence stays in registers too.  A sequence of 1100 tokens then evaluates each exponential once and forms each
 // score once, where three sweeps over recomputed scores (the kernels further down) evaluate it twice and form it three
 // times: three sequences of 1100 tokens (twelve heads) 94 -> 52 us, two of 2048 190 -> 118 us.
-template <int NT, bool PU, bool HIST, int NW = 4>
+template <int NT, bool PU, bool HIST, int NW = 4, bool FETCH = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5 ? 4 : 2))) void attention_i8_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu,
                                                            int max_len, int H, float m_sc, float inv_sp, float m_ctx,
-                                                           int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist)
+                                                           int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist, typename FetchArg<FETCH>::type fetch)
 {
+    if (fetch_instead(fetch)) return;
     __shared__ unsigned hist[HIST ? 256 : 1];
     // One slab per wave: first its V tiles (written and read by that wave alone), then, once its last P.V
     // product has read them, its partial context for the other waves; sharing the bytes lets a fourth block fit a CU.
@@ -259,7 +275,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
     // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
     const int seq = item / (nqb * heads), head = (item / nqb) % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int q0 = (item % nqb) * QB;
@@ -836,12 +852,13 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
 // of token rows (the row-major kernel: 80 KB).  Every value is formed by the same operations as there.
 // Forwards, row-major / packed: BERT-base 32 x 128 Fully-Quant 848 / 822 us, 64 x 16..128 with six Fully-Quant layers 1404 / 1392; three stages
 // in flight instead of two: the same.
-template <bool PU, int D>
+template <bool PU, int D, bool FETCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__restrict__ Wp, const float *__restrict__ m_tab,
                                     const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, float m_sc,
-                                    float inv_sp, float m_ctx, int8_t *__restrict__ ctx)
+                                    float inv_sp, float m_ctx, int8_t *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
+    if (fetch_instead(fetch)) return;
     constexpr int MT = 8, BM = 16 * MT, RING = stream_ring_bytes<false, MT, D>();
     constexpr int K_OFF = BM * QK_STRIDE_I8, VT_OFF = 2 * K_OFF;
     static_assert(VT_OFF + 64 * VT_ROW_I8<1> <= RING, "q, k and V^T take the place of the ring");
@@ -849,7 +866,7 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
     ExpTable &exp_table = *reinterpret_cast<ExpTable *>(lds + RING);
 
     const int heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, gridDim.x);       // sequences outermost, as in the attention kernel
+    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));       // sequences outermost, as in the attention kernel
     const int seq = item / heads, head = item % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
@@ -921,11 +938,12 @@ constexpr int QKV_F16_PACKED_D = 2, QKV_F16_PACKED_RING = stream_ring_bytes<true
 // 2 x 2 arrangement of waves (six channel blocks do not deal out over four waves), so two waves each load the same weight rows.  55 KB of
 // LDS instead of 80, two stages in flight instead of one; BERT-base 32 x 128 forward, us, row-major / packed: FP16 1240 / 1196, Quant-FFN-Only
 // 941 / 891.
-template <int QT, int STAGE, bool PACKED>
+template <int QT, int STAGE, bool PACKED, bool FETCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ bias,
-                              const int *__restrict__ cu, int max_len, int H, float scale, __half *__restrict__ ctx)
+                              const int *__restrict__ cu, int max_len, int H, float scale, __half *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
+    if (fetch_instead(fetch)) return;
     typedef QkvTile<QT, STAGE> Tile;
     constexpr bool LATE = Tile::LATE && !PACKED;
     constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, NKT = 4 * QT;
@@ -940,7 +958,7 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     float *tab = reinterpret_cast<float *>(lds + (!LATE ? TAB_OFF : (H / 64) & 1 ? RING_BYTES - TAB_BYTES : 0));
 
     const int heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
     const int seq = item / heads, head = item % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
@@ -1165,11 +1183,12 @@ __device__ __forceinline__ void store_vt_tile_f16(const v8h (&d)[2][2], int lane
 // three-sweep kernel, tile by tile, so both give the same bytes.  V rows
 // are transposed in registers two keys at a time (dword stores).  Twelve heads, three sequences of 1100 tokens: 76 -> 51 us, 17 of
 // 301 36.5 -> 30 us.
-template <int NT>
+template <int NT, bool FETCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
                                                             int max_len, int H, float scale, __half *__restrict__ ctx,
-                                                            float *__restrict__ p_absmax)
+                                                            float *__restrict__ p_absmax, typename FetchArg<FETCH>::type fetch)
 {
+    if (fetch_instead(fetch)) return;
     // one slab per wave, as in the INT8 kernel: first its V^T tiles (two; a further one takes a tile's place when that one has
     // been multiplied), then its partial context for the other waves.  TIGHT: ten tiles of scores leave two waves per SIMD just
     // enough registers if V rows are requested one tile later (four tiles in the slab) and tiles past the end are skipped in
@@ -1186,7 +1205,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
     // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
     const int seq = item / (nqb * heads), head = (item / nqb) % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int q0 = (item % nqb) * QB;
@@ -1569,11 +1588,12 @@ __device__ __forceinline__ v8h codes_to_half(int d0, int d1)
     return __builtin_bit_cast(v8h, out);
 }
 
-template <int NT, int NW = 4>
+template <int NT, int NW = 4, bool FETCH = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 3 ? 4 : 2))) void
 attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, float m_sc, float m_ctx,
-                        int8_t *__restrict__ ctx)
+                        int8_t *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
+    if (fetch_instead(fetch)) return;
     static_assert(32 * NT <= P16_WAVE_KEYS, "the bound on the sum of the low parts");
     constexpr int K_AHEAD = NT <= 4 ? NT : 2;
     __shared__ __attribute__((aligned(1024))) int8_t slab[NW][NT * V_TILE];
@@ -1583,7 +1603,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     __shared__ ExpTable exp_table;
 
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
     const int seq = item / (nqb * heads), head = (item / nqb) % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int q0 = (item % nqb) * QB;
@@ -1924,7 +1944,7 @@ template <bool PU>
 static void launch_attention_i8_8waves(const int8_t *qkv, const int *cu, int max_len, int H, float m_sc, float inv_sp, float m_ctx,
                                        int8_t *ctx, dim3 grid, hipStream_t st, const Timing *tm)
 {
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, (unsigned long long *)nullptr); };
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, (unsigned long long *)nullptr, NoFetch()); };
     switch ((max_len + 255) / 256) {
     case 3: return go(attention_i8_kernel<3, PU, false, 8>);
     case 4: return go(attention_i8_kernel<4, PU, false, 8>);
@@ -1937,17 +1957,24 @@ static void launch_attention_i8_8waves(const int8_t *qkv, const int *cu, int max
 template <bool PU, bool HIST>
 static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
                                         float inv_sp, float m_ctx, int8_t *ctx, unsigned long long *p_hist, hipStream_t st,
-                                        const Timing *tm)
+                                        const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
+    if constexpr (!HIST) {
+        const dim3 more(grid.x + (fetch ? fetch->blocks : 0));
+        if (fetch && max_len <= 128)
+            return launch_kernel(attention_i8_kernel<1, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+        if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN)
+            return launch_kernel(attention_i8_kernel<2, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+    }
     if (max_len <= 128)
-        launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
+        launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= 256)
-        launch_kernel(attention_i8_kernel<2, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
+        launch_kernel(attention_i8_kernel<2, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= 384)
-        launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
+        launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= ONE_PASS_MAX_LEN)
-        launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist);
+        launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (!HIST && max_len <= 8 * 256)
         launch_attention_i8_8waves<PU>(qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, grid, st, tm);
     else
@@ -1956,14 +1983,14 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
 
 hipError_t launch_attention_i8(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
                                float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx, unsigned long long *p_hist,
-                               hipStream_t st, const Timing *tm)
+                               hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     if (p_unsigned) {
-        if (p_hist) launch_attention_i8_variant<true, true>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm);
-        else launch_attention_i8_variant<true, false>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm);
+        if (p_hist) launch_attention_i8_variant<true, true>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm, nullptr);
+        else launch_attention_i8_variant<true, false>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm, fetch);
     } else {
-        if (p_hist) launch_attention_i8_variant<false, true>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm);
-        else launch_attention_i8_variant<false, false>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm);
+        if (p_hist) launch_attention_i8_variant<false, true>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm, nullptr);
+        else launch_attention_i8_variant<false, false>(qkv, cu, B, max_len, H, heads, m_sc, inv_sp, m_ctx, ctx, p_hist, st, tm, fetch);
     }
     return hipGetLastError();
 }
@@ -2013,61 +2040,75 @@ hipError_t launch_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const f
 
 hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const float *m, const float *b, const int *cu, int B,
                                           int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
-                                          hipStream_t st, const Timing *tm)
+                                          hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     if (max_len > 128 || H % 256 || B <= 0) return hipErrorNotSupported;
-    auto go = [&](auto kern) {
-        launch_kernel(kern, dim3((unsigned)(B * (H / 64))), dim3(256), stream_ring_bytes<false, 8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
-                      (const char *)w_packed, m, b, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx);
+    auto go = [&](auto kern, unsigned more, auto what) {
+        launch_kernel(kern, dim3((unsigned)(B * (H / 64)) + more), dim3(256), stream_ring_bytes<false, 8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
+                      (const char *)w_packed, m, b, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, what);
         return hipGetLastError();
     };
-    return p_unsigned ? go(qkv_attention_i8_packed_kernel<true, 2>) : go(qkv_attention_i8_packed_kernel<false, 2>);
+    if (fetch)
+        return p_unsigned ? go(qkv_attention_i8_packed_kernel<true, 2, true>, fetch->blocks, *fetch)
+                          : go(qkv_attention_i8_packed_kernel<false, 2, true>, fetch->blocks, *fetch);
+    return p_unsigned ? go(qkv_attention_i8_packed_kernel<true, 2, false>, 0, NoFetch()) : go(qkv_attention_i8_packed_kernel<false, 2, false>, 0, NoFetch());
 }
 
 hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const __half *w_packed, const float *bias, const int *cu, int B,
-                                    int max_len, int H, float scale, __half *ctx, hipStream_t st, const Timing *tm)
+                                    int max_len, int H, float scale, __half *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     if (max_len > 256 || H % 64 || B <= 0) return hipErrorInvalidValue;
     const bool packed = w_packed && max_len <= 128 && H % 128 == 0;
     if (!packed && !w_qkv) return hipErrorNotSupported;
     const dim3 grid((unsigned)(B * (H / 64)));
-    auto go = [&](auto kern, size_t lds, std::atomic<bool> &attr_set) {
+    auto go = [&](auto kern, size_t lds, std::atomic<bool> &attr_set, unsigned more, auto what) {
         if (!attr_set.load(std::memory_order_acquire)) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             attr_set.store(true, std::memory_order_release);
         }
-        launch_kernel(kern, grid, dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, scale, ctx);
+        launch_kernel(kern, dim3(grid.x + more), dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, scale, ctx, what);
         return hipGetLastError();
     };
-    static std::atomic<bool> attr_set[3];
+    static std::atomic<bool> attr_set[4];
     constexpr size_t tab = 192 * sizeof(float);
     constexpr auto qkv_bytes = [](size_t BM) { return 2 * BM * 144 + 64 * (2 * BM + 8); };
-    if (packed) return go(qkv_attention_f16_kernel<1, 128, true>, std::max<size_t>(qkv_bytes(128), QKV_F16_PACKED_RING) + tab, attr_set[1]);
-    if (max_len > 128) return go(qkv_attention_f16_kernel<2, 64, false>, std::max<size_t>(qkv_bytes(256), QkvTile<2, 64>::RING_BYTES) + tab, attr_set[2]);
-    return go(qkv_attention_f16_kernel<1, 128, false>, QkvTile<1, 128>::RING_BYTES, attr_set[0]);
+    constexpr size_t packed_lds = std::max<size_t>(qkv_bytes(128), QKV_F16_PACKED_RING) + tab;
+    if (packed && fetch) return go(qkv_attention_f16_kernel<1, 128, true, true>, packed_lds, attr_set[3], fetch->blocks, *fetch);
+    if (packed) return go(qkv_attention_f16_kernel<1, 128, true>, packed_lds, attr_set[1], 0, NoFetch());
+    if (max_len > 128) return go(qkv_attention_f16_kernel<2, 64, false>, std::max<size_t>(qkv_bytes(256), QkvTile<2, 64>::RING_BYTES) + tab, attr_set[2], 0, NoFetch());
+    return go(qkv_attention_f16_kernel<1, 128, false>, QkvTile<1, 128>::RING_BYTES, attr_set[0], 0, NoFetch());
 }
 
 hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
-                                   float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm)
+                                   float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
-    auto go = [&](auto kern, int waves) { launch_kernel(kern, grid, dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx); };
-    if (max_len <= 128) go(attention_i8_p16_kernel<1>, 4);
-    else if (max_len <= 256) go(attention_i8_p16_kernel<2>, 4);
-    else if (max_len <= 384) go(attention_i8_p16_kernel<3>, 4);
-    else if (max_len <= ONE_PASS_MAX_LEN) go(attention_i8_p16_kernel<4>, 4);
-    else if (max_len <= 1024) go(attention_i8_p16_kernel<4, 8>, 8);
-    else if (max_len <= 1536) go(attention_i8_p16_kernel<6, 8>, 8);      // (beyond, V^T and the sums do not fit LDS together)
-    else go(attention_i8_p16_long_kernel, 4);
+    auto go = [&](auto kern, int waves, unsigned more, auto what) {
+        launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx, what);
+    };
+    if (fetch && max_len <= 128) go(attention_i8_p16_kernel<1, 4, true>, 4, fetch->blocks, *fetch);
+    else if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) go(attention_i8_p16_kernel<2, 4, true>, 4, fetch->blocks, *fetch);
+    else if (max_len <= 128) go(attention_i8_p16_kernel<1>, 4, 0, NoFetch());
+    else if (max_len <= 256) go(attention_i8_p16_kernel<2>, 4, 0, NoFetch());
+    else if (max_len <= 384) go(attention_i8_p16_kernel<3>, 4, 0, NoFetch());
+    else if (max_len <= ONE_PASS_MAX_LEN) go(attention_i8_p16_kernel<4>, 4, 0, NoFetch());
+    else if (max_len <= 1024) go(attention_i8_p16_kernel<4, 8>, 8, 0, NoFetch());
+    else if (max_len <= 1536) go(attention_i8_p16_kernel<6, 8>, 8, 0, NoFetch());      // (beyond, V and the sums do not fit LDS together)
+    else launch_kernel(attention_i8_p16_long_kernel, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx);
     return hipGetLastError();
 }
 
 hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max_len, int H, int heads, float scale,
-                                __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm)
+                                __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax); };
+    if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
+        auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax, *fetch); };
+        if (max_len <= 128) with(attention_f16_kernel<1, true>); else with(attention_f16_kernel<2, true>);
+        return hipGetLastError();
+    }
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax, NoFetch()); };
     switch ((max_len + 127) / 128) {                              // key tiles per wave
     case 1: go(attention_f16_kernel<1>); break;
     case 2: go(attention_f16_kernel<2>); break;
@@ -2078,7 +2119,7 @@ hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max
     case 9: case 10: go(attention_f16_kernel<10>); break;
     case 11: case 12: go(attention_f16_kernel<12>); break;
     case 13: case 14: case 15: case 16: go(attention_f16_kernel<16>); break;
-    default: go(attention_f16_long_kernel);
+    default: launch_kernel(attention_f16_long_kernel, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax);
     }
     return hipGetLastError();
 }

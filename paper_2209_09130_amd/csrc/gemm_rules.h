@@ -4,8 +4,8 @@
 
 namespace samp {
 
-// From this many padded token rows on the LayerNorm steps ask for the weights that come next (api.hip), so that a GEMM finds them in the
-// memory-side cache; below, a GEMM waits for memory beyond it.
+// From this many padded token rows on the LayerNorm steps ask for the weights that come next where the attention kernels do not (api.hip), so that a
+// GEMM finds them in the memory-side cache.  (Below, only attention kernels ask; the figures here are of GEMMs that wait for memory.)
 constexpr int FETCH_AHEAD_MIN_ROWS = 256;
 
 // FP16: the rows as they lie while the 32 x 32 tiles of gemm_nt_small_f16_kernel are all on the chip at once.  The packed kernel's narrowest tile is

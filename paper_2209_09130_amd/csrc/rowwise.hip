@@ -126,19 +126,7 @@ __device__ __forceinline__ bool prefetch_block(const AddLnPrefetchArgs &a)
 {
     const int first = (int)gridDim.x - PREFETCH_BLOCKS, block = (int)blockIdx.x;
     if (block < first) return false;
-    const int xcd = block & 7, index = (block - first) >> 3, count = PREFETCH_BLOCKS >> 3;
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-        const unsigned eighth = a.prefetch[k].bytes >> 7, step = count * blockDim.x;            // in units of 16 bytes
-        const v4i *from = reinterpret_cast<const v4i *>(a.prefetch[k].from) + (size_t)xcd * eighth;
-        for (unsigned i = index * blockDim.x + threadIdx.x; i < eighth; i += 8 * step) {
-            v4i d[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) d[u] = from[min(i + u * step, eighth - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; u++) asm volatile("" ::"v"(d[u]));
-        }
-    }
+    fetch_block(a.prefetch, block & 7, (unsigned)(block - first) >> 3, PREFETCH_BLOCKS >> 3);
     return true;
 }
 

@@ -17,6 +17,11 @@ typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
 namespace samp {
 
+// Weights that the next kernels will read: extra blocks of a launch ask for them
+struct Prefetch { const void *from; unsigned bytes; };
+struct FetchAhead { Prefetch part[4]; int blocks; };        // blocks: a multiple of 8
+constexpr int ATTENTION_FETCH_MAX_LEN = 256;               // up to here the attention kernels exist with such blocks
+
 // ---- quantiser: round half to even, symmetric clamp (Appendix B) --------------------------------
 __device__ __forceinline__ int qcode(float v)
 {
@@ -132,6 +137,26 @@ __device__ __forceinline__ int xcd_contiguous(int block, int total)
     return block < body ? (block & 7) * per + (block >> 3) : block;
 }
 
+// A block that only asks for weights, `index` of the `count` of its XCD: the XCD's eighth of each part, which it will read itself where channels are dealt
+// out to the XCDs (few rows).
+template <int N> __device__ __forceinline__ void fetch_block(const Prefetch (&part)[N], int xcd, unsigned index, unsigned count)
+{
+    const unsigned step = 16 * count * blockDim.x;
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        const unsigned eighth = part[k].bytes >> 3;
+        // (loads past the end cost nothing: the descriptor cuts them off)
+        const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(part[k].from) + (size_t)xcd * eighth, 0, (int)eighth, 0x00027000);
+        for (unsigned first = 16 * index * blockDim.x; first < eighth; first += 8 * step) {          // (block-uniform)
+            v4i d[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) d[u] = __builtin_amdgcn_raw_buffer_load_b128(from, first + 16 * threadIdx.x + u * step, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 8; u++) asm volatile("" ::"v"(d[u]));
+        }
+    }
+}
+
 // ---- wave reductions (64 lanes) ----------------------------------------------------------------
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -193,27 +218,26 @@ hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float
                                   int tile, hipStream_t st, const Timing *tm);
 
 // cu == nullptr: every sequence has exactly max_len rows (row b*max_len is its first).
+// fetch (may be null; up to ATTENTION_FETCH_MAX_LEN tokens, longer ones leave it out): weights that extra blocks ask for
 // p_unsigned: softmax codes 0..255 instead of -127..127; p_hist (optional): 256 counters of the codes used
 hipError_t launch_attention_i8(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
                                float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx, unsigned long long *p_hist,
-                               hipStream_t st, const Timing *tm);
+                               hipStream_t st, const Timing *tm, const FetchAhead *fetch = nullptr);
 hipError_t launch_qkv_attention_i8(const int8_t *x, const int8_t *w_qkv, const float *m, const float *b, const int *cu, int B,
                                    int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
                                    hipStream_t st, const Timing *tm);
 // on weights in the order of launch_pack_weight; hipErrorNotSupported: more than 128 tokens, or H is no multiple of 256
 hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packed, const float *m, const float *b, const int *cu, int B,
                                           int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
-                                          hipStream_t st, const Timing *tm);
+                                          hipStream_t st, const Timing *tm, const FetchAhead *fetch = nullptr);
 hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const __half *w_packed, const float *bias, const int *cu, int B,
-                                    int max_len, int H, float scale, __half *ctx, hipStream_t st, const Timing *tm);
+                                    int max_len, int H, float scale, __half *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch = nullptr);
 hipError_t launch_code_histogram(const int8_t *codes, size_t n, unsigned long long *hist, hipStream_t st);
 hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
-                                   float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm);
+                                   float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch = nullptr);
 hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max_len, int H, int heads, float scale,
-                                __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm);
+                                __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm, const FetchAhead *fetch = nullptr);
 
-// Weights that the next kernels will read: extra blocks of the launch ask for them (prefetch_block)
-struct Prefetch { const void *from; unsigned bytes; };
 struct AddLnArgs {
     const void *in; bool in_i8; float s_in; const float *bias;
     const void *res; bool res_i8; float s_res;
