@@ -219,12 +219,10 @@ __device__ __forceinline__ void bound_codes(float (&e)[NT][16], float &rS, float
 struct NoFetch {};
 template <bool FETCH> struct FetchArg { typedef NoFetch type; };
 template <> struct FetchArg<true> { typedef FetchAhead type; };
-__device__ __forceinline__ int work_blocks(const NoFetch &) { return (int)gridDim.x; }
-__device__ __forceinline__ int work_blocks(const FetchAhead &f) { return (int)gridDim.x - f.blocks; }
-__device__ __forceinline__ bool fetch_instead(const NoFetch &) { return false; }
-__device__ __forceinline__ bool fetch_instead(const FetchAhead &f)
+__device__ __forceinline__ bool fetch_instead(const NoFetch &, int) { return false; }
+__device__ __forceinline__ bool fetch_instead(const FetchAhead &f, int items)
 {
-    const int index = (int)blockIdx.x - work_blocks(f);
+    const int index = (int)blockIdx.x - items;
     if (index < 0) return false;
     fetch_block(f.part, (int)blockIdx.x & 7, (unsigned)index >> 3, (unsigned)f.blocks >> 3);
     return true;
@@ -254,10 +252,10 @@ __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 // times: three sequences of 1100 tokens (twelve heads) 94 -> 52 us, two of 2048 190 -> 118 us.
 template <int NT, bool PU, bool HIST, int NW = 4, bool FETCH = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5 ? 4 : 2))) void attention_i8_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu,
-                                                           int max_len, int H, float m_sc, float inv_sp, float m_ctx,
+                                                           int max_len, int H, int items, float m_sc, float inv_sp, float m_ctx,
                                                            int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist, typename FetchArg<FETCH>::type fetch)
 {
-    if (fetch_instead(fetch)) return;
+    if (fetch_instead(fetch, items)) return;
     __shared__ unsigned hist[HIST ? 256 : 1];
     // One slab per wave: first its V tiles (written and read by that wave alone), then, once its last P.V
     // product has read them, its partial context for the other waves; sharing the bytes lets a fourth block fit a CU.
@@ -275,7 +273,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
     // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
+    const int item = xcd_contiguous(blockIdx.x, items);
     const int seq = item / (nqb * heads), head = (item / nqb) % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int q0 = (item % nqb) * QB;
@@ -855,10 +853,10 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
 template <bool PU, int D, bool FETCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__restrict__ Wp, const float *__restrict__ m_tab,
-                                    const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, float m_sc,
+                                    const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, int items, float m_sc,
                                     float inv_sp, float m_ctx, int8_t *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
-    if (fetch_instead(fetch)) return;
+    if (fetch_instead(fetch, items)) return;
     constexpr int MT = 8, BM = 16 * MT, RING = stream_ring_bytes<false, MT, D>();
     constexpr int K_OFF = BM * QK_STRIDE_I8, VT_OFF = 2 * K_OFF;
     static_assert(VT_OFF + 64 * VT_ROW_I8<1> <= RING, "q, k and V^T take the place of the ring");
@@ -866,7 +864,7 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
     ExpTable &exp_table = *reinterpret_cast<ExpTable *>(lds + RING);
 
     const int heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));       // sequences outermost, as in the attention kernel
+    const int item = xcd_contiguous(blockIdx.x, items);       // sequences outermost, as in the attention kernel
     const int seq = item / heads, head = item % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
@@ -941,9 +939,9 @@ constexpr int QKV_F16_PACKED_D = 2, QKV_F16_PACKED_RING = stream_ring_bytes<true
 template <int QT, int STAGE, bool PACKED, bool FETCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ bias,
-                              const int *__restrict__ cu, int max_len, int H, float scale, __half *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
+                              const int *__restrict__ cu, int max_len, int H, int items, float scale, __half *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
-    if (fetch_instead(fetch)) return;
+    if (fetch_instead(fetch, items)) return;
     typedef QkvTile<QT, STAGE> Tile;
     constexpr bool LATE = Tile::LATE && !PACKED;
     constexpr int TM = Tile::TM, TN = Tile::TN, BM = Tile::BM, BN = Tile::BN, NKT = 4 * QT;
@@ -958,7 +956,7 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     float *tab = reinterpret_cast<float *>(lds + (!LATE ? TAB_OFF : (H / 64) & 1 ? RING_BYTES - TAB_BYTES : 0));
 
     const int heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
+    const int item = xcd_contiguous(blockIdx.x, items);
     const int seq = item / heads, head = item % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
@@ -1185,10 +1183,10 @@ __device__ __forceinline__ void store_vt_tile_f16(const v8h (&d)[2][2], int lane
 // 301 36.5 -> 30 us.
 template <int NT, bool FETCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
-                                                            int max_len, int H, float scale, __half *__restrict__ ctx,
+                                                            int max_len, int H, int items, float scale, __half *__restrict__ ctx,
                                                             float *__restrict__ p_absmax, typename FetchArg<FETCH>::type fetch)
 {
-    if (fetch_instead(fetch)) return;
+    if (fetch_instead(fetch, items)) return;
     // one slab per wave, as in the INT8 kernel: first its V^T tiles (two; a further one takes a tile's place when that one has
     // been multiplied), then its partial context for the other waves.  TIGHT: ten tiles of scores leave two waves per SIMD just
     // enough registers if V rows are requested one tile later (four tiles in the slab) and tiles past the end are skipped in
@@ -1205,7 +1203,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
     // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
+    const int item = xcd_contiguous(blockIdx.x, items);
     const int seq = item / (nqb * heads), head = (item / nqb) % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int q0 = (item % nqb) * QB;
@@ -1590,10 +1588,10 @@ __device__ __forceinline__ v8h codes_to_half(int d0, int d1)
 
 template <int NT, int NW = 4, bool FETCH = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 3 ? 4 : 2))) void
-attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, float m_sc, float m_ctx,
+attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, int items, float m_sc, float m_ctx,
                         int8_t *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
-    if (fetch_instead(fetch)) return;
+    if (fetch_instead(fetch, items)) return;
     static_assert(32 * NT <= P16_WAVE_KEYS, "the bound on the sum of the low parts");
     constexpr int K_AHEAD = NT <= 4 ? NT : 2;
     __shared__ __attribute__((aligned(1024))) int8_t slab[NW][NT * V_TILE];
@@ -1603,7 +1601,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     __shared__ ExpTable exp_table;
 
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, work_blocks(fetch));
+    const int item = xcd_contiguous(blockIdx.x, items);
     const int seq = item / (nqb * heads), head = (item / nqb) % heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int q0 = (item % nqb) * QB;
@@ -1944,7 +1942,7 @@ template <bool PU>
 static void launch_attention_i8_8waves(const int8_t *qkv, const int *cu, int max_len, int H, float m_sc, float inv_sp, float m_ctx,
                                        int8_t *ctx, dim3 grid, hipStream_t st, const Timing *tm)
 {
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, (unsigned long long *)nullptr, NoFetch()); };
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, (unsigned long long *)nullptr, NoFetch()); };
     switch ((max_len + 255) / 256) {
     case 3: return go(attention_i8_kernel<3, PU, false, 8>);
     case 4: return go(attention_i8_kernel<4, PU, false, 8>);
@@ -1963,18 +1961,18 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
     if constexpr (!HIST) {
         const dim3 more(grid.x + (fetch ? fetch->blocks : 0));
         if (fetch && max_len <= 128)
-            return launch_kernel(attention_i8_kernel<1, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+            return launch_kernel(attention_i8_kernel<1, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
         if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN)
-            return launch_kernel(attention_i8_kernel<2, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+            return launch_kernel(attention_i8_kernel<2, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
     }
     if (max_len <= 128)
-        launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= 256)
-        launch_kernel(attention_i8_kernel<2, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<2, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= 384)
-        launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= ONE_PASS_MAX_LEN)
-        launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (!HIST && max_len <= 8 * 256)
         launch_attention_i8_8waves<PU>(qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, grid, st, tm);
     else
@@ -2045,7 +2043,7 @@ hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packe
     if (max_len > 128 || H % 256 || B <= 0) return hipErrorNotSupported;
     auto go = [&](auto kern, unsigned more, auto what) {
         launch_kernel(kern, dim3((unsigned)(B * (H / 64)) + more), dim3(256), stream_ring_bytes<false, 8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
-                      (const char *)w_packed, m, b, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, what);
+                      (const char *)w_packed, m, b, cu, max_len, H, B * (H / 64), m_sc, inv_sp, m_ctx, ctx, what);
         return hipGetLastError();
     };
     if (fetch)
@@ -2067,7 +2065,7 @@ hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const 
             if (e != hipSuccess) return e;
             attr_set.store(true, std::memory_order_release);
         }
-        launch_kernel(kern, dim3(grid.x + more), dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, scale, ctx, what);
+        launch_kernel(kern, dim3(grid.x + more), dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, (int)grid.x, scale, ctx, what);
         return hipGetLastError();
     };
     static std::atomic<bool> attr_set[4];
@@ -2085,7 +2083,7 @@ hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int 
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
     auto go = [&](auto kern, int waves, unsigned more, auto what) {
-        launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, m_sc, m_ctx, ctx, what);
+        launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, m_ctx, ctx, what);
     };
     if (fetch && max_len <= 128) go(attention_i8_p16_kernel<1, 4, true>, 4, fetch->blocks, *fetch);
     else if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) go(attention_i8_p16_kernel<2, 4, true>, 4, fetch->blocks, *fetch);
@@ -2104,11 +2102,11 @@ hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
     if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
-        auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax, *fetch); };
+        auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, scale, ctx, p_absmax, *fetch); };
         if (max_len <= 128) with(attention_f16_kernel<1, true>); else with(attention_f16_kernel<2, true>);
         return hipGetLastError();
     }
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, scale, ctx, p_absmax, NoFetch()); };
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, scale, ctx, p_absmax, NoFetch()); };
     switch ((max_len + 127) / 128) {                              // key tiles per wave
     case 1: go(attention_f16_kernel<1>); break;
     case 2: go(attention_f16_kernel<2>); break;

@@ -18,6 +18,8 @@
 // lane i's 16 bytes at LDS position i of a 1 KiB run; the XOR swizzle that keeps the operand
 // fetches (ds_read_b128) conflict-free is therefore applied to the global address instead.
 // Work-groups are renumbered so that each XCD (own L2) owns a contiguous range of tiles.
+// What the first loads need comes first among a kernel's arguments: the launch puts 14 dwords of them into registers (up to the first struct),
+// the rest is loaded.  A load of arguments costs a launch 0.2 to 0.4 us, which is what a small forward consists of (build.py has the figures).
 // That is the row-major kernels.  An encoder keeps its weights packed as well and runs most of its GEMMs on those (gemm_nt_stream_kernel):
 // the row-major ones are left with few rows (gemm_rules.h), INT8 rows that are no whole pairs of 128-byte stages (widths 384, 640, 896, ...), GELU
 // without a table, the step entries, forced configurations and encoders whose arena has no room for packed copies.
@@ -337,8 +339,8 @@ template <class Epi> int extra_lds_of(const Epi &, long) { return 0; }
 // A block is WGM x WGN waves, each computing 32 TM tokens x 32 TN channels.
 template <class T, class Epi, int TM, int TN, int BKB, int NSTAGE, int WAVES_PER_EU, int WGM = 2, int WGN = 2>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(WAVES_PER_EU, 8)))
-void gemm_nt_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, Epi epi, int host_rows,
-                    const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+void gemm_nt_kernel(const char *__restrict__ A, const char *__restrict__ W, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
+                    int tiles_n, char *__restrict__ out, Epi epi)
 {
     constexpr int NWAVES = WGM * WGN, NT = 64 * NWAVES;
     constexpr int BM = 32 * WGM * TM, BN = 32 * WGN * TN;
@@ -506,8 +508,7 @@ hipError_t launch_cfg(const void *A, const void *W, void *out, const Epi &epi, R
     }
     const int tiles_n = N / BN, tiles_m = (rows.host_rows + BM - 1) / BM, total = tiles_n * tiles_m;
     launch_kernel(kern, dim3(total), dim3(64 * WGM * WGN), LDS, st, tm,
-                          (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows, rows.dev_rows, N, K * T::ELEM,
-                          tiles_n);
+                          (const char *)A, (const char *)W, rows.dev_rows, rows.host_rows, N, K * T::ELEM, tiles_n, (char *)out, epi);
     return hipGetLastError();
 }
 
@@ -539,8 +540,8 @@ template <class Epi> constexpr bool big_tables_late(int bm, int bn, int bkb, int
 
 template <class T, class Epi, int TM, int TN, int BKB, int NSTAGE, int WPE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, Epi epi, int host_rows,
-                        const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+void gemm_nt_big_kernel(const char *__restrict__ A, const char *__restrict__ W, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
+                        int tiles_n, char *__restrict__ out, Epi epi)
 {
     constexpr int CH = BKB / 16, RPI = 64 / CH, KS = BKB / 32, NWAVES = 4, NT = 256;
     constexpr int BM = 64 * TM, BN = 64 * TN;
@@ -753,7 +754,7 @@ hipError_t launch_big(const void *A, const void *W, void *out, const Epi &epi, R
     }
     const int tiles_n = N / BN, tiles_m = (rows.host_rows + BM - 1) / BM;
     launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm,
-                  (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows, rows.dev_rows, N, K * T::ELEM, tiles_n);
+                  (const char *)A, (const char *)W, rows.dev_rows, rows.host_rows, N, K * T::ELEM, tiles_n, (char *)out, epi);
     return hipGetLastError();
 }
 
@@ -781,8 +782,8 @@ template <class T, class Epi, int MT, int NTW, int D> struct StreamTile {
 
 template <class T, class Epi, int MT, int NTW, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ Wp, char *__restrict__ out, Epi epi, int host_rows,
-                           const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n, bool channels_first)
+void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ Wp, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
+                           int tiles_n, int channels_first, char *__restrict__ out, Epi epi)
 {
     typedef StreamTile<T, Epi, MT, NTW, D> Tile;
     constexpr bool HALF = Tile::HALF;
@@ -904,8 +905,8 @@ hipError_t launch_stream(const void *A, const void *Wp, void *out, const Epi &ep
     // 4096 x 1024, 512 rows 6.9 / 6.1, 1024 rows 10.6 / 8.6; 768 x 3072 and 3072 x 768 +-2 % up to 1024 rows)
     const bool channels_first = (long)N * K * T::ELEM >= 3 << 20 && rows.host_rows <= 1024;
     const int tiles_n = N / Tile::BN, tiles_m = (rows.host_rows + Tile::BM - 1) / Tile::BM;
-    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)Wp, (char *)out, epi,
-                  rows.host_rows, rows.dev_rows, N, K * T::ELEM, tiles_n, channels_first);
+    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)Wp, rows.dev_rows,
+                  rows.host_rows, N, K * T::ELEM, tiles_n, (int)channels_first, (char *)out, epi);
     return hipGetLastError();
 }
 
@@ -1009,8 +1010,8 @@ hipError_t launch_packed_f16(const void *A, const void *Wp, void *out, const Epi
 // what is won is the LDS (40 KB against 61 KB for the three-deep ring).
 template <class T, class Epi, int WGN, int DEPTH>
 __global__ __launch_bounds__(128 * WGN)
-void gemm_nt_longk_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, Epi epi, int host_rows,
-                          const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+void gemm_nt_longk_kernel(const char *__restrict__ A, const char *__restrict__ W, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
+                          int tiles_n, char *__restrict__ out, Epi epi)
 {
     constexpr int BKB = 128, BM = 64, BN = 32 * WGN, NWAVES = 2 * WGN, NT = 64 * NWAVES;
     constexpr int NPIECE = (BM + BN) / 8, NLD = (NPIECE + NWAVES - 1) / NWAVES;      // 1 KiB pieces of 8 rows; loads per wave and stage
@@ -1119,7 +1120,7 @@ hipError_t launch_longk(const void *A, const void *W, void *out, const Epi &epi,
     const size_t LDS = 2 * (size_t)(64 + BN) * 128 + (size_t)Epi::NTAB * BN * sizeof(float);
     const int tiles_n = N / BN, tiles_m = (rows.host_rows + 63) / 64;
     launch_kernel(gemm_nt_longk_kernel<T, Epi, WGN, DEPTH>, dim3(tiles_n * tiles_m), dim3(128 * WGN), LDS, st, tm,
-                  (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows, rows.dev_rows, N, kbytes, tiles_n);
+                  (const char *)A, (const char *)W, rows.dev_rows, rows.host_rows, N, kbytes, tiles_n, (char *)out, epi);
     return hipGetLastError();
 }
 
@@ -1140,8 +1141,8 @@ struct SmallGemm {
 
 template <class Epi, int MT, int NT, int NWAVES, int R>
 __global__ __launch_bounds__(64 * NWAVES)
-void gemm_nt_small_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, Epi epi, int host_rows,
-                          const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+void gemm_nt_small_kernel(const char *__restrict__ A, const char *__restrict__ W, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
+                          int tiles_n, char *__restrict__ out, Epi epi)
 {
     typedef SmallGemm<Epi, MT, NT, NWAVES, R> G;
     constexpr int BM = G::BM, BN = G::BN;
@@ -1244,8 +1245,8 @@ hipError_t launch_small(const void *A, const void *W, void *out, const Epi &epi,
         attr_set.store(true, std::memory_order_release);
     }
     const int tiles_n = N / G::BN, tiles_m = (rows.host_rows + G::BM - 1) / G::BM;
-    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(64 * NWAVES), LDS, st, tm, (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows,
-                  rows.dev_rows, N, K, tiles_n);
+    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(64 * NWAVES), LDS, st, tm, (const char *)A, (const char *)W, rows.dev_rows,
+                  rows.host_rows, N, K, tiles_n, (char *)out, epi);
     return hipGetLastError();
 }
 
@@ -1302,8 +1303,11 @@ struct LnGemm {
 
 template <class Epi, int NW>
 __global__ __launch_bounds__(64 * NW)
-void gemm_nt_ln_kernel(AddLnArgs a, const char *__restrict__ Wp, char *__restrict__ out, Epi epi, int N, int tiles_n)
+void gemm_nt_ln_kernel(const char *__restrict__ Wp, const int *a_dev_rows, const void *a_in, const void *a_res, const float *a_bias,
+                       const float *a_gamma, int a_host_rows, int tiles_n, AddLnArgs a, char *__restrict__ out, Epi epi, int N)
 {
+    a.in = a_in, a.res = a_res, a.bias = a_bias, a.gamma = a_gamma;
+    a.rows.dev_rows = a_dev_rows, a.rows.host_rows = a_host_rows;
     typedef LnGemm<Epi, NW> G;
     constexpr int K = G::K, CPL = K / 64;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -1365,8 +1369,8 @@ hipError_t launch_ln_gemm(const AddLnArgs &a, const void *Wp, void *out, const E
     static_assert(G::TAB_OFF + 2 * 64 * sizeof(float) + GELU_TABLE_MAX_BINS * 8 <= 64 * 1024, "");
     const size_t LDS = G::TAB_OFF + 2 * 64 * sizeof(float) + extra_lds_of(epi, 0);
     const int tiles_n = N / 64, tiles_m = (a.rows.host_rows + NW - 1) / NW;
-    launch_kernel(gemm_nt_ln_kernel<Epi, NW>, dim3(tiles_n * tiles_m), dim3(64 * NW), LDS, st, nullptr, a, (const char *)Wp, (char *)out, epi, N,
-                  tiles_n);
+    launch_kernel(gemm_nt_ln_kernel<Epi, NW>, dim3(tiles_n * tiles_m), dim3(64 * NW), LDS, st, nullptr, (const char *)Wp, a.rows.dev_rows,
+                  a.in, a.res, a.bias, a.gamma, a.rows.host_rows, tiles_n, a, (char *)out, epi, N);
     return hipGetLastError();
 }
 template <class Epi>
@@ -1383,8 +1387,8 @@ hipError_t launch_ln_gemm_width(const AddLnArgs &a, const void *Wp, void *out, c
 // four 128-byte slabs, wave w loading slab w, and the first CW waves each multiply one 32 x 32 tile.
 template <int CW, int R>
 __global__ __launch_bounds__(256)
-void gemm_nt_small_f16_kernel(const char *__restrict__ A, const char *__restrict__ W, char *__restrict__ out, EpiF16 epi, int host_rows,
-                              const int *__restrict__ dev_rows, int N, int Kbytes, int tiles_n)
+void gemm_nt_small_f16_kernel(const char *__restrict__ A, const char *__restrict__ W, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
+                              int tiles_n, char *__restrict__ out, EpiF16 epi)
 {
     constexpr int BM = 32, BN = 32 * CW, SLAB = (BM + BN) * 128, PIECES = SLAB / 1024, STAGE = 4 * SLAB;
     static_assert(R >= 2 && (R - 1) * PIECES < 64, "wait count range");
@@ -1475,8 +1479,8 @@ hipError_t launch_small_f16(const void *A, const void *W, void *out, const EpiF1
         attr_set.store(true, std::memory_order_release);
     }
     const int tiles_n = N / (32 * CW), tiles_m = (rows.host_rows + 31) / 32;
-    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)W, (char *)out, epi, rows.host_rows,
-                  rows.dev_rows, N, K * 2, tiles_n);
+    launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)W, rows.dev_rows,
+                  rows.host_rows, N, K * 2, tiles_n, (char *)out, epi);
     return hipGetLastError();
 }
 

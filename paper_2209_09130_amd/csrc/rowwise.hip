@@ -130,10 +130,18 @@ __device__ __forceinline__ bool prefetch_block(const AddLnPrefetchArgs &a)
     return true;
 }
 
+// What the first loads need comes as arguments of its own: 13 dwords, which the launch puts into registers (build.py); a struct's fields are loaded.
+#define LN_FIRST_ARGS \
+    const void *a_in, const void *a_res, const float *a_bias, const int *a_dev_rows, const float *a_gamma, const float *a_beta, int a_host_rows
+#define TAKE_LN_FIRST_ARGS(a)                                                                                \
+    (a).in = a_in, (a).res = a_res, (a).bias = a_bias, (a).gamma = a_gamma, (a).beta = a_beta;               \
+    (a).rows.dev_rows = a_dev_rows, (a).rows.host_rows = a_host_rows
+
 template <int NJ, bool IN_I8, bool RES_I8, bool OUT_I8, bool WHOLE, class Args>
-__global__ __launch_bounds__(16 * LN_ROWS) void add_ln_kernel(Args a)
+__global__ __launch_bounds__(16 * LN_ROWS) void add_ln_kernel(LN_FIRST_ARGS, Args a)
 {
     if (prefetch_block(a)) return;
+    TAKE_LN_FIRST_ARGS(a);
     const int M = a.rows.dev_rows ? *a.rows.dev_rows : a.rows.host_rows;
     const int nblk = (M + LN_ROWS - 1) / LN_ROWS;
     if ((int)blockIdx.x >= nblk) return;
@@ -193,9 +201,10 @@ __device__ __forceinline__ void ln_finish_wave(const float (&z)[CPL], double sum
 }
 
 template <int CPL, bool IN_I8, bool RES_I8, bool OUT_I8, class Args>
-__global__ __launch_bounds__(256) void add_ln_wave_kernel(Args a)
+__global__ __launch_bounds__(256) void add_ln_wave_kernel(LN_FIRST_ARGS, Args a)
 {
     if (prefetch_block(a)) return;
+    TAKE_LN_FIRST_ARGS(a);
     constexpr int H = 64 * CPL;
     const int M = a.rows.dev_rows ? *a.rows.dev_rows : a.rows.host_rows;
     const int nblk = (M + 3) / 4;
@@ -235,9 +244,9 @@ hipError_t launch_add_ln_nj(const Args &a, hipStream_t st, const Timing *tm)
     dim3 grid((a.rows.host_rows + per_block - 1) / per_block + (std::is_same<Args, AddLnPrefetchArgs>::value ? PREFETCH_BLOCKS : 0)), block(wave ? 256 : 16 * LN_ROWS);
 #define SAMP_LN_CASE(I, R, O)                                                                              \
     if (a.in_i8 == I && a.res_i8 == R && a.out_i8 == O) {                                                  \
-        if (wave) launch_kernel(add_ln_wave_kernel<WAVE ? 4 * NJ : 4, I, R, O, Args>, grid, block, 0, st, tm, a); \
-        else if (WHOLE_WIDTHS && a.H == 256 * NJ) launch_kernel(add_ln_kernel<NJ, I, R, O, WHOLE_WIDTHS, Args>, grid, block, 0, st, tm, a); \
-        else launch_kernel(add_ln_kernel<NJ, I, R, O, false, Args>, grid, block, 0, st, tm, a);                  \
+        if (wave) launch_kernel(add_ln_wave_kernel<WAVE ? 4 * NJ : 4, I, R, O, Args>, grid, block, 0, st, tm, a.in, a.res, a.bias, a.rows.dev_rows, a.gamma, a.beta, a.rows.host_rows, a); \
+        else if (WHOLE_WIDTHS && a.H == 256 * NJ) launch_kernel(add_ln_kernel<NJ, I, R, O, WHOLE_WIDTHS, Args>, grid, block, 0, st, tm, a.in, a.res, a.bias, a.rows.dev_rows, a.gamma, a.beta, a.rows.host_rows, a); \
+        else launch_kernel(add_ln_kernel<NJ, I, R, O, false, Args>, grid, block, 0, st, tm, a.in, a.res, a.bias, a.rows.dev_rows, a.gamma, a.beta, a.rows.host_rows, a); \
         return hipGetLastError();                                                                          \
     }
     SAMP_LN_CASE(true, true, true) SAMP_LN_CASE(true, true, false) SAMP_LN_CASE(false, false, true)
