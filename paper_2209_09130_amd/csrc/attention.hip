@@ -18,6 +18,7 @@
 #include "samp_common.h"
 #include "mfma_tile.h"
 #include "exp2_table.h"
+#include "divisor.h"
 
 #include <algorithm>
 #include <atomic>
@@ -252,8 +253,8 @@ __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 // times: three sequences of 1100 tokens (twelve heads) 94 -> 52 us, two of 2048 190 -> 118 us.
 template <int NT, bool PU, bool HIST, int NW = 4, bool FETCH = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5 ? 4 : 2))) void attention_i8_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu,
-                                                           int max_len, int H, int items, float m_sc, float inv_sp, float m_ctx,
-                                                           int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist, typename FetchArg<FETCH>::type fetch)
+                                                           int max_len, int H, int items, unsigned by_nqb, unsigned by_heads, float m_sc,
+                                                           float inv_sp, float m_ctx, int8_t *__restrict__ ctx, unsigned long long *__restrict__ p_hist, typename FetchArg<FETCH>::type fetch)
 {
     if (fetch_instead(fetch, items)) return;
     __shared__ unsigned hist[HIST ? 256 : 1];
@@ -274,9 +275,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, items);
-    const int seq = item / (nqb * heads), head = (item / nqb) % heads;
+    const int strip = (int)over(item, by_nqb, nqb), seq = (int)over(strip, by_heads, heads), head = strip - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
-    const int q0 = (item % nqb) * QB;
+    const int q0 = (item - strip * nqb) * QB;
     if (q0 >= sq.n) return;
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
@@ -853,7 +854,7 @@ void qkv_attention_i8_kernel(const char *__restrict__ X, const char *__restrict_
 template <bool PU, int D, bool FETCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__restrict__ Wp, const float *__restrict__ m_tab,
-                                    const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, int items, float m_sc,
+                                    const float *__restrict__ b_tab, const int *__restrict__ cu, int max_len, int H, int items, unsigned by_heads, float m_sc,
                                     float inv_sp, float m_ctx, int8_t *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
     if (fetch_instead(fetch, items)) return;
@@ -865,7 +866,7 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
 
     const int heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, items);       // sequences outermost, as in the attention kernel
-    const int seq = item / heads, head = item % heads;
+    const int seq = (int)over(item, by_heads, heads), head = item - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
     if (n <= 0) return;
@@ -939,7 +940,7 @@ constexpr int QKV_F16_PACKED_D = 2, QKV_F16_PACKED_RING = stream_ring_bytes<true
 template <int QT, int STAGE, bool PACKED, bool FETCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 2 : 1, QT == 1 ? 2 : 1)))
 void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict__ W, const float *__restrict__ bias,
-                              const int *__restrict__ cu, int max_len, int H, int items, float scale, __half *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
+                              const int *__restrict__ cu, int max_len, int H, int items, unsigned by_heads, float scale, __half *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
     if (fetch_instead(fetch, items)) return;
     typedef QkvTile<QT, STAGE> Tile;
@@ -957,7 +958,7 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
 
     const int heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, items);
-    const int seq = item / heads, head = item % heads;
+    const int seq = (int)over(item, by_heads, heads), head = item - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
     if (n <= 0) return;
@@ -1183,7 +1184,7 @@ __device__ __forceinline__ void store_vt_tile_f16(const v8h (&d)[2][2], int lane
 // 301 36.5 -> 30 us.
 template <int NT, bool FETCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
-                                                            int max_len, int H, int items, float scale, __half *__restrict__ ctx,
+                                                            int max_len, int H, int items, unsigned by_nqb, unsigned by_heads, float scale, __half *__restrict__ ctx,
                                                             float *__restrict__ p_absmax, typename FetchArg<FETCH>::type fetch)
 {
     if (fetch_instead(fetch, items)) return;
@@ -1204,9 +1205,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, items);
-    const int seq = item / (nqb * heads), head = (item / nqb) % heads;
+    const int strip = (int)over(item, by_nqb, nqb), seq = (int)over(strip, by_heads, heads), head = strip - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
-    const int q0 = (item % nqb) * QB;
+    const int q0 = (item - strip * nqb) * QB;
     if (q0 >= sq.n) return;
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
@@ -1588,7 +1589,7 @@ __device__ __forceinline__ v8h codes_to_half(int d0, int d1)
 
 template <int NT, int NW = 4, bool FETCH = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 3 ? 4 : 2))) void
-attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, int items, float m_sc, float m_ctx,
+attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ cu, int max_len, int H, int items, unsigned by_nqb, unsigned by_heads, float m_sc, float m_ctx,
                         int8_t *__restrict__ ctx, typename FetchArg<FETCH>::type fetch)
 {
     if (fetch_instead(fetch, items)) return;
@@ -1602,9 +1603,9 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
 
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
     const int item = xcd_contiguous(blockIdx.x, items);
-    const int seq = item / (nqb * heads), head = (item / nqb) % heads;
+    const int strip = (int)over(item, by_nqb, nqb), seq = (int)over(strip, by_heads, heads), head = strip - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
-    const int q0 = (item % nqb) * QB;
+    const int q0 = (item - strip * nqb) * QB;
     if (q0 >= sq.n) return;
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
@@ -1942,7 +1943,11 @@ template <bool PU>
 static void launch_attention_i8_8waves(const int8_t *qkv, const int *cu, int max_len, int H, float m_sc, float inv_sp, float m_ctx,
                                        int8_t *ctx, dim3 grid, hipStream_t st, const Timing *tm)
 {
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, (unsigned long long *)nullptr, NoFetch()); };
+    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
+    auto go = [&](auto kern) {
+        launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx,
+                      (unsigned long long *)nullptr, NoFetch());
+    };
     switch ((max_len + 255) / 256) {
     case 3: return go(attention_i8_kernel<3, PU, false, 8>);
     case 4: return go(attention_i8_kernel<4, PU, false, 8>);
@@ -1958,21 +1963,22 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
                                         const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
+    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     if constexpr (!HIST) {
         const dim3 more(grid.x + (fetch ? fetch->blocks : 0));
         if (fetch && max_len <= 128)
-            return launch_kernel(attention_i8_kernel<1, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+            return launch_kernel(attention_i8_kernel<1, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
         if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN)
-            return launch_kernel(attention_i8_kernel<2, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+            return launch_kernel(attention_i8_kernel<2, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
     }
     if (max_len <= 128)
-        launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= 256)
-        launch_kernel(attention_i8_kernel<2, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<2, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= 384)
-        launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<3, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (max_len <= ONE_PASS_MAX_LEN)
-        launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
+        launch_kernel(attention_i8_kernel<4, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
     else if (!HIST && max_len <= 8 * 256)
         launch_attention_i8_8waves<PU>(qkv, cu, max_len, H, m_sc, inv_sp, m_ctx, ctx, grid, st, tm);
     else
@@ -2043,7 +2049,7 @@ hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packe
     if (max_len > 128 || H % 256 || B <= 0) return hipErrorNotSupported;
     auto go = [&](auto kern, unsigned more, auto what) {
         launch_kernel(kern, dim3((unsigned)(B * (H / 64)) + more), dim3(256), stream_ring_bytes<false, 8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
-                      (const char *)w_packed, m, b, cu, max_len, H, B * (H / 64), m_sc, inv_sp, m_ctx, ctx, what);
+                      (const char *)w_packed, m, b, cu, max_len, H, B * (H / 64), divisor((unsigned)B * (H / 64), H / 64), m_sc, inv_sp, m_ctx, ctx, what);
         return hipGetLastError();
     };
     if (fetch)
@@ -2065,7 +2071,7 @@ hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const 
             if (e != hipSuccess) return e;
             attr_set.store(true, std::memory_order_release);
         }
-        launch_kernel(kern, dim3(grid.x + more), dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, (int)grid.x, scale, ctx, what);
+        launch_kernel(kern, dim3(grid.x + more), dim3(256), lds, st, tm, (const char *)x, (const char *)(packed ? w_packed : w_qkv), bias, cu, max_len, H, (int)grid.x, divisor(grid.x, H / 64), scale, ctx, what);
         return hipGetLastError();
     };
     static std::atomic<bool> attr_set[4];
@@ -2082,8 +2088,9 @@ hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int 
                                    float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
+    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     auto go = [&](auto kern, int waves, unsigned more, auto what) {
-        launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, m_sc, m_ctx, ctx, what);
+        launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, m_ctx, ctx, what);
     };
     if (fetch && max_len <= 128) go(attention_i8_p16_kernel<1, 4, true>, 4, fetch->blocks, *fetch);
     else if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) go(attention_i8_p16_kernel<2, 4, true>, 4, fetch->blocks, *fetch);
@@ -2101,12 +2108,13 @@ hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max
                                 __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
+    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
-        auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, scale, ctx, p_absmax, *fetch); };
+        auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, *fetch); };
         if (max_len <= 128) with(attention_f16_kernel<1, true>); else with(attention_f16_kernel<2, true>);
         return hipGetLastError();
     }
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, scale, ctx, p_absmax, NoFetch()); };
+    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, NoFetch()); };
     switch ((max_len + 127) / 128) {                              // key tiles per wave
     case 1: go(attention_f16_kernel<1>); break;
     case 2: go(attention_f16_kernel<2>); break;

@@ -27,6 +27,7 @@
 #include "mfma_tile.h"
 #include "ln_wave.h"
 #include "gemm_rules.h"
+#include "divisor.h"
 
 #include <atomic>
 #include <type_traits>
@@ -34,6 +35,21 @@
 
 namespace samp {
 namespace {
+
+// Where tile `tile` lies when the row tiles of a channel tile come one after the other.  by_m: divisor() of the row tiles that the host counted; a ragged
+// batch may have fewer.  Forward, us, three encoders in turn, with divisions in the GEMM and attention kernels / with these: BERT-base 7 x 61 354 / 349,
+// 16 x 128 529 / 523, 32 x 128 685 / 676, 33 x 40..301 1233 / 1216.
+struct TileAt { int m, n; };
+__device__ __forceinline__ TileAt tile_channels_first(int tile, int tiles_m, int host_tiles_m, unsigned by_m)
+{
+    const int n = (int)over(tile, tiles_m == host_tiles_m ? by_m : 1u, tiles_m);
+    return {tile - n * tiles_m, n};
+}
+__device__ __forceinline__ TileAt tile_rows_first(int tile, int tiles_n, unsigned by_n)
+{
+    const int m = (int)over(tile, by_n, tiles_n);
+    return {m, tile - m * tiles_n};
+}
 
 struct I8 {
     typedef v16i acc_t;
@@ -783,7 +799,7 @@ template <class T, class Epi, int MT, int NTW, int D> struct StreamTile {
 template <class T, class Epi, int MT, int NTW, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ Wp, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
-                           int tiles_n, int channels_first, char *__restrict__ out, Epi epi)
+                           int tiles_n, unsigned by, int channels_first, char *__restrict__ out, Epi epi)
 {
     typedef StreamTile<T, Epi, MT, NTW, D> Tile;
     constexpr bool HALF = Tile::HALF;
@@ -795,7 +811,8 @@ void gemm_nt_stream_kernel(const char *__restrict__ A, const char *__restrict__ 
     const int tiles_m = (M + BM - 1) / BM, tiles = tiles_m * tiles_n;
     if ((int)blockIdx.x >= tiles) return;
     const int tile = xcd_contiguous(blockIdx.x, tiles);
-    const int m0 = (channels_first ? tile % tiles_m : tile / tiles_n) * BM, n0 = (channels_first ? tile / tiles_m : tile % tiles_n) * BN;
+    const TileAt at = channels_first ? tile_channels_first(tile, tiles_m, (host_rows + BM - 1) / BM, by) : tile_rows_first(tile, tiles_n, by);
+    const int m0 = at.m * BM, n0 = at.n * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & (ROWS - 1), q = lane / ROWS;
 
@@ -906,7 +923,8 @@ hipError_t launch_stream(const void *A, const void *Wp, void *out, const Epi &ep
     const bool channels_first = (long)N * K * T::ELEM >= 3 << 20 && rows.host_rows <= 1024;
     const int tiles_n = N / Tile::BN, tiles_m = (rows.host_rows + Tile::BM - 1) / Tile::BM;
     launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)Wp, rows.dev_rows,
-                  rows.host_rows, N, K * T::ELEM, tiles_n, (int)channels_first, (char *)out, epi);
+                  rows.host_rows, N, K * T::ELEM, tiles_n, divisor(tiles_n * tiles_m, channels_first ? tiles_m : tiles_n), (int)channels_first,
+                  (char *)out, epi);
     return hipGetLastError();
 }
 
@@ -1316,6 +1334,7 @@ void gemm_nt_ln_kernel(const char *__restrict__ Wp, const int *a_dev_rows, const
     const int tiles_m = (M + NW - 1) / NW, tiles = tiles_m * tiles_n;
     if ((int)blockIdx.x >= tiles) return;
     const int tile = xcd_contiguous(blockIdx.x, tiles);
+    // (a divisor among the preloaded arguments would take the place of a vector's address: BERT-large 1 x 19 529 / 540 us)
     const int m0 = (tile % tiles_m) * NW, n0 = (tile / tiles_m) * 64;          // channels outermost: an XCD reads an eighth of the weights
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, q = lane >> 4;
 
@@ -1388,7 +1407,7 @@ hipError_t launch_ln_gemm_width(const AddLnArgs &a, const void *Wp, void *out, c
 template <int CW, int R>
 __global__ __launch_bounds__(256)
 void gemm_nt_small_f16_kernel(const char *__restrict__ A, const char *__restrict__ W, const int *__restrict__ dev_rows, int host_rows, int N, int Kbytes,
-                              int tiles_n, char *__restrict__ out, EpiF16 epi)
+                              int tiles_n, unsigned by_m, char *__restrict__ out, EpiF16 epi)
 {
     constexpr int BM = 32, BN = 32 * CW, SLAB = (BM + BN) * 128, PIECES = SLAB / 1024, STAGE = 4 * SLAB;
     static_assert(R >= 2 && (R - 1) * PIECES < 64, "wait count range");
@@ -1397,7 +1416,8 @@ void gemm_nt_small_f16_kernel(const char *__restrict__ A, const char *__restrict
     const int tiles_m = (M + BM - 1) / BM, tiles = tiles_m * tiles_n;
     if ((int)blockIdx.x >= tiles) return;
     const int tile = xcd_contiguous(blockIdx.x, tiles);
-    const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+    const TileAt at = tile_channels_first(tile, tiles_m, (host_rows + BM - 1) / BM, by_m);
+    const int m0 = at.m * BM, n0 = at.n * BN;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, g = lane >> 5;
     const char *src[PIECES];
@@ -1480,7 +1500,7 @@ hipError_t launch_small_f16(const void *A, const void *W, void *out, const EpiF1
     }
     const int tiles_n = N / (32 * CW), tiles_m = (rows.host_rows + 31) / 32;
     launch_kernel(kern, dim3(tiles_n * tiles_m), dim3(256), LDS, st, tm, (const char *)A, (const char *)W, rows.dev_rows,
-                  rows.host_rows, N, K * 2, tiles_n, (char *)out, epi);
+                  rows.host_rows, N, K * 2, tiles_n, divisor(tiles_n * tiles_m, tiles_m), (char *)out, epi);
     return hipGetLastError();
 }
 
