@@ -229,6 +229,16 @@ __device__ __forceinline__ bool fetch_instead(const FetchAhead &f, int items)
     return true;
 }
 
+// 4 N consecutive codes
+template <int N> __device__ __forceinline__ void store_codes(int8_t *dst, const int (&pk)[N])
+{
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int d = 0; d < N / 4; d++) *reinterpret_cast<v4i *>(dst + 16 * d) = v4i{pk[4 * d], pk[4 * d + 1], pk[4 * d + 2], pk[4 * d + 3]};
+    } else if constexpr (N == 2) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
+    else *reinterpret_cast<int *>(dst) = pk[0];
+}
+
 struct SeqInfo { int t0, n; };
 __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 {
@@ -286,7 +296,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     // rows from j0 to the end of the sequence; a row past it reads as zeros, so no load needs a test or an address of its own
     auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, max((n - j0) * (int)ld - head * 64, 0)); };
     auto first_key = [&](int i) { return (w + NW * i) * 32; };
-    const uint64_t table_entry = EXP2_TABLE[tid & 255];
+    constexpr int ENTRIES = NW < 4 ? 4 / NW : 1;                  // of the exponential's table, per thread
+    uint64_t table_entry[ENTRIES];
+#pragma unroll
+    for (int i = 0; i < ENTRIES; i++) table_entry[i] = EXP2_TABLE[(tid + 64 * NW * i) & 255];
     if (HIST && tid < 256) hist[tid] = 0;                                      // ordered before its use by the barriers below
 
     // lane (row r, half g) holds 16 consecutive bytes of the head dim of a query row (second MFMA operand) or a key row (first)
@@ -339,7 +352,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     }
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
-    if (NW == 4 || tid < 256) exp_table[tid] = table_entry;
+#pragma unroll
+    for (int i = 0; i < ENTRIES; i++)
+        if (NW <= 4 || tid < 256) exp_table[tid + 64 * NW * i] = table_entry[i];
     wait_vm<0>();                                                 // the wave's V tiles are in its slab
     __syncthreads();
 #pragma unroll
@@ -425,7 +440,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
         for (int e = 0; e < 16; e++) so(w)[8 * (e >> 2) + 4 * g + (e & 3)][cb * 32 + r] = o[cb][e];
     __syncthreads();
 
-    constexpr int CPT = 32 / NW;                                  // channels per thread: 8 or 4
+    constexpr int CPT = 32 / NW;                                  // channels per thread: 4 to 32
     const int query = tid / (64 / CPT), c0 = tid % (64 / CPT) * CPT;
     if (q0 + query < n) {
         int pk[CPT / 4];
@@ -442,8 +457,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
             pk[d] = pack_codes(codes[0], codes[1], codes[2], codes[3]);
         }
         int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0;
-        if constexpr (CPT == 8) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
-        else *reinterpret_cast<int *>(dst) = pk[0];
+        store_codes(dst, pk);
     }
     if (HIST && tid < 256 && hist[tid]) atomicAdd(&p_hist[tid], (unsigned long long)hist[tid]);   // after the barrier above
 }
@@ -1182,8 +1196,8 @@ __device__ __forceinline__ void store_vt_tile_f16(const v8h (&d)[2][2], int lane
 // three-sweep kernel, tile by tile, so both give the same bytes.  V rows
 // are transposed in registers two keys at a time (dword stores).  Twelve heads, three sequences of 1100 tokens: 76 -> 51 us, 17 of
 // 301 36.5 -> 30 us.
-template <int NT, bool FETCH = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
+template <int NT, bool FETCH = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
                                                             int max_len, int H, int items, unsigned by_nqb, unsigned by_heads, float scale, __half *__restrict__ ctx,
                                                             float *__restrict__ p_absmax, typename FetchArg<FETCH>::type fetch)
 {
@@ -1196,10 +1210,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     constexpr bool TIGHT = NT == 10;
     constexpr int VT_TILE = 64 * VT_STRIDE_F16, SO_BYTES = QB * 64 * 4, VT_TILES = TIGHT ? 4 : NT < 2 ? NT : 2, AHEAD = TIGHT ? 2 : 1;
     constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
-    __shared__ __attribute__((aligned(16))) char slab[4][SLAB];
+    __shared__ __attribute__((aligned(16))) char slab[NW][SLAB];
     auto so = [&](int wave) { return reinterpret_cast<float(*)[64]>(slab[wave]); };
-    __shared__ float smax[4][QB];
-    __shared__ float ssum[4][QB];
+    __shared__ float smax[NW][QB];
+    __shared__ float ssum[NW][QB];
 
     // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
     // sequences, whose tokens it also owns in the kernels before and after this one
@@ -1223,7 +1237,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + 4 * i) * 32;
+        const int j0 = (w + NW * i) * 32;
         if (j0 < n) {
             const __half *kp = base + (unsigned)min(j0 + r, n - 1) * ld + H;
             v8h kf[4], d[2][2];                                  // all loads are issued before the first is used
@@ -1250,12 +1264,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
     __syncthreads();
-    mx = __builtin_fmaxf(__builtin_fmaxf(smax[0][r], smax[1][r]), __builtin_fmaxf(smax[2][r], smax[3][r]));
+#pragma unroll
+    for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
 
     float part = 0.0f;
 #pragma unroll
     for (int i = 0; i < NT; i++)
-        if (!TIGHT || (w + 4 * i) * 32 < n) {                     // tiles past the end add zeros
+        if (!TIGHT || (w + NW * i) * 32 < n) {                     // tiles past the end add zeros
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const float ev = __builtin_amdgcn_exp2f((sc[i][e] - mx) * 1.44269504088896341f);
@@ -1266,7 +1281,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
     part += __shfl_xor(part, 32, 64);
     if (g == 0) ssum[w][r] = part;
     __syncthreads();
-    const float S = ((ssum[0][r] + ssum[1][r]) + ssum[2][r]) + ssum[3][r];
+    float S = ssum[0][r];
+#pragma unroll
+    for (int u = 1; u < NW; u++) S += ssum[u][r];
     const float rS = __fdiv_rn(1.0f, S);
     if (p_absmax && w == 0 && g == 0 && q0 + r < n)              // the row's largest P is exp(0) / S
         atomicMax(reinterpret_cast<int *>(p_absmax), __float_as_int((float)(_Float16)rS));
@@ -1278,11 +1295,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
         for (int e = 0; e < 16; e++) o[cb][e] = 0.0f;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j1 = (w + 4 * (i + AHEAD)) * 32;                 // the tile that takes the place of tile i - AHEAD
+        const int j1 = (w + NW * (i + AHEAD)) * 32;                 // the tile that takes the place of tile i - AHEAD
         const bool more = i >= AHEAD && i + AHEAD < NT && j1 < n;
         v8h d[2][2];
         if (more) load_v_tile_f16(vp, ld, j1, n, lane, d);
-        if ((w + 4 * i) * 32 < n) {
+        if ((w + NW * i) * 32 < n) {
 #pragma unroll
             for (int hf = 0; hf < 2; hf++) {                    // keys 8q+4g+t for q in {2hf, 2hf+1}
                 v8h pf;
@@ -1306,13 +1323,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 
         for (int e = 0; e < 16; e++) so(w)[8 * (e >> 2) + 4 * g + (e & 3)][cb * 32 + r] = o[cb][e];
     __syncthreads();
 
-    const int query = tid >> 3, c0 = (tid & 7) * 8;
-    if (q0 + query < n) {
-        v8h outv;
+    // (fewer waves than four: those without a key tile would have added +0)
 #pragma unroll
-        for (int e = 0; e < 8; e++)
-            outv[e] = to_half(((so(0)[query][c0 + e] + so(1)[query][c0 + e]) + so(2)[query][c0 + e]) + so(3)[query][c0 + e]);
-        *reinterpret_cast<v8h *>(ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0) = outv;
+    for (int i = 0; i < 4 / NW; i++) {
+        const int query = (tid >> 3) + 8 * NW * i, c0 = (tid & 7) * 8;
+        if (q0 + query < n) {
+            v8h outv;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                float o_sum = so(0)[query][c0 + e];
+#pragma unroll
+                for (int u = 1; u < NW; u++) o_sum += so(u)[query][c0 + e];
+                if (NW < 4) o_sum += 0.0f;
+                outv[e] = to_half(o_sum);
+            }
+            *reinterpret_cast<v8h *>(ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0) = outv;
+        }
     }
 }
 
@@ -1730,8 +1756,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
         pk[d] = pack_codes(codes[0], codes[1], codes[2], codes[3]);
     }
     int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0;
-    if constexpr (CPT == 8) *reinterpret_cast<v2i *>(dst) = v2i{pk[0], pk[1]};
-    else *reinterpret_cast<int *>(dst) = pk[0];
+    store_codes(dst, pk);
 }
 
 // Any length: three sweeps (as attention_i8_long_kernel), digit planes.
@@ -1937,6 +1962,12 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
 
 }  // namespace
 
+// One or two key tiles and blocks enough for the chip: no waves without a tile.  Forward, us, four waves / as many as tiles: BERT-base Fully-Quant 512 x 8
+// 878 / 738, 256 x 16 782 / 720, 128 x 32 734 / 715, 24 x 48 413 / 413, BERT-large 128 x 32 2075 / 2002; FP16 512 x 8 1351 / 1299, 256 x 16 1264 / 1262, 128 x 32
+// 1258 / 1231, Quant-FFN-Only 256 x 16 968 / 921; with fewer blocks Fully-Quant 16 x 24 345 / 345, 1 x 19 241 / 242, BERT-large 64 x 32 1256 / 1275.  (The binary16
+// softmax output keeps four waves: 256 x 16 774 / 786.)
+static bool few_waves(unsigned blocks) { return blocks >= 768; }
+
 // 513 to 2048 tokens: eight waves, a wave's NT key tiles as few as the longest sequence allows (registers and LDS, and with
 // them the blocks per CU, follow NT)
 template <bool PU>
@@ -1965,11 +1996,14 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
     const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     if constexpr (!HIST) {
-        const dim3 more(grid.x + (fetch ? fetch->blocks : 0));
-        if (fetch && max_len <= 128)
-            return launch_kernel(attention_i8_kernel<1, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
-        if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN)
-            return launch_kernel(attention_i8_kernel<2, PU, HIST, 4, true>, more, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, *fetch);
+        auto go = [&](auto kern, int waves, unsigned more, auto what) {
+            launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx,
+                          p_hist, what);
+        };
+        if (fetch && max_len <= 128) return go(attention_i8_kernel<1, PU, HIST, 4, true>, 4, fetch->blocks, *fetch);
+        if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) return go(attention_i8_kernel<2, PU, HIST, 4, true>, 4, fetch->blocks, *fetch);
+        if (few_waves(grid.x) && max_len <= 32) return go(attention_i8_kernel<1, PU, HIST, 1>, 1, 0, NoFetch());
+        if (few_waves(grid.x) && max_len <= 64) return go(attention_i8_kernel<1, PU, HIST, 2>, 2, 0, NoFetch());
     }
     if (max_len <= 128)
         launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
@@ -2114,7 +2148,13 @@ hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max
         if (max_len <= 128) with(attention_f16_kernel<1, true>); else with(attention_f16_kernel<2, true>);
         return hipGetLastError();
     }
-    auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, NoFetch()); };
+    auto go = [&](auto kern, int waves = 4) {
+        launch_kernel(kern, grid, dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, NoFetch());
+    };
+    if (few_waves(grid.x) && max_len <= 64) {
+        if (max_len <= 32) go(attention_f16_kernel<1, false, 1>, 1); else go(attention_f16_kernel<1, false, 2>, 2);
+        return hipGetLastError();
+    }
     switch ((max_len + 127) / 128) {                              // key tiles per wave
     case 1: go(attention_f16_kernel<1>); break;
     case 2: go(attention_f16_kernel<2>); break;

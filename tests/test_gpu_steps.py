@@ -739,6 +739,30 @@ def test_fp16_qkv_gemm_and_attention_in_one_kernel(P, lens, heads, offsets):
                           host(P.attention_f16(P.gemm_f16(dev(x), dev(w), None, False), cu_dev, max(lens), heads)).view(np.uint16))
 
 
+@pytest.mark.parametrize("longest,B,heads", [(1, 800, 1), (31, 384, 2), (32, 383, 2), (32, 64, 12), (33, 384, 1), (64, 130, 3), (64, 127, 3), (65, 260, 1)])
+def test_attention_of_many_short_sequences(P, longest, B, heads):
+    """From 768 blocks on, sequences of one or two key tiles take one or two waves: sizes on either side, ragged; INT8 in its three softmax
+    forms and the clamp bit-exact, FP16 the same bytes as the same sequences in a batch of fewer blocks (four waves)."""
+    rng = np.random.default_rng(longest * B)
+    lens = rng.integers(1, longest + 1, B)
+    lens[::7] = longest
+    cu, H = _cu(lens), heads * 64
+    qkv = np.clip(np.rint(rng.standard_normal((int(cu[-1]), 3 * H)) * 30), -127, 127).astype(np.int8)
+    for sc in ((0.0209, 0.0249, 0.021, 0.004, 0.0021), (0.0209, 0.0249, 0.021, 0.02, 0.0021)):
+        for kw in ({}, {"p_unsigned": True}):
+            want = oracle.attention_i8(qkv, cu, heads, *sc, **kw)
+            assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), longest, heads, *sc, **kw)), want)
+    want = oracle.attention_i8_p16(qkv, cu, heads, sc[0], sc[1], sc[2], sc[4])
+    assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), longest, heads, *sc, p_fp16=True)), want)
+    f = (rng.standard_normal((int(cu[-1]), 3 * H)) * 0.6).astype(np.float16)
+    whole = host(P.attention_f16(dev(f), dev(cu), longest, heads)).view(np.uint16)
+    step = 40
+    for b in range(0, B, step):
+        e = min(B, b + step)
+        part = host(P.attention_f16(dev(f[cu[b]:cu[e]]), dev(cu[b:e + 1] - cu[b]), longest, heads)).view(np.uint16)
+        assert np.array_equal(part, whole[cu[b]:cu[e]])
+
+
 @pytest.mark.parametrize("lens,heads", [([513], 1), ([700, 31, 1024], 2), ([2048, 515], 1)])
 def test_long_sequence_attention_matches_the_oracle(P, lens, heads):
     """More than 512 keys: the calls that count codes take the three-sweep kernels (row maxima, row sums, codes and P.V,
