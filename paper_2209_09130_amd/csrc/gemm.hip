@@ -1153,8 +1153,7 @@ hipError_t launch_longk(const void *A, const void *W, void *out, const Epi &epi,
 template <class Epi, int MT, int NT, int NWAVES, int R>
 struct SmallGemm {
     static constexpr int BM = 16 * MT, BN = 16 * NT, SLAB = (BM + BN) * 128, PIECES = SLAB / 1024;
-    static constexpr int RING_BYTES = NWAVES * R * SLAB, PART_BYTES = NWAVES * MT * NT * 1024;
-    static constexpr int TAB_OFF = RING_BYTES > PART_BYTES ? RING_BYTES : PART_BYTES;
+    static constexpr int TAB_OFF = NWAVES * R * SLAB;             // behind the rings
 };
 
 template <class Epi, int MT, int NT, int NWAVES, int R>
@@ -1231,18 +1230,18 @@ void gemm_nt_small_kernel(const char *__restrict__ A, const char *__restrict__ W
     for (int u = 0; u < R; u++)
         if (s + u < slabs) consume(u);
 
-    // partial tiles take the ring's place: [wave][tile][lane]
-    __syncthreads();
+    // a wave's partial tiles take the place of its own part of the ring, which no other wave reads: [tile][lane]
+    static_assert(MT * NT * 1024 <= R * G::SLAB, "");
 #pragma unroll
     for (int i = 0; i < MT; i++)
 #pragma unroll
-        for (int j = 0; j < NT; j++) *reinterpret_cast<v4i *>(lds + ((wave * MT + i) * NT + j) * 1024 + lane * 16) = acc[i][j];
+        for (int j = 0; j < NT; j++) *reinterpret_cast<v4i *>(ring + (i * NT + j) * 1024 + lane * 16) = acc[i][j];
     __syncthreads();
     // lane: token 16 i + (lane & 15), channels 16 j + 4 (lane >> 4) .. + 3
     for (int t = wave; t < MT * NT; t += NWAVES) {
         v4i sum = {0, 0, 0, 0};
 #pragma unroll
-        for (int w = 0; w < NWAVES; w++) sum += *reinterpret_cast<const v4i *>(lds + (w * MT * NT + t) * 1024 + lane * 16);
+        for (int w = 0; w < NWAVES; w++) sum += *reinterpret_cast<const v4i *>(lds + w * (R * G::SLAB) + t * 1024 + lane * 16);
         const int i = t / NT, j = t % NT, row = m0 + 16 * i + r, nl = 16 * j + 4 * q;
         const int pk = epi.four(sum, tab, BN, nl);
         if (row < M) *reinterpret_cast<int *>(out + (size_t)row * N + n0 + nl) = pk;
