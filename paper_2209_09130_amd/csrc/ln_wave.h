@@ -25,6 +25,38 @@ __device__ __forceinline__ double row16_sum(double v)
     v += dpp_mov<0x140>(v);           // row_mirror
     return v;
 }
+// A row's statistics are a chain of dependent binary64 operations that every launch of few rows waits for.  At width 768, where mean and variance take
+// divisions, they have short forms of the divisions and of the root (some 45 operations with the library's) and sums in four chains; at the other
+// widths, where dividing is a product, those are no gain (BERT-large 1 x 19 527 / 529, 16 x 64 1013 / 1020).  Forwards, us, before / now: BERT-base Fully-Quant
+// 1 x 19 242 / 238, 1 x 64 292 / 286, 16 x 128 538 / 533, FP16 1 x 64 441 / 439.  (With four rows per wave the chain is shared and the kernel's registers are
+// what counts: 32 x 128 754 / 761; not used there.)
+template <int H> constexpr bool SHORT_STATISTICS = (H & (H - 1)) != 0;
+template <int H> struct RowSum {                          // sum of a lane's values
+    double part[SHORT_STATISTICS<H> ? 4 : 1] = {};
+    __device__ __forceinline__ void add(int e, double v) { part[SHORT_STATISTICS<H> ? e & 3 : 0] += v; }
+    __device__ __forceinline__ void add_square(int e, double v) { double &p = part[SHORT_STATISTICS<H> ? e & 3 : 0]; p = __builtin_fma(v, v, p); }
+    __device__ __forceinline__ double total() const
+    {
+        if constexpr (SHORT_STATISTICS<H>) return (part[0] + part[1]) + (part[2] + part[3]);
+        else return part[0];
+    }
+};
+// v / H: the product with the reciprocal, corrected once, is the rounding of the division
+template <int H> __device__ __forceinline__ double over_width(double v)
+{
+    constexpr double inv = 1.0 / H;
+    if constexpr (!SHORT_STATISTICS<H>) return v * inv;
+    const double q = v * inv;
+    return __builtin_fma(__builtin_fma(-q, (double)H, v), inv, q);
+}
+// 1 / sqrt(v); short: one third-order step on the hardware's estimate, relative error below 2^-51 before the rounding to binary32
+template <int H> __device__ __forceinline__ float reciprocal_root(double v)
+{
+    if (!SHORT_STATISTICS<H> || !(v > 0x1p-900 && v < 0x1p900)) return (float)(1.0 / sqrt(v));
+    const double y = __builtin_amdgcn_rsq(v), e = __builtin_fma(-v * y, y, 1.0);
+    return (float)__builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
 template <bool I8, int CPL> __device__ __forceinline__ void load_lane(const void *p, size_t elem, float (&v)[CPL])
 {
     static_assert(CPL % 4 == 0, "whole dwords of int8 channels per lane");
@@ -65,12 +97,12 @@ __device__ __forceinline__ void ln_normalise_wave(const float (&z)[CPL], double 
                                                   float (&y)[CPL])
 {
     constexpr int H = 64 * CPL;
-    const double mu = row64_sum(sum) / (double)H;
-    double sq = 0.0;
+    const double mu = over_width<H>(row64_sum(sum));
+    RowSum<H> sq;
 #pragma unroll
-    for (int e = 0; e < CPL; e++) { const double d = (double)z[e] - mu; sq = __builtin_fma(d, d, sq); }
-    const double var = row64_sum(sq) / (double)H;
-    const float mu32 = (float)mu, rstd32 = (float)(1.0 / sqrt(var + (double)eps));
+    for (int e = 0; e < CPL; e++) sq.add_square(e, (double)z[e] - mu);
+    const double var = over_width<H>(row64_sum(sq.total()));
+    const float mu32 = (float)mu, rstd32 = reciprocal_root<H>(var + (double)eps);
 #pragma unroll
     for (int e = 0; e < CPL; e++) y[e] = __builtin_fmaf((z[e] - mu32) * rstd32, gamma[e], beta[e]);
 }
@@ -88,14 +120,14 @@ __device__ __forceinline__ double ln_row_wave(const AddLnArgs &a, int row, int c
     load_lane_f32(a.bias + c, z);
     load_lane_f32(a.gamma + c, gamma);
     load_lane_f32(a.beta + c, beta);
-    double sum = 0.0;
+    RowSum<H> sum;
 #pragma unroll
     for (int e = 0; e < CPL; e++) {
         const float u = IN_I8 ? __builtin_fmaf(x[e], a.s_in, z[e]) : x[e] + z[e];
         z[e] = RES_I8 ? __builtin_fmaf(r[e], a.s_res, u) : u + r[e];
-        sum += (double)z[e];
+        sum.add(e, (double)z[e]);
     }
-    return sum;
+    return sum.total();
 }
 
 }  // namespace

@@ -338,13 +338,13 @@ __global__ __launch_bounds__(256) void embed_ln_wave_kernel(EmbedArgs a)
     load_lane<false>(a.pos, (size_t)pid * H + c, z);
     load_lane_f32(a.gamma + c, gamma);
     load_lane_f32(a.beta + c, beta);
-    double sum = 0.0;
+    RowSum<H> sum;
 #pragma unroll
     for (int e = 0; e < CPL; e++) {
         z[e] = (x[e] + g[e]) + z[e];
-        sum += (double)z[e];
+        sum.add(e, (double)z[e]);
     }
-    ln_finish_wave<CPL, OUT_I8>(z, sum, gamma, beta, a.eps, a.s_out, a.out, (size_t)t * H + c);
+    ln_finish_wave<CPL, OUT_I8>(z, sum.total(), gamma, beta, a.eps, a.s_out, a.out, (size_t)t * H + c);
 }
 
 template <int NJ>
