@@ -239,6 +239,27 @@ template <int N> __device__ __forceinline__ void store_codes(int8_t *dst, const 
     else *reinterpret_cast<int *>(dst) = pk[0];
 }
 
+// Which (sequence, head) pair and which strip of 32 queries a block works on.  Sequences of one length: XCD x takes the x-th eighth of the sequences, whose
+// tokens it also owns in the kernels before and after this one.  Ragged: a strip's work grows with the length of its sequence, and an XCD that owns
+// long sequences would still be at work when the others are done, so the pairs are dealt out, all strips of a pair to one XCD.  Forward, three encoders in
+// turn, us, eighths / dealt out: BERT-base Fully-Quant 6 x 500..1100 1432 / 1318, 33 x 40..301 1117 / 1064, 30 x 20..200 772 / 757, 3 x 300..2000 1927 / 1753,
+// binary16 softmax 33 x 40..301 1168 / 1103, Quant-FFN-Only 6 x 500..1100 1716 / 1577, FP16 20 x 30..400 1660 / 1570; of two strips 7 x 5..61 344 / 346.
+constexpr int DEALT_MIN_STRIPS = 4;
+struct Strip { int pair, strip; };
+__device__ __forceinline__ Strip strip_of(int block, int items, int nqb, unsigned by_nqb, bool ragged)
+{
+    int first = 0, index = block, scale = 1;
+    if (ragged) {
+        const int dealt = (int)over(items, by_nqb, nqb) & ~7;     // pairs; the last items / nqb % 8 keep their own index
+        if (block < dealt * nqb) first = block & 7, index = block >> 3, scale = 8;
+        else first = dealt, index = block - dealt * nqb;
+    } else {
+        index = xcd_contiguous(block, items);
+    }
+    const int pair = (int)over(index, by_nqb, nqb);
+    return {first + scale * pair, index - pair * nqb};
+}
+
 struct SeqInfo { int t0, n; };
 __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
 {
@@ -281,13 +302,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     __shared__ double ssum[NW][QB];
     __shared__ ExpTable exp_table;
 
-    // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
-    // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, items);
-    const int strip = (int)over(item, by_nqb, nqb), seq = (int)over(strip, by_heads, heads), head = strip - seq * heads;
+    const Strip at = strip_of(blockIdx.x, items, nqb, by_nqb, cu && nqb >= DEALT_MIN_STRIPS);
+    const int seq = (int)over(at.pair, by_heads, heads), head = at.pair - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
-    const int q0 = (item - strip * nqb) * QB;
+    const int q0 = at.strip * QB;
     if (q0 >= sq.n) return;
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
@@ -879,7 +898,8 @@ void qkv_attention_i8_packed_kernel(const char *__restrict__ X, const char *__re
     ExpTable &exp_table = *reinterpret_cast<ExpTable *>(lds + RING);
 
     const int heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, items);       // sequences outermost, as in the attention kernel
+    // sequences outermost, as in the attention kernel; ragged ones dealt out to the XCDs (64 x 16..128 Fully-Quant 900 / 886 us, half FP16 1178 / 1168)
+    const int item = cu ? (int)blockIdx.x : xcd_contiguous(blockIdx.x, items);
     const int seq = (int)over(item, by_heads, heads), head = item - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
@@ -971,7 +991,7 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     float *tab = reinterpret_cast<float *>(lds + (!LATE ? TAB_OFF : (H / 64) & 1 ? RING_BYTES - TAB_BYTES : 0));
 
     const int heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, items);
+    const int item = cu ? (int)blockIdx.x : xcd_contiguous(blockIdx.x, items);
     const int seq = (int)over(item, by_heads, heads), head = item - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
     const int n = sq.n;
@@ -1215,13 +1235,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 1
     __shared__ float smax[NW][QB];
     __shared__ float ssum[NW][QB];
 
-    // work item = (sequence, head, query block), sequences outermost: XCD x works on the x-th eighth of the
-    // sequences, whose tokens it also owns in the kernels before and after this one
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, items);
-    const int strip = (int)over(item, by_nqb, nqb), seq = (int)over(strip, by_heads, heads), head = strip - seq * heads;
+    const Strip at = strip_of(blockIdx.x, items, nqb, by_nqb, cu && nqb >= DEALT_MIN_STRIPS);
+    const int seq = (int)over(at.pair, by_heads, heads), head = at.pair - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
-    const int q0 = (item - strip * nqb) * QB;
+    const int q0 = at.strip * QB;
     if (q0 >= sq.n) return;
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
@@ -1628,10 +1646,10 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     __shared__ ExpTable exp_table;
 
     const int nqb = (max_len + QB - 1) / QB, heads = H >> 6;
-    const int item = xcd_contiguous(blockIdx.x, items);
-    const int strip = (int)over(item, by_nqb, nqb), seq = (int)over(strip, by_heads, heads), head = strip - seq * heads;
+    const Strip at = strip_of(blockIdx.x, items, nqb, by_nqb, cu && nqb >= DEALT_MIN_STRIPS);
+    const int seq = (int)over(at.pair, by_heads, heads), head = at.pair - seq * heads;
     const SeqInfo sq = seq_info(cu, seq, max_len);
-    const int q0 = (item - strip * nqb) * QB;
+    const int q0 = at.strip * QB;
     if (q0 >= sq.n) return;
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
@@ -1974,7 +1992,7 @@ template <bool PU>
 static void launch_attention_i8_8waves(const int8_t *qkv, const int *cu, int max_len, int H, float m_sc, float inv_sp, float m_ctx,
                                        int8_t *ctx, dim3 grid, hipStream_t st, const Timing *tm)
 {
-    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
+    const unsigned by_nqb = divisor(grid.x + 1u, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     auto go = [&](auto kern) {
         launch_kernel(kern, grid, dim3(512), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx,
                       (unsigned long long *)nullptr, NoFetch());
@@ -1994,7 +2012,7 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
                                         const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
-    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
+    const unsigned by_nqb = divisor(grid.x + 1u, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     if constexpr (!HIST) {
         auto go = [&](auto kern, int waves, unsigned more, auto what) {
             launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx,
@@ -2122,7 +2140,7 @@ hipError_t launch_attention_i8_p16(const int8_t *qkv, const int *cu, int B, int 
                                    float m_ctx, int8_t *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
-    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
+    const unsigned by_nqb = divisor(grid.x + 1u, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     auto go = [&](auto kern, int waves, unsigned more, auto what) {
         launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, m_ctx, ctx, what);
     };
@@ -2142,7 +2160,7 @@ hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max
                                 __half *ctx, float *p_absmax, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
-    const unsigned by_nqb = divisor(grid.x, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
+    const unsigned by_nqb = divisor(grid.x + 1u, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
     if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
         auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, *fetch); };
         if (max_len <= 128) with(attention_f16_kernel<1, true>); else with(attention_f16_kernel<2, true>);

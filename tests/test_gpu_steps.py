@@ -739,6 +739,24 @@ def test_fp16_qkv_gemm_and_attention_in_one_kernel(P, lens, heads, offsets):
                           host(P.attention_f16(P.gemm_f16(dev(x), dev(w), None, False), cu_dev, max(lens), heads)).view(np.uint16))
 
 
+@pytest.mark.parametrize("longest,B,heads", [(96, 5, 3), (97, 5, 3), (128, 8, 1), (200, 4, 2), (301, 7, 3), (512, 2, 5), (640, 3, 3), (1100, 4, 3)])
+def test_attention_of_ragged_batches_dealt_out_to_the_xcds(P, longest, B, heads):
+    """From four strips of queries on, the (sequence, head) pairs of a ragged batch are dealt out: with and without pairs left over after
+    whole rounds of eight, fewer than eight, and sequences that end in a block's first strip; INT8 bit-exact, FP16 within tolerance."""
+    rng = np.random.default_rng(longest + B * heads)
+    lens = rng.integers(1, longest + 1, B)
+    lens[B // 2] = longest
+    cu, H = _cu(lens), heads * 64
+    qkv = np.clip(np.rint(rng.standard_normal((int(cu[-1]), 3 * H)) * 26), -127, 127).astype(np.int8)
+    sc = (0.0209, 0.0249, 0.021, 0.0003, 0.0021)
+    assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), longest, heads, *sc)), oracle.attention_i8(qkv, cu, heads, *sc))
+    want = oracle.attention_i8_p16(qkv, cu, heads, sc[0], sc[1], sc[2], sc[4])
+    assert np.array_equal(host(P.attention_i8(dev(qkv), dev(cu), longest, heads, *sc, p_fp16=True)), want)
+    f = (rng.standard_normal((int(cu[-1]), 3 * H)) * 0.6).astype(np.float16)
+    want = oracle.attention_f16(f, cu, heads).astype(np.float64)
+    assert np.abs(host(P.attention_f16(dev(f), dev(cu), longest, heads)).astype(np.float64) - want).max() <= 2e-3
+
+
 @pytest.mark.parametrize("longest,B,heads", [(1, 800, 1), (31, 384, 2), (32, 383, 2), (32, 64, 12), (33, 384, 1), (64, 130, 3), (64, 127, 3), (65, 260, 1)])
 def test_attention_of_many_short_sequences(P, longest, B, heads):
     """From 768 blocks on, sequences of one or two key tiles take one or two waves: sizes on either side, ragged; INT8 in its three softmax
