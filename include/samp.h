@@ -31,8 +31,9 @@
  *   - Threads: an encoder handle is used by one thread at a time (a forward
  *     updates its graph cache and event pool); different handles, and the step
  *     entry points, may be used from different threads.  samp_last_error() is
- *     per thread.  An encoder owns a few HIP streams and events for its batch
- *     groups and graph capture; samp_encoder_destroy releases them.
+ *     per thread.  An encoder owns a stream for graph capture and a few events, and
+ *     shares the streams of its batch groups with the encoders used on the same caller's
+ *     stream; samp_encoder_destroy releases them, the shared ones with their last user.
  *   - Quantiser (Appendix B: multiply by a scale, round, symmetric 8-bit range):
  *     code = clamp(round_half_even(x * (1/s)), -127, 127), where the step s is
  *     absmax/127 from a min-max calibration (Table 2 caption) and 1/s is formed
@@ -60,7 +61,7 @@ typedef struct samp_encoder samp_encoder_t;
  * SAMP_P_FP16, valid only together with bit 0 and not with SAMP_P_UNSIGNED, is the other remedy:
  * the softmax output of that layer is rounded to binary16 instead of being put on an 8-bit grid
  * and multiplies the integer V codes, ctx = rne(fl32(sum P16 V) * s_v / s_ctx); the sum is
- * evaluated exactly (integer digit planes of P16 * 2^24 on the matrix cores); s_p is not used.   */
+ * evaluated exactly (two binary16 parts of P16, beyond 1536 keys integer digit planes of P16 * 2^24); s_p is not used.   */
 enum { SAMP_FP16 = 0, SAMP_MHA_INT8 = 1, SAMP_FFN_INT8 = 2, SAMP_FULL_INT8 = 3, SAMP_P_UNSIGNED = 4, SAMP_P_FP16 = 8 };
 
 enum {
@@ -174,7 +175,7 @@ SAMP_API int samp_encoder_forward_ids(samp_encoder_t *enc, const samp_embedding_
                                       void *workspace, size_t workspace_bytes, void *stream);
 
 /* Sequences are independent (all scales are static, Appendix B), so a forward may cut a batch
- * into up to 4 groups of sequences that run concurrently on streams owned by the encoder, forked
+ * into up to 4 groups of sequences that run concurrently on the library's side streams, forked
  * from and joined back into the caller's stream; results do not depend on the split.  groups = 0
  * (default) chooses by size (two groups from two million token rows x hidden on, if that times the layers is at least 3.2 million,
  * in Fully-Quant stacks 6.5 million), 1 disables the split, 2..4 force it.                       */
