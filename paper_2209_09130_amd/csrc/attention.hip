@@ -30,7 +30,6 @@ namespace {
 constexpr int QB = 32;                 // queries per block
 constexpr int ONE_PASS_MAX_LEN = 512;  // longest sequence that four waves take in the INT8 flavour
 constexpr int VT_STRIDE_I8 = 36;       // bytes per V^T row (32 keys + pad), int8
-constexpr int VT_STRIDE_F16 = 72;      // bytes per V^T row (32 keys + pad), fp16
 
 // exp(x) for x <= 0 in binary64: x = k ln2 + r with |r| <= ln2 / 2 (two-part ln2), then
 //     exp(r) = 1 + r (1 + r q(r)),
@@ -1186,51 +1185,58 @@ void qkv_attention_f16_kernel(const char *__restrict__ X, const char *__restrict
     }
 }
 
-// The V rows of key tile j0 as a lane transposes them: d[u][t] holds eight channels (8 (lane & 7) ..) of key
-// j0 + 2 ((lane >> 3) + 8 u) + t; and V^T of that tile into LDS, as dwords of two consecutive keys per channel.
-__device__ __forceinline__ void load_v_tile_f16(const __half *vp, unsigned ld, int j0, int n, int lane, v8h (&d)[2][2])
-{
-#pragma unroll
-    for (int u = 0; u < 2; u++)
-#pragma unroll
-        for (int t = 0; t < 2; t++)
-            d[u][t] = *reinterpret_cast<const v8h *>(vp + (unsigned)min(j0 + 2 * ((lane >> 3) + 8 * u) + t, n - 1) * ld + 8 * (lane & 7));
-}
-__device__ __forceinline__ void store_vt_tile_f16(const v8h (&d)[2][2], int lane, char *slab)
-{
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const v4i a = __builtin_bit_cast(v4i, d[u][0]), b = __builtin_bit_cast(v4i, d[u][1]);
-        char *dst = slab + 8 * (lane & 7) * VT_STRIDE_F16 + 4 * ((lane >> 3) + 8 * u);
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            *reinterpret_cast<unsigned *>(dst + (2 * e) * VT_STRIDE_F16) = __builtin_amdgcn_perm((unsigned)b[e], (unsigned)a[e], 0x05040100u);
-            *reinterpret_cast<unsigned *>(dst + (2 * e + 1) * VT_STRIDE_F16) = __builtin_amdgcn_perm((unsigned)b[e], (unsigned)a[e], 0x07060302u);
-        }
+// V rows of a key tile as they lie (32 keys x 64 binary16) in LDS, and V^T operands out of it: ds_read_b64_tr_b16 hands lane i of sixteen the
+// half i & 3 of the four halves that lanes (i >> 2) + 4 t, t = 0..3, point at, so that with lanes 4 t .. 4 t + 3 at 16 channels of key t a lane gets
+// one channel of four keys.  16-byte chunk c of key k lies at position c ^ 4 ((k >> 1) & 1): the 32 lanes of a read's phase hit 64 different banks.
+constexpr int V_TILE_F16 = 32 * 64 * 2;
+struct VLaneF16 {                                         // what a lane loads and reads of every tile, in bytes
+    unsigned from, at;                                    // offset of its 16 bytes in the first 8 rows (of 2 ld bytes); of its first read in a tile
+    __device__ __forceinline__ VLaneF16(unsigned ld, int lane)
+    {
+        from = (unsigned)(lane >> 3) * 2 * ld + (((lane & 7) ^ (((lane >> 4) & 1) << 2)) << 4);
+        const int key = 4 * (lane >> 5) + ((lane >> 2) & 3), chunk = 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+        at = key * 128 + ((chunk ^ (((key >> 1) & 1) << 2)) << 4) + 8 * (lane & 1);
     }
+};
+// channel 32 cb + (lane & 31), keys 16 hf + 4 (lane >> 5) + (0..3, 8..11)
+__device__ __forceinline__ v8h read_vt_f16(const char *tile, unsigned at, int hf, int cb)
+{
+    typedef __attribute__((address_space(3))) v4s *Lds;
+    const char *p = tile + (at ^ (cb << 6)) + hf * 2048;
+    const v4h lo = __builtin_bit_cast(v4h, __builtin_amdgcn_ds_read_tr16_b64_v4i16((Lds)p));
+    const v4h hi = __builtin_bit_cast(v4h, __builtin_amdgcn_ds_read_tr16_b64_v4i16((Lds)(p + 1024)));
+    return v8h{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+}
+__device__ __forceinline__ void request_v_tile_f16(__amdgpu_buffer_rsrc_t rows, unsigned from, unsigned ld, char *tile)
+{
+#pragma unroll
+    for (int u = 0; u < 4; u++) buffer_to_lds128(rows, from + u * 16 * ld, 0, tile + u * 1024);
 }
 
 // FP16 flavour: fp16 q, k, v; binary32 scores, fast exp; P rounded to fp16 before P.V; binary32
 // accumulation of P.V.  Optionally records the largest softmax output (calibration of the P step).
 // Up to 2048 keys (NT = 16 key tiles per wave) the strip of scores stays in registers; the order of all sums is that of the
-// three-sweep kernel, tile by tile, so both give the same bytes.  V rows
-// are transposed in registers two keys at a time (dword stores).  Twelve heads, three sequences of 1100 tokens: 76 -> 51 us, 17 of
-// 301 36.5 -> 30 us.
+// three-sweep kernel, tile by tile, so both give the same bytes.  Twelve heads, three sequences of 1100 tokens: 76 -> 51 us, 17 of
+// 301 36.5 -> 30 us.  V rows are loaded straight into LDS and transposed by the reads, rows past the end are cut off by the buffer
+// descriptor, and a full key tile's scores need no mask; tiles beyond the first two take a read tile's place by direct loads, so that four
+// tiles of scores leave registers for four waves per SIMD instead of two, which is what bounded them.  Twelve heads, us, before / now: 64 x 512 255 /
+// 200, 3 x 1100 51 / 42, 12 x 1250 191 / 170, 20 x 30..400 33.6 / 27.5; 16 x 256 of sixteen heads 27.2 / 26.9 (two tiles: as many waves as before).
 template <int NT, bool FETCH = false, int NW = 4>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 4 ? 4 : NT <= 10 ? 2 : 1))) void attention_f16_kernel(const __half *__restrict__ qkv, const int *__restrict__ cu,
                                                             int max_len, int H, int items, unsigned by_nqb, unsigned by_heads, float scale, __half *__restrict__ ctx,
                                                             float *__restrict__ p_absmax, typename FetchArg<FETCH>::type fetch)
 {
     if (fetch_instead(fetch, items)) return;
     // one slab per wave, as in the INT8 kernel: first its V^T tiles (two; a further one takes a tile's place when that one has
-    // been multiplied), then its partial context for the other waves.  TIGHT: ten tiles of scores leave two waves per SIMD just
-    // enough registers if V rows are requested one tile later (four tiles in the slab) and tiles past the end are skipped in
-    // the sums of exponentials; without either it took 48 bytes of scratch (12 heads, 12 sequences of 1250 tokens: 213 -> 194 us).
+    // been read), then its partial context for the other waves.  TIGHT: ten tiles of scores leave two waves per SIMD just
+    // enough registers if V rows are requested one tile earlier (four tiles in the slab) and tiles past the end are skipped in
+    // the sums of exponentials; without either it takes 20 bytes of scratch (12 heads, 12 sequences of 1250 tokens, when it was 48: 213 -> 194 us).
     // Fewer or more tiles do not need it, and 12 sequences of 1500 would lose 3 %.
     constexpr bool TIGHT = NT == 10;
-    constexpr int VT_TILE = 64 * VT_STRIDE_F16, SO_BYTES = QB * 64 * 4, VT_TILES = TIGHT ? 4 : NT < 2 ? NT : 2, AHEAD = TIGHT ? 2 : 1;
-    constexpr int SLAB = VT_TILES * VT_TILE > SO_BYTES ? VT_TILES * VT_TILE : SO_BYTES;
-    __shared__ __attribute__((aligned(16))) char slab[NW][SLAB];
+    constexpr int SO_BYTES = QB * 64 * 4, VT_TILES = TIGHT ? 4 : NT < 2 ? NT : 2, AHEAD = TIGHT ? 2 : 1;
+    constexpr int SLAB = VT_TILES * V_TILE_F16 > SO_BYTES ? VT_TILES * V_TILE_F16 : SO_BYTES;
+    constexpr int K_AHEAD = NT == 1 || NT == 3 || NT == 4 ? 1 : 2;   // key tiles whose rows are requested before the first product (as many as registers hold)
+    __shared__ __attribute__((aligned(1024))) char slab[NW][SLAB];
     auto so = [&](int wave) { return reinterpret_cast<float(*)[64]>(slab[wave]); };
     __shared__ float smax[NW][QB];
     __shared__ float ssum[NW][QB];
@@ -1244,43 +1250,64 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 1
     const int n = sq.n;
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;
-    const __half *base = qkv + (size_t)sq.t0 * ld + head * 64, *vp = base + 2 * H;
+    const __half *base = qkv + (size_t)sq.t0 * ld + head * 64;
+    // as in attention_i8_kernel
+    auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, 2 * max((n - j0) * (int)ld - head * 64, 0)); };
+    auto first_key = [&](int i) { return (w + NW * i) * 32; };
 
-    const int qrow = min(q0 + r, n - 1);
-    v8h qf[4];
+    const unsigned row_at = 2 * (unsigned)r * ld + g * 16, key_at = row_at + 2 * H;
+    const VLaneF16 vl(ld, lane);
+    v4i qf[4], kf[K_AHEAD][4];
+    auto request_keys = [&](int i) {
+        const auto rows = rows_from(first_key(i));
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++) qf[ks] = *reinterpret_cast<const v8h *>(base + (unsigned)qrow * ld + ks * 16 + g * 8);
+        for (int ks = 0; ks < 4; ks++) kf[i % K_AHEAD][ks] = __builtin_amdgcn_raw_buffer_load_b128(rows, key_at + ks * 32, 0, 0);
+    };
+    {
+        const auto rows = rows_from(q0);
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) qf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rows, row_at + ks * 32, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < K_AHEAD; i++) request_keys(i);
+#pragma unroll
+    for (int i = 0; i < VT_TILES; i++) request_v_tile_f16(rows_from(first_key(i)), vl.from + 4 * H, ld, &slab[w][i * V_TILE_F16]);
 
     float sc[NT][16];
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-        const int j0 = (w + NW * i) * 32;
+        const int j0 = first_key(i);
         if (j0 < n) {
-            const __half *kp = base + (unsigned)min(j0 + r, n - 1) * ld + H;
-            v8h kf[4], d[2][2];                                  // all loads are issued before the first is used
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) kf[ks] = *reinterpret_cast<const v8h *>(kp + ks * 16 + g * 8);
-            if (i < VT_TILES) load_v_tile_f16(vp, ld, j0, n, lane, d);
             v16f acc;
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[e] = 0.0f;
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[ks], qf[ks], acc, 0, 0, 0);
-            if (i < VT_TILES) store_vt_tile_f16(d, lane, &slab[w][i * VT_TILE]);
+            for (int ks = 0; ks < 4; ks++)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, kf[i % K_AHEAD][ks]), __builtin_bit_cast(v8h, qf[ks]), acc, 0, 0, 0);
+            if (j0 + 32 <= n) {                                  // a full tile needs no masking
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
-                sc[i][e] = key < n ? acc[e] * scale : -INFINITY;
-                mx = __builtin_fmaxf(mx, sc[i][e]);
+                for (int e = 0; e < 16; e++) {
+                    sc[i][e] = acc[e] * scale;
+                    mx = __builtin_fmaxf(mx, sc[i][e]);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const int key = j0 + 8 * (e >> 2) + 4 * g + (e & 3);
+                    sc[i][e] = key < n ? acc[e] * scale : -INFINITY;
+                    mx = __builtin_fmaxf(mx, sc[i][e]);
+                }
             }
         } else {
 #pragma unroll
             for (int e = 0; e < 16; e++) sc[i][e] = -INFINITY;
         }
+        if (i + K_AHEAD < NT) request_keys(i + K_AHEAD);
     }
     mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (g == 0) smax[w][r] = mx;
+    wait_vm<0>();                                                 // the wave's V tiles are in its slab
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NW; u++) mx = __builtin_fmaxf(mx, smax[u][r]);
@@ -1315,8 +1342,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 1
     for (int i = 0; i < NT; i++) {
         const int j1 = (w + NW * (i + AHEAD)) * 32;                 // the tile that takes the place of tile i - AHEAD
         const bool more = i >= AHEAD && i + AHEAD < NT && j1 < n;
-        v8h d[2][2];
-        if (more) load_v_tile_f16(vp, ld, j1, n, lane, d);
+        if (more) {
+            wait_lds();                                             // the reads of tile i - AHEAD have returned
+            request_v_tile_f16(rows_from(j1), vl.from + 4 * H, ld, &slab[w][(i + AHEAD) % VT_TILES * V_TILE_F16]);
+        }
         if ((w + NW * i) * 32 < n) {
 #pragma unroll
             for (int hf = 0; hf < 2; hf++) {                    // keys 8q+4g+t for q in {2hf, 2hf+1}
@@ -1325,15 +1354,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 1
                 for (int e = 0; e < 8; e++) pf[e] = to_half(sc[i][8 * hf + e] * rS);
 #pragma unroll
                 for (int cb = 0; cb < 2; cb++) {
-                    const char *rowp = &slab[w][i % VT_TILES * VT_TILE + (cb * 32 + r) * VT_STRIDE_F16];
-                    const v4h lo = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 4 * g) * 2);
-                    const v4h hi = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 8 + 4 * g) * 2);
-                    const v8h vf = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    const v8h vf = read_vt_f16(&slab[w][i % VT_TILES * V_TILE_F16], vl.at, hf, cb);
                     o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(pf, vf, o[cb], 0, 0, 0);
                 }
             }
         }
-        if (more) store_vt_tile_f16(d, lane, &slab[w][(i + AHEAD) % VT_TILES * VT_TILE]);
+        if (NT > VT_TILES) {                                        // tile i + 1 is there
+            if (AHEAD > 1 && more) wait_vm<4 * (AHEAD - 1)>();
+            else wait_vm<0>();
+        }
     }
 #pragma unroll
     for (int cb = 0; cb < 2; cb++)
@@ -1886,7 +1915,7 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
                                                                  int max_len, int H, float scale, __half *__restrict__ ctx,
                                                                  float *__restrict__ p_absmax)
 {
-    __shared__ __attribute__((aligned(16))) char vt[4][64 * VT_STRIDE_F16];
+    __shared__ __attribute__((aligned(1024))) char vt[4][V_TILE_F16];
     __shared__ __attribute__((aligned(16))) float so[4][QB][64];
     __shared__ float smax[4][QB];
     __shared__ float ssum[4][QB];
@@ -1938,13 +1967,16 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
     for (int cb = 0; cb < 2; cb++)
 #pragma unroll
         for (int e = 0; e < 16; e++) o[cb][e] = 0.0f;
-    const __half *vp = base + 2 * H;
+    const VLaneF16 vl(ld, lane);
     for (int j0 = w * 32; j0 < n; j0 += 128) {
+        const auto rows = buffer_of(base + (size_t)j0 * ld, 2 * max((n - j0) * (int)ld - head * 64, 0));
+        v4i d[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) d[u] = __builtin_amdgcn_raw_buffer_load_b128(rows, vl.from + 4 * H + u * 16 * ld, 0, 0);
         score_tile_f16(base, ld, H, j0, n, r, g, qf, scale, sc);
         __builtin_amdgcn_wave_barrier();
-        v8h d[2][2];
-        load_v_tile_f16(vp, ld, j0, n, lane, d);
-        store_vt_tile_f16(d, lane, vt[w]);
+#pragma unroll
+        for (int u = 0; u < 4; u++) *reinterpret_cast<v4i *>(&vt[w][u * 1024 + lane * 16]) = d[u];
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int hf = 0; hf < 2; hf++) {
@@ -1954,10 +1986,7 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
                 pf[e] = to_half(__builtin_amdgcn_exp2f((sc[8 * hf + e] - mx) * 1.44269504088896341f) * rS);
 #pragma unroll
             for (int cb = 0; cb < 2; cb++) {
-                const char *rowp = &vt[w][(cb * 32 + r) * VT_STRIDE_F16];
-                const v4h lo = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 4 * g) * 2);
-                const v4h hi = *reinterpret_cast<const v4h *>(rowp + (16 * hf + 8 + 4 * g) * 2);
-                const v8h vf = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                const v8h vf = read_vt_f16(vt[w], vl.at, hf, cb);
                 o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(pf, vf, o[cb], 0, 0, 0);
             }
         }

@@ -33,6 +33,8 @@ template <int N> __device__ __forceinline__ void wait_vm()
     static_assert(N >= 0 && N < 64, "vmcnt range");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// all LDS reads of the wave have returned: what they read may be overwritten by direct loads
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // Loads through a buffer descriptor: scalar base + 32-bit vector offset + scalar offset, so no address arithmetic in vector registers.  The
 // compiler counts such loads one by one when it waits for a register; after a direct load of the global_load_lds kind, which it takes for

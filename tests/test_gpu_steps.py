@@ -712,6 +712,19 @@ def test_fp16_attention_within_tolerance(P, lens, heads):
     assert np.abs(got - want).mean() <= 1e-4
 
 
+@pytest.mark.parametrize("n", [1, 31, 33, 127, 129, 160, 257, 288, 385, 511, 512, 513, 769, 1025, 1250, 1537, 2047, 2049])
+def test_fp16_attention_at_the_edges_of_its_key_tiles(P, n):
+    """Every number of key tiles per wave, ends inside and between tiles (tolerances as above); the rows of the sequence behind it,
+    NaN here, must not reach a sequence whose last tile overlaps them."""
+    rng = np.random.default_rng(n)
+    qkv = (rng.standard_normal((n + 40, 192)) * 0.6).astype(np.float16)
+    want = oracle.attention_f16(qkv[:n], _cu([n]), 1).astype(np.float64)
+    qkv[n:] = np.nan
+    got = host(P.attention_f16(dev(qkv), dev(_cu([n, 40])), max(n, 40), 1))[:n].astype(np.float64)
+    assert np.abs(got - want).max() <= 2e-3
+    assert np.abs(got - want).mean() <= 1e-4
+
+
 @pytest.mark.parametrize("lens,heads,offsets", [([128, 128, 128], 2, False), ([1, 5, 32, 33, 64, 17, 128, 97], 2, True),
                                                 ([128, 2, 65], 12, True), ([96] * 3, 4, False),
                                                 ([256, 256], 2, False), ([200, 129, 256, 7, 160], 2, True), ([192] * 3, 4, False)])
