@@ -1619,14 +1619,16 @@ __device__ __forceinline__ void p16_store(const long long (&so)[2][QB][32], floa
 // Up to 1536 keys the strip of scores stays in registers (one pass, as attention_i8_kernel), and the exact sum needs no digits: P16 splits into two
 // binary16 numbers, hi = (P16 + C) - C with C = 1.5 / 16 and lo = P16 - hi, both exact, whose products with the V codes (as binary16) the FP16 matrix
 // instruction adds up exactly in binary32, whatever its order:
-//     hi is a multiple of 2^-14 and sum |hi V| <= 127 (1.001 + 2^-15 keys) < 2^24 2^-14;
-//     lo is a multiple of 2^-24 with |lo| <= 2^-15 (P16 below 2^-5) or P16 / 2^9, so sum |lo V| <= 127 (2^-15 keys + 1.01 / 2^9) < 2^24 2^-24 as long as a
-//     wave has at most 192 keys.
-// In units of 2^-24 the whole sum is below 127 (1 + 2^-7) 2^24 < 2^31, so the waves' parts meet in an array of int32.
+//     hi is a multiple of 2^-14 and sum |hi V| <= 128 (1.001 + 2^-15 keys) < 2^24 2^-14;
+//     lo is a multiple of 2^-24 with |lo| <= 2^-15 + P16 / 2^10, so sum |lo V| <= 128 (2^-15 keys + 1.01 / 2^10) < 2^24 2^-24 as long as a wave has at most
+//     192 keys.
+// The waves' parts meet in int32 in units of 2^-24, modulo 2^32: hi sums in their own unit, shifted up, lo sums as they are.  With S = sum P16 <= 1.001
+// the whole sum lies in [-128 S, 127 S], which is wider than int32's [-128, 128) to the left and shorter to the right, so the parts are added to a half
+// (P16_HALF) that is taken off again in binary64.
 // What bounds the kernel is vector arithmetic: 19 operations of the softmax per score, then 3 for the parts and 2.5 for V as binary16, where the
 // digits took 9.3 and the recombination of the waves' sums twice the operations; it also fits four blocks to a CU instead of two.  Forward,
 // BERT-base 33 x 40..301, us, digits / parts: 1458 / 1265.
-constexpr int P16_WAVE_KEYS = 192;
+constexpr int P16_WAVE_KEYS = 192, P16_HALF = 1 << 23;
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
@@ -1669,7 +1671,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     static_assert(32 * NT <= P16_WAVE_KEYS, "the bound on the sum of the low parts");
     constexpr int K_AHEAD = NT <= 4 ? NT : 2;
     __shared__ __attribute__((aligned(1024))) int8_t slab[NW][NT * V_TILE];
-    __shared__ __attribute__((aligned(16))) int so[QB][64];
+    __shared__ __attribute__((aligned(16))) unsigned so[QB][64];
     __shared__ float smax[NW][QB];
     __shared__ double ssum[NW][QB];
     __shared__ ExpTable exp_table;
@@ -1706,7 +1708,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
 #pragma unroll
     for (int i = 0; i < NT; i++) request_v_tile(rows_from(first_key(i)), vl.from + 2 * H, ld, &slab[w][i * V_TILE]);
 #pragma unroll
-    for (int i = 0; i < QB * 64 / 4 / (64 * NW); i++) reinterpret_cast<v4i *>(&so[0][0])[i * 64 * NW + tid] = v4i{0, 0, 0, 0};      // used after two barriers
+    for (int i = 0; i < QB * 64 / 4 / (64 * NW); i++) reinterpret_cast<v4i *>(&so[0][0])[i * 64 * NW + tid] = v4i{P16_HALF, P16_HALF, P16_HALF, P16_HALF};      // used after two barriers
 
     float sc[NT][16];                                             // scores / 128, then exponentials
     const float m_unit = m_sc * SCORE_UNIT;
@@ -1785,7 +1787,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
                 }
 #pragma unroll
             for (int e = 0; e < 16; e++)
-                atomicAdd(&so[8 * (e >> 2) + 4 * g + (e & 3)][cb * 32 + r], (int)(o[0][e] * 16777216.0f) + (int)(o[1][e] * 16777216.0f));
+                atomicAdd(&so[8 * (e >> 2) + 4 * g + (e & 3)][cb * 32 + r], ((unsigned)(int)(o[0][e] * 0x1p14f) << 10) + (unsigned)(int)(o[1][e] * 0x1p24f));
         }
     }
     __syncthreads();
@@ -1799,7 +1801,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     for (int d = 0; d < CPT / 4; d++) {
         float codes[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) codes[e] = code_bits((float)so[query][c0 + 4 * d + e] * 0x1p-24f * m_ctx);
+        for (int e = 0; e < 4; e++) codes[e] = code_bits((float)((double)(int)so[query][c0 + 4 * d + e] - P16_HALF) * 0x1p-24f * m_ctx);
         pk[d] = pack_codes(codes[0], codes[1], codes[2], codes[3]);
     }
     int8_t *dst = ctx + (size_t)(sq.t0 + q0 + query) * H + head * 64 + c0;

@@ -648,15 +648,18 @@ def test_int8_attention_with_binary16_softmax_output_bit_exact(P, lens, heads):
     assert np.abs(want).max() > 20
 
 
-@pytest.mark.parametrize("n", [1, 31, 127, 128, 129, 343, 381, 511, 513, 1024, 1191, 1425, 1536])
-def test_binary16_softmax_output_at_the_bounds_of_its_exact_sum(P, n):
+@pytest.mark.parametrize("low", [-127, -128])
+@pytest.mark.parametrize("n", [1, 17, 31, 33, 127, 128, 129, 343, 381, 511, 513, 1024, 1191, 1425, 1536, 1537])
+def test_binary16_softmax_output_at_the_bounds_of_its_exact_sum(P, n, low):
     """The kernel splits P16 into a multiple of 2^-14 and a rest and adds the products with V up in binary32, which is exact as long as
     the sums stay below 2^24 units.  Largest sums: V codes of 127 throughout, with equal probabilities (1 / n; near an odd multiple of
-    2^-15 at 343, 381, 1191 and 1425, where the rests are largest) and with one key that has nearly all of it; both signs."""
+    2^-15 at 343, 381, 1191 and 1425, where the rests are largest) and with one key that has nearly all of it; both signs.  The step takes
+    any int8, so also -128, with which the whole sum passes -2^31 units of 2^-24 wherever the probabilities add up to more than 1 (17, 33, 343 and
+    1425 of them)."""
     heads = 2
     qkv = np.zeros((n, 3, heads, 64), np.int8)
-    qkv[:, 2, 0, :32], qkv[:, 2, 0, 32:] = 127, -127
-    qkv[:, 2, 1] = np.where(np.arange(n) % 2, -127, 127)[:, None]
+    qkv[:, 2, 0, :32], qkv[:, 2, 0, 32:] = 127, low
+    qkv[:, 2, 1] = np.where(np.arange(n) % 2, low, 127)[:, None]
     qkv[n // 2:, 0], qkv[n // 3, 1] = 60, 60
     qkv = qkv.reshape(n, -1)
     cu = _cu([n])
