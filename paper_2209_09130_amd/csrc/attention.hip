@@ -265,6 +265,10 @@ __device__ __forceinline__ SeqInfo seq_info(const int *cu, int b, int max_len)
     if (cu) { const int t0 = cu[b]; return {t0, cu[b + 1] - t0}; }
     return {b * max_len, max_len};
 }
+// The 32 rows from j0 on of a sequence of n, base: its first row at the head's Q columns.  A row past the end reads as zeros, so no load needs a test or an
+// address of its own.  (No more than 32 rows, so that their bytes fit 31 bits at any width.)
+template <class T> __device__ __forceinline__ __amdgpu_buffer_rsrc_t strip_rows(const T *base, unsigned ld, int head, int j0, int n)
+{ return buffer_of(base + (size_t)j0 * ld, (int)sizeof(T) * max(min(n - j0, 32) * (int)ld - head * 64, 0)); }
 
 // PU: the softmax codes are unsigned, rne(P / s_p) in [0, 255] (the variant that spends all 256 codes
 //     on [0, 1]).  The matrix core multiplies signed bytes, so it is fed code - 128 (a flip of the top
@@ -311,8 +315,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 5
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;                          // row offsets inside a sequence fit 32 bits
     const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64;
-    // rows from j0 to the end of the sequence; a row past it reads as zeros, so no load needs a test or an address of its own
-    auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, max((n - j0) * (int)ld - head * 64, 0)); };
+    auto rows_from = [&](int j0) { return strip_rows(base, ld, head, j0, n); };
     auto first_key = [&](int i) { return (w + NW * i) * 32; };
     constexpr int ENTRIES = NW < 4 ? 4 / NW : 1;                  // of the exponential's table, per thread
     uint64_t table_entry[ENTRIES];
@@ -1251,8 +1254,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT <= 4
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;
     const __half *base = qkv + (size_t)sq.t0 * ld + head * 64;
-    // as in attention_i8_kernel
-    auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, 2 * max((n - j0) * (int)ld - head * 64, 0)); };
+    auto rows_from = [&](int j0) { return strip_rows(base, ld, head, j0, n); };
     auto first_key = [&](int i) { return (w + NW * i) * 32; };
 
     const unsigned row_at = 2 * (unsigned)r * ld + g * 16, key_at = row_at + 2 * H;
@@ -1686,7 +1688,7 @@ attention_i8_p16_kernel(const int8_t *__restrict__ qkv, const int *__restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), r = lane & 31, g = lane >> 5;
     const unsigned ld = 3u * (unsigned)H;
     const int8_t *base = qkv + (size_t)sq.t0 * ld + head * 64;
-    auto rows_from = [&](int j0) { return buffer_of(base + (size_t)j0 * ld, max((n - j0) * (int)ld - head * 64, 0)); };     // as in attention_i8_kernel
+    auto rows_from = [&](int j0) { return strip_rows(base, ld, head, j0, n); };
     auto first_key = [&](int i) { return (w + NW * i) * 32; };
     const uint64_t table_entry = EXP2_TABLE[tid & 255];
 
@@ -1971,7 +1973,7 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
         for (int e = 0; e < 16; e++) o[cb][e] = 0.0f;
     const VLaneF16 vl(ld, lane);
     for (int j0 = w * 32; j0 < n; j0 += 128) {
-        const auto rows = buffer_of(base + (size_t)j0 * ld, 2 * max((n - j0) * (int)ld - head * 64, 0));
+        const auto rows = strip_rows(base, ld, head, j0, n);
         v4i d[4];
 #pragma unroll
         for (int u = 0; u < 4; u++) d[u] = __builtin_amdgcn_raw_buffer_load_b128(rows, vl.from + 4 * H + u * 16 * ld, 0, 0);

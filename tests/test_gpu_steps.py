@@ -430,6 +430,33 @@ def test_int8_attention_bit_exact(P, lens, heads):
     assert np.abs(want).max() > 20
 
 
+@pytest.mark.parametrize("kind,n", [("int8", 500), ("int8", 2048), ("p16", 1536), ("fp16", 2047), ("fp16", 2100)])
+def test_attention_of_a_sequence_with_2_to_the_31_values(P, kind, n):
+    """The steps bound the tokens of a sequence and not the heads: rows times row length pass 2^31 here.  The first, a middle and the last head
+    against the oracle; INT8 bit-exact, FP16 within tolerance."""
+    import torch
+    heads = 2 ** 31 // (3 * 64 * n) + 8
+    g = torch.Generator(device="cuda").manual_seed(n)
+    if kind == "fp16":
+        qkv = torch.empty((n, 3, heads, 64), dtype=torch.float16, device="cuda").normal_(0, 0.6, generator=g)
+    else:
+        qkv = torch.randint(-60, 61, (n, 3, heads, 64), dtype=torch.int8, generator=g, device="cuda")
+    cu, flat, sc = _cu([n]), qkv.view(n, -1), (0.0209, 0.0249, 0.021, 0.0003, 0.0021)
+    if kind == "fp16":
+        ctx = P.attention_f16(flat, dev(cu), n, heads)
+    else:
+        ctx = P.attention_i8(flat, dev(cu), n, heads, *sc, p_fp16=kind == "p16")
+    ctx = ctx.view(n, heads, 64)
+    for h in (0, heads // 2, heads - 1):
+        one, got = np.ascontiguousarray(host(qkv[:, :, h])).reshape(n, -1), host(ctx[:, h])
+        if kind == "fp16":
+            assert np.abs(got.astype(np.float64) - oracle.attention_f16(one, cu, 1).astype(np.float64)).max() <= 2e-3
+        elif kind == "p16":
+            assert np.array_equal(got, oracle.attention_i8_p16(one, cu, 1, sc[0], sc[1], sc[2], sc[4]))
+        else:
+            assert np.array_equal(got, oracle.attention_i8(one, cu, 1, *sc))
+
+
 @pytest.mark.parametrize("lens,heads,offsets", [([128, 128, 128], 2, False), ([1, 5, 32, 33, 64, 17, 128, 97], 3, True),
                                                 ([96] * 4, 1, False), ([128, 2, 65], 12, True), ([31], 16, True),
                                                 ([256, 256], 2, False), ([200, 129, 256, 7, 160], 3, True), ([192] * 3, 4, False)])
