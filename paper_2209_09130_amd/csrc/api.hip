@@ -2,14 +2,13 @@
 // per-layer kernel sequence of Section 3.2 (seven kernels per layer plus entry / exit handling).
 #include "../../include/samp.h"
 #include "samp_common.h"
+#include "side_streams.h"
 #include "gemm_rules.h"
 
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <memory>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -149,19 +148,15 @@ int noalloc_scratch(void **out)
 
 }  // namespace
 
-constexpr int MAX_GROUPS = 4;
-
-// The streams on which batch groups run beside a caller's stream.  Encoders that are used on the same stream share them: a forward that takes up a
-// stream which has been idle starts some 60 us late (three BERT-base encoders in turn, 32 x 128 Fully-Quant, streams of their own / shared: 740 /
-// 680 us), and the streams of one caller have one order anyway.  Different streams never share, so that none waits for another.  The last
-// encoder that holds them gives them back.
-struct SideStreams {
-    int device = -1;
-    hipStream_t caller = nullptr, side[MAX_GROUPS - 1] = {};
-    ~SideStreams()
+struct HipStreams {
+    typedef hipStream_t Stream;
+    typedef hipError_t Error;
+    static hipError_t create(hipStream_t *s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking); }
+    static void destroy(hipStream_t s) { (void)hipStreamDestroy(s); }
+    static bool capturing(hipStream_t s)
     {
-        for (hipStream_t s : side)
-            if (s) (void)hipStreamDestroy(s);
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
     }
 };
 
@@ -176,7 +171,7 @@ struct samp_encoder {
     // batch-group concurrency: sequences are independent, so a batch is cut into groups that run on side
     // streams at the same time (one chain's kernels leave the chip idle while they start up and drain)
     int groups_wanted = 0;                          // 0 = choose by size
-    std::vector<std::shared_ptr<SideStreams>> sides;   // of the streams it was used on last, the latest first
+    HeldSides<HipStreams> sides;
     hipEvent_t fork = nullptr, join[MAX_GROUPS - 1] = {};
     bool events_ready = false;
     // whole-forward HIP graphs, one per distinct argument set (the forward is launch-bound: a few
@@ -466,51 +461,21 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     return SAMP_OK;
 }
 
-constexpr size_t MAX_SIDES = 4;
-std::mutex g_sides_mutex;
-std::vector<std::weak_ptr<SideStreams>> g_sides;
-
-// The side streams that go with the caller's stream, `count` of them, created on first use.
-int side_streams(samp_encoder_t *enc, hipStream_t st, int count, std::shared_ptr<SideStreams> *out)
-{
-    int device = -1;
-    HIP_TRY(hipGetDevice(&device));
-    const std::lock_guard<std::mutex> lock(g_sides_mutex);
-    std::shared_ptr<SideStreams> found;
-    for (size_t i = 0; i < enc->sides.size() && !found; i++)
-        if (enc->sides[i]->caller == st && enc->sides[i]->device == device) {
-            found = enc->sides[i];
-            enc->sides.erase(enc->sides.begin() + (long)i);
-        }
-    if (!found) {
-        for (size_t i = 0; i < g_sides.size();) {
-            const std::shared_ptr<SideStreams> s = g_sides[i].lock();
-            // (one handle, a stream of its own for each thread: not shared)
-            if (s && s->caller == st && s->device == device && st != hipStreamPerThread) found = s;
-            if (s) i++;
-            else g_sides.erase(g_sides.begin() + i);
-        }
-        if (!found) {
-            found = std::make_shared<SideStreams>();
-            found->device = device;
-            found->caller = st;
-            g_sides.push_back(found);
-        }
-        if (enc->sides.size() >= MAX_SIDES) enc->sides.pop_back();
-    }
-    enc->sides.insert(enc->sides.begin(), found);
-    for (int i = 0; i < count; i++)
-        if (!found->side[i]) HIP_TRY(hipStreamCreateWithFlags(&found->side[i], hipStreamNonBlocking));
-    *out = found;
-    return SAMP_OK;
-}
+SidePool<HipStreams> g_side_pool;
 
 // Runs each(g, stream) for every group, group 0 on the caller's stream and the others beside it.
 template <class F>
-int fork_join(samp_encoder_t *enc, int groups, hipStream_t st, F each)
+int fork_join_groups(samp_encoder_t *enc, int groups, hipStream_t st, F each)
 {
-    std::shared_ptr<SideStreams> streams;
-    if (int rc = side_streams(enc, st, groups - 1, &streams)) return rc;
+    int device = -1;
+    HIP_TRY(hipGetDevice(&device));
+    std::shared_ptr<SideStreams<HipStreams>> sides;
+    try {
+        // (hipStreamPerThread: one handle, a stream of its own for each thread)
+        HIP_TRY(g_side_pool.take(enc->sides, device, st, st != hipStreamPerThread, groups - 1, &sides));
+    } catch (...) {
+        return fail(SAMP_ERR_ARG, "out of host memory");
+    }
     if (!enc->events_ready) {
         for (hipEvent_t &e : enc->join)
             if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -519,12 +484,12 @@ int fork_join(samp_encoder_t *enc, int groups, hipStream_t st, F each)
     }
     HIP_TRY(hipEventRecord(enc->fork, st));
     for (int g = 0; g < groups; g++) {
-        hipStream_t gs = g ? streams->side[g - 1] : st;
+        hipStream_t gs = g ? sides->side[g - 1] : st;
         if (g) HIP_TRY(hipStreamWaitEvent(gs, enc->fork, 0));
         if (int rc = each(g, gs)) return rc;
     }
     for (int g = 1; g < groups; g++) {
-        HIP_TRY(hipEventRecord(enc->join[g - 1], streams->side[g - 1]));
+        HIP_TRY(hipEventRecord(enc->join[g - 1], sides->side[g - 1]));
         HIP_TRY(hipStreamWaitEvent(st, enc->join[g - 1], 0));
     }
     return SAMP_OK;
@@ -551,7 +516,7 @@ int forward_eager(samp_encoder_t *enc, const void *hidden, const Ids *ids, const
     const int G = choose_groups(enc, B, S), filled = filled_groups(B, G);
     auto each = [&](int g, hipStream_t gs) { return run_group(enc, hidden, ids, mask, B, S, out, workspace, G, g, gs); };
     if (G == 1) return each(0, st);
-    if (enc->prof_which == SAMP_PROF_OFF) return fork_join(enc, filled, st, each);
+    if (enc->prof_which == SAMP_PROF_OFF) return fork_join_groups(enc, filled, st, each);
     // while a kernel is being timed the groups run one after another on the caller's stream, so that
     // each timed launch has the device to itself (same launch shapes, no overlap in the figures)
     for (int g = 0; g < filled; g++)
@@ -842,7 +807,7 @@ static int forward_common(samp_encoder_t *enc, const void *hidden, const Ids *id
     const int filled = filled_groups(B, G);
     auto replay = [&]() -> int {
         auto each = [&](int i, hipStream_t gs) -> int { HIP_TRY(hipGraphLaunch(g->exec[i], gs)); return SAMP_OK; };
-        return filled == 1 ? each(0, st) : fork_join(enc, filled, st, each);
+        return filled == 1 ? each(0, st) : fork_join_groups(enc, filled, st, each);
     };
     if (g && g->exec[0]) return replay();
     if (!g) {                                       // first sight of these arguments: run eagerly (one-off set-up happens here)
@@ -911,10 +876,6 @@ int samp_encoder_destroy(samp_encoder_t *enc)
     if (enc->fork) (void)hipEventDestroy(enc->fork);
     for (auto &g : enc->graphs) destroy_graph(g);
     if (enc->cap) (void)hipStreamDestroy(enc->cap);
-    {
-        const std::lock_guard<std::mutex> lock(g_sides_mutex);
-        enc->sides.clear();
-    }
     delete enc;
     return SAMP_OK;
 }

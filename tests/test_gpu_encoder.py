@@ -737,6 +737,39 @@ def test_encoders_that_share_the_streams_of_their_groups(P, groups):
         e.close()
 
 
+def test_two_encoders_on_more_streams_than_they_keep_side_streams_for(P):
+    """Side streams go over from one caller's stream to another when an encoder is used on more than four: six streams in turn, eager, captured
+    and replayed, two encoders on each, with nothing to wait for between them but an encoder's own workspace."""
+    import torch
+    w = small((FULL_INT8, FFN_INT8), batch=6, seq=64, varlen=True)
+    wts = W.make_weights(w)
+    hid, lens, mask = W.make_hidden(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    h, m = torch.from_numpy(hid).cuda(), torch.from_numpy(mask).cuda()
+    encs = [P.Encoder(*args(w), w.modes, wts, sc, max_batch=w.batch, max_seq=w.seq) for _ in range(3)]
+    encs[0].set_groups(1)
+    want = encs[0].forward(h, m).clone()
+    streams, last = [torch.cuda.Stream() for _ in range(6)], [None, None]
+    outs = [[torch.full_like(h, 3.0) for _ in streams] for _ in encs[1:]]
+    torch.cuda.synchronize()
+    for e in encs[1:]:
+        e.set_groups(2)
+        e._workspace(w.batch, w.seq)
+    torch.cuda.synchronize()
+    for turn in range(4):
+        for k, st in enumerate(streams):
+            for i, e in enumerate(encs[1:]):
+                if last[i] is not None:
+                    st.wait_stream(last[i])
+                last[i] = st
+                with torch.cuda.stream(st):
+                    e.forward(h, m, outs[i][k])
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, want) for o in outs[0] + outs[1])
+    for e in encs:
+        e.close()
+
+
 @pytest.mark.parametrize("varlen", [False, True])
 def test_forward_captured_into_a_graph_of_the_caller(P, varlen):
     """A caller that records the forward into a HIP graph of its own switches the library's graph cache off; the plain
