@@ -150,6 +150,7 @@ int noalloc_scratch(void **out)
 
 struct HipStreams {
     typedef hipStream_t Stream;
+    typedef hipEvent_t Event;
     typedef hipError_t Error;
     static hipError_t create(hipStream_t *s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking); }
     static void destroy(hipStream_t s) { (void)hipStreamDestroy(s); }
@@ -158,6 +159,9 @@ struct HipStreams {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
         return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
     }
+    static hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
+    static hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
+    static int rc(hipError_t e) { HIP_TRY(e); return SAMP_OK; }
 };
 
 struct samp_encoder {
@@ -482,17 +486,7 @@ int fork_join_groups(samp_encoder_t *enc, int groups, hipStream_t st, F each)
         if (!enc->fork) HIP_TRY(hipEventCreateWithFlags(&enc->fork, hipEventDisableTiming));
         enc->events_ready = true;
     }
-    HIP_TRY(hipEventRecord(enc->fork, st));
-    for (int g = 0; g < groups; g++) {
-        hipStream_t gs = g ? sides->side[g - 1] : st;
-        if (g) HIP_TRY(hipStreamWaitEvent(gs, enc->fork, 0));
-        if (int rc = each(g, gs)) return rc;
-    }
-    for (int g = 1; g < groups; g++) {
-        HIP_TRY(hipEventRecord(enc->join[g - 1], sides->side[g - 1]));
-        HIP_TRY(hipStreamWaitEvent(st, enc->join[g - 1], 0));
-    }
-    return SAMP_OK;
+    return fork_join<HipStreams>(groups, st, sides->side, enc->fork, enc->join, each);
 }
 
 // Group g of G: its slice of the input and of the output, and its own workspace piece.

@@ -1,5 +1,5 @@
-// The streams on which batch groups run beside a caller's stream: which ones a forward takes.  Written against a small set of
-// operations (Hip), so that the host can test the rules on their own.
+// The streams on which batch groups run beside a caller's stream: which ones a forward takes, and the fork to them and back.  Written against a
+// small set of operations (Hip), so that the host can test the rules on their own.
 #pragma once
 
 #include <cstddef>
@@ -89,5 +89,27 @@ public:
 
     size_t sets() const { return all_.size(); }
 };
+
+// Runs each(g, stream) for every group, group 0 on the caller's stream and the others beside it.  Whatever fails, every side stream that was forked is
+// joined again: the caller's stream then stands for all work that was started (and a caller's capture has no loose ends).  Returns the first error.
+template <class Hip, class Each>
+int fork_join(int groups, typename Hip::Stream st, const typename Hip::Stream *side, typename Hip::Event fork, const typename Hip::Event *join, Each each)
+{
+    int rc = Hip::rc(Hip::record(fork, st)), forked = 0;
+    for (int g = 0; g < groups && !rc; g++) {
+        if (g) {
+            rc = Hip::rc(Hip::wait(side[g - 1], fork));
+            if (rc) break;
+            forked = g;
+        }
+        rc = each(g, g ? side[g - 1] : st);
+    }
+    for (int g = 0; g < forked; g++) {
+        typename Hip::Error e = Hip::record(join[g], side[g]);
+        if (!e) e = Hip::wait(st, join[g]);
+        if (!rc) rc = Hip::rc(e);
+    }
+    return rc;
+}
 
 }  // namespace samp

@@ -1,4 +1,5 @@
-"""Which side streams the batch groups of a forward take (csrc/side_streams.h), compiled for the host on counters in place of streams."""
+"""Which side streams the batch groups of a forward take, and the fork to them and back (csrc/side_streams.h), compiled for the host on counters
+in place of streams."""
 import ctypes as C
 import os
 import shutil
@@ -9,15 +10,29 @@ import pytest
 CSRC = os.path.join(os.path.dirname(__file__), "..", "paper_2209_09130_amd", "csrc")
 SOURCE = r"""
 #include "side_streams.h"
+#include <cstring>
 #include <set>
+#include <string>
 static long created, destroyed;
 static std::set<long> captured;
+static std::string trace;
+static const char *failing = "";
 struct Fake {
     typedef long Stream;
+    typedef long Event;
     typedef int Error;
     static int create(long *s) { *s = ++created; return 0; }
     static void destroy(long) { destroyed++; }
     static bool capturing(long s) { return captured.count(s) != 0; }
+    static int step(std::string what)
+    {
+        const bool bad = what == failing;
+        trace += what + (bad ? "! " : " ");
+        return bad ? 7 : 0;
+    }
+    static int record(long e, long s) { return step("r" + std::to_string(e) + "@" + std::to_string(s)); }
+    static int wait(long s, long e) { return step("w" + std::to_string(e) + "@" + std::to_string(s)); }
+    static int rc(int e) { return e ? -e : 0; }
 };
 typedef samp::HeldSides<Fake> Held;
 static samp::SidePool<Fake> pool;
@@ -36,6 +51,14 @@ long held(Held *h) { return (long)h->size(); }
 long made() { return created; }
 long gone() { return destroyed; }
 void capture(long s, int on) { if (on) captured.insert(s); else captured.erase(s); }
+const char *fork(int groups, const char *fails, int bad_group, int *rc)
+{
+    const long side[3] = {101, 102, 103}, join[3] = {11, 12, 13};
+    trace.clear();
+    failing = fails;
+    *rc = samp::fork_join<Fake>(groups, 100L, side, 10L, join, [&](int g, long s) { trace += "g" + std::to_string(g) + "@" + std::to_string(s) + " "; return g == bad_group ? -5 : 0; });
+    return trace.c_str();
+}
 }
 """
 
@@ -57,6 +80,7 @@ def lib(built, tmp_path):
     lib.take.argtypes, lib.take.restype = [C.c_void_p, C.c_int, C.c_long, C.c_int, C.c_int], C.c_long
     lib.held.restype = lib.made.restype = lib.gone.restype = C.c_long
     lib.capture.argtypes = [C.c_long, C.c_int]
+    lib.fork.argtypes, lib.fork.restype = [C.c_int, C.c_char_p, C.c_int, C.POINTER(C.c_int)], C.c_char_p
     return lib
 
 
@@ -125,3 +149,23 @@ def test_the_set_unused_for_longest_goes_over_and_none_that_is_captured(lib):
     lib.close_encoder(a)
     lib.close_encoder(b)
 
+
+def test_every_forked_stream_is_joined_whatever_fails(lib):
+    rc = C.c_int()
+
+    def run(groups, fails="", bad=-1):
+        steps = lib.fork(groups, fails.encode(), bad, C.byref(rc)).decode().split()
+        return steps, rc.value
+
+    steps, code = run(4)
+    assert code == 0
+    assert steps == ("r10@100 g0@100 w10@101 g1@101 w10@102 g2@102 w10@103 g3@103 r11@101 w11@100 r12@102 w12@100 r13@103 w13@100").split()
+    assert run(1) == (["r10@100", "g0@100"], 0)
+    assert run(4, bad=0) == (["r10@100", "g0@100"], -5)
+    # a group fails: no further one is started, and those before it and its own stream are joined
+    assert run(4, bad=2) == ("r10@100 g0@100 w10@101 g1@101 w10@102 g2@102 r11@101 w11@100 r12@102 w12@100".split(), -5)
+    # so with a stream that cannot be forked, and with one that cannot be joined; the first error is the one returned
+    assert run(3, "w10@102") == ("r10@100 g0@100 w10@101 g1@101 w10@102! r11@101 w11@100".split(), -7)
+    assert run(3, "r11@101") == ("r10@100 g0@100 w10@101 g1@101 w10@102 g2@102 r11@101! r12@102 w12@100".split(), -7)
+    assert run(3, "w11@100", bad=2)[1] == -5
+    assert run(2, "r10@100") == (["r10@100!"], -7)
