@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -148,16 +149,30 @@ int noalloc_scratch(void **out)
 
 }  // namespace
 
+// the hardware queue that this dispatch came through, for SideStreams
+__global__ void queue_of_kernel(uint64_t *answer, uint64_t tag)
+{
+    const uint64_t queue = (uint64_t)(uintptr_t)__builtin_amdgcn_queue_ptr();
+    if (threadIdx.x == 0) __hip_atomic_store(answer, tag << 48 | (queue & ~(~0ull << 48)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct HipStreams {
     typedef hipStream_t Stream;
     typedef hipEvent_t Event;
     typedef hipError_t Error;
     static hipError_t create(hipStream_t *s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking); }
     static void destroy(hipStream_t s) { (void)hipStreamDestroy(s); }
+    static void ask(hipStream_t s, uint64_t *answer, unsigned tag)
+    {
+        hipLaunchKernelGGL(queue_of_kernel, dim3(1), dim3(64), 0, s, answer, (uint64_t)tag);
+        (void)hipGetLastError();
+    }
     static bool capturing(hipStream_t s)
     {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+        (void)hipGetLastError();                    // the null stream, beside a capture
+        return true;
     }
     static hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
     static hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
@@ -465,7 +480,29 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     return SAMP_OK;
 }
 
-SidePool<HipStreams> g_side_pool;
+AnswerPage g_answers;
+SidePool<HipStreams> g_side_pool(g_answers);
+
+// The page for the answers of queue_of_kernel: pinned, for the whole process.  Allocated with an encoder, since a forward may be part of a capture; without
+// it the streams of groups are taken as they come.
+void provide_answers()
+{
+    static std::mutex mutex;
+    const std::lock_guard<std::mutex> lock(mutex);
+    if (g_answers.at.load()) return;
+    void *p = nullptr;
+    const size_t bytes = sizeof(uint64_t) * AnswerPage::BLOCKS * AnswerPage::ANSWERS;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;      // (another thread may be capturing)
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocPortable);
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    std::memset(p, 0, bytes);
+    g_answers.at.store(static_cast<uint64_t *>(p));
+}
 
 // Runs each(g, stream) for every group, group 0 on the caller's stream and the others beside it.
 template <class F>
@@ -473,10 +510,10 @@ int fork_join_groups(samp_encoder_t *enc, int groups, hipStream_t st, F each)
 {
     int device = -1;
     HIP_TRY(hipGetDevice(&device));
-    std::shared_ptr<SideStreams<HipStreams>> sides;
+    hipStream_t sides[MAX_GROUPS - 1] = {};
     try {
         // (hipStreamPerThread: one handle, a stream of its own for each thread)
-        HIP_TRY(g_side_pool.take(enc->sides, device, st, st != hipStreamPerThread, groups - 1, &sides));
+        HIP_TRY(g_side_pool.take(enc->sides, device, st, st != hipStreamPerThread, groups - 1, sides));
     } catch (...) {
         return fail(SAMP_ERR_ARG, "out of host memory");
     }
@@ -486,7 +523,7 @@ int fork_join_groups(samp_encoder_t *enc, int groups, hipStream_t st, F each)
         if (!enc->fork) HIP_TRY(hipEventCreateWithFlags(&enc->fork, hipEventDisableTiming));
         enc->events_ready = true;
     }
-    return fork_join<HipStreams>(groups, st, sides->side, enc->fork, enc->join, each);
+    return fork_join<HipStreams>(groups, st, sides, enc->fork, enc->join, each);
 }
 
 // Group g of G: its slice of the input and of the output, and its own workspace piece.
@@ -568,6 +605,7 @@ int samp_encoder_create(const samp_config_t *cfg, const uint8_t *modes, const sa
     for (int l = 0; l < cfg->layers; l++) need -= layer_packed_bytes(*cfg, modes[l]);
     if (arena_bytes < need) return fail(SAMP_ERR_SPACE, "arena has %zu bytes, %zu needed", arena_bytes, need);
     const bool pack = arena_bytes >= whole;
+    provide_answers();
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     samp_encoder *E = new (std::nothrow) samp_encoder();
