@@ -340,7 +340,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     // single layer's weights are in the caches anyway (1 x 128 33.5 / 33.7).
     const bool fetches = prefetch && (long)Tmax * H <= 3200000;
     const bool attention_fetches = fetches && !beside && Lc > 1 && S <= ATTENTION_FETCH_MAX_LEN;
-    const bool fetch_ahead = fetches && !attention_fetches && Tmax >= FETCH_AHEAD_MIN_ROWS;
+    const bool norm_fetches = fetches && Tmax >= FETCH_AHEAD_MIN_ROWS;
     // A GEMM that forms the LayerNorm rows it multiplies waits for them longer than for its weights, as long as the rows are few: BERT-base 1 x 8, 19,
     // 32, 40, 48, 56, 64 tokens, none / all but those / all: 269 / 266 / 293, 274 / 268 / 286, 295 / 284 / 311, 288 / 287 / 305, 304 / 300 / 301, 307 / 301 / 295, 327 /
     // 319 / 316; BERT-large 1 x 19 621 / 608 / 626, 32 645 / 613 / 623, 48 723 / 714 / 695
@@ -381,7 +381,12 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
         const Layer &X = enc->L[last ? l : l + 1];      // the layer that comes next
         FetchAhead next_weights = {};
         const FetchAhead *fetch = nullptr;
-        if (attention_fetches) {
+        auto can_ask = [&](const Layer &Z) {
+            const bool i8 = Z.mode & 1;
+            return !one_qkv_kernel(Z) || qkv_attention_packed(i8, Z.p_qkv, S, H);
+        };
+        const Asks asks = who_asks(attention_fetches, norm_fetches, can_ask(Y), can_ask(X));
+        if (asks.attention) {
             const bool few = Tmax < FETCH_LN_GEMM_MIN_ROWS;
             next_weights.part[0] = ahead(Y.w_o, Y.p_o, H, H, mha8);
             if (!(few && mha8 && ffn8)) next_weights.part[1] = ahead(Y.w_f1, Y.p_f1, F, H, ffn8);
@@ -448,7 +453,7 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
                         w.h1, ffn8, Y.s.ffn_in, nullptr, am ? am + 7 : nullptr, rows, H};
             if (int rc = ln_and_gemm(a, EPI_GELU_QUANT, Y.p_f1, w.f1, Y.m_f1, Y.b_f1, &Y.gelu, F, &ffn1_done)) return rc;
             const Prefetch next[2] = {ahead(Y.w_f1, Y.p_f1, F, H, ffn8), ahead(Y.w_f2, Y.p_f2, H, F, ffn8)};
-            if (!ffn1_done) HIP_TRY(launch_add_ln(a, fetch_ahead ? next : nullptr, st, timing(enc, SAMP_PROF_LN1)));
+            if (!ffn1_done) HIP_TRY(launch_add_ln(a, asks.norm1 ? next : nullptr, st, timing(enc, SAMP_PROF_LN1)));
         }
         if (ffn8) {
             if (!ffn1_done)
@@ -468,11 +473,12 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
             void *dst = last ? (calib ? ybuf[yi] : out) : ybuf[yi];
             AddLnArgs a{w.f2, ffn8, Y.s.ffn_out, Y.b_f2, w.h1, ffn8, Y.s.ffn_in, Y.g2, Y.be2, c.ln_eps,
                         dst, next8, next8 ? enc->L[l + 1].s.x : 1.0f, (last && !calib) ? row_map : nullptr, nullptr, rows, H};
-            const Prefetch next[2] = {ahead(X.w_qkv, X.p_qkv, 3 * H, H, X.mode & 1), ahead(X.w_o, X.p_o, H, H, X.mode & 1)};
+            const Prefetch next[2] = {asks.norm2_qkv ? ahead(X.w_qkv, X.p_qkv, 3 * H, H, X.mode & 1) : Prefetch{},
+                                      asks.norm2_out ? ahead(X.w_o, X.p_o, H, H, X.mode & 1) : Prefetch{}};
             qkv_done = false;
             if (next8 && !one_qkv_kernel(X))
                 if (int rc = ln_and_gemm(a, EPI_REQUANT, X.p_qkv, w.qkv, X.m_qkv, X.bq_qkv, nullptr, 3 * H, &qkv_done)) return rc;
-            if (!qkv_done) HIP_TRY(launch_add_ln(a, fetch_ahead && !last ? next : nullptr, st, timing(enc, SAMP_PROF_LN2)));
+            if (!qkv_done) HIP_TRY(launch_add_ln(a, (asks.norm2_qkv || asks.norm2_out) && !last ? next : nullptr, st, timing(enc, SAMP_PROF_LN2)));
             x = dst;
             yi ^= 1;
         }

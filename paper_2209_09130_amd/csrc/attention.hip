@@ -19,6 +19,7 @@
 #include "mfma_tile.h"
 #include "exp2_table.h"
 #include "divisor.h"
+#include "gemm_rules.h"
 
 #include <algorithm>
 #include <atomic>
@@ -2131,7 +2132,7 @@ hipError_t launch_qkv_attention_i8_packed(const int8_t *x, const int8_t *w_packe
                                           int max_len, int H, float m_sc, float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx,
                                           hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
-    if (max_len > 128 || H % 256 || B <= 0) return hipErrorNotSupported;
+    if (!qkv_attention_packed(true, w_packed, max_len, H) || B <= 0) return hipErrorNotSupported;
     auto go = [&](auto kern, unsigned more, auto what) {
         launch_kernel(kern, dim3((unsigned)(B * (H / 64)) + more), dim3(256), stream_ring_bytes<false, 8, 2>() + sizeof(ExpTable), st, tm, (const char *)x,
                       (const char *)w_packed, m, b, cu, max_len, H, B * (H / 64), divisor((unsigned)B * (H / 64), H / 64), m_sc, inv_sp, m_ctx, ctx, what);
@@ -2147,7 +2148,7 @@ hipError_t launch_qkv_attention_f16(const __half *x, const __half *w_qkv, const 
                                     int max_len, int H, float scale, __half *ctx, hipStream_t st, const Timing *tm, const FetchAhead *fetch)
 {
     if (max_len > 256 || H % 64 || B <= 0) return hipErrorInvalidValue;
-    const bool packed = w_packed && max_len <= 128 && H % 128 == 0;
+    const bool packed = qkv_attention_packed(false, w_packed, max_len, H);
     if (!packed && !w_qkv) return hipErrorNotSupported;
     const dim3 grid((unsigned)(B * (H / 64)));
     auto go = [&](auto kern, size_t lds, std::atomic<bool> &attr_set, unsigned more, auto what) {

@@ -1,5 +1,5 @@
 // Which of the two copies of a matrix a GEMM of few token rows reads: the rows as they lie (the kernels for few rows) or the packed order (the
-// kernels that stream weights into registers).  Host arithmetic on sizes and nothing else, so that the rules can be read and tested on their own.
+// kernels that stream weights into registers).  And which kernels ask for the weights that come next.  Host arithmetic on sizes and nothing else, so that the rules can be read and tested on their own.
 #pragma once
 
 namespace samp {
@@ -7,6 +7,21 @@ namespace samp {
 // From this many padded token rows on the LayerNorm steps ask for the weights that come next where the attention kernels do not (api.hip), so that a
 // GEMM finds them in the memory-side cache.  (Below, only attention kernels ask; the figures here are of GEMMs that wait for memory.)
 constexpr int FETCH_AHEAD_MIN_ROWS = 256;
+
+// The kernels of QKV GEMM and attention in one on packed weights, which exist with blocks that ask; those on rows as they lie exist without.
+inline bool qkv_attention_packed(bool i8, bool has_packed, int max_len, int H) { return has_packed && max_len <= 128 && H % (i8 ? 256 : 128) == 0; }
+
+// Of a layer: its attention asks for attention output, FFN1, FFN2 and the next layer's QKV; or its LayerNorm steps ask, the first for FFN1 and FFN2, the
+// second for the next layer's QKV and attention output, each for what no attention kernel does.  attention_may, norm_may: whether they do so at all in
+// this forward; here_can, next_can: whether the attention kernels of this layer and the next exist with blocks that ask.  Forward, us, three encoders in
+// turn, nobody asks / the LayerNorm steps do, where the attention cannot: 12 Fully-Quant layers of width 896, 10 x 128 tokens 819 / 754, 17 x 100 with
+// FP16 FFN 1037 / 939; with the weights in the memory-side cache anyway, width 640 13 x 128 607 / 610, width 384 24 x 64 392 / 395, 32 x 128 502 / 508.
+struct Asks { bool attention, norm1, norm2_qkv, norm2_out; };
+inline Asks who_asks(bool attention_may, bool norm_may, bool here_can, bool next_can)
+{
+    const bool here = attention_may && here_can, next = attention_may && next_can;
+    return {here, norm_may && !here, norm_may && !here, norm_may && !next};
+}
 
 // FP16: the rows as they lie while the 32 x 32 tiles of gemm_nt_small_f16_kernel are all on the chip at once.  The packed kernel's narrowest tile is
 // 128 channels wide: 32 rows of 1024 x 4096 are 8 blocks of it, 32 of the small one, and what bounds such a GEMM is how many CUs ask for its weights.

@@ -219,7 +219,8 @@ hipError_t launch_gemm_f16_packed(const __half *A, const __half *Wp, const float
                                   int tile, hipStream_t st, const Timing *tm);
 
 // cu == nullptr: every sequence has exactly max_len rows (row b*max_len is its first).
-// fetch (may be null; up to ATTENTION_FETCH_MAX_LEN tokens, longer ones leave it out): weights that extra blocks ask for
+// fetch (may be null; up to ATTENTION_FETCH_MAX_LEN tokens, and of the kernels with the QKV GEMM those on packed weights, the others leave it out):
+// weights that extra blocks ask for
 // p_unsigned: softmax codes 0..255 instead of -127..127; p_hist (optional): 256 counters of the codes used
 hipError_t launch_attention_i8(const int8_t *qkv, const int *cu, int B, int max_len, int H, int heads, float m_sc,
                                float inv_sp, float m_ctx, bool p_unsigned, int8_t *ctx, unsigned long long *p_hist,

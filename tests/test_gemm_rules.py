@@ -15,7 +15,10 @@ def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text('#include "gemm_rules.h"\n'
                                  'extern "C" int f16(long rows, int N, int K, long cus) { return samp::f16_reads_rows(rows, N, K, cus); }\n'
-                                 'extern "C" int i8(long rows, int N, int K) { return samp::i8_reads_rows(rows, N, K); }\n')
+                                 'extern "C" int i8(long rows, int N, int K) { return samp::i8_reads_rows(rows, N, K); }\n'
+                                 'extern "C" int one_packed(int i8, int packed, int S, int H) { return samp::qkv_attention_packed(i8, packed, S, H); }\n'
+                                 'extern "C" int asks(int am, int nm, int h, int n) { samp::Asks a = samp::who_asks(am, nm, h, n);\n'
+                                 '    return a.attention + 2 * a.norm1 + 4 * a.norm2_qkv + 8 * a.norm2_out; }\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "rules.so"), str(d / "rules.cpp")], check=True)
     lib = C.CDLL(str(d / "rules.so"))
     lib.f16.argtypes = [C.c_long, C.c_int, C.c_int, C.c_long]
@@ -88,3 +91,32 @@ def test_few_int8_rows_of_both_copies_give_the_same_codes(M, N, K):
     want = oracle.epilogue_requant(oracle.gemm_i8_i32(A, W), m, b)
     assert np.array_equal(P.gemm_i8_requant(*t).cpu().numpy(), want)
     assert np.array_equal(P.gemm_i8_requant_packed(t[0], P.pack_weight_i8(t[1]), t[2], t[3]).cpu().numpy(), want)
+
+
+def test_each_matrix_is_asked_for_by_one_kernel(rules):
+    """A stack whose layers differ in whether their attention kernels can ask: where LayerNorm steps may ask, every matrix from the first layer's
+    attention output on is asked for exactly once, and by the attention wherever that can."""
+    for n in range(1, 6):
+        for can in range(2 ** n):
+            for attention_may in (0, 1):
+                for norm_may in (0, 1):
+                    count = {}
+                    for l in range(n):
+                        here, there = can >> l & 1, can >> min(l + 1, n - 1) & 1
+                        a = rules.asks(attention_may, norm_may, here, there)
+                        assert (a & 1) == (attention_may and here)
+                        asked = [(l, "o"), (l, "f1"), (l, "f2"), (l + 1, "qkv")] if a & 1 else []
+                        asked += [(l, "f1"), (l, "f2")] if a & 2 else []
+                        asked += [(l + 1, "qkv")] if a & 4 else []
+                        asked += [(l + 1, "o")] if a & 8 else []
+                        for m in asked:
+                            count[m] = count.get(m, 0) + 1
+                    assert set(count.values()) <= {1}
+                    if norm_may:
+                        assert all((l, m) in count for l in range(n) for m in ("f1", "f2"))
+                        assert all((l, m) in count for l in range(1, n) for m in ("qkv", "o"))
+    for H in range(128, 2049, 128):
+        for S in (49, 128, 129, 256):
+            assert rules.one_packed(1, 1, S, H) == (S <= 128 and H % 256 == 0)
+            assert rules.one_packed(0, 1, S, H) == (S <= 128)
+            assert not rules.one_packed(0, 0, S, H) and not rules.one_packed(1, 0, S, H)
