@@ -2018,7 +2018,16 @@ __global__ __launch_bounds__(256) void attention_f16_long_kernel(const __half *_
 // 878 / 738, 256 x 16 782 / 720, 128 x 32 734 / 715, 24 x 48 413 / 413, BERT-large 128 x 32 2075 / 2002; FP16 512 x 8 1351 / 1299, 256 x 16 1264 / 1262, 128 x 32
 // 1258 / 1231, Quant-FFN-Only 256 x 16 968 / 921; with fewer blocks Fully-Quant 16 x 24 345 / 345, 1 x 19 241 / 242, BERT-large 64 x 32 1256 / 1275.  (The binary16
 // softmax output keeps four waves: 256 x 16 774 / 786.)
-static bool few_waves(unsigned blocks) { return blocks >= 768; }
+// Blocks that ask for weights beside them change nothing about it, us, three encoders in turn, four waves / as many as tiles: BERT-base Fully-Quant 64 x 16
+// 400 / 395, 128 x 16 545 / 511, 80 x 32 560 / 537, 40 x 48 535 / 517, FP16 128 x 16 834 / 788, Quant-FFN-Only 128 x 16 676 / 634, BERT-large 100 x 16
+// 1327 / 1255.
+static int waves_of(unsigned blocks, int max_len) { return blocks < 768 || max_len > 64 ? 4 : max_len <= 32 ? 1 : 2; }
+// blocks that ask with as many threads as blocks of four waves would
+static FetchAhead fetch_with(FetchAhead fetch, int waves)
+{
+    fetch.blocks *= 4 / waves;
+    return fetch;
+}
 
 // 513 to 2048 tokens: eight waves, a wave's NT key tiles as few as the longest sequence allows (registers and LDS, and with
 // them the blocks per CU, follow NT)
@@ -2052,10 +2061,16 @@ static void launch_attention_i8_variant(const int8_t *qkv, const int *cu, int B,
             launch_kernel(kern, dim3(grid.x + more), dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx,
                           p_hist, what);
         };
-        if (fetch && max_len <= 128) return go(attention_i8_kernel<1, PU, HIST, 4, true>, 4, fetch->blocks, *fetch);
-        if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) return go(attention_i8_kernel<2, PU, HIST, 4, true>, 4, fetch->blocks, *fetch);
-        if (few_waves(grid.x) && max_len <= 32) return go(attention_i8_kernel<1, PU, HIST, 1>, 1, 0, NoFetch());
-        if (few_waves(grid.x) && max_len <= 64) return go(attention_i8_kernel<1, PU, HIST, 2>, 2, 0, NoFetch());
+        const int waves = waves_of(grid.x, max_len);
+        if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
+            const FetchAhead f = fetch_with(*fetch, waves);
+            if (waves == 1) return go(attention_i8_kernel<1, PU, HIST, 1, true>, 1, f.blocks, f);
+            if (waves == 2) return go(attention_i8_kernel<1, PU, HIST, 2, true>, 2, f.blocks, f);
+            if (max_len <= 128) return go(attention_i8_kernel<1, PU, HIST, 4, true>, 4, f.blocks, f);
+            return go(attention_i8_kernel<2, PU, HIST, 4, true>, 4, f.blocks, f);
+        }
+        if (waves == 1) return go(attention_i8_kernel<1, PU, HIST, 1>, 1, 0, NoFetch());
+        if (waves == 2) return go(attention_i8_kernel<1, PU, HIST, 2>, 2, 0, NoFetch());
     }
     if (max_len <= 128)
         launch_kernel(attention_i8_kernel<1, PU, HIST>, grid, dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, m_sc, inv_sp, m_ctx, ctx, p_hist, NoFetch());
@@ -2195,16 +2210,23 @@ hipError_t launch_attention_f16(const __half *qkv, const int *cu, int B, int max
 {
     dim3 grid((unsigned)((max_len + QB - 1) / QB) * heads * B);
     const unsigned by_nqb = divisor(grid.x + 1u, (max_len + QB - 1) / QB), by_heads = divisor(grid.x, H / 64);
-    if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
-        auto with = [&](auto kern) { launch_kernel(kern, dim3(grid.x + fetch->blocks), dim3(256), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, *fetch); };
-        if (max_len <= 128) with(attention_f16_kernel<1, true>); else with(attention_f16_kernel<2, true>);
-        return hipGetLastError();
-    }
+    const int few = waves_of(grid.x, max_len);
     auto go = [&](auto kern, int waves = 4) {
         launch_kernel(kern, grid, dim3(64 * waves), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, NoFetch());
     };
-    if (few_waves(grid.x) && max_len <= 64) {
-        if (max_len <= 32) go(attention_f16_kernel<1, false, 1>, 1); else go(attention_f16_kernel<1, false, 2>, 2);
+    if (fetch && max_len <= ATTENTION_FETCH_MAX_LEN) {
+        const FetchAhead f = fetch_with(*fetch, few);
+        auto with = [&](auto kern) {
+            launch_kernel(kern, dim3(grid.x + f.blocks), dim3(64 * few), 0, st, tm, qkv, cu, max_len, H, (int)grid.x, by_nqb, by_heads, scale, ctx, p_absmax, f);
+        };
+        if (few == 1) with(attention_f16_kernel<1, true, 1>);
+        else if (few == 2) with(attention_f16_kernel<1, true, 2>);
+        else if (max_len <= 128) with(attention_f16_kernel<1, true>);
+        else with(attention_f16_kernel<2, true>);
+        return hipGetLastError();
+    }
+    if (few < 4) {
+        if (few == 1) go(attention_f16_kernel<1, false, 1>, 1); else go(attention_f16_kernel<1, false, 2>, 2);
         return hipGetLastError();
     }
     switch ((max_len + 127) / 128) {                              // key tiles per wave

@@ -825,6 +825,20 @@ def test_error_paths_on_the_device_side(P):
     enc.close()
 
 
+@pytest.mark.parametrize("mode", [FULL_INT8, FULL_INT8 | P_UNSIGNED, FULL_INT8 | P_FP16, FP16])
+@pytest.mark.parametrize("B,S", [(384, 8), (390, 32), (384, 33), (200, 48), (383, 32)])
+def test_many_short_sequences_in_one_group(P, mode, B, S):
+    """From 768 blocks on the attention kernels have one or two waves, and beside them blocks of as many that ask for weights: sizes on either side,
+    ragged, against the oracle."""
+    w = W.Workload("short", 2, 128, 2, 256, B, S, (mode,) * 2, varlen=True, min_len=1, plain_params=False, calib_batch=4, calib_seq=S)
+    wts = W.make_weights(w)
+    hid, lens, mask = W.make_hidden(w)
+    sc = oracle.calibrate(*args(w), wts, W.make_calibration_batch(w))
+    want = oracle.Encoder(*args(w), w.modes, wts, sc).forward(hid, lens)
+    d = compare(run_gpu(P, w, wts, sc, hid, mask), want, lens, True, f"{B} x {S} {mode}")
+    assert mode == FP16 or (d == 0).all()
+
+
 @pytest.mark.parametrize("hidden,ffn,B,S,varlen", [(768, 3072, 1, 1, False), (768, 3072, 1, 6, False), (768, 768, 1, 7, False), (768, 3072, 3, 9, True),
                                                    (768, 3072, 1, 64, False), (768, 3072, 5, 13, True), (1024, 4096, 1, 8, False), (1024, 1024, 3, 17, True)])
 def test_layernorm_and_gemm_in_one_launch_gives_the_same_bytes(P, hidden, ffn, B, S, varlen):
