@@ -928,41 +928,6 @@ hipError_t launch_stream(const void *A, const void *Wp, void *out, const Epi &ep
     return hipGetLastError();
 }
 
-// The tile is the one whose estimated time is least.  The estimate, in us, is a fit to the times of these tiles at 16 to 16384 rows of eight
-// N x K from 768 x 768 to 4096 x 1024 (each alone on the chip, in chains over other weights at every launch, as in a forward; the choice
-// costs 1 % on average over the best of all tiles and depths): per 128-byte stage of K the products and the operand bytes of the blocks
-// that the busiest CU gets, and their epilogues.  Beside another batch group all CUs count as well: larger tiles for half of them lose (forward, us, all /
-// half: BERT-base 32 x 128 Fully-Quant 756 / 795, FP16 1144 / 1345, 6 x 500..1100 1695 / 1829, 33 x 40..301 1436 / 1418).  Smallest first.
-struct StreamShape { int mt, ntw; };
-constexpr StreamShape STREAM_TILES[] = {{2, 1}, {4, 1}, {4, 2}, {4, 3}, {4, 4}, {8, 2}, {8, 3}};
-constexpr int STREAM_TILE_COUNT = sizeof(STREAM_TILES) / sizeof(STREAM_TILES[0]);
-// How often the chip is filled by the tiles: of all padded rows, or for a ragged batch, whose rows only the device knows, on average over 55 to 100 % of
-// them.  Forward, us, three encoders in turn, padded rows / average: BERT-base Fully-Quant 7 x 5..61 335 / 326, 12 x 80..128 513 / 485, 20 x 4..40 387 / 382, 40 x
-// 80..110 693 / 694, 8 x 200..256 563 / 571.  Beside another batch group the larger tiles that padded rows ask for are the better ones (64 x 16..128 846 /
-// 908, 33 x 40..301 1078 / 1109), and the FP16 tiles come out the same.
-double chip_rounds(Rows rows, int bm, int tiles_n)
-{
-    double sum = 0.0;
-    int count = 0;
-    for (int percent = rows.dev_rows && !rows.beside ? 55 : 100; percent <= 100; percent += 15, count++) {
-        const long tiles = (long)tiles_n * (((long)rows.host_rows * percent / 100 + bm - 1) / bm);
-        sum += (double)((tiles + 255) / 256);
-    }
-    return sum / count;
-}
-int stream_tile(Rows rows, int N, int K)
-{
-    int best = -1;
-    double best_cost = 0.0;
-    for (int i = 0; i < STREAM_TILE_COUNT; i++) {
-        const int bm = 16 * STREAM_TILES[i].mt, bn = 64 * STREAM_TILES[i].ntw;
-        if (N % bn) continue;
-        const double area = bm * bn / 8192.0, sides = (bm + bn) / 256.0;
-        const double cost = chip_rounds(rows, bm, N / bn) * (K / 128 * (0.016 * area + 0.30 * sides) + 0.81 * area);
-        if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
-    }
-    return best;
-}
 // Stages in flight: a small tile's stage is short next to the latency of its loads (the weights of a layer come from beyond L2), so it asks
 // for more of them (us, 2 stages / as chosen here: 32 x 64 tiles, 768 x 768 at 427 rows 4.1 / 3.5, 1024 x 4096 at 427 rows 9.1 / 6.4; 64 x 64,
 // 768 x 3072 at 1024 rows 8.5 / 7.2; 64 x 128, 768 x 3072 at 2048 rows 10.2 / 9.0; 64 x 192, 768 x 3072 at 4096 rows 12.2 / 11.7; the
@@ -971,7 +936,7 @@ template <class Epi>
 hipError_t launch_packed(const void *A, const void *Wp, void *out, const Epi &epi, Rows rows, int N, int K, int tile, hipStream_t st, const Timing *tm)
 {
     if (K % 256 || N % 64) return hipErrorNotSupported;
-    switch (tile < 0 ? stream_tile(rows, N, K) : tile) {
+    switch (tile < 0 ? stream_tile(rows.host_rows, rows.dev_rows && !rows.beside, N, K) : tile) {
     case 0:
         if (K % 512 == 0) return launch_stream<I8, Epi, 2, 1, 4>(A, Wp, out, epi, rows, N, K, st, tm);
         if (K % 768 == 0) return launch_stream<I8, Epi, 2, 1, 6>(A, Wp, out, epi, rows, N, K, st, tm);

@@ -1,5 +1,6 @@
 // Which of the two copies of a matrix a GEMM of few token rows reads: the rows as they lie (the kernels for few rows) or the packed order (the
-// kernels that stream weights into registers).  And which kernels ask for the weights that come next.  Host arithmetic on sizes and nothing else, so that the rules can be read and tested on their own.
+// kernels that stream weights into registers).  And which kernels ask for the weights that come next,
+// and the tiles of the INT8 GEMMs on packed weights.  Host arithmetic on sizes and nothing else, so that the rules can be read and tested on their own.
 #pragma once
 
 namespace samp {
@@ -58,6 +59,44 @@ inline int i8_small_waves(int K) { return K % 1024 == 0 ? 8 : K % 768 == 0 ? 6 :
 inline bool i8_reads_rows(long rows, int N, int K)
 {
     return i8_small_waves(K) && rows * N <= (N <= 1024 ? 300000 : N > 2048 ? 128000 : K > N ? 330000 : 262144);
+}
+
+// INT8 GEMMs on packed weights (gemm_nt_stream_kernel): the tile is the one whose estimated time is least.  The estimate, in us, is a fit to the times of these tiles at 16 to 16384 rows of eight
+// N x K from 768 x 768 to 4096 x 1024 (each alone on the chip, in chains over other weights at every launch, as in a forward; the choice
+// costs 1 % on average over the best of all tiles and depths): per 128-byte stage of K the products and the operand bytes of the blocks
+// that the busiest CU gets, and their epilogues.  Beside another batch group all CUs count as well: larger tiles for half of them lose (forward, us, all /
+// half: BERT-base 32 x 128 Fully-Quant 756 / 795, FP16 1144 / 1345, 6 x 500..1100 1695 / 1829, 33 x 40..301 1436 / 1418).  Smallest first.
+struct StreamShape { int mt, ntw; };
+constexpr StreamShape STREAM_TILES[] = {{2, 1}, {4, 1}, {4, 2}, {4, 3}, {4, 4}, {8, 2}, {8, 3}};
+constexpr int STREAM_TILE_COUNT = sizeof(STREAM_TILES) / sizeof(STREAM_TILES[0]);
+// with as many rows as the host counts, or `percent` of them
+inline double stream_cost(StreamShape tile, long rows, int percent, int N, int K)
+{
+    const int bm = 16 * tile.mt, bn = 64 * tile.ntw;
+    const double area = bm * bn / 8192.0, sides = (bm + bn) / 256.0;
+    const long tiles = (long)(N / bn) * ((rows * percent / 100 + bm - 1) / bm);
+    return (double)((tiles + 255) / 256) * (K / 128 * (0.016 * area + 0.30 * sides) + 0.81 * area);
+}
+// fewer: a batch with a mask, of whose rows only the device knows how many there are.  Lengths spread evenly up to the longest make 50 to 100 % of them, and a
+// mask may also leave out nothing, so the full batch counts as much as 55, 70 and 85 % together: a tile that suits fewer rows is taken where it saves them
+// more than it costs a full batch.  Forward, us, three encoders in turn, at 100, 90, 75 and 55 % of the rows, tiles for all rows / for the plain average of 55
+// to 100 % / these: BERT-base Fully-Quant 12 x 128 517, 517, 513, 501 / 518, 513, 476, 464 / 520, 519, 479, 469; 7 x 61 358, 356, 348, 342 / 358, 357, 333, 325 /
+// 352, 351, 329, 323; 40 x 48 529, 522, 516, 505 / 558, 534, 523, 462 / 529, 523, 515, 495; 9 x 200 558, 550, 539, 519 / 588, 558, 530, 477 / 560, 550,
+// 538, 512; 24 x 100 612, 593, 564, 536 / 634, 615, 555, 537 / 612, 593, 564, 536; 8 x 256 575, 564, 552, 541 / 581, 573, 539, 528 / 574, 564, 552, 539;
+// BERT-large 7 x 200 1380, 1349, 1317, 1213 / 1438, 1367, 1322, 1072 / 1369, 1339, 1308, 1190; 6 x 256 1433, 1380, 1354, 1227 / 1384, 1371, 1339,
+// 1205 / 1435, 1383, 1356, 1228.  Beside another batch group the larger tiles that padded rows ask for are the better ones (64 x 16..128 846 / 908, 33 x
+// 40..301 1078 / 1109), and the FP16 tiles come out the same.
+inline int stream_tile(long rows, bool fewer, int N, int K)
+{
+    int best = -1;
+    double best_cost = 0.0;
+    for (int i = 0; i < STREAM_TILE_COUNT; i++) {
+        if (N % (64 * STREAM_TILES[i].ntw)) continue;
+        double cost = (fewer ? 3 : 1) * stream_cost(STREAM_TILES[i], rows, 100, N, K);
+        for (int percent = 55; fewer && percent < 100; percent += 15) cost += stream_cost(STREAM_TILES[i], rows, percent, N, K);
+        if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+    }
+    return best;
 }
 
 }  // namespace samp
