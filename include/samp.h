@@ -17,7 +17,8 @@
  *   - All `dev` pointers are device memory of the current HIP device, owned by
  *     the caller, 16-byte aligned unless a stricter alignment is stated.  `host`
  *     pointers are ordinary host memory.  The library never allocates or frees
- *     device memory; it owns only the host-side encoder handle.
+ *     device memory; it owns the host-side encoder handles and, from the first
+ *     samp_encoder_create on, one page of pinned host memory.
  *   - fp16 = IEEE binary16 stored as uint16_t; matrices are row-major; weight
  *     matrices are [out, in] (K contiguous).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).

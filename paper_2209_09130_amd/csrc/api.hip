@@ -220,21 +220,14 @@ int choose_groups(const samp_encoder *e, int B, int S)
     int g = e->groups_wanted;
     // Two groups from two million values (token rows x hidden) on, if the layers are many enough: forking to another stream and joining again costs a
     // forward some 40 us, which every layer pays back in part by hiding one group's launches and tails behind the other's kernels, a layer with FP16
-    // blocks more of it.  Below, one chain is faster.  Forwards on sequences of 128 tokens, us, one group / two groups, by number of layers and
-    // sequences: width 768 Fully-Quant 1 layer 22 sequences 65 / 108, 47 96 / 110, 61 105 / 118, 102 159 / 163, 132 207 / 196; 2 layers 41 151 /
-    // 161, 81 250 / 242; 4 layers 22 230 / 238, 35 284 / 267; 6 layers 22 343 / 333; 12 layers 18 544 / 616, 22 673 / 639, 31 714 / 686; Quant-FFN-Only
-    // 1 layer 22 67 / 95, 47 106 / 111, 81 147 / 147, 132 231 / 219; 2 layers 41 168 / 179, 61 228 / 226; 4 layers 22 255 / 252; 12 layers 18 588 / 667, 22
-    // 755 / 718; FP16 1 layer 22 92 / 100, 35 105 / 114, 47 143 / 140, 61 158 / 166, 102 254 / 248; 2 layers 102 504 / 477; 4 layers 22 357 / 336; 12
-    // layers 18 781 / 943, 22 1066 / 973.  Width 1024 Fully-Quant 1 layer 46 131 / 134, 99 244 / 234; 3 layers 17 220 / 209, 24 231 / 235; 24 layers 14
-    // 1333 / 1318, 17 1729 / 1557; FP16 3 layers 17 336 / 314; 24 layers 14 1946 / 2308, 17 2749 / 2483.  Width 512, 4 layers Fully-Quant 34 231 /
-    // 215; width 256 4 layers 67 196 / 207, 98 213 / 211.  Where three such encoders and their buffers take turns, so that less is in the caches, two
-    // groups pay earlier: 1 layer of width 768, FP16 35 x 128 108 / 115, 9 x 490 154 / 150, 4 x 1024 154 / 154, 44 x 128 158 / 144, 61 x 128 182 / 179, Fully-Quant
-    // 60 x 128 106 / 119, 65 x 128 - / 123, 90 x 128 159 / 164.  Ragged batches (16 to 100 % of the tokens, which only the device knows) break even
-    // where the others do.  (Before the GEMMs read packed weights three or four groups never beat two.)
-    // (All of that with each encoder's groups on streams of its own.  With the streams shared, three encoders in turn, one group / two: width 768
-    // Fully-Quant 1 layer 102 sequences 162 / 167, 132 210 / 201; 2 layers 61 205 / 210, 90 286 / 275; 4 layers 22 230 / 233, 35 290 / 267; 12 layers 20 577 /
-    // 592, 24 701 / 661; Quant-FFN-Only 1 layer 61 120 / 126, 102 186 / 188; 2 layers 41 171 / 176, 61 243 / 228; 4 layers 22 253 / 254; FP16 1 layer 61 173 /
-    // 170 and 152 / 164 for one encoder, 102 265 / 261; 2 layers 24 184 / 185; 4 layers 22 368 / 357: the same bounds.)
+    // blocks more of it.  Below, one chain is faster.  Forwards of three encoders in turn on sequences of 128 tokens, us, one group / two groups, by number of
+    // layers and sequences: width 768 Fully-Quant 1 layer 61 106 / 124, 102 163 / 169, 132 213 / 204; 2 layers 61 200 / 211, 90 288 / 273; 4 layers 22
+    // 219 / 218, 35 276 / 263; 12 layers 16 519 / 513, 20 547 / 544, 24 651 / 621, 32 755 / 679; Quant-FFN-Only 1 layer 61 124 / 131, 102 189 / 192; 2 layers 41
+    // 177 / 178, 61 244 / 242; 4 layers 22 245 / 245; 12 layers 16 570 / 631, 22 741 / 706; FP16 1 layer 61 174 / 174, 102 272 / 266; 2 layers 24 178 /
+    // 180, 41 254 / 239; 4 layers 22 353 / 339; 12 layers 16 753 / 891, 22 1046 / 963.  Width 1024 Fully-Quant 3 layers 17 212 / 204, 24 223 / 230; 24 layers 14
+    // 1277 / 1217, 17 1637 / 1464; FP16 24 layers 14 1898 / 2153, 17 2631 / 2413.  Width 512, 4 layers Fully-Quant 34 219 / 205; width 256, 8 layers 67
+    // 349 / 325, 98 385 / 358.  One encoder alone, whose weights stay in the caches, breaks even later (1 layer of width 768, Fully-Quant 22 sequences
+    // 65 / 108, 47 96 / 110).  Ragged batches (16 to 100 % of the tokens, which only the device knows) break even where the others do.
     const long values = (long)B * S * e->cfg.hidden;
     if (g <= 0) g = values >= 2000000 && values * e->cfg.layers >= (e->all_int8 ? 6500000 : 3200000) ? 2 : 1;
     if (g > MAX_GROUPS) g = MAX_GROUPS;
@@ -351,12 +344,12 @@ int run(samp_encoder_t *enc, const void *hidden, const Ids *ids, const int32_t *
     };
     // Attention blocks whose QKV GEMM and attention run as one kernel.  Its block is one (sequence, head) and a tile of 128 tokens: from 49 to 128
     // tokens, and about 128 such blocks per launch.  Shorter sequences leave most of the tile empty, and every sequence reads all of the
-    // weights; longer ones do better with the QKV GEMM on packed weights and the attention kernel.  Forward, us, one kernel / two, by sequences x
-    // tokens: BERT-base Fully-Quant 256 x 16 1191 / 877, 128 x 32 924 / 827, 24 x 40 471 / 451, 64 x 64 813 / 831, 32 x 128 788 / 845; FP16
-    // 256 x 16 2060 / 1314, 24 x 40 686 / 671, 64 x 64 1269 / 1320, 32 x 128 1202 / 1319, 64 x 144 3060 / 2521, 32 x 40..200 1683 / 1548, 16 x 256
-    // 1347 / 1347; BERT-large Fully-Quant 128 x 32 2683 / 2266, 64 x 64 2290 / 2281, 16 x 64 1069 / 1109, 32 x 128 2114 / 2305, FP16 64 x 64 3776 /
-    // 3659, 32 x 128 3300 / 3638, Quant-FFN-Only 8 x 160 2010 / 1650, 32 x 256 4880 / 4841 (BERT-base there 1589 / 1623).  By blocks, 128 tokens,
-    // before the weights were packed: batch 4 +12 %, 8 +-0, 16 -1.6 %, 32 -4.9 %, 256 -6.8 %.
+    // weights; longer ones do better with the QKV GEMM on packed weights and the attention kernel.  Forward, us, three encoders in turn, one kernel / two, by
+    // sequences x tokens: BERT-base Fully-Quant 256 x 16 1047 / 696, 128 x 32 811 / 694, 24 x 40 439 / 410, 30 x 50 512 / 495, 64 x 64 691 / 698, 32 x 128
+    // 679 / 719, 10 x 128 (120 blocks) 444 / 432, 16 x 200 973 / 687; FP16 128 x 32 1405 / 1187, 24 x 40 636 / 608, 64 x 64 1151 / 1228, 32 x 128 1100 / 1217, 10 x
+    // 128 628 / 643, 8 x 128 604 / 609, 64 x 144 2886 / 2364, 16 x 256 1266 / 1236; BERT-large Fully-Quant 16 x 64 993 / 953, 64 x 64 2016 / 1923, 32 x 128
+    // 1864 / 2010, FP16 32 x 128 3142 / 3637, Quant-FFN-Only 32 x 256 4649 / 4568.  (Around 50 to 64 tokens two kernels have become the better choice
+    // for INT8 blocks, by up to 5 %, since their attention has no idle waves; the bound is from before.)
     auto one_qkv_kernel = [&](const Layer &Y) {
         if (Y.mode & SAMP_P_FP16) return false;
         return enc->fusion_wanted == 2 ? S <= 256 : enc->fusion_wanted == 0 && S > 48 && S <= 128 && B * heads >= 128;

@@ -1,6 +1,7 @@
 // Which of the two copies of a matrix a GEMM of few token rows reads: the rows as they lie (the kernels for few rows) or the packed order (the
 // kernels that stream weights into registers).  And which kernels ask for the weights that come next,
-// and the tiles of the INT8 GEMMs on packed weights.  Host arithmetic on sizes and nothing else, so that the rules can be read and tested on their own.
+// and the tiles of the INT8 GEMMs on packed weights.  Host arithmetic on sizes and nothing else, so that the rules can be read and tested on their
+// own.
 #pragma once
 
 namespace samp {

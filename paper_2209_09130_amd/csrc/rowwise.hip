@@ -222,18 +222,15 @@ template <int NJ, class Args>
 hipError_t launch_add_ln_nj(const Args &a, hipStream_t st, const Timing *tm)
 {
     // one wave per row at widths of 256, 512, 768 and 1024 (calibration, which also wants the absmax of the output, keeps the other
-    // form), as long as a launch lasts no longer than a row's chain: forward of 6 layers, one batch group, us, four rows / one row per
-    // wave, width 768 at 2048 rows Fully-Quant 331 / 314 and FP16 509 / 491, at 2560 rows 378 / 354 and 578 / 555, width 512 at 3840
-    // rows 322 / 313 and 406 / 384; width 256 at 4096 rows 247 / 245 and 267 / 263, at 7680 rows 255 / 262 and 302 / 302.  Beside
-    // another batch group a launch takes vector time away from that group's GEMMs, of which four rows per wave need a third less
-    // (BERT-large 32 x 256: 4484 against 4809 us), and the forward crosses at about one and a half million values (same units,
-    // Fully-Quant / MHA-only / Quant-FFN-Only / FP16): width 768, 1664 and 1536 rows 420 / 573 / 465 / 609 against 407 / 567 / 458 / 609, 2048 and 1920 rows
-    // 438 / 635 / 491 / 667 against 442 / 623 / 508 / 671; width 1024, 2 x 1152 rows 531 / 721 / 594 / 773 against 507 / 694 / 591 / 751,
-    // 2 x 1792 rows 587 / 869 / 666 / 948 against 616 / 852 / 705 / 930; at 2 x 1536 rows it is one wave per row for sequences of 256 and 512
-    // tokens (Fully-Quant / Quant-FFN-Only / FP16 620 / 742 / 977 against 597 / 724 / 951 and 663 / 804 / 1035 against 641 / 796 / 1032) and 16
-    // lanes for 128 (559 / 631 / 892 against 550 / 646 / 889).  Ragged batches have fewer rows than are counted here (two groups of 1920
-    // padded rows, 1080 tokens each, Fully-Quant / FP16 404 / 572 against 393 / 559, 2560: 432 / 637 against 418 / 627, 3328: 504 / 757 against
-    // 505 / 751; width 1024, 1536 padded rows, Fully-Quant / Quant-FFN-Only 509 / 576 against 473 / 553, 2048: 550 / 626 against 539 / 609).
+    // form), as long as a launch lasts no longer than a row's chain.  Beside another batch group a launch takes vector time away from that group's GEMMs, of
+    // which four rows per wave need a third less.  Forward of 6 layers on sequences of 128 tokens, three encoders in turn, us, four rows / one row per wave:
+    // one batch group, width 768 at 2048, 2560, 3968, 4608 rows Fully-Quant 275 / 255, 290 / 267, 369 / 347, 430 / 413, FP16 400 / 378, 426 / 404, 589 / 574,
+    // 707 / 688, width 512 at 3840 rows 247 / 235, width 256 at 5120 rows 202 / 200; two groups, width 768, of 1536, 1792, 1920, 2048, 2304, 2560 rows each,
+    // Fully-Quant 331 / 314, 344 / 329, 347 / 335, 350 / 336, 388 / 370, 414 / 383, Quant-FFN-Only 371 / 364, 387 / 383, 391 / 392, 396 / 397, 445 / 428, 472 / 453,
+    // FP16 500 / 491, 522 / 524, 541 / 544, 555 / 556, 589 / 604, 640 / 629; width 1024, of 1152, 1536, 1792 rows, Fully-Quant 423 / 407, 453 / 438, 477 / 460,
+    // Quant-FFN-Only 486 / 487, 537 / 548, 562 / 558, FP16 644 / 637, 700 / 706, 751 / 814; ragged, 55 % of two groups of 2560 and 3328 padded rows of 768,
+    // Fully-Quant 345 / 324, 405 / 386, FP16 511 / 504, 664 / 642.  (The bounds are from before the short statistics of ln_wave.h, which made one row per
+    // wave the faster form for some way beyond them in Fully-Quant stacks.)
     // width 768 has an instance of that form without tests against H (at 1024 the requests of a whole row in flight take so many
     // registers that the forward gets slower)
     constexpr bool WHOLE_WIDTHS = NJ == 3, WAVE = NJ <= 4;

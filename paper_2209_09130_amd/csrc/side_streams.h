@@ -121,7 +121,7 @@ template <class Hip> struct SideStreams {
 template <class Hip> using HeldSides = std::vector<std::shared_ptr<SideStreams<Hip>>>;
 
 // Encoders that are used on the same stream share a set: a forward that takes up a stream which has been idle starts some 60 us late (three BERT-base
-// encoders in turn, 32 x 128 Fully-Quant, streams of their own / shared: 740 / 680 us), and the forwards of one caller's stream have one order anyway.
+// encoders in turn, 32 x 128 Fully-Quant, streams of their own / shared: 740 / 700 us), and the forwards of one caller's stream have one order anyway.
 // An encoder holds up to MAX_SIDES sets, so that callers that take turns do not wait for each other.  Beyond, nothing is created or destroyed in a
 // forward: the set that this encoder alone holds and has not used for longest goes over to the new caller (events order what is still queued on it),
 // one that others hold too is left to them.  A set that is part of a capture still open stays with its caller.  So n encoders never have more than

@@ -661,9 +661,9 @@ def test_int8_attention_where_some_rows_pass_the_calibrated_range(P, lens, unsig
 
 @pytest.mark.parametrize("lens,heads", [([128], 2), ([1, 5, 32, 33, 64, 17, 2], 3), ([300, 512, 129], 1), ([700, 1, 1030], 1)])
 def test_int8_attention_with_binary16_softmax_output_bit_exact(P, lens, heads):
-    """P rounded to binary16 times integer V: the kernel splits P16 * 2^24 into four 7-bit digit planes for the int8
-    matrix core and recombines in 64-bit integers, so the context must equal the oracle's exact binary64 sum, also for
-    a single key (P = 1 = 2^24 units, the largest digit pattern) and for subnormal probabilities (peaked softmax)."""
+    """P rounded to binary16 times integer V, added up exactly (up to 1536 keys as two binary16 parts on the FP16 matrix core, beyond as four byte planes
+    of P16 * 2^24 on the int8 one), so the context must equal the oracle's exact binary64 sum, also for
+    a single key (P = 1 = 2^24 units, the largest number) and for subnormal probabilities (peaked softmax)."""
     rng = np.random.default_rng(sum(lens) + 5)
     H = heads * 64
     cu = _cu(lens)
