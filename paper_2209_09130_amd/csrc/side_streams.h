@@ -85,18 +85,18 @@ template <class Hip> struct SideStreams {
     // Puts `count` streams in front that lie apart from each other and from the caller's, as far as is known.
     void part(int count, unsigned *last_tag)
     {
-        const bool again = ++uses % 64 == 0;        // (a handle may be another stream's by now, an answer may be lost)
+        const bool again = ++uses % 64 == 0, lost = uses % 1024 == 0;      // (a handle may be another stream's by now; an answer may not have come)
         if (settled >= count && !again) return;
         if (!answers || in_capture() || Hip::capturing(caller.stream)) return;
         bool known = true;
         auto ask = [&](Asked &s) {
-            if (!s.tag || (again && !queue(s))) {
+            if (!s.tag || (lost && !queue(s))) {
                 s.tag = *last_tag = *last_tag % 0xffff + 1;
                 Hip::ask(s.stream, answers + s.slot, s.tag);
             }
             known = known && queue(s);
         };
-        if (again) caller.tag = 0;
+        if (again && queue(caller)) caller.tag = 0;
         ask(caller);
         for (Asked &s : side)
             if (s.stream) ask(s);

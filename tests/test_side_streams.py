@@ -239,6 +239,31 @@ def test_a_handle_that_comes_to_be_another_stream_is_noticed(lib):
     assert lib.made() <= 2
 
 
+def test_answers_that_take_their_time(lib):
+    """A program that enqueues hundreds of forwards ahead: the questions wait behind them, are not asked again, and count when they are answered;
+    one that is never answered is asked again after a thousand forwards."""
+    lib.provide_page()
+    lib.queue_count(1, 1)
+    e = lib.encoder()
+    lib.caller(5)
+    lib.take(e, 0, 5, 1, 1)
+    lib.queue_count(4, 1)
+    for _ in range(500):
+        lib.take(e, 0, 5, 1, 1)
+    assert (lib.asked(), lib.made()) == (2, 1)
+    lib.answer()
+    for _ in range(3):
+        side = lib.take(e, 0, 5, 1, 1)
+        lib.answer()
+    assert lib.queue(side) != lib.queue(5) and lib.made() == 2
+    other = lib.encoder()
+    lib.caller(6)
+    asked = lib.asked()
+    for _ in range(1030):
+        lib.take(other, 0, 6, 1, 1)
+    assert lib.asked() == asked + 4
+
+
 def test_nothing_is_asked_in_a_capture_and_without_a_page(lib):
     e = lib.encoder()
     lib.caller(5)
